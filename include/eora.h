@@ -104,9 +104,10 @@ size_t eora_sp24q4_meta_bytes(int d_in, int d_out);                  /* d_out*(d
  * first forward call on it; every forward call leaves it usable for the next, so no per-call
  * clearing (and nothing a HIP graph could not replay) is needed.  Calls that may overlap in time
  * (different streams) need different workspaces.  r == 0 still needs a workspace.  A workspace of
- * the size of the largest (M, r) serves smaller calls too.  For 5 .. 127 tokens and d_in >= 16384 the
- * size also holds 4 * M * d_out floats: a 2:4 call of such a shape may cut its contraction into ranges
- * whose partial outputs are added, in a fixed order, by a second kernel of the same call. */
+ * the size of the largest (M, r) serves smaller calls too.  For 5 .. 127 tokens the size also holds
+ * 12 MiB (for d_in >= 16384 at least 4 * M * d_out floats): a call may cut its contraction into ranges
+ * whose partial outputs are added, in a fixed order, by a second kernel of the same call.  A quantised
+ * call with a smaller workspace (from about 3.3 MiB on) is served without that. */
 size_t eora_workspace_bytes(int M, int d_in, int d_out, int r);
 /* Size that lets eora_linear_q_group() serve n_members members in one pass also for M >= 128 (the
  * down-projections of all members then sit side by side in the scratch).  With a workspace of only
@@ -204,7 +205,7 @@ int eora_linear_q(const void* x, const void* qweight, const void* scales, const 
 
 /* eora_linear_q for callers that cannot allocate device memory or pass a workspace (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): same arguments without the workspace, same
- * kernels, bit-identical results.  The workspace is an array inside the library's device code (3.3 MiB on every
+ * kernels, bit-identical results.  The workspace is an array inside the library's device code (15.3 MiB on every
  * GPU the library runs on, held until the process ends), found once per device with hipGetSymbolAddress and
  * cleared once, on the first call's stream; the call allocates nothing.
  * Limit: M <= 127 (EORA_ERR_WORKSPACE beyond: the many-token path needs scratch that grows with M); all other

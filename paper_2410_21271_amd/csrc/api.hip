@@ -56,13 +56,15 @@ int check_group(int d_in, int group)
     return EORA_OK;
 }
 
-// workspace = header | tagged partials (decode kernel) | fp32 partials (fused.hip, sparse.hip) | t (fp16, prefill).
+// workspace = header | tagged partials of t | fp32 partials (sparse.hip) | t (fp16, prefill) or partial outputs.
 // The regions sit at fixed offsets whatever (M, r) a call has, so that calls of different shapes on one
 // workspace never read one region's bytes as another's.  (token blocks) x kcn <= 32 and r <= 512.
 constexpr size_t MAX_PART_ELEMS = 32 * 16 * 512;
 constexpr size_t WS_PAIRS = WS_HEADER;
 constexpr size_t WS_PARTS = WS_PAIRS + MAX_PART_ELEMS * 8;
 constexpr size_t WS_T = WS_PARTS + MAX_PART_ELEMS * 4;
+// fp32 partial outputs of a quantised call of 5 .. 127 tokens whose contraction is cut into parts in different workgroups
+constexpr size_t WIDE_SPLIT_BYTES = 12u << 20;
 
 // one launch of the kernel for 5 .. 16 tokens (x resident in LDS) for validated members that share x; the caller has
 // checked stream_fits
@@ -93,6 +95,45 @@ int launch_stream_group(const void* x, const eora_q_member* members, int n, int 
     a.adapter = adapter;
     a.r_per = r_per;
     if (failed(launch_stream(a, backbone_format(w_bits), fa, fe, stream), "linear_q (stream)")) return EORA_ERR_LAUNCH;
+    return EORA_OK;
+}
+
+// the kernel for 5 and more tokens for validated members that share x, in launches of at most CHUNK_TOKENS tokens
+int launch_wide_group(const void* x, const eora_q_member* members, int n, int M, int d_in, int r, int w_bits, int group,
+                      int fa, int fe, void* workspace, size_t workspace_bytes, hipStream_t stream, const int* adapter = nullptr, int r_per = 0)
+{
+    for (int m0 = 0; m0 < M; m0 += CHUNK_TOKENS) {
+        WideArgs a{};
+        a.x = (const _Float16*)x + (size_t)m0 * d_in;
+        for (int m = 0; m < n; ++m) {
+            const eora_q_member& e = members[m];
+            a.w[m] = e.qweight;
+            a.w_scales[m] = (const _Float16*)e.scales;
+            a.w_zeros[m] = (const uint32_t*)e.qzeros;
+            a.A[m] = e.A;
+            a.A_scales[m] = (const _Float16*)e.A_scales;
+            a.B[m] = e.B;
+            a.B_scales[m] = (const _Float16*)e.B_scales;
+            a.y[m] = (_Float16*)e.y + (size_t)m0 * e.d_out;
+            a.d_out[m] = e.d_out;
+        }
+        a.n = n;
+        a.fa = fa;
+        a.fe = fe;
+        a.hdr = (uint32_t*)workspace;
+        a.tpair = (unsigned long long*)((char*)workspace + WS_PAIRS);
+        a.tpair_count = MAX_PART_ELEMS;
+        a.ypart = (float*)((char*)workspace + WS_T);
+        a.ypart_count = M < PREFILL_MIN_TOKENS && workspace_bytes >= WS_T + WIDE_SPLIT_BYTES ? WIDE_SPLIT_BYTES / sizeof(float) : 0;
+        a.M = M - m0 < CHUNK_TOKENS ? M - m0 : CHUNK_TOKENS;
+        a.d_in = d_in;
+        a.r = r;
+        a.group = group;
+        a.spin_limit = g_spin_limit;
+        a.adapter = adapter ? adapter + m0 : nullptr;
+        a.r_per = r_per;
+        if (failed(launch_wide_q(a, backbone_format(w_bits), stream), "linear_q (wide)")) return EORA_ERR_LAUNCH;
+    }
     return EORA_OK;
 }
 
@@ -249,6 +290,13 @@ int launch_group(const void* x, const eora_q_member* members, int n, int M, int 
     return EORA_OK;
 }
 
+// the least a call works with: a quantised call of 5 .. 127 tokens with less than eora_workspace_bytes() never cuts its
+// contraction
+size_t workspace_min_bytes(int M, int d_in, int d_out, int r)
+{
+    return WS_T + (M >= PREFILL_MIN_TOKENS ? prefill_scratch_bytes(M, d_in, r, 1) : sparse_split_bytes(M, d_in, d_out));
+}
+
 }  // namespace
 
 extern "C" {
@@ -258,7 +306,8 @@ size_t eora_workspace_bytes(int M, int d_in, int d_out, int r)
     if (check_backbone_shape(M, d_in, d_out, r) != EORA_OK) return 0;
     // partials of t for the small-M kernels, and t itself as fp16 M x r for the prefill GEMM
     // (and, for a 2:4 call with a long contraction at 5 .. 127 tokens, the partial outputs of its ranges)
-    return WS_T + (M >= PREFILL_MIN_TOKENS ? prefill_scratch_bytes(M, d_in, r, 1) : sparse_split_bytes(M, d_in, d_out));
+    const size_t base = workspace_min_bytes(M, d_in, d_out, r), split = M > 4 && M < PREFILL_MIN_TOKENS ? WS_T + WIDE_SPLIT_BYTES : 0;
+    return base > split ? base : split;
 }
 
 size_t eora_workspace_bytes_group(int M, int d_in, int r, int n_members)
@@ -351,17 +400,14 @@ static int validate_linear_q(const void* x, const eora_q_member& e, int M, int d
         return EORA_ERR_ALIGN;
     if (!workspace) return EORA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return EORA_ERR_ALIGN;
-    if (workspace_bytes < eora_workspace_bytes(M, d_in, e.d_out, r)) return EORA_ERR_WORKSPACE;
+    if (workspace_bytes < workspace_min_bytes(M, d_in, e.d_out, r)) return EORA_ERR_WORKSPACE;
     return EORA_OK;
 }
 
 // one validated quantised layer
 static int run_linear_q(const void* x, const eora_q_member& e, int M, int d_in, int r, int w_bits, int group, int ab_bits,
-                        int fa, int fe, void* workspace, void* stream)
+                        int fa, int fe, void* workspace, size_t workspace_bytes, void* stream)
 {
-    const void *qweight = e.qweight, *scales = e.scales, *qzeros = e.qzeros, *A = e.A, *B = e.B;
-    const void *A_scales = e.A_scales, *B_scales = e.B_scales;
-    void* y = e.y;
     const int d_out = e.d_out;
     if (M == 0) return EORA_OK;
 
@@ -374,35 +420,7 @@ static int run_linear_q(const void* x, const eora_q_member& e, int M, int d_in, 
     if (stream_fits(M, d_in, group, r, backbone_format(w_bits), fa, &d_out, 1))
         return launch_stream_group(x, &e, 1, M, d_in, r, w_bits, fa, fe, workspace, (hipStream_t)stream);
 
-    // k-ranges of the down-projection: a divisor of the number of 128-wide k-tiles
-    const int kcn = pick_kcn(M, d_in);
-    for (int m0 = 0; m0 < M; m0 += CHUNK_TOKENS) {
-        FusedArgs a{};
-        a.x = (const _Float16*)x + (size_t)m0 * d_in;
-        a.w = qweight;
-        a.w_scales = (const _Float16*)scales;
-        a.w_zeros = (const uint32_t*)qzeros;
-        a.A = A;
-        a.A_scales = (const _Float16*)A_scales;
-        a.B = B;
-        a.B_scales = (const _Float16*)B_scales;
-        a.y = (_Float16*)y + (size_t)m0 * d_out;
-        a.hdr = (uint32_t*)workspace;
-        a.tpart = (float*)((char*)workspace + WS_PARTS);
-        a.tpair = (unsigned long long*)((char*)workspace + WS_PAIRS);
-        a.M = M - m0 < CHUNK_TOKENS ? M - m0 : CHUNK_TOKENS;
-        a.d_in = d_in;
-        a.d_out = d_out;
-        a.r = r;
-        a.group = group;
-        a.kcn = kcn;
-        a.spin_limit = g_spin_limit;
-        const int fm = backbone_format(w_bits);
-        const hipError_t e = wide_q_fits(a.M, d_in, d_out, r) ? launch_wide_q(a, fm, fa, fe, (hipStream_t)stream)
-                                                               : launch_fused(a, fm, fa, fe, (hipStream_t)stream);
-        if (failed(e, "linear_q")) return EORA_ERR_LAUNCH;
-    }
-    return EORA_OK;
+    return launch_wide_group(x, &e, 1, M, d_in, r, w_bits, group, fa, fe, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int eora_linear_q(const void* x, const void* qweight, const void* scales, const void* qzeros,
@@ -414,7 +432,7 @@ int eora_linear_q(const void* x, const void* qweight, const void* scales, const 
     int fa, fe;
     const int rc = validate_linear_q(x, e, M, d_in, r, w_bits, group, ab_bits, workspace, workspace_bytes, &fa, &fe);
     if (rc != EORA_OK) return rc;
-    return run_linear_q(x, e, M, d_in, r, w_bits, group, ab_bits, fa, fe, workspace, stream);
+    return run_linear_q(x, e, M, d_in, r, w_bits, group, ab_bits, fa, fe, workspace, workspace_bytes, stream);
 }
 
 // ---- the same layer for callers that cannot allocate ---------------------------------------------------------
@@ -423,7 +441,7 @@ namespace {
 // ends.  Its size is that of eora_workspace_bytes() for any call below PREFILL_MIN_TOKENS tokens (header, tagged
 // partials, fp32 partials).  In host code the array's name is only a handle for hipGetSymbolAddress: the device
 // address it yields (per device) is what kernels and the clearing launch are given.
-constexpr size_t STATIC_SCRATCH_BYTES = WS_T;
+constexpr size_t STATIC_SCRATCH_BYTES = WS_T + WIDE_SPLIT_BYTES;
 __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mutex;
@@ -465,7 +483,7 @@ int eora_linear_q_static(const void* x, const void* qweight, const void* scales,
     void* ws = nullptr;
     rc = static_scratch(&ws, (hipStream_t)stream);
     if (rc != EORA_OK) return rc;
-    return run_linear_q(x, e, M, d_in, r, w_bits, group, ab_bits, fa, fe, ws, stream);
+    return run_linear_q(x, e, M, d_in, r, w_bits, group, ab_bits, fa, fe, ws, STATIC_SCRATCH_BYTES, stream);
 }
 
 int eora_linear_q_multi(const void* x, const void* qweight, const void* scales, const void* qzeros,
@@ -493,36 +511,7 @@ int eora_linear_q_multi(const void* x, const void* qweight, const void* scales, 
     // 5 .. 16 tokens and enough rows: the kernel with x resident in LDS, with t masked where it goes to LDS
     if (stream_fits(M, d_in, group, R, backbone_format(w_bits), fa, &d_out, 1))
         return launch_stream_group(x, &e, 1, M, d_in, R, w_bits, fa, fe, workspace, (hipStream_t)stream, (const int*)adapter_of_row, r);
-    const int kcn = pick_kcn(M, d_in);
-    for (int m0 = 0; m0 < M; m0 += CHUNK_TOKENS) {
-        FusedArgs a{};
-        a.x = (const _Float16*)x + (size_t)m0 * d_in;
-        a.w = qweight;
-        a.w_scales = (const _Float16*)scales;
-        a.w_zeros = (const uint32_t*)qzeros;
-        a.A = A_all;
-        a.A_scales = (const _Float16*)A_scales;
-        a.B = B_all;
-        a.B_scales = (const _Float16*)B_scales;
-        a.y = (_Float16*)y + (size_t)m0 * d_out;
-        a.hdr = (uint32_t*)workspace;
-        a.tpart = (float*)((char*)workspace + WS_PARTS);
-        a.tpair = (unsigned long long*)((char*)workspace + WS_PAIRS);
-        a.M = M - m0 < CHUNK_TOKENS ? M - m0 : CHUNK_TOKENS;
-        a.d_in = d_in;
-        a.d_out = d_out;
-        a.r = R;
-        a.group = group;
-        a.kcn = kcn;
-        a.spin_limit = g_spin_limit;
-        a.adapter = (const int*)adapter_of_row + m0;
-        a.r_per = r;
-        const int fm = backbone_format(w_bits);
-        const hipError_t err = wide_q_fits(a.M, d_in, d_out, R) ? launch_wide_q(a, fm, fa, fe, (hipStream_t)stream)
-                                                                 : launch_fused(a, fm, fa, fe, (hipStream_t)stream);
-        if (failed(err, "linear_q_multi")) return EORA_ERR_LAUNCH;
-    }
-    return EORA_OK;
+    return launch_wide_group(x, &e, 1, M, d_in, R, w_bits, group, fa, fe, workspace, workspace_bytes, (hipStream_t)stream, (const int*)adapter_of_row, r);
 }
 
 int eora_linear_q_group(const void* x, const eora_q_member* members, int n_members,
@@ -548,49 +537,10 @@ int eora_linear_q_group(const void* x, const eora_q_member* members, int n_membe
         if (stream_fits(M, d_in, group, r, backbone_format(w_bits), fa, rows, n_members))
             return launch_stream_group(x, members, n_members, M, d_in, r, w_bits, fa, fe, workspace, (hipStream_t)stream);
     }
-    if (n_members > 1 && M > 4 && M < PREFILL_MIN_TOKENS) {
-        // 5 .. 127 tokens: the members' workgroups in one launch of the kernel that shares x through LDS, if together
-        // they have the rows it wants.  k-ranges: the members' partials and flags share the regions of one call.
-        int d_outs[MAX_GROUP];
-        for (int m = 0; m < n_members; ++m) d_outs[m] = members[m].d_out;
-        const int yblocks = (M + 15) / 16;
-        int kcn = 1;
-        for (int c = 2; c <= 4; ++c)
-            if ((d_in / 128) % c == 0 && n_members * yblocks * c <= 32) kcn = c;
-        const bool regions_ok = n_members * yblocks * kcn <= 32 && (r / 16) * kcn * n_members <= HDR_FLAGS_PER_BLOCK;
-        if (regions_ok && wide_q_group_fits(M, d_in, d_outs, n_members, r)) {
-            FusedArgs as[MAX_GROUP];
-            for (int m = 0; m < n_members; ++m) {
-                const eora_q_member& e = members[m];
-                FusedArgs a{};
-                a.x = (const _Float16*)x;
-                a.w = e.qweight;
-                a.w_scales = (const _Float16*)e.scales;
-                a.w_zeros = (const uint32_t*)e.qzeros;
-                a.A = e.A;
-                a.A_scales = (const _Float16*)e.A_scales;
-                a.B = e.B;
-                a.B_scales = (const _Float16*)e.B_scales;
-                a.y = (_Float16*)e.y;
-                a.hdr = (uint32_t*)workspace;
-                a.tpart = (float*)((char*)workspace + WS_PARTS);
-                a.tpair = (unsigned long long*)((char*)workspace + WS_PAIRS) + (size_t)m * yblocks * kcn * 16 * r;
-                a.M = M;
-                a.d_in = d_in;
-                a.d_out = e.d_out;
-                a.r = r;
-                a.group = group;
-                a.kcn = kcn;
-                a.spin_limit = g_spin_limit;
-                as[m] = a;
-            }
-            if (failed(launch_wide_q_group(as, n_members, backbone_format(w_bits), fa, fe, (hipStream_t)stream), "linear_q_group"))
-                return EORA_ERR_LAUNCH;
-            return EORA_OK;
-        }
-    }
+    if (n_members > 1 && M > 4 && M < PREFILL_MIN_TOKENS)
+        return launch_wide_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, workspace, workspace_bytes, (hipStream_t)stream);
     for (int m = 0; m < n_members; ++m) {               // other shapes (or a workspace sized for one member): one after the other
-        const int rc = run_linear_q(x, members[m], M, d_in, r, w_bits, group, ab_bits, fa, fe, workspace, stream);
+        const int rc = run_linear_q(x, members[m], M, d_in, r, w_bits, group, ab_bits, fa, fe, workspace, workspace_bytes, stream);
         if (rc != EORA_OK) return rc;
     }
     return EORA_OK;
@@ -612,7 +562,7 @@ int run_linear_sparse(const void* x, const void* values, const void* indices, co
     if (!aligned16(x) || !aligned16(values) || !aligned16(qtiles) || !aligned16(qmeta) || !aligned16(indices) || !aligned16(y)) return EORA_ERR_ALIGN;
     if (!workspace) return EORA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return EORA_ERR_ALIGN;
-    if (workspace_bytes < eora_workspace_bytes(M, d_in, d_out, r)) return EORA_ERR_WORKSPACE;
+    if (workspace_bytes < workspace_min_bytes(M, d_in, d_out, r)) return EORA_ERR_WORKSPACE;
     if (M == 0) return EORA_OK;
     int kcn = pick_kcn(M, d_in);
     // (the longest contractions at 1..4 tokens: sixteen ranges, so that the producers are done before the first
@@ -666,7 +616,7 @@ int eora_linear_sp24_group(const void* x, const eora_sp_member* members, int n_m
             return EORA_ERR_ALIGN;
         if (!workspace) return EORA_ERR_WORKSPACE;
         if (!aligned16(workspace)) return EORA_ERR_ALIGN;
-        if (workspace_bytes < eora_workspace_bytes(M, d_in, e.d_out, r)) return EORA_ERR_WORKSPACE;
+        if (workspace_bytes < workspace_min_bytes(M, d_in, e.d_out, r)) return EORA_ERR_WORKSPACE;
     }
     if (M == 0) return EORA_OK;
     // one launch when the members' partials and flags fit the regions of one call; else one after the other

@@ -33,42 +33,41 @@ constexpr int MAX_KCN = 8;                      // k-ranges of the down-projecti
 // cover).  `fmt` is a printf format for up to six ints and must be a string literal.  Not synchronised.
 void note_launch(const char* fmt, int a = 0, int b = 0, int c = 0, int d = 0, int e = 0, int f = 0, int g = 0);
 
-struct FusedArgs {
-    const _Float16* x;        // M x d_in fp16 row-major
-    const void* w;            // backbone tiles
-    const _Float16* w_scales;
-    const uint32_t* w_zeros;
-    const void* A;            // r x d_in tiles
-    const _Float16* A_scales;
-    const void* B;            // d_out x r tiles
-    const _Float16* B_scales;
-    _Float16* y;              // M x d_out fp16 row-major
-    uint32_t* hdr;            // workspace header
-    float* tpart;             // (timeline builds: stamps)
-    unsigned long long* tpair;   // token blocks x kcn x 16 x r (value, tag) pairs: partials of t
-    int M, d_in, d_out, r, group, kcn, spin_limit;
-    // several adapters side by side in A and B (r = their ranks together): token row m keeps only the
-    // r_per columns of t that belong to adapter[m] (-1: none).  nullptr: one adapter, nothing masked.
-    // Read by fused.hip and wideq.hip.
-    const int* adapter;
-    int r_per;
+// General kernel of the quantised backbone (wideq.hip): 5 and more tokens, and the shapes the decode kernel does not take.
+// x is shared through LDS by the wavefronts of a workgroup.  Up to four linears that read the same x in one launch.
+struct WideArgs {
+    const _Float16* x;                  // M x d_in fp16 row-major, shared
+    const void* w[4];                   // backbone tiles
+    const _Float16* w_scales[4];
+    const uint32_t* w_zeros[4];
+    const void* A[4];                   // r x d_in tiles
+    const _Float16* A_scales[4];
+    const void* B[4];                   // d_out x r tiles
+    const _Float16* B_scales[4];
+    _Float16* y[4];                     // M x d_out fp16 row-major
+    int d_out[4];
+    int n;                              // members, 1..4
+    int fa, fe;                         // factor formats (S_NONE without factors)
+    uint32_t* hdr;                      // workspace header
+    unsigned long long* tpair;          // [member][token group][kcn][16 TB tokens][r] tagged partials of t
+    size_t tpair_count;                 // pairs the region holds
+    int M, d_in, r, group, spin_limit;
+    const int* adapter;                 // null, or one adapter index per token row (several adapters side by side in A and B)
+    int r_per;                          // rank of one adapter (adapter != null)
+    float* ypart;                       // per member [part][M][d_out] fp32 partial outputs (S > 1)
+    size_t ypart_count;                 // floats the region holds (0: the contraction is never cut)
+    // set by the launcher
+    int ntg;                            // groups of TB token blocks
+    int kcn;                            // k-ranges of t
+    int nprod;                          // producer workgroups
+    int S;                              // parts of the contraction in different workgroups
+    int first[4];                       // first workgroup of member i
+    int ycol[4];                        // rows of the members before member i
+    int ng;                             // quantisation groups of a row
+    uint32_t gmagic;                    // ceil(2^31 / (tiles of a group))
+    int seg;                            // tiles of a row block whose scales sit in LDS at a time
 };
-
-hipError_t launch_fused(const FusedArgs& a, int fm, int fa, int fe, hipStream_t stream);
-
-// Kernel for 5 .. 127 tokens (wideq.hip): x shared through LDS by the wavefronts of a workgroup.
-bool wide_q_fits(int M, int d_in, int d_out, int r);
-hipError_t launch_wide_q(const FusedArgs& a, int fm, int fa, int fe, hipStream_t stream);
-// The same kernel for up to four linears that read the same x (same M, d_in, r, kcn, formats; own weights,
-// factors, y, d_out, tpair region): the members' workgroups follow one another in one launch.
-struct WideGroupArgs {
-    FusedArgs m[4];
-    int first[4];             // first workgroup of member i
-    int flag0[4];             // first flag of member i inside a token block's flags
-    int n;
-};
-bool wide_q_group_fits(int M, int d_in, const int* d_out, int n, int r);
-hipError_t launch_wide_q_group(const FusedArgs* members, int n, int fm, int fa, int fe, hipStream_t stream);
+hipError_t launch_wide_q(const WideArgs& a, int fm, hipStream_t stream);
 
 // Kernel for 5 .. 16 tokens with x resident in LDS (stream.hip): one workgroup of 16 wavefronts per compute unit keeps
 // the whole x (d_in <= 4096) and finishes every output tile it starts; t is handed over as tagged pairs.

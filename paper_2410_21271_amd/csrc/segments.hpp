@@ -125,79 +125,6 @@ struct Backbone {
     int G, NG, NGW, gdiv;
 };
 
-template <int FMT, int RB>
-__device__ __forceinline__ void load_quad_meta(Quad<FMT, RB>& s, const Backbone& bb, int R0, int q, int lane)
-{
-    const int n = lane & 15, g0 = 4 * q;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const size_t row = (size_t)(R0 + rb) * 16 + n;
-        if (bb.gdiv == 1 && (bb.NG & 3) == 0 && g0 + 3 < bb.G) {      // 8-byte aligned: NG and g0 are multiples of 4
-            s.sc[rb] = *(const uint2*)(bb.scales + row * bb.NG + g0);
-            s.zq[rb] = (bb.zeros[row * bb.NGW + (g0 >> 3)] >> (4 * (g0 & 7))) & 0xFFFFu;
-        } else {                                  // coarser groups or a ragged last quad: element by element
-            uint32_t sw[4] = {0u, 0u, 0u, 0u}, zq = 0u;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int g = g0 + i;
-                if (g < bb.G) {
-                    const int grp = g / bb.gdiv;
-                    sw[i] = __builtin_bit_cast(uint16_t, bb.scales[row * bb.NG + grp]);
-                    zq |= ((bb.zeros[row * bb.NGW + (grp >> 3)] >> (4 * (grp & 7))) & 0xFu) << (4 * i);
-                }
-            }
-            s.sc[rb] = uint2{sw[0] | (sw[1] << 16), sw[2] | (sw[3] << 16)};
-            s.zq[rb] = zq;
-        }
-    }
-}
-
-template <int FMT, int RB>
-__device__ __forceinline__ void load_quad_words(Quad<FMT, RB>& s, const Backbone& bb, int R0, int q, int lane)
-{
-    constexpr int WORDS = Fmt<FMT>::WORDS;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int g = 4 * q + i;
-            if (g < bb.G) {
-                const size_t tile = (size_t)(R0 + rb) * bb.G + g;
-                load_words<WORDS>(s.w[rb][i], bb.w + (tile * 64 + lane) * WORDS);
-            } else {
-#pragma unroll
-                for (int k = 0; k < WORDS; ++k) s.w[rb][i][k] = 0u;
-            }
-        }
-    }
-}
-
-template <int FMT, int RB, bool XLDS>
-__device__ __forceinline__ void compute_quad(const Quad<FMT, RB>& s, const Backbone& bb, int q, f4 (&acc)[RB],
-                                             const ActSrc<XLDS>& act, int lane, int m, bool row_ok)
-{
-    const int j = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int g = 4 * q + i;
-        if (g < bb.G) {
-            h8 xa[4];
-            load_act<4, XLDS>(xa, act, g * 128 + 32 * j, m, row_ok);
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                h8 b[4];
-                decode_tile<FMT>(s.w[rb][i], (s.zq[rb] >> (4 * i)) & 0xFu, b);
-                f4 part = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int t = 0; t < 4; ++t) part = mfma16(xa[t], b[t], part);
-                const uint32_t sw = (i < 2) ? s.sc[rb].x : s.sc[rb].y;
-                const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)((i & 1) ? (sw >> 16) : (sw & 0xFFFFu)));
-                acc[rb] += (float)sc * part;     // exact integers times x, scaled once per group in fp32
-            }
-        }
-    }
-}
-
 // ------------------------------------------------------------------------------------------------
 // Factor tiles (A in phase A with x, B in phase B with t): plain per-tile steps.
 struct Factor {
@@ -261,49 +188,6 @@ __device__ __forceinline__ f4 run_factor_a(const Factor& f, int R, int g_begin, 
     return acc;
 }
 
-
-// The same partial for a PRODUCER workgroup, which has nothing else to do: the tiles of A and the
-// activation fragments of up to PD steps are all requested before the first one is used (one memory
-// round trip for the whole unit when it has at most PD steps per wavefront).
-template <int FMT, int NW>
-__device__ __forceinline__ f4 run_factor_a_eager(const Factor& f, int R, int g_begin, int g_end, int wave, int lane,
-                                                 const _Float16* __restrict__ xg, int ldg, int m, bool row_ok)
-{
-    constexpr int KT = Fmt<FMT>::KT, NMF = KT / 32, PD = NMF == 1 ? 8 : 2;
-    const int j = lane >> 4;
-    const int first = g_begin + wave;
-    const int nsteps = first < g_end ? (g_end - first + NW - 1) / NW : 0;
-    const _Float16* xrow = xg + (size_t)(row_ok ? m : 0) * ldg + (KT / 4) * j;
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int base = 0; base < nsteps; base += PD) {
-        FTile<FMT> buf[PD];
-        h8 xa[PD][NMF];
-#pragma unroll
-        for (int u = 0; u < PD; ++u) {
-            const int s = base + u < nsteps ? base + u : nsteps - 1;         // clamped: always a valid tile
-            const int g = first + s * NW;
-            load_ftile<FMT>(buf[u], f, R, g, lane);
-#pragma unroll
-            for (int t = 0; t < NMF; ++t) xa[u][t] = *(const h8*)(xrow + (size_t)g * KT + 8 * t);
-        }
-#pragma unroll
-        for (int u = 0; u < PD; ++u) {
-            if (base + u < nsteps) {
-                h8 b[NMF];
-                decode_tile<FMT>(buf[u].w, 8u, b);
-                if constexpr (FMT == S_F16) {
-                    acc = mfma16(xa[u][0], b[0], acc);
-                } else {
-                    f4 part = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int t = 0; t < NMF; ++t) part = mfma16(xa[u][t], b[t], part);
-                    acc += (float)buf[u].sc * part;
-                }
-            }
-        }
-    }
-    return acc;
-}
 
 // Every workgroup of a low-rank launch reads the epoch and then checks in on one of HDR_NSUB
 // spread-out counters; the last one to check in advances the epoch for the next launch.  One thread

@@ -1,4 +1,4 @@
-// Decode kernel for one to four tokens: the same layer as fused.hip,
+// Decode kernel for one to four tokens: the same layer as wideq.hip,
 //
 //      y = x.What^T + (x.A^T).B^T          (Sec. 3 forward equation, Alg. 1 step 7)
 //

@@ -1,566 +1,730 @@
-// The compensated quantised layer for 5 .. 127 tokens, in ONE launch:
+// The compensated quantised layer for 5 and more tokens, in ONE launch:
 //
 //      y = x.What^T + (x.A^T).B^T          (Sec. 3 forward equation, Alg. 1 step 7)
 //
-// HBM-bound like the decode kernel, but a token block's x (16 tokens) is now as many bytes as four row blocks
-// of 4-bit weights, so it must not be fetched per stored tile by every wavefront that needs it.  A workgroup
-// is NWR row blocks x NWK ranges of the contraction length, one wavefront each, and up to TB token blocks.
-// Per step every range advances by one 128-column chunk: x[16 TB tokens][128] of the range goes global ->
-// registers (requested 2 or 4 steps before its LDS write) -> one of the range's two LDS slots and is read from
-// there by the range's NWR wavefronts; a stored tile, decoded once, serves all TB token blocks.  Stored tiles
-// come in quads (one 8-byte load brings a row's four group scales, one word its four zero-points): one quad is
-// in flight while the other is consumed, and it is refilled into the registers just used.  All requests are
-// plain loads and every step issues the same ones (past the end: the last chunk again, never used), so the
-// compiler's wait counts stay exact.  One barrier per step: after it chunk c is visible to the range's readers
-// and everyone has left the other slot, which is rewritten at once.
+// A workgroup is eight wavefronts: NWR groups of RW row blocks x NWK ranges of the contraction, for up to TB token
+// blocks of 16.  Per step every range advances by one 128-column chunk of x.
+//  - x is read row by row (256 contiguous bytes per token: 125 B/ns and compute unit from L2, against 37 when every
+//    lane fetches its own 16-byte MFMA fragment from global memory) into registers, PX steps ahead, and goes through
+//    LDS, where the wavefronts of a range find their fragments.  With NWR = 1 a chunk belongs to one wavefront: one
+//    slot and no barrier (a wavefront's LDS operations are carried out in order); otherwise two slots and one barrier
+//    per step.
+//  - Stored tiles come straight into the registers of the wavefront that owns the row block, D steps ahead, with the
+//    row's group scale and zero-point word beside them.  Every stored tile is decoded once per workgroup and serves all
+//    TB token blocks.  All requests are unconditional plain loads (past the end: the last tile again, never used), so
+//    that the compiler's wait counts stay exact.
+//  - Arithmetic: integer codes minus zero-point exact in fp16, fp32 accumulation per 128 columns, scaled in fp32; t in
+//    fp32, split into a high and a low fp16 part for B's product.
+//  - Low-rank path: the launch's first workgroups are producers, one (16 rows of A) x (one of kcn ranges of the
+//    contraction) for TB token blocks each; they publish t as (value, epoch + 1) pairs and never wait.  After its
+//    backbone every consumer adds the kcn partials of its tokens' t in a fixed order, checks the tags, re-reads past the
+//    caches while one is stale (bounded), and leaves t in LDS as two fp16 planes in fragment order; the wavefronts share
+//    B's tiles.
+//  - The ranges' accumulators are added through LDS in a fixed order.  With S > 1 the contraction is cut into S parts in
+//    different workgroups, which write fp32 partial outputs that a second kernel adds in a fixed order.
 //
-// LDS slot layout: 16-byte piece q of token row t (columns 8q .. 8q+7 of the chunk) sits at piece index
-// 16 t + (q ^ (t & 15)): the 16 lanes that read one q for 16 tokens hit 16 different bank groups.
-//
-// Arithmetic is the decode kernel's: integer codes minus zero-point exact in fp16, fp32 accumulation per
-// 128-group, scaled once per group in fp32; t in fp32, split into a high and a low fp16 part for B's product.
-// Low-rank path: producer workgroups first (one unit of t = x.A^T each, per token block), partials as tagged
-// (value, epoch + 1) pairs, flags, fixed-order sums.  After the backbone the wavefronts of a row block share
-// B's tiles, then the ranges' accumulators are added in a fixed order through LDS.
+// LDS slot of a chunk: 16-byte piece q of token row t sits at piece index 16 t + (q ^ (t & 15)).
 #include "segments.hpp"
+
+#include <type_traits>
 
 namespace eora {
 
-#ifdef EORA_TIMELINE
-// debug build only: per-workgroup time stamps (100 MHz counter) behind the partials of t
-#define WTL_STAMP(slot) do { if (threadIdx.x == 0) ((unsigned long long*)(a.tpart + (1 << 20)))[blockIdx.x * 8 + (slot)] = wall_clock64(); } while (0)
-#else
-#define WTL_STAMP(slot) do { } while (0)
-#endif
+constexpr int WQ_NW = 8, WQ_NT = WQ_NW * 64;
+constexpr size_t WQ_LDS_MAX = 160 * 1024 - 256;            // dynamic LDS of a workgroup at most
 
-
-// gbid: index of the workgroup in the launch; bid: its index among its member's workgroups; flag0: the member's
-// first flag inside a token block's flags
-template <int FM, int FA, int FE, int NWR, int NWK, int TB>
-__device__ __forceinline__ void wide_q_body(const FusedArgs& a, const int gbid, const int bid, const int flag0)
+// the member's value of an argument array without a run-time index into kernel arguments
+template <typename T>
+__device__ __forceinline__ T wq_pick(const T (&v)[4], int m)
 {
-    constexpr int NW = NWR * NWK;
-    constexpr bool LOWRANK = FA != S_NONE;
-    constexpr int SLOT = TB * 4096;                       // bytes: 16 TB tokens x 128 columns
-    static_assert((4 * TB) % NWR == 0, "the 1 KiB pieces of a chunk divide evenly over a range's wavefronts");
-    constexpr int XN = 4 * TB / NWR;                      // pieces per wavefront
-    constexpr int WQ_D = XN > 2 ? 2 : 4;                  // steps between a request for x and its LDS write (registers: WQ_D x XN x 4)
-    __shared__ f4 pred[NW > 1 ? NW - 1 : 1][64];          // a producer's cross-wavefront sum
-    __shared__ uint32_t s_epoch, s_ok;
+    T r = v[0];
+    r = m == 1 ? v[1] : r;
+    r = m == 2 ? v[2] : r;
+    r = m == 3 ? v[3] : r;
+    return r;
+}
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+// where lane `lane` finds, for piece i of a chunk (token rows 4 i .. 4 i + 3), its 16 bytes of x: row offset in halves
+__device__ __forceinline__ size_t wq_xrow(const WideArgs& a, int m0, int i, int lane)
+{
+    const int row = m0 + 4 * i + (lane >> 4);
+    // rows beyond the tokens: all their lanes read one valid piece (their results are dropped)
+    return row < a.M ? (size_t)row * a.d_in + 8 * (lane & 15) : (size_t)m0 * a.d_in;
+}
+__device__ __forceinline__ int wq_xdst(int i, int lane)
+{
+    const int t = 4 * i + (lane >> 4);
+    return (t * 16 + ((lane & 15) ^ (t & 15))) * 16;
+}
+// fragment piece p (columns 8 p .. 8 p + 7 of the chunk) of token row n of a token block
+__device__ __forceinline__ int wq_frag(int n, int p) { return (n * 16 + (p ^ n)) * 16; }
+
+// ---- producer: one block of A, one range of the contraction, TB token blocks -------------------------------------------
+template <int FA, int TB>
+__device__ __forceinline__ void wq_produce(const WideArgs& a, const void* A, const _Float16* A_scales, int rho, int m0, int ka, int len,
+                                           unsigned char* xs, int lane, f4 (&acc)[TB])
+{
+    constexpr int NT = 128 / Fmt<FA>::KT, NMF = Fmt<FA>::KT / 32;
     const int n = lane & 15, j = lane >> 4;
-    const int wr = wave % NWR, wk = wave / NWR;
-    const int yblocks = (a.M + 15) / 16;
-    const int units = LOWRANK ? (a.r / 16) * a.kcn : 0;
-    const int nprod = units * yblocks;
-
-    CheckIn ci{0u, 0u, 0u};
-    if constexpr (LOWRANK) {
-        if (tid == 0) check_in_load(ci, a.hdr);
-        if (bid < nprod) {
-            // ===================================================================== producer
-            __builtin_amdgcn_s_setprio(3);                 // everyone's critical path
-            WTL_STAMP(0);
-            constexpr int KTA = Fmt<FA>::KT;
-            const int yb = bid / units, u = bid % units;
-            const int m_blk = 16 * yb;
-            const int mt = a.M - m_blk < 16 ? a.M - m_blk : 16;
-            const int NRB = a.r / 16;
-            const int rho = u % NRB, kc = u / NRB;
-            const Factor fa{(const uint32_t*)a.A, a.A_scales, a.d_in / KTA};
-            const int tpc = fa.ntk / a.kcn;
-            const f4 part = run_factor_a_eager<FA, NW>(fa, rho, kc * tpc, (kc + 1) * tpc, wave, lane,
-                                                       a.x + (size_t)m_blk * a.d_in, a.d_in, n, n < mt);
-            if (tid == 0) {
-                check_in_issue(ci, a.hdr, gbid);
-                s_epoch = ci.epoch;
-            }
-            WTL_STAMP(1);
-            if (wave > 0) pred[wave - 1][lane] = part;
-            __syncthreads();
-            if (wave == 0) {
-                f4 v = part;
+    const Factor fa{(const uint32_t*)A, A_scales, a.d_in / Fmt<FA>::KT};
+    const int last = a.d_in / 128 - 1;
+    auto tile_at = [&](int s) {
+        const int k = ka + (s < len ? s : (len > 0 ? len - 1 : 0));
+        return k < last ? k : last;
+    };
+    FTile<FA> at[2][NT];
+    u4 xr[4 * TB];
+    auto load_a = [&](FTile<FA> (&t)[NT], int s) {
+        const int k = tile_at(s);
 #pragma unroll
-                for (int w2 = 0; w2 < NW - 1; ++w2) v += pred[w2][lane];
-                // partial layout: [token block][kc][token row][r], every element an 8-byte (value, epoch + 1)
-                // pair written by ONE write-through store: a reader that finds this launch's tag has this
-                // launch's value, so the flag (same wavefront, later instruction) need not wait for these
-                // stores to be acknowledged.  Register i is token row 4*j+i, column n.
-                unsigned long long* dst = a.tpair + ((size_t)(yb * a.kcn + kc) * 16) * a.r + 16 * rho + n;
+        for (int i = 0; i < NT; ++i) load_ftile<FA>(t[i], fa, rho, k * NT + i, lane);
+    };
+    auto load_x = [&](int s) {
+        const _Float16* p = a.x + (size_t)tile_at(s) * 128;
+#pragma unroll
+        for (int i = 0; i < 4 * TB; ++i) xr[i] = *(const u4*)(p + wq_xrow(a, m0, i, lane));
+    };
+    load_x(0);
+    load_a(at[0], 0);
+    load_a(at[1], 1);
+    for (int s0 = 0; s0 < len; s0 += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int s = s0 + h;
+            if (s < len) {
+#pragma unroll
+                for (int i = 0; i < 4 * TB; ++i) *(u4*)(xs + wq_xdst(i, lane)) = xr[i];
+                load_x(s + 1);
+                asm volatile("" ::: "memory");            // (the fragments read below were written by other lanes of this wavefront)
+                if constexpr (FA == S_F16) {
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        h8 b[1];
+                        decode_tile<FA>(at[h][t].w, 8u, b);
+#pragma unroll
+                        for (int tb = 0; tb < TB; ++tb) acc[tb] = mfma16(*(const h8*)(xs + tb * 4096 + wq_frag(n, 4 * t + j)), b[0], acc[tb]);
+                    }
+                } else {
+                    h8 b[NMF];
+                    decode_tile<FA>(at[h][0].w, 8u, b);
+                    const float sc = (float)at[h][0].sc;
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) {
+                        f4 part = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int t = 0; t < NMF; ++t) part = mfma16(*(const h8*)(xs + tb * 4096 + wq_frag(n, 4 * j + t)), b[t], part);
+                        acc[tb] += sc * part;
+                    }
+                }
+                asm volatile("" ::: "memory");
+                load_a(at[h], s + 2);
+            }
+        }
+    }
+}
+
+// ---- consumer: acc += t.B^T for the wavefront's row blocks, its share of B's tiles -------------------------------------
+// planes: t of TB token blocks as a high and a low fp16 part, piece p (columns 8 p ..) of token n of block tb at
+// tb * tbs + p * 272 + 16 n; the low plane `plane` bytes behind
+template <int FE, int RW>
+__device__ __forceinline__ void wq_up_load(const Factor& fb, const int (&R)[RW], int g, int lane, uint32_t (&bw)[RW][4], _Float16 (&bs)[RW])
+{
+    constexpr int W = Fmt<FE>::WORDS;
+    g = g < fb.ntk ? g : 0;                               // (a wavefront without a tile fetches a valid one)
+#pragma unroll
+    for (int rw = 0; rw < RW; ++rw) {
+        FTile<FE> t;
+        load_ftile<FE>(t, fb, R[rw], g, lane);
+#pragma unroll
+        for (int i = 0; i < W; ++i) bw[rw][i] = t.w[i];
+        bs[rw] = t.sc;
+    }
+}
+
+template <int FE, int TB, int RW, int NWK>
+__device__ __forceinline__ void wq_up(const Factor& fb, const int (&R)[RW], int wk, int tbs, int plane, int lane,
+                                      uint32_t (&bw)[RW][4], _Float16 (&bs)[RW], int g0, int g1, f4 (&acc)[RW][TB])
+{
+    constexpr int KT = Fmt<FE>::KT, NMF = KT / 32, W = Fmt<FE>::WORDS;
+    const int n = lane & 15, j = lane >> 4;
+    for (int g = g0 + wk; g < g1; g += NWK) {
+        if (g != g0 + wk) wq_up_load<FE, RW>(fb, R, g, lane, bw, bs);
+#pragma unroll
+        for (int rw = 0; rw < RW; ++rw) {
+            uint32_t w[W];
+#pragma unroll
+            for (int i = 0; i < W; ++i) w[i] = bw[rw][i];
+            h8 b[NMF];
+            decode_tile<FE>(w, 8u, b);
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) {
+                f4 part = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (FE == S_F16) part = acc[rw][tb];
+#pragma unroll
+                for (int q = 0; q < NMF; ++q) {
+                    const unsigned char* p = eora_smem + tb * tbs + ((KT / 8) * (g - g0) + (KT / 32) * j + q) * 272 + 16 * n;
+                    part = mfma16(*(const h8*)p, b[q], part);
+                    part = mfma16(*(const h8*)(p + plane), b[q], part);
+                }
+                if constexpr (FE == S_F16) acc[rw][tb] = part;
+                else acc[rw][tb] += (float)bs[rw] * part;
+            }
+        }
+    }
+}
+
+template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK>
+__global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kernel(WideArgs a)
+{
+    static_assert(NWR * NWK == WQ_NW, "eight wavefronts");
+    constexpr int SLOT = TB * 4096;                       // bytes: 16 TB tokens x 128 columns
+    constexpr int NSLOT = NWR == 1 ? 1 : 2;
+    constexpr int XN = (4 * TB) / NWR > 0 ? (4 * TB) / NWR : 1;      // 1 KiB pieces of a chunk per wavefront
+    constexpr int PX = XN > 8 ? 1 : 2;                    // steps between a request for x and its LDS write
+    constexpr int D = RW >= 4 ? 2 : 4;                    // steps between a request for a stored tile and its use
+    static_assert((4 * TB) % NWR == 0, "the pieces of a chunk divide evenly over a range's wavefronts");
+    __shared__ uint32_t s_epoch;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 15, j = lane >> 4;
+    const int bid = blockIdx.x;
+    const int G = a.d_in / 128;
+    const int ntg = a.ntg;
+
+    uint32_t epoch_v = 0;
+    if constexpr (LOWRANK) {
+        if (tid == 0) epoch_v = ld_relaxed(&a.hdr[HDR_EPOCH]);
+        if (bid < a.nprod) {
+            // ===================================================================== producer
+            __builtin_amdgcn_s_setprio(3);
+            const int NRB = a.r / 16;
+            int u = bid;
+            const int rho = u % NRB; u /= NRB;
+            const int kc = u % a.kcn; u /= a.kcn;
+            const int tg = u % ntg, mem = u / ntg;
+            const int m0 = tg * TB * 16;
+            const int pa = G * kc / a.kcn, pb = G * (kc + 1) / a.kcn;
+            const int ka = pa + (pb - pa) * wave / WQ_NW, kb = pa + (pb - pa) * (wave + 1) / WQ_NW;
+            f4 acc[TB];
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) acc[tb] = f4{0.f, 0.f, 0.f, 0.f};
+            const void* A = wq_pick(a.A, mem);
+            const _Float16* As = wq_pick(a.A_scales, mem);
+            unsigned char* xs = eora_smem + wave * SLOT;
+            if (a.fa == S_F16) wq_produce<S_F16, TB>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
+            else if (a.fa == S_Q4S128) wq_produce<S_Q4S128, TB>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
+            else wq_produce<S_Q3S128, TB>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
+            if (tid == 0) {
+                s_epoch = epoch_v;
+                arrive(epoch_v, a.hdr, bid);
+            }
+            __syncthreads();                              // x is dead: the partial tiles go over it
+            f4* red = (f4*)eora_smem;                     // [wavefront][token block][lane]
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) red[(wave * TB + tb) * 64 + lane] = acc[tb];
+            __syncthreads();
+            if (wave < TB) {
+                const int tb = wave;
+                f4 v = red[tb * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < WQ_NW; ++w) v += red[(w * TB + tb) * 64 + lane];
+                // [member][token group][kc][token][r] pairs, one write-through store each
+                unsigned long long* dst = a.tpair + (((size_t)(mem * ntg + tg) * a.kcn + kc) * (16 * TB) + 16 * tb) * a.r + 16 * rho + n;
                 const float vs[4] = {v.x, v.y, v.z, v.w};
                 const unsigned long long tag = (unsigned long long)(s_epoch + 1) << 32;
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    if (4 * j + i < mt)
-                        __hip_atomic_store(&dst[(size_t)(4 * j + i) * a.r], tag | __builtin_bit_cast(uint32_t, vs[i]),
-                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                WTL_STAMP(2);
-                if (lane == 0) {
-                    __hip_atomic_store(&a.hdr[HDR_FLAGS0 + HDR_FLAGS_PER_BLOCK * yb + flag0 + u], s_epoch + 1, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                    check_in_finish(ci, a.hdr, gridDim.x);
-                }
+                    if (m0 + 16 * tb + 4 * j + i < a.M)
+                        __hip_atomic_store(&dst[(size_t)(4 * j + i) * a.r], tag | __builtin_bit_cast(uint32_t, vs[i]), __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
             }
             return;
         }
     }
 
     // ========================================================================= consumer
-    WTL_STAMP(0);
-    const int RBs = a.d_out / 16;
-    const int NTG = (yblocks + TB - 1) / TB;              // groups of TB token blocks
-    const int cidx = bid - nprod;
-    const int tg = cidx % NTG, rg = cidx / NTG;
-    const int m0 = tg * TB * 16;                          // first token of the group
-    const int Rw = rg * NWR + wr;
-    const bool active = Rw < RBs;                         // a ragged last row group: the wavefront only helps staging
-    const int R = active ? Rw : RBs - 1;
-    const Backbone bb{(const uint32_t*)a.w, a.w_scales, a.w_zeros, a.d_in / 128, a.d_in / a.group,
-                      (a.d_in / a.group + 7) / 8, a.group / 128};
-    const int GK = bb.G / NWK;                            // chunks = stored tiles per range; a multiple of 4
-    const int NQ = GK / 4;                                // quads per range
-    const int q0 = wk * NQ;                               // the range's first quad
-    unsigned char* xk = eora_smem + wk * 2 * SLOT;        // the range's two slots
-    // piece q of a chunk: token rows 4 q .. 4 q + 3, lane -> row 4 q + lane / 16, 16-byte piece lane % 16
-    const _Float16* xsrc[XN];
-    int xdst[XN];
-#pragma unroll
-    for (int i = 0; i < XN; ++i) {
-        const int trow = 4 * (wr + i * NWR) + (lane >> 4);
-        // rows beyond the tokens: all their lanes read one and the same valid piece (one cache line per request
-        // instead of sixteen; no divergent branch); their results are dropped
-        const bool live = m0 + trow < a.M;
-        xsrc[i] = a.x + (size_t)(live ? m0 + trow : m0) * a.d_in + (size_t)wk * GK * 128 + (live ? 8 * (lane & 15) : 0);
-        xdst[i] = (trow * 16 + ((lane & 15) ^ (trow & 15))) * 16;
-    }
-    // Workgroups walk their ranges from different starting chunks (quads rotated by rq, the tiles inside a quad
-    // by ri): the rows of x are a multiple of 4 KiB apart, so workgroups in step would all ask the same L2
-    // channel for the same chunk at the same time.
-    const int rot = cidx % GK, rq = rot >> 2, ri = rot & 3;
-    auto quad_at = [&](int qq) {                          // qq < 2 NQ
-        const int v = qq + rq;
-        return v >= NQ ? v - NQ : v;
-    };
-    auto chunk_at = [&](int step) {                       // steps past the end: the last one again
-        const int st = step < GK ? step : GK - 1;
-        return 4 * quad_at(st >> 2) + ((st + ri) & 3);
-    };
-    auto load_quad = [&](Quad<FM, 1>& qd, int qq) {       // register slot i holds tile (i + ri) % 4 of the quad
-        const int q = q0 + quad_at(qq < NQ ? qq : NQ - 1);
-        load_quad_meta<FM, 1>(qd, bb, R, q, lane);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const size_t tile = (size_t)R * bb.G + 4 * q + ((i + ri) & 3);
-            load_words<Fmt<FM>::WORDS>(qd.w[0][i], bb.w + (tile * 64 + lane) * Fmt<FM>::WORDS);
-        }
-    };
-    Quad<FM, 1> qb[2];
-    u4 xr[WQ_D][XN];
-#pragma unroll
-    for (int s = 0; s < WQ_D; ++s) {
-#pragma unroll
-        for (int i = 0; i < XN; ++i) xr[s][i] = *(const u4*)(xsrc[i] + chunk_at(s) * 128);
-    }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) load_quad(qb[h], h);
-    // B's first tile of this wavefront (its words do not depend on t)
-    constexpr int FEB = LOWRANK ? FE : S_F16;
-    const Factor fb{(const uint32_t*)a.B, a.B_scales, LOWRANK ? a.r / Fmt<FEB>::KT : 0};
-    FTile<FEB> bpre;
-    if constexpr (LOWRANK) load_ftile<FE>(bpre, fb, R, wk < fb.ntk ? wk : 0, lane);
-    if constexpr (LOWRANK) {
-        if (tid == 0) {
-            check_in_issue(ci, a.hdr, gbid);
-            s_epoch = ci.epoch;
-        }
-    }
-    // chunk 0 -> slot 0; its registers take chunk WQ_D
-#pragma unroll
-    for (int i = 0; i < XN; ++i) {
-        *(u4*)(xk + xdst[i]) = xr[0][i];
-        xr[0][i] = *(const u4*)(xsrc[i] + chunk_at(WQ_D) * 128);
-    }
-
-    WTL_STAMP(1);
-    f4 acc[TB];
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[tb] = f4{0.f, 0.f, 0.f, 0.f};
-    // this lane's activation fragments of a tile: 32 consecutive columns from 32 j, pieces 4 j .. 4 j + 3
-    int poff[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) poff[t] = (n * 16 + ((4 * j + t) ^ n)) * 16;
-
-    // a first look at the flags, requested before the last quads and examined after them: when the producers
-    // are done by then, the wait below costs no round trip
-    uint32_t early = 0;
-    for (int qi = 0; qi < NQ; qi += 2) {
-        if constexpr (LOWRANK && TB == 1) {
-            if (wave == 0 && qi + 2 >= NQ)
-                early = ld_relaxed(a.hdr + HDR_FLAGS0 + HDR_FLAGS_PER_BLOCK * tg + flag0 + (lane < units ? lane : units - 1));
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int qq = qi + h;
-            if (qq < NQ) {                                // uniform over the workgroup
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int c = 4 * qq + i;             // step = chunk of the range
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own LDS writes of chunk c done
-                    __builtin_amdgcn_s_barrier();
-                    // chunk c + 1 -> the slot everyone has just left; its registers take the chunk WQ_D further on
-                    const int s1 = (i + 1) % WQ_D;
-                    const int cx = chunk_at(c + 1 + WQ_D);
-#pragma unroll
-                    for (int k = 0; k < XN; ++k) {
-                        *(u4*)(xk + ((c + 1) & 1) * SLOT + xdst[k]) = xr[s1][k];
-                        xr[s1][k] = *(const u4*)(xsrc[k] + cx * 128);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    h8 b[4];
-                    const int ti = (i + ri) & 3;          // the tile's place in its quad: its zero-point nibble and scale
-                    decode_tile<FM>(qb[h].w[0][i], (qb[h].zq[0] >> (4 * ti)) & 0xFu, b);
-                    const unsigned long long s64 = qb[h].sc[0].x | ((unsigned long long)qb[h].sc[0].y << 32);
-                    const float sc = (float)__builtin_bit_cast(_Float16, (uint16_t)(s64 >> (16 * ti)));
-                    const unsigned char* xs = xk + (c & 1) * SLOT;
-#pragma unroll
-                    for (int tb = 0; tb < TB; ++tb) {
-                        const unsigned char* px = xs + tb * 4096;
-                        f4 part = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int t = 0; t < 4; ++t) part = mfma16(*(const h8*)(px + poff[t]), b[t], part);
-                        acc[tb] += sc * part;             // exact integers times x, scaled once per group in fp32
-                    }
-                }
-                // the quad's registers are free again: the request for the quad two on goes out last
-                __builtin_amdgcn_sched_barrier(0);
-                load_quad(qb[h], qq + 2);
-            }
-        }
-    }
-    __syncthreads();                                      // nobody reads x any more: the slots are reused below
-    WTL_STAMP(2);
-
-    // ---- low-rank continuation: acc[token][row] += t[token][:] . B[row][:] ----------------------------------
-    if constexpr (LOWRANK) {
-        // t (16 x r fp32 per token block) goes over the x slots, as many token blocks at a time as fit
-        float* ts = (float*)eora_smem;
-        const int tsz = 16 * a.r;                         // floats per token block
-        const int lds_floats = NWK * 2 * SLOT / 4 > tsz ? NWK * 2 * SLOT / 4 : tsz;
-        const int nb = lds_floats / tsz;                  // >= 1
-        const uint32_t epoch = s_epoch;
-        if (wave == 0) {
-            bool ok = true;
-            const bool seen = a.spin_limit >= 0 && TB == 1 && units <= 64 && __all(early == epoch + 1);   // a negative limit: every wait counts as expired (test hook)
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) {
-                const int yb = tg * TB + tb;
-                if (yb >= yblocks || !ok || seen) continue;
-                const uint32_t* flags = a.hdr + HDR_FLAGS0 + HDR_FLAGS_PER_BLOCK * yb + flag0;
-                bool up = false;
-                for (int spins = 0; spins <= a.spin_limit; ++spins) {
-                    bool all = true;
-                    for (int f = lane; f < units; f += 64) all = all && (ld_relaxed(&flags[f]) == epoch + 1);
-                    if (__all(all)) { up = true; break; }
-                    __builtin_amdgcn_s_sleep(2);
-                }
-                ok = up;
-            }
-            if (lane == 0) {
-                s_ok = ok ? 1u : 0u;
-                if (!ok) atomicOr(&a.hdr[HDR_ERROR], 1u);  // never expected: producers do not wait
-            }
-        }
-        __syncthreads();
-        WTL_STAMP(3);
-        if (s_ok) {
-            constexpr int KTB = Fmt<FE>::KT, NMF = KTB / 32;
-            bool good_all = true;
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) {
-                if (tb % nb == 0) {                       // uniform over the workgroup: the next nb token blocks' t
-                    if (tb > 0) __syncthreads();          // the previous ones have been used
-                    for (int q = 0; q < nb && tb + q < TB; ++q) {
-                        const int yq = tg * TB + tb + q;
-                        if (yq >= yblocks) break;
-                        const int mq = a.M - 16 * yq < 16 ? a.M - 16 * yq : 16;
-                        // Every thread adds the kcn partials of four elements of t, in a fixed order.  Ordinary
-                        // cached loads first: the flags are up, so the stores were issued long ago and have all
-                        // but certainly landed; the tags say whether that held, and a thread that finds an old
-                        // tag reads again past the caches until it does (bounded).
-                        const int T = mq * a.r;
-                        for (int e = 4 * tid; e < T; e += 4 * NW * 64) {
-                            const unsigned long long* p = a.tpair + ((size_t)(yq * a.kcn) * 16) * a.r + e;     // row e / r, column e % r
-                            float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f;
-                            uint32_t bad = 0;
-#pragma unroll 4
-                            for (int kc = 0; kc < a.kcn; ++kc) {                       // fixed order
-                                const uint2* pk = (const uint2*)(p + (size_t)kc * 16 * a.r);
-                                const uint2 p0 = pk[0], p1 = pk[1], p2 = pk[2], p3 = pk[3];      // .x value, .y tag
-                                bad |= (p0.y ^ (epoch + 1)) | (p1.y ^ (epoch + 1)) | (p2.y ^ (epoch + 1)) | (p3.y ^ (epoch + 1));
-                                v0 += __builtin_bit_cast(float, p0.x);
-                                v1 += __builtin_bit_cast(float, p1.x);
-                                v2 += __builtin_bit_cast(float, p2.x);
-                                v3 += __builtin_bit_cast(float, p3.x);
-                            }
-                            bool good = bad == 0;
-                            for (int spins = 0; !good && spins <= a.spin_limit; ++spins) {
-                                bad = 0;
-                                float w[4] = {0.f, 0.f, 0.f, 0.f};
-                                for (int kc = 0; kc < a.kcn; ++kc) {
-#pragma unroll
-                                    for (int c = 0; c < 4; ++c) {
-                                        const unsigned long long pr = __hip_atomic_load(p + (size_t)kc * 16 * a.r + c, __ATOMIC_RELAXED,
-                                                                                        __HIP_MEMORY_SCOPE_AGENT);
-                                        bad |= (uint32_t)(pr >> 32) ^ (epoch + 1);
-                                        w[c] += __builtin_bit_cast(float, (uint32_t)pr);
-                                    }
-                                }
-                                good = bad == 0;
-                                v0 = w[0]; v1 = w[1]; v2 = w[2]; v3 = w[3];
-                            }
-                            good_all = good_all && good;
-                            if (a.adapter) {   // several adapters side by side: a token row keeps its own adapter's columns
-                                if (a.adapter[16 * yq + e / a.r] != (e % a.r) / a.r_per) v0 = v1 = v2 = v3 = 0.f;
-                            }
-                            *(f4*)(ts + q * tsz + e) = f4{v0, v1, v2, v3};
-                        }
-                    }
-                    __syncthreads();
-                }
-                const int yb = tg * TB + tb;
-                if (yb < yblocks) {
-                    const int mt = a.M - 16 * yb < 16 ? a.M - 16 * yb : 16;
-                    const float* trow = ts + (tb % nb) * tsz + (n < mt ? n : 0) * a.r + (KTB / 4) * j;
-                    for (int g = wk; g < fb.ntk; g += NWK) {      // the row block's wavefronts share B's tiles
-                        FTile<FE> cur;
-                        if (g == wk) cur = bpre;
-                        else load_ftile<FE>(cur, fb, R, g, lane);
-                        h8 b[NMF];
-                        decode_tile<FE>(cur.w, 8u, b);
-                        f4 part = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                        for (int q = 0; q < NMF; ++q) {
-                            const float* p = trow + g * KTB + 8 * q;
-                            const f4 v0 = *(const f4*)p, v1 = *(const f4*)(p + 4);
-                            const float e0[4] = {v0.x, v0.y, v0.z, v0.w}, e1[4] = {v1.x, v1.y, v1.z, v1.w};
-                            h8 hi, lo;
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) {
-                                const _Float16 h0 = (_Float16)e0[i], h1 = (_Float16)e1[i];
-                                hi[i] = h0;
-                                hi[4 + i] = h1;
-                                lo[i] = (_Float16)(e0[i] - (float)h0);
-                                lo[4 + i] = (_Float16)(e1[i] - (float)h1);
-                            }
-                            part = mfma16(hi, b[q], part);
-                            part = mfma16(lo, b[q], part);
-                        }
-                        acc[tb] += (float)cur.sc * part;
-                    }
-                }
-            }
-            if (!good_all) atomicOr(&a.hdr[HDR_ERROR], 1u);            // never expected
-        }
-        if constexpr (NWK > 1) __syncthreads();           // t has been used: the LDS is reused below
-    }
-
-    WTL_STAMP(4);
-    // ---- add the ranges' accumulators in a fixed order, convert, store ---------------------------------------
-    if constexpr (NWK > 1) {
-        f4* red = (f4*)eora_smem;                         // [range - 1][row block][token block][lane]
-        if (wk > 0) {
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) red[(((wk - 1) * NWR + wr) * TB + tb) * 64 + lane] = acc[tb];
-        }
-        __syncthreads();
-        if (wk == 0) {
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) {
-#pragma unroll
-                for (int k2 = 1; k2 < NWK; ++k2) acc[tb] += red[(((k2 - 1) * NWR + wr) * TB + tb) * 64 + lane];
-            }
-        }
-    }
-    if (wk == 0 && active) {
-        // register i is token row 4*j+i of the token block, output column n of the row block
-#pragma unroll
-        for (int tb = 0; tb < TB; ++tb) {
-            const f4 v = acc[tb];
-            const float vs[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int m = m0 + 16 * tb + 4 * j + i;
-                if (m < a.M) a.y[(size_t)m * a.d_out + R * 16 + n] = (_Float16)vs[i];
-            }
-        }
-    }
-    WTL_STAMP(5);
-    if constexpr (LOWRANK) {
-        if (tid == 0) check_in_finish(ci, a.hdr, gridDim.x);
-    }
-}
-
-// one linear: the arguments sit at fixed places of the kernel's argument block
-template <int FM, int FA, int FE, int NWR, int NWK, int TB>
-__global__ __launch_bounds__(NWR * NWK * 64, TB == 1 ? 4 : 2) void wide_q_kernel(FusedArgs a)
-{
-    wide_q_body<FM, FA, FE, NWR, NWK, TB>(a, blockIdx.x, blockIdx.x, 0);
-}
-
-// several linears that share x: each workgroup first finds the member it works for (uniform; one more dependent
-// scalar load at the start than the kernel above, which is why that one is kept).  The members' workgroups
-// follow one another, each member's producers before its consumers, so a waiting workgroup's producers always
-// have lower indices.
-template <int FM, int FA, int FE, int NWR, int NWK, int TB>
-__global__ __launch_bounds__(NWR * NWK * 64, TB == 1 ? 4 : 2) void wide_q_group_kernel(WideGroupArgs grp)
-{
+    const int wr = wave % NWR, wk = wave / NWR;
     int mem = 0;
 #pragma unroll
     for (int i = 1; i < 4; ++i)
-        if (i < grp.n && (int)blockIdx.x >= grp.first[i]) mem = i;
-    wide_q_body<FM, FA, FE, NWR, NWK, TB>(grp.m[mem], blockIdx.x, (int)blockIdx.x - grp.first[mem], grp.flag0[mem]);
+        if (i < a.n && bid >= a.first[i]) mem = i;
+    // workgroups that read the same stored tiles (the token groups of one row group) sit eight apart: same XCD, same L2
+    const int RBs = wq_pick(a.d_out, mem) / 16;
+    int rg = bid - wq_pick(a.first, mem), tg = 0, part_id = 0;
+    if (a.S > 1 || ntg > 1) {
+        // workgroups that read the same stored tiles (the token groups of one row group) sit eight apart: same XCD, same L2
+        const int nrg = (RBs + NWR * RW - 1) / (NWR * RW);
+        part_id = rg / (nrg * ntg);                       // which part of the contraction (S > 1)
+        const int c = rg - part_id * nrg * ntg;
+        const int oct = c / (8 * ntg), in_oct = c - oct * 8 * ntg;
+        const int width = nrg - 8 * oct < 8 ? nrg - 8 * oct : 8;     // row groups of this octet
+        tg = in_oct / width;
+        rg = 8 * oct + in_oct - tg * width;
+    }
+    const int m0 = tg * TB * 16;
+    const int ga0 = a.S > 1 ? G * part_id / a.S : 0, ga1 = a.S > 1 ? G * (part_id + 1) / a.S : G;         // this workgroup's tiles of a row block
+    int R[RW];
+#pragma unroll
+    for (int rw = 0; rw < RW; ++rw) {
+        const int Rw = rg * NWR * RW + wr * RW + rw;
+        R[rw] = Rw < RBs ? Rw : RBs - 1;                  // a ragged last row group: computed on the last block, not stored
+    }
+    const uint32_t* const w = (const uint32_t*)wq_pick(a.w, mem);
+    const _Float16* const w_scales = wq_pick(a.w_scales, mem);
+    const uint32_t* const w_zeros = wq_pick(a.w_zeros, mem);
+    const int gdiv = a.group / 128, NG = a.ng, NGW = (NG + 7) / 8;
+    // quantisation group of tile k: k / gdiv by a multiplication and a correction, without a branch
+    const uint32_t gmagic = a.gmagic;
+    auto group_of = [&](int k) {
+        const uint32_t q = (uint32_t)(((unsigned long long)(uint32_t)k * gmagic) >> 31);
+        return (int)(q * (uint32_t)gdiv > (uint32_t)k ? q - 1 : q);
+    };
+    struct Pre { uint32_t w[Fmt<FM>::WORDS]; };
+    Pre pre[D][RW];
+    unsigned char* const xk = eora_smem + wk * NSLOT * SLOT;
+    size_t xsrc[XN];
+    int xdst[XN];
+#pragma unroll
+    for (int i = 0; i < XN; ++i) {
+        xsrc[i] = wq_xrow(a, m0, wr + i * NWR, lane);
+        xdst[i] = wq_xdst(wr + i * NWR, lane);
+    }
+    u4 xr[PX][XN];
+    f4 acc[RW][TB];
+#pragma unroll
+    for (int rw = 0; rw < RW; ++rw)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) acc[rw][tb] = f4{0.f, 0.f, 0.f, 0.f};
+    int poff[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) poff[t] = wq_frag(n, 4 * j + t);
+    // Group scales and zero-point words of the workgroup's rows sit in LDS behind the slots, [group][row] and
+    // [word][row]: a scale is two bytes of a 64-byte row segment, and sixteen rows' worth of it per tile from global
+    // memory fetched sixteen cache lines per tile (33.6 us for a gate+up launch at 64 tokens, bare).
+    constexpr int ROWS = NWR * RW * 16;
+    uint16_t* const m_sc = (uint16_t*)(eora_smem + NWK * NSLOT * SLOT);
+    uint32_t* const m_zq = (uint32_t*)(m_sc + (size_t)ROWS * a.seg);
+
+    // the contraction in segments of at most a.seg tiles (one for every usual shape): their scales fit the LDS
+    for (int ga = ga0; ga < ga1; ga += a.seg) {
+    const int gl = ga1 - ga < a.seg ? ga1 - ga : a.seg;
+    const int ka = ga + gl * wk / NWK, len = ga + gl * (wk + 1) / NWK - ka;   // this range's
+    const int steps = (gl + NWK - 1) / NWK;
+    auto tile_at = [&](int s) {                           // tile (= chunk of x) of step s of this range
+        const int k = ka + (s < len ? s : (len > 0 ? len - 1 : 0));
+        return k < G - 1 ? k : G - 1;
+    };
+    auto load_tile = [&](Pre& p, int rw, int s) {
+        load_words<Fmt<FM>::WORDS>(p.w, w + (((size_t)R[rw] * G + tile_at(s)) * 64 + lane) * Fmt<FM>::WORDS);
+    };
+    auto load_x = [&](u4 (&v)[XN], int s) {
+        const _Float16* p = a.x + (size_t)tile_at(s) * 128;
+#pragma unroll
+        for (int i = 0; i < XN; ++i) v[i] = *(const u4*)(p + xsrc[i]);
+    };
+    const int g_lo = group_of(ga), ng = group_of(ga + gl - 1) - g_lo + 1, z_lo = g_lo >> 3, nz = ((g_lo + ng - 1) >> 3) - z_lo + 1;
+    if (ga > ga0) __syncthreads();                        // the previous segment's slots and scales are dead
+    // All requests of the start before the first wait, the scales' first (loads return in the order of their requests).
+    // Thread -> row tid % ROWS, pieces from tid / ROWS on: no division, and consecutive threads write consecutive rows.
+    constexpr int TPR = WQ_NT / ROWS;
+    const int mrow = tid % ROWS, mq = tid / ROWS, mblk = rg * NWR * RW + (mrow >> 4);
+    const size_t msrc = (size_t)(mblk < RBs ? mblk : RBs - 1) * 16 + (mrow & 15);       // a ragged last row group: the last block again
+    const uint16_t* const ps = (const uint16_t*)w_scales + msrc * NG + g_lo;
+    const uint32_t* const pz = w_zeros + msrc * NGW + z_lo;
+    const bool by8 = ((NG | g_lo | ng) & 7) == 0;         // eight scales in one aligned 16-byte load
+    u4 ms = {0u, 0u, 0u, 0u};
+    if (by8) {
+        ms = *(const u4*)(ps + (8 * mq < ng ? 8 * mq : 0));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ms[i] = ps[mq + i * TPR < ng ? mq + i * TPR : 0];
+    }
+    const uint32_t mz = pz[mq < nz ? mq : 0];
+#pragma unroll
+    for (int s = 0; s < PX; ++s) load_x(xr[s], s);
+#pragma unroll
+    for (int s = 0; s < D; ++s)
+#pragma unroll
+        for (int rw = 0; rw < RW; ++rw) load_tile(pre[s][rw], rw, s);
+    if (by8) {
+        if (8 * mq < ng) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m_sc[(8 * mq + i) * ROWS + mrow] = (uint16_t)(ms[i >> 1] >> (16 * (i & 1)));
+        }
+        for (int g = 8 * (mq + TPR); g < ng; g += 8 * TPR) {
+            const u4 v = *(const u4*)(ps + g);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m_sc[(g + i) * ROWS + mrow] = (uint16_t)(v[i >> 1] >> (16 * (i & 1)));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (mq + i * TPR < ng) m_sc[(mq + i * TPR) * ROWS + mrow] = (uint16_t)ms[i];
+        for (int g = mq + 4 * TPR; g < ng; g += TPR) m_sc[g * ROWS + mrow] = ps[g];
+    }
+    if (mq < nz) m_zq[mq * ROWS + mrow] = mz;
+    for (int z = mq + TPR; z < nz; z += TPR) m_zq[z * ROWS + mrow] = pz[z];
+    if constexpr (LOWRANK) {
+        if (tid == 0 && ga == ga0) {
+            s_epoch = epoch_v;
+            arrive(epoch_v, a.hdr, bid);
+        }
+    }
+    if constexpr (NWR > 1) {                              // chunk 0 -> slot 0
+#pragma unroll
+        for (int i = 0; i < XN; ++i) *(u4*)(xk + xdst[i]) = xr[0][i];
+        load_x(xr[0], PX);
+    } else {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();                     // the scales are visible (NWR > 1: with the first chunk)
+    }
+    auto step = [&](auto itag, int s) {
+        constexpr int i = decltype(itag)::value;          // s % D
+        const unsigned char* xs = xk;
+        if constexpr (NWR > 1) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own LDS writes of chunk s done
+            __builtin_amdgcn_s_barrier();                 // chunk s is visible, everyone has left the other slot
+            xs = xk + (i & 1) * SLOT;
+#pragma unroll
+            for (int q = 0; q < XN; ++q) *(u4*)(xk + ((i + 1) & 1) * SLOT + xdst[q]) = xr[(i + 1) % PX][q];
+            load_x(xr[(i + 1) % PX], s + 1 + PX);
+        } else {
+#pragma unroll
+            for (int q = 0; q < XN; ++q) *(u4*)(xk + xdst[q]) = xr[i % PX][q];
+            load_x(xr[i % PX], s + PX);
+        }
+        asm volatile("" ::: "memory");                    // (fragments are read by other lanes than the ones that wrote them)
+        __builtin_amdgcn_sched_barrier(0);
+        if (s < len) {                                    // uniform over the wavefront; no global load inside
+            h8 b[RW][4];
+            f4 part[RW][TB];
+            const int grp = group_of(ka + s), zs = 4 * (grp & 7);
+            const int lrow = wr * RW * 16 + n;
+            float sc[RW];
+#pragma unroll
+            for (int rw = 0; rw < RW; ++rw) {
+                sc[rw] = (float)__builtin_bit_cast(_Float16, m_sc[(grp - g_lo) * ROWS + lrow + 16 * rw]);
+                decode_tile<FM>(pre[i][rw].w, (m_zq[((grp >> 3) - z_lo) * ROWS + lrow + 16 * rw] >> zs) & 0xFu, b[rw]);
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) part[rw][tb] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) {
+                    const h8 xf = *(const h8*)(xs + tb * 4096 + poff[t]);
+#pragma unroll
+                    for (int rw = 0; rw < RW; ++rw) part[rw][tb] = mfma16(xf, b[rw][t], part[rw][tb]);
+                }
+#pragma unroll
+            for (int rw = 0; rw < RW; ++rw) {
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) acc[rw][tb] += sc[rw] * part[rw][tb];
+            }
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int rw = 0; rw < RW; ++rw) load_tile(pre[i][rw], rw, s + D);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // D steps at a time without a branch around a load, so that the compiler knows how many requests follow the one it
+    // waits for (with a test per step it waits for all of them); the last up to D - 1 apart
+    int s0 = 0;
+    for (; s0 + D <= steps; s0 += D) {
+        step(std::integral_constant<int, 0>{}, s0);
+        step(std::integral_constant<int, 1>{}, s0 + 1);
+        if constexpr (D == 4) {
+            step(std::integral_constant<int, 2>{}, s0 + 2);
+            step(std::integral_constant<int, 3>{}, s0 + 3);
+        }
+    }
+    if (s0 < steps) step(std::integral_constant<int, 0>{}, s0);
+    if constexpr (D == 4) {
+        if (s0 + 1 < steps) step(std::integral_constant<int, 1>{}, s0 + 1);
+        if (s0 + 2 < steps) step(std::integral_constant<int, 2>{}, s0 + 2);
+    }
+    }
+    __syncthreads();                                      // nobody reads x any more: the LDS is reused below
+
+    // ---- low-rank continuation: acc[token][row] += t[token][:] . B[row][:] ----------------------------------
+    if constexpr (LOWRANK) {
+        // with S > 1 every part takes its share [g0, g1) of B's tiles (and reads those columns of t only)
+        const int KTb = a.fe == S_F16 ? 32 : a.fe == S_Q4S64 ? 64 : 128, ntk = a.r / KTb;
+        const int g0 = a.S > 1 ? ntk * part_id / a.S : 0, g1 = a.S > 1 ? ntk * (part_id + 1) / a.S : ntk;
+        if (g0 < g1) {                                    // (uniform over the workgroup)
+            if (a.spin_limit < 0) {                       // test hook: every wait counts as expired
+                if (tid == 0) atomicOr(&a.hdr[HDR_ERROR], 1u);
+            } else {
+                const int P = (g1 - g0) * KTb / 8, tbs = P * 272, plane = TB * tbs;
+                const uint32_t want = s_epoch + 1;
+                // the first tiles of B on their way before t is read (their words do not depend on it)
+                const Factor fb{(const uint32_t*)wq_pick(a.B, mem), wq_pick(a.B_scales, mem), ntk};
+                uint32_t bw[RW][4];
+                _Float16 bs[RW];
+                if (a.fe == S_F16) wq_up_load<S_F16, RW>(fb, R, g0 + wk, lane, bw, bs);
+                else if (a.fe == S_Q4S128) wq_up_load<S_Q4S128, RW>(fb, R, g0 + wk, lane, bw, bs);
+                else if (a.fe == S_Q4S64) wq_up_load<S_Q4S64, RW>(fb, R, g0 + wk, lane, bw, bs);
+                else wq_up_load<S_Q3S128, RW>(fb, R, g0 + wk, lane, bw, bs);
+                const int rows = a.M - m0 < 16 * TB ? a.M - m0 : 16 * TB;
+                const unsigned long long* const src = a.tpair + (size_t)(mem * ntg + tg) * a.kcn * (16 * TB) * a.r + g0 * KTb;
+                bool good_all = true;
+                for (int e = tid; e < rows * P; e += WQ_NT) {
+                    const int tok = e / P, p = e - tok * P;
+                    const unsigned long long* const q = src + (size_t)tok * a.r + 8 * p;
+                    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    uint32_t bad = 0;
+#pragma unroll 2
+                    for (int kc = 0; kc < a.kcn; ++kc) {  // fixed order; ordinary cached loads, the tags say whether they were late enough
+                        const u4* pk = (const u4*)(q + (size_t)kc * (16 * TB) * a.r);
+#pragma unroll
+                        for (int h = 0; h < 4; ++h) {
+                            const u4 pr = pk[h];
+                            const uint32_t e0 = pr[0], t0 = pr[1], e1 = pr[2], t1 = pr[3];
+                            bad |= (t0 ^ want) | (t1 ^ want);
+                            v[2 * h] += __builtin_bit_cast(float, e0);
+                            v[2 * h + 1] += __builtin_bit_cast(float, e1);
+                        }
+                    }
+                    for (int spins = 0; bad != 0 && spins <= a.spin_limit; ++spins) {
+                        bad = 0;
+#pragma unroll
+                        for (int h = 0; h < 8; ++h) v[h] = 0.f;
+                        for (int kc = 0; kc < a.kcn; ++kc)
+#pragma unroll
+                            for (int h = 0; h < 8; ++h) {
+                                const unsigned long long pr = __hip_atomic_load(q + (size_t)kc * (16 * TB) * a.r + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                bad |= (uint32_t)(pr >> 32) ^ want;
+                                v[h] += __builtin_bit_cast(float, (uint32_t)pr);
+                            }
+                    }
+                    good_all = good_all && bad == 0;
+                    // several adapters side by side: a token row keeps its own adapter's columns (r_per is a multiple of 8)
+                    const bool keep = !a.adapter || a.adapter[m0 + tok] == (g0 * KTb + 8 * p) / a.r_per;
+                    h8 hi, lo;
+#pragma unroll
+                    for (int h = 0; h < 8; ++h) {
+                        const float t = keep ? v[h] : 0.f;
+                        hi[h] = (_Float16)t;
+                        lo[h] = (_Float16)(t - (float)hi[h]);
+                    }
+                    unsigned char* const d = eora_smem + (tok >> 4) * tbs + p * 272 + 16 * (tok & 15);
+                    *(h8*)d = hi;
+                    *(h8*)(d + plane) = lo;
+                }
+                if (!good_all) atomicOr(&a.hdr[HDR_ERROR], 1u);       // never expected: producers do not wait
+                __syncthreads();
+                if (a.fe == S_F16) wq_up<S_F16, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
+                else if (a.fe == S_Q4S128) wq_up<S_Q4S128, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
+                else if (a.fe == S_Q4S64) wq_up<S_Q4S64, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
+                else wq_up<S_Q3S128, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
+                __syncthreads();                          // t has been used: the LDS is reused below
+            }
+        }
+    }
+
+    // ---- add the ranges' accumulators in a fixed order, convert, store ---------------------------------------
+    // through LDS as [range][token][row], so that a thread adds and stores eight consecutive rows of a token (rows of
+    // 4 bytes more than a multiple of 16 banks keep the four token rows of a store apart)
+    constexpr int RS = ROWS + 4;
+    float* const red = (float*)eora_smem;
+#pragma unroll
+    for (int rw = 0; rw < RW; ++rw)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) {
+            // register i is token row 4 j + i of the token block, output column n of the row block
+            float* const d = red + ((size_t)wk * 16 * TB + 16 * tb + 4 * j) * RS + (wr * RW + rw) * 16 + n;
+            const f4 v = acc[rw][tb];
+            d[0] = v.x;
+            d[RS] = v.y;
+            d[2 * RS] = v.z;
+            d[3 * RS] = v.w;
+        }
+    __syncthreads();
+    _Float16* const y = wq_pick(a.y, mem);
+    const int d_out = RBs * 16;
+    for (int e = tid; e < 16 * TB * ROWS / 8; e += WQ_NT) {
+        const int tok = e / (ROWS / 8), r8 = 8 * (e % (ROWS / 8));
+        const int m = m0 + tok, o = rg * ROWS + r8;
+        if (m >= a.M || o >= d_out) continue;
+        const float* p = red + (size_t)tok * RS + r8;
+        f4 v0 = *(const f4*)p, v1 = *(const f4*)(p + 4);
+#pragma unroll
+        for (int k2 = 1; k2 < NWK; ++k2) {
+            v0 += *(const f4*)(p + (size_t)k2 * 16 * TB * RS);
+            v1 += *(const f4*)(p + (size_t)k2 * 16 * TB * RS + 4);
+        }
+        if (a.S > 1) {
+            float* const q = a.ypart + (size_t)a.S * a.M * wq_pick(a.ycol, mem) + ((size_t)part_id * a.M + m) * d_out + o;
+            *(f4*)q = v0;
+            *(f4*)(q + 4) = v1;
+        } else {
+            *(h8*)(y + (size_t)m * d_out + o) = h8{(_Float16)v0[0], (_Float16)v0[1], (_Float16)v0[2], (_Float16)v0[3],
+                                                   (_Float16)v1[0], (_Float16)v1[1], (_Float16)v1[2], (_Float16)v1[3]};
+        }
+    }
+    if constexpr (LOWRANK) {
+        if (bid == (int)gridDim.x - 1 && wave == WQ_NW - 1) {
+            if (!advance_epoch(s_epoch, a.hdr, gridDim.x, lane, a.spin_limit) && lane == 0) atomicOr(&a.hdr[HDR_ERROR], 1u);
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
-struct WideCfg { int nwr, nwk, tb; };
-
-// the split of a workgroup into row blocks and ranges, and the token blocks per workgroup, for a shape
-static bool pick_wide(int M, int d_in, int d_out, int r, WideCfg* out)
+// y = fp16(sum over the S parts, in order); one launch for all members
+__global__ __launch_bounds__(256) void wide_q_sum_kernel(WideArgs a)
 {
-    if (M <= 4 || d_in % 512 != 0) return false;
-    const int yblocks = (M + 15) / 16, rbs = d_out / 16;
-    // More row blocks per workgroup first: x is fetched once per workgroup, and that traffic (workgroups x 16
-    // tokens x d_in) is what bounds these launches.  Measured on the 8B shapes: with the low-rank term half as
-    // many workgroups as compute units still win; the bare layer wants the chip filled.
-    static const int cand[4][2] = {{4, 2}, {2, 4}, {1, 8}, {1, 4}};
-    for (int c = 0; c < 4; ++c) {
-        const int nwr = cand[c][0], nwk = cand[c][1];
-        if (d_in % (512 * nwk) != 0) continue;
-        const int need = r > 0 ? 128 : (c == 0 ? 192 : 256);
-        const int groups = (rbs + nwr - 1) / nwr;
-        if (groups * yblocks >= need) {
-            // several token blocks per workgroup (a stored tile is decoded once for all of them, and the weights
-            // cross from L2 once per workgroup instead of once per token block) as long as the chip stays filled
-            // (192 workgroups, one per compute unit at their register count; measured at 64 tokens on the 8B
-            // shapes: the gate projection 39.8 -> 31.9 us with four token blocks per workgroup and 224 workgroups,
-            // the 4096-row linears lose with 128)
-            int tb = 1;
-            if (c == 0) {
-                if (yblocks >= 4 && groups * ((yblocks + 3) / 4) >= 192) tb = 4;
-                else if (yblocks >= 2 && groups * ((yblocks + 1) / 2) >= 192) tb = 2;
-            }
-            *out = {nwr, nwk, tb};
-            return true;
+    int mem = 0, b = blockIdx.x;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int nb = (int)(((size_t)a.M * a.d_out[i] / 8 + 255) / 256);
+        if (mem == i && i + 1 < a.n && b >= nb) {
+            b -= nb;
+            mem = i + 1;
         }
     }
-    return false;                                         // too few rows to fill the chip this way
-}
-
-bool wide_q_fits(int M, int d_in, int d_out, int r)
-{
-    WideCfg c;
-    return r <= 512 && pick_wide(M, d_in, d_out, r, &c);
-}
-
-template <int NWR, int TB>
-static int wide_blocks(const FusedArgs& a, bool lowrank)
-{
-    const int yblocks = (a.M + 15) / 16;
-    const int nprod = lowrank ? (a.r / 16) * a.kcn * yblocks : 0;
-    const int nrg = (a.d_out / 16 + NWR - 1) / NWR;
-    return nrg * ((yblocks + TB - 1) / TB) + nprod;
-}
-
-template <int FM, int FA, int FE, int NWR, int NWK, int TB>
-static hipError_t launch_wide_one(const FusedArgs* members, int n, hipStream_t stream)
-{
-    const FusedArgs& a = members[0];
-    const size_t xb = (size_t)NWK * 2 * TB * 4096, tb = (size_t)16 * a.r * 4;
-    const size_t lds = xb > tb ? xb : tb;
-    note_launch("wide_q FM=%d FA=%d NWR=%d NWK=%d TB=%d n=%d", FM, FA, NWR, NWK, TB, n);
-    if (n == 1) {
-        auto kern1 = wide_q_kernel<FM, FA, FE, NWR, NWK, TB>;
-        if (lds > 48 * 1024) {
-            hipError_t e = hipFuncSetAttribute((const void*)kern1, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-        }
-        hipLaunchKernelGGL(kern1, dim3(wide_blocks<NWR, TB>(a, FA != S_NONE)), dim3(NWR * NWK * 64), lds, stream, a);
-        return hipGetLastError();
+    const size_t count = (size_t)a.M * wq_pick(a.d_out, mem);
+    const size_t e = 8 * ((size_t)b * 256 + threadIdx.x);
+    if (e >= count) return;
+    const float* p = a.ypart + (size_t)a.S * a.M * wq_pick(a.ycol, mem) + e;
+    f4 v0 = *(const f4*)p, v1 = *(const f4*)(p + 4);
+    for (int s = 1; s < a.S; ++s) {
+        v0 += *(const f4*)(p + s * count);
+        v1 += *(const f4*)(p + s * count + 4);
     }
-    auto kern = wide_q_group_kernel<FM, FA, FE, NWR, NWK, TB>;
+    *(h8*)(wq_pick(a.y, mem) + e) = h8{(_Float16)v0[0], (_Float16)v0[1], (_Float16)v0[2], (_Float16)v0[3],
+                                       (_Float16)v1[0], (_Float16)v1[1], (_Float16)v1[2], (_Float16)v1[3]};
+}
+
+// ------------------------------------------------------------------------------------------------
+template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK>
+static hipError_t launch_wide_one(WideArgs a, hipStream_t stream)
+{
+    constexpr int NSLOT = NWR == 1 ? 1 : 2;
+    constexpr int ROWS = NWR * RW * 16;
+    const size_t slots = (size_t)NWK * NSLOT * TB * 4096;
+    // tiles whose scales (2 bytes a row) and zero-point words (4 bytes a row and eight groups, one more at either end) fit
+    const int G = a.d_in / 128, gdiv = a.group / 128;
+    size_t fit = (WQ_LDS_MAX - slots) / ROWS;
+    fit = fit > 16 ? (fit - 16) * 2 / 5 : 0;
+    if (fit < 8) return hipErrorInvalidValue;
+    a.seg = (int)(fit < (size_t)G ? fit & ~(size_t)7 : G);
+    size_t lds = slots + (size_t)ROWS * a.seg * 2 + (size_t)ROWS * (a.seg / 8 + 2) * 4;
+    a.ng = G / gdiv;
+    a.gmagic = (uint32_t)((0x80000000ull + gdiv - 1) / gdiv);
+    const size_t red = (size_t)NWK * 16 * TB * (ROWS + 4) * 4, prod = (size_t)WQ_NW * TB * 4096, t = (size_t)2 * TB * (a.r / 8) * 272;
+    lds = lds > red ? lds : red;
+    if (LOWRANK) lds = lds > prod ? lds : prod;
+    if (LOWRANK) lds = lds > t ? lds : t;
+    auto kern = wide_q_kernel<FM, TB, RW, NWR, NWK, LOWRANK>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    WideGroupArgs g{};
-    g.n = n;
-    int total = 0;
-    const int units = (FA != S_NONE) ? (a.r / 16) * a.kcn : 0;
+    int total = a.nprod;
     for (int i = 0; i < 4; ++i) {
-        g.m[i] = members[i < n ? i : 0];
-        g.first[i] = total;
-        g.flag0[i] = (i < n ? i : 0) * units;
-        if (i < n) total += wide_blocks<NWR, TB>(members[i], FA != S_NONE);
+        a.first[i] = total;
+        a.ycol[i] = i > 0 && i < a.n ? a.ycol[i - 1] + a.d_out[i - 1] : 0;
+        if (i < a.n) total += (a.d_out[i] / 16 + NWR * RW - 1) / (NWR * RW) * a.ntg * a.S;
     }
-    hipLaunchKernelGGL(kern, dim3(total), dim3(NWR * NWK * 64), lds, stream, g);
+    note_launch("wide_q FM=%d FA=%d NWR=%d NWK=%d TB=%d n=%d", FM, a.fa, NWR, NWK, TB, a.n);
+    hipLaunchKernelGGL(kern, dim3(total), dim3(WQ_NT), lds, stream, a);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || a.S == 1) return e;
+    int blocks = 0;
+    for (int i = 0; i < a.n; ++i) blocks += (int)(((size_t)a.M * a.d_out[i] / 8 + 255) / 256);
+    hipLaunchKernelGGL(wide_q_sum_kernel, dim3(blocks), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
-// one configuration for all members: chosen for the rows of all of them together
-static bool pick_wide_group(const FusedArgs* members, int n, WideCfg* c)
+template <int FM, int TB, bool LOWRANK>
+static hipError_t launch_wide_cfg(const WideArgs& a, int cfg, hipStream_t stream)
 {
-    int rows = 0;
-    for (int i = 0; i < n; ++i) rows += members[i].d_out;
-    return pick_wide(members[0].M, members[0].d_in, rows, members[0].r, c);
-}
-
-template <int FM, int FA, int FE>
-static hipError_t launch_wide_cfg(const FusedArgs* members, int n, hipStream_t stream)
-{
-    WideCfg c;
-    if (!pick_wide_group(members, n, &c)) return hipErrorInvalidValue;
-    if (c.nwr == 4 && c.tb == 4) return launch_wide_one<FM, FA, FE, 4, 2, 4>(members, n, stream);
-    if (c.nwr == 4 && c.tb == 2) return launch_wide_one<FM, FA, FE, 4, 2, 2>(members, n, stream);
-    if (c.nwr == 4) return launch_wide_one<FM, FA, FE, 4, 2, 1>(members, n, stream);
-    if (c.nwr == 2) return launch_wide_one<FM, FA, FE, 2, 4, 1>(members, n, stream);
-    if (c.nwk == 8) return launch_wide_one<FM, FA, FE, 1, 8, 1>(members, n, stream);
-    return launch_wide_one<FM, FA, FE, 1, 4, 1>(members, n, stream);
+    switch (cfg) {
+        case 0: return launch_wide_one<FM, TB, 2, 4, 2, LOWRANK>(a, stream);
+        case 1: return launch_wide_one<FM, TB, 1, 4, 2, LOWRANK>(a, stream);
+        case 2: return launch_wide_one<FM, TB, 1, 2, 4, LOWRANK>(a, stream);
+        default: return launch_wide_one<FM, TB, 1, 1, 8, LOWRANK>(a, stream);
+    }
 }
 
 template <int FM>
-static hipError_t launch_wide_ab(const FusedArgs* members, int n, int fa, int fe, hipStream_t stream)
+static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
 {
-    if (fe == S_NONE) return launch_wide_cfg<FM, S_NONE, S_NONE>(members, n, stream);
-    if (fa == S_F16 && fe == S_F16) return launch_wide_cfg<FM, S_F16, S_F16>(members, n, stream);
-    if (fa == S_Q4S128 && fe == S_Q4S128) return launch_wide_cfg<FM, S_Q4S128, S_Q4S128>(members, n, stream);
-    if (fa == S_Q4S128 && fe == S_Q4S64) return launch_wide_cfg<FM, S_Q4S128, S_Q4S64>(members, n, stream);
-    if (fa == S_Q3S128 && fe == S_Q3S128) return launch_wide_cfg<FM, S_Q3S128, S_Q3S128>(members, n, stream);
-    return hipErrorInvalidValue;
+    const int yblocks = (a.M + 15) / 16;
+    const int tb = yblocks >= 3 ? 4 : yblocks;
+    a.ntg = (yblocks + tb - 1) / tb;
+    const int G = a.d_in / 128;
+    // k-ranges of t: a producer's eight wavefronts take four chunks each (one range at d_in 4096: with two the consumers
+    // of a gate+up launch at 64 tokens lose more to the producers' compute units than t arrives earlier, 33.3 -> 37.4 us)
+    int kcn = (G + 31) / 32;
+    while (kcn > 1 && (size_t)a.n * a.ntg * tb * 16 * kcn * a.r > a.tpair_count) --kcn;
+    a.kcn = kcn;
+    a.nprod = a.r > 0 ? a.n * (a.r / 16) * kcn * a.ntg : 0;
+    // The split of a workgroup and the parts S of the contraction: the cheapest by steps.  A step of 128 columns per range
+    // costs STEP microseconds whatever the launch's size (LDS traffic and the barrier), a workgroup's start, hand-over of t
+    // and end about 9, the sum of the parts 8 more; workgroups beyond the chip's slots come in further rounds.  Measured
+    // on one-linear launches of 64 and 24 tokens, contractions of 4096 .. 14336 (down projection of the 8B layer, 64
+    // tokens: two row blocks per workgroup and one part 46.9 us, eight and seven parts 27.3).
+    static const int per[4] = {8, 4, 2, 1}, ranges[4] = {2, 2, 4, 8};
+    static const float STEP[3][4] = {{0.5f, 0.4f, 0.45f, 0.6f}, {0.85f, 0.55f, 0.65f, 1.2f}, {1.2f, 0.85f, 1.3f, 2.8f}};
+    const float* const step_us = STEP[tb == 4 ? 2 : tb - 1];
+    size_t rows = 0;
+    for (int i = 0; i < a.n; ++i) rows += a.d_out[i];
+    int cfg = 0;
+    float best = 1e30f;
+    a.S = 1;
+    for (int c = 0; c < 4; ++c) {
+        int cons = 0;
+        for (int i = 0; i < a.n; ++i) cons += (a.d_out[i] / 16 + per[c] - 1) / per[c] * a.ntg;
+        const int slots = tb == 1 && c < 3 ? 512 : 256;   // workgroups the chip holds (registers)
+        for (int S = 1; S <= 8; ++S) {
+            if (S > 1 && (S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;
+            const int rounds = (cons * S + a.nprod + slots - 1) / slots, tiles = (G + S - 1) / S;
+            const float t = rounds * (9.f + step_us[c] * ((tiles + ranges[c] - 1) / ranges[c])) + (S > 1 ? 8.f : 0.f);
+            if (t < best) {
+                best = t;
+                cfg = c;
+                a.S = S;
+            }
+        }
+    }
+    if (a.r > 0) {
+        switch (tb) {
+            case 1: return launch_wide_cfg<FM, 1, true>(a, cfg, stream);
+            case 2: return launch_wide_cfg<FM, 2, true>(a, cfg, stream);
+            default: return launch_wide_cfg<FM, 4, true>(a, cfg, stream);
+        }
+    }
+    switch (tb) {
+        case 1: return launch_wide_cfg<FM, 1, false>(a, cfg, stream);
+        case 2: return launch_wide_cfg<FM, 2, false>(a, cfg, stream);
+        default: return launch_wide_cfg<FM, 4, false>(a, cfg, stream);
+    }
 }
 
-hipError_t launch_wide_q_group(const FusedArgs* members, int n, int fm, int fa, int fe, hipStream_t stream)
+hipError_t launch_wide_q(const WideArgs& a, int fm, hipStream_t stream)
 {
-    if (n < 1 || n > 4) return hipErrorInvalidValue;
     switch (fm) {
-        case S_Q4: return launch_wide_ab<S_Q4>(members, n, fa, fe, stream);
-        case S_Q3: return launch_wide_ab<S_Q3>(members, n, fa, fe, stream);
-        case S_Q2: return launch_wide_ab<S_Q2>(members, n, fa, fe, stream);
+        case S_Q4: return launch_wide_fm<S_Q4>(a, stream);
+        case S_Q3: return launch_wide_fm<S_Q3>(a, stream);
+        case S_Q2: return launch_wide_fm<S_Q2>(a, stream);
         default: return hipErrorInvalidValue;
     }
 }
 
-hipError_t launch_wide_q(const FusedArgs& a, int fm, int fa, int fe, hipStream_t stream)
+// every word 0, except the epoch word, which starts at `epoch0`
+__global__ void clear_words_kernel(uint32_t* p, int nwords, uint32_t epoch0)
 {
-    return launch_wide_q_group(&a, 1, fm, fa, fe, stream);
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < nwords) p[i] = i == HDR_EPOCH ? epoch0 : 0u;
 }
 
-bool wide_q_group_fits(int M, int d_in, const int* d_out, int n, int r)
+hipError_t launch_clear_words(uint32_t* p, int nwords, uint32_t epoch0, hipStream_t stream)
 {
-    int rows = 0;
-    for (int i = 0; i < n; ++i) rows += d_out[i];
-    WideCfg c;
-    return n >= 1 && n <= 4 && r <= 512 && pick_wide(M, d_in, rows, r, &c);
+    hipLaunchKernelGGL(clear_words_kernel, dim3((nwords + 255) / 256), dim3(256), 0, stream, p, nwords, epoch0);
+    return hipGetLastError();
 }
 
 }  // namespace eora
