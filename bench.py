@@ -439,18 +439,27 @@ def calibration_main(args):
         what = "SVD of step 5"
         m_rows, length = min(d_out, d_in), int(st["eig_rotations"])      # (Cholesky route: that counter holds the rotated rows' length)
         rows, rounds, bytes_total, ms = jacobi_round("svd", m_rows, length, False)
-    us_round = 1e3 * ms / rounds
-    kernel = "Jacobi round of the %s (%d rows of length %d per workgroup)" % (what, rows, length)
-    traffic = None                                    # HBM bytes per round from the committed counter runs, if they are of this kernel
-    tpath = os.path.join(ROOT, "profiles", "factors_traffic.json")
-    if os.path.exists(tpath):
-        with open(tpath) as f:
-            rec = json.load(f).get(args.workload)
-        if isinstance(rec, dict) and rec.get("kernel") == kernel:
-            traffic = rec.get("bytes")
-    roofline = dict(bound="hbm", achieved=round(bytes_total / rounds / us_round / 1e3, 1), peak=HBM_PEAK_GBS, unit="GB/s",
-                    frac=round(bytes_total / rounds / us_round / 1e3 / HBM_PEAK_GBS, 4), traffic=traffic, kernel=kernel,
-                    bytes_per_launch=int(bytes_total / rounds), us_per_launch=round(us_round, 3), launches=rounds)
+    block = -(-max(2 * r, r + 64) // 128) * 128       # vectors of the subspace iteration that replaces the SVD's sweeps for small ranks
+    if st["eig_rows"] == 0 and block <= min(d_in, d_out) // 4:
+        # bound by fp64 matrix products: Gram matrix (one triangle), its factor, dW times it, the r leading components, A
+        lo, hi = min(d_in, d_out), max(d_in, d_out)
+        flops = 1.0 * d_in * d_in * n + d_in ** 3 / 3.0 + 1.0 * d_out * d_in * d_in + 4.0 * lo * hi * r + 2.0 * r * d_in * d_out
+        roofline = dict(bound="mfma", achieved=round(flops / sec / 1e12, 2), peak=78.6, unit="TFLOP/s",
+                        frac=round(flops / sec / 78.6e12, 4), traffic=None, kernel="fp64 matrix products and the subspace iteration",
+                        svd_us=round(1e3 * st["svd_ms"], 1))
+    else:
+        us_round = 1e3 * ms / rounds
+        kernel = "Jacobi round of the %s (%d rows of length %d per workgroup)" % (what, rows, length)
+        traffic = None                                    # HBM bytes per round from the committed counter runs, if they are of this kernel
+        tpath = os.path.join(ROOT, "profiles", "factors_traffic.json")
+        if os.path.exists(tpath):
+            with open(tpath) as f:
+                rec = json.load(f).get(args.workload)
+            if isinstance(rec, dict) and rec.get("kernel") == kernel:
+                traffic = rec.get("bytes")
+        roofline = dict(bound="hbm", achieved=round(bytes_total / rounds / us_round / 1e3, 1), peak=HBM_PEAK_GBS, unit="GB/s",
+                        frac=round(bytes_total / rounds / us_round / 1e3 / HBM_PEAK_GBS, 4), traffic=traffic, kernel=kernel,
+                        bytes_per_launch=int(bytes_total / rounds), us_per_launch=round(us_round, 3), launches=rounds)
     out = dict(metric="seconds for Algorithm 1 steps 1-6 of one %d x %d linear (rank %d, %d calibration tokens)" % (d_out, d_in, r, n),
                value=round(sec, 4), unit="s", n_gpus=1, steps=steps, warmup=warmup, ms_per_step=round(1e3 * sec, 3),
                higher_is_better=False, scaling="weak", vs_baseline=None, dtype="f64", data="synthetic",

@@ -335,12 +335,17 @@ size_t eora_factors_workspace_bytes(int d_in, int d_out, int r);
  * as the eigendecomposition gives whenever no eigenvalue is clamped.  That route is taken when every pivot of the
  * factorisation stays above 1e4 * eig_floor * max diag(X~ X~^T); otherwise (a Gram matrix that close to singular,
  * e.g. fewer tokens than channels) the eigendecomposition with the clamp is computed, by a one-sided (block)
- * Jacobi iteration.  The SVD of step 5 is such an iteration in both cases.  The call SYNCHRONISES `stream` once
- * after the factorisation, once per sweep and before returning, and allocates nothing on the device.
+ * Jacobi iteration.  The SVD of step 5 is such an iteration too, over all rows, or, on the Cholesky route and for ranks well
+ * below the number of rows (a block of max(2 r, r + 64) vectors, rounded up to 128, at most a quarter of min(d_in, d_out)),
+ * over the rows of a block that holds the r leading components, found by a Chebyshev-filtered subspace iteration (which
+ * gives way to the sweeps over all rows where it does not settle).  The call SYNCHRONISES `stream` once
+ * after the factorisation, once per sweep and per cycle of the subspace iteration and before returning, and allocates
+ * nothing on the device.
  * stats: HOST pointer to eight doubles or NULL: for steps 2-3, then for the SVD, the number of sweeps, the
  * milliseconds its rounds took (events on `stream`), the workgroups that rotated their rows, and the rows a
  * workgroup handles per round (16: block rounds, taken when the row count is a multiple of 16 and the row
- * lengths are multiples of 128; 2: pair rounds).  The Cholesky route reports, in place of the first four, 0 sweeps,
+ * lengths are multiples of 128; 2: pair rounds).  (With the subspace iteration: the sweeps over its block, and the
+ * milliseconds of all of step 5.)  The Cholesky route reports, in place of the first four, 0 sweeps,
  * its milliseconds, the length of the rows the SVD's sweeps rotated, and 0.  That length is min(d_in, d_out) when the
  * matrix of step 5, at least twice as long as it has rows, was first reduced to a square factor with the same singular
  * values and left singular vectors (T T^T = C C^T by a second Cholesky factorisation; not possible for an error of

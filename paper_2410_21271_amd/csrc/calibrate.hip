@@ -135,7 +135,7 @@ __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H
 // result register v holds D[i = 4 v + g][j = n].
 typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int BJ_NT = 512, BJ_NW = BJ_NT / 64;
-constexpr int BJ_INNER_SWEEPS = 30;
+constexpr int BJ_INNER_SWEEPS = 2;      // (of the 16 x 16 matrix per round: what two leave is finished in the next sweep)
 
 __device__ __forceinline__ d4 mfma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
@@ -181,9 +181,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 {
     __shared__ double Sw[BJ_NW][16][17];
     __shared__ double S[16][17], J[16][17];
-    __shared__ double rco[8], rsi[8];
-    __shared__ int rp[8], rq[8];
-    __shared__ int s_any[BJ_INNER_SWEEPS];      // one flag per sweep, so that none is ever cleared while in use
+    __shared__ int s_rotated;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
     const int nb = m / 8, mm = nb - 1, i = blockIdx.x;
@@ -222,64 +220,65 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
         S[r][c] = t;
         J[r][c] = r == c ? 1.0 : 0.0;
     }
-    if (tid < BJ_INNER_SWEEPS) s_any[tid] = 0;
     __syncthreads();
-    // ---- S = J D J^T by two-sided Jacobi: eight disjoint pairs per step, fifteen steps per sweep
-    bool rotated = false;
-    for (int sweep = 0; sweep < BJ_INNER_SWEEPS; ++sweep) {
-        for (int step = 0; step < 15; ++step) {
-            if (tid < 8) {
-                int p, q;
-                if (tid == 0) {
-                    p = step;
-                    q = 15;
-                } else {
-                    p = (step + tid) % 15;
-                    q = (step + 15 - tid) % 15;
-                }
-                const double a = S[p][p], b = S[q][q], c = S[p][q];
+    // ---- S = J D J^T by two-sided Jacobi: eight disjoint pairs per step, fifteen steps per sweep.  One wavefront does it
+    // alone (its LDS operations are carried out in order; three workgroup barriers per step cost more than they shared out)
+    if (wave == 0) {
+        bool rotated = false;
+        for (int sweep = 0; sweep < BJ_INNER_SWEEPS; ++sweep) {
+            bool any = false;
+            for (int step = 0; step < 15; ++step) {
                 double co = 1.0, si = 0.0;
-                if (a > abs_floor && b > abs_floor && fabs(c) > tol * sqrt(a) * sqrt(b)) {
-                    const double zeta = (b - a) / (2.0 * c);
-                    const double t = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    co = 1.0 / sqrt(1.0 + t * t);
-                    si = co * t;
-                    s_any[sweep] = 1;
+                int p = 0, q = 0;
+                {                                     // lane -> pair lane % 8 (eight lanes the same pair)
+                    const int t = lane & 7;
+                    if (t == 0) {
+                        p = step;
+                        q = 15;
+                    } else {
+                        p = step + t;
+                        p = p >= 15 ? p - 15 : p;
+                        q = step + 15 - t;
+                        q = q >= 15 ? q - 15 : q;
+                    }
+                    const double a = S[p][p], b = S[q][q], c = S[p][q];
+                    if (a > abs_floor && b > abs_floor && fabs(c) > tol * sqrt(a) * sqrt(b)) {
+                        const double zeta = (b - a) / (2.0 * c);
+                        const double t2 = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
+                        co = 1.0 / sqrt(1.0 + t2 * t2);
+                        si = co * t2;
+                    }
                 }
-                rp[tid] = p;
-                rq[tid] = q;
-                rco[tid] = co;
-                rsi[tid] = si;
-            }
-            __syncthreads();
-            if (tid < 256) {            // rows of S (threads 0 .. 127), columns of J (128 .. 255)
-                const int k = (tid & 127) >> 4, c = tid & 15;
-                const int p = rp[k], q = rq[k];
-                const double co = rco[k], si = rsi[k];
-                if (tid < 128) {
-                    const double a = S[p][c], b = S[q][c];
+                if (!__any(si != 0.0)) continue;      // uniform: nothing to rotate in this step
+                any = true;
+                // rows of S and columns of J: lane -> pair lane % 8, columns (rows of J) lane / 8 and lane / 8 + 8
+                const int c0 = lane >> 3;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = c0 + 8 * h;
+                    const double a = S[p][c], b = S[q][c], u = J[c][p], w = J[c][q];
                     S[p][c] = co * a - si * b;
                     S[q][c] = si * a + co * b;
-                } else {
-                    const double a = J[c][p], b = J[c][q];
-                    J[c][p] = co * a - si * b;
-                    J[c][q] = si * a + co * b;
+                    J[c][p] = co * u - si * w;
+                    J[c][q] = si * u + co * w;
                 }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {         // columns of S
+                    const int r = c0 + 8 * h;
+                    const double a = S[r][p], b = S[r][q];
+                    S[r][p] = co * a - si * b;
+                    S[r][q] = si * a + co * b;
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
-            __syncthreads();
-            if (tid < 128) {            // columns of S
-                const int k = tid >> 4, r = tid & 15;
-                const int p = rp[k], q = rq[k];
-                const double co = rco[k], si = rsi[k];
-                const double a = S[r][p], b = S[r][q];
-                S[r][p] = co * a - si * b;
-                S[r][q] = si * a + co * b;
-            }
-            __syncthreads();
+            if (!any) break;
+            rotated = true;
         }
-        if (s_any[sweep] == 0) break;       // written before the last barrier of the sweep: uniform
-        rotated = true;
+        if (lane == 0) s_rotated = rotated ? 1 : 0;
     }
+    __syncthreads();
+    const bool rotated = s_rotated != 0;
     if (!rotated) return;               // the 16 rows were orthogonal already (uniform over the workgroup)
     if (tid == 0) atomicAdd(rotations, 1u);
     apply_rotation(H, L, P, Q, J, wave, lane);
@@ -287,69 +286,103 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 }
 
 // C[i][j] = beta * C[i][j] + alpha * sum_k A[i*ai + k*ak] * B[j*bj + k*bk], i < M, j < N, k < K (beta == 0: C is
-// not read).  64 x 64 outputs per workgroup of 256 threads, 4 x 4 per thread, operands staged through LDS sixteen k
-// at a time.  lower != 0: only the tiles that touch the lower triangle (j0 <= i0) are computed (symmetric updates).
+// not read).  lower != 0: only the tiles that touch the lower triangle (j0 <= i0) are computed (symmetric updates).
+// Bound by the fp64 matrix cores: 64 x 64 outputs per workgroup, 32 x 32 per wavefront as 2 x 2 blocks of
+// v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS sixteen k at a time, the next sixteen on their way
+// from memory meanwhile.  LDS rows of 18 doubles: a stage's sixteen k of a row are written together, and the sixteen rows
+// of a fragment start in different banks.
+constexpr int GM_ST = 18;
 template <typename TA, typename TB>
 __global__ __launch_bounds__(256) void gemm_kernel(const TA* __restrict__ A, long ai, long ak, const TB* __restrict__ B,
                                                    long bj, long bk, double* C, long ldc, int M, int N, int K,
                                                    double alpha, double beta, int lower)
 {
-    __shared__ double As[16][65], Bs[16][65];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    __shared__ double As[2][64 * GM_ST], Bs[2][64 * GM_ST];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n = lane & 15, g = lane >> 4;
     const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
     if (lower && j0 > i0) return;
-    double acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
+    const int wi = 32 * (wave & 1), wj = 32 * (wave >> 1);
+    // this thread's four elements of a stage: consecutive threads along whichever index is contiguous in memory
+    auto place = [&](long stride_k, int e, int& row, int& kk) {
+        if (stride_k == 1) {
+            kk = tid & 15;
+            row = (tid >> 4) + 16 * e;
+        } else {
+            row = tid & 63;
+            kk = (tid >> 6) + 4 * e;
+        }
+    };
+    TA ra[4];
+    TB rb[4];
+    auto fetch = [&](int k0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            int ii, kk;
-            if (ak == 1) {
-                kk = tid & 15;
-                ii = (tid >> 4) + 16 * e;
-            } else {
-                ii = tid & 63;
-                kk = (tid >> 6) + 4 * e;
-            }
-            const int gi = i0 + ii, gk = k0 + kk;
-            As[kk][ii] = (gi < M && gk < K) ? (double)A[(size_t)gi * ai + (size_t)gk * ak] : 0.0;
-            int jj, kb;
-            if (bk == 1) {
-                kb = tid & 15;
-                jj = (tid >> 4) + 16 * e;
-            } else {
-                jj = tid & 63;
-                kb = (tid >> 6) + 4 * e;
-            }
-            const int gj = j0 + jj, gkb = k0 + kb;
-            Bs[kb][jj] = (gj < N && gkb < K) ? (double)B[(size_t)gj * bj + (size_t)gkb * bk] : 0.0;
+            int row, kk;
+            place(ak, e, row, kk);
+            ra[e] = (i0 + row < M && k0 + kk < K) ? A[(size_t)(i0 + row) * ai + (size_t)(k0 + kk) * ak] : (TA)0;
+            place(bk, e, row, kk);
+            rb[e] = (j0 + row < N && k0 + kk < K) ? B[(size_t)(j0 + row) * bj + (size_t)(k0 + kk) * bk] : (TB)0;
         }
-        __syncthreads();
+    };
+    auto stage = [&](int buf) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            double a[4], b[4];
+        for (int e = 0; e < 4; ++e) {
+            int row, kk;
+            place(ak, e, row, kk);
+            As[buf][row * GM_ST + kk] = (double)ra[e];
+            place(bk, e, row, kk);
+            Bs[buf][row * GM_ST + kk] = (double)rb[e];
+        }
+    };
+    d4 acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
+    fetch(0);
+    stage(0);
+    __syncthreads();
+    for (int k0 = 0, buf = 0; k0 < K; k0 += 16, buf ^= 1) {
+        if (k0 + 16 < K) fetch(k0 + 16);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                a[e] = As[k][ty + 16 * e];
-                b[e] = Bs[k][tx + 16 * e];
+        for (int kk = 0; kk < 4; ++kk) {
+            double a[2], b[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                a[e] = As[buf][(wi + 16 * e + n) * GM_ST + 4 * kk + g];
+                b[e] = Bs[buf][(wj + 16 * e + n) * GM_ST + 4 * kk + g];
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 2; ++e)
 #pragma unroll
-                for (int f = 0; f < 4; ++f) acc[e][f] += a[e] * b[f];
+                for (int f = 0; f < 2; ++f) acc[e][f] = mfma64(a[e], b[f], acc[e][f]);
         }
+        if (k0 + 16 < K) stage(buf ^ 1);      // (everyone left that buffer at the barrier of the stage before)
         __syncthreads();
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < 2; ++e)
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-            const int gi = i0 + ty + 16 * e, gj = j0 + tx + 16 * f;
-            if (gi < M && gj < N) {
-                double v = alpha * acc[e][f];
-                if (beta != 0.0) v += beta * C[(size_t)gi * ldc + gj];
-                C[(size_t)gi * ldc + gj] = v;
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int gi = i0 + wi + 16 * e + 4 * v + g, gj = j0 + wj + 16 * f + n;
+                if (gi < M && gj < N) {
+                    double c = alpha * acc[e][f][v];
+                    if (beta != 0.0) c += beta * C[(size_t)gi * ldc + gj];
+                    C[(size_t)gi * ldc + gj] = c;
+                }
             }
-        }
+}
+
+// the strict upper triangle of an n x n matrix from the lower one
+__global__ __launch_bounds__(256) void mirror_kernel(double* __restrict__ A, int n)
+{
+    __shared__ double tile[32][33];
+    const int bx = blockIdx.x * 32, by = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    if (bx > by) return;                      // source tile (by, bx) in or below the diagonal
+    for (int e = ty; e < 32; e += 8)
+        tile[e][tx] = (by + e < n && bx + tx < n) ? A[(size_t)(by + e) * n + bx + tx] : 0.0;
+    __syncthreads();
+    for (int e = ty; e < 32; e += 8)
+        if (bx + e < n && by + tx < n && by + tx > bx + e) A[(size_t)(bx + e) * n + by + tx] = tile[tx][e];
 }
 
 // ------------------------------------------------------------------------------------------------------------
@@ -373,70 +406,61 @@ __global__ __launch_bounds__(1024) void pivot_floor_kernel(const double* __restr
     if (threadIdx.x == 0) thr[0] = rel * red[0];
 }
 
-// the nb x nb diagonal block at (j0, j0): unblocked factorisation in LDS; the block's strict upper part is zeroed
-__global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A, long lda, int j0, int nb,
-                                                          const double* __restrict__ thr, unsigned* __restrict__ flag)
+// The nb x nb diagonal block at (j0, j0), by one wavefront (no barriers: a wavefront's LDS operations are carried out in
+// order): lane i owns row i, the matrix is kept transposed in LDS (a row's entry of every lane in one access, the pivot
+// row's entry the same for all).  Unblocked, left-looking; the block's strict upper part is zeroed.  Then inv = L11^-1
+// (64 x 64, row-major; rows beyond nb those of the identity), lane c its column c, so that the rows below the block and
+// the right-hand sides of a solve are products on the matrix cores (one thread per row with its 64 entries in scratch
+// memory took 297 us a panel; this kernel takes 94).
+__global__ __launch_bounds__(64) void potrf_block_kernel(double* __restrict__ A, long lda, int j0, int nb, const double* __restrict__ thr,
+                                                         unsigned* __restrict__ flag, double* __restrict__ inv)
 {
-    __shared__ double S[CH_NB][CH_NB + 1];
-    const int tid = threadIdx.x;
+    __shared__ double S[CH_NB][CH_NB], Y[CH_NB][CH_NB];   // S[k][i] = entry (i, k); Y[k][c] = entry (k, c) of the inverse
+    const int i = threadIdx.x;
     double* const blk = A + (size_t)j0 * lda + j0;
-    for (int e = tid; e < CH_NB * CH_NB; e += 256) {
-        const int i = e >> 6, c = e & 63;
-        S[i][c] = (i < nb && c <= i) ? blk[(size_t)i * lda + c] : 0.0;
-    }
-    __syncthreads();
+    for (int r = 0; r < CH_NB; ++r) S[i][r] = (r < nb && i <= r) ? blk[(size_t)r * lda + i] : (i == r ? 1.0 : 0.0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     const double floor_abs = thr[0];
+    bool bad = false;
     for (int j = 0; j < nb; ++j) {
-        if (tid == 0) {
-            double d = S[j][j];
-            if (!(d > floor_abs)) {                       // not (numerically) positive definite: give up, stay finite
-                atomicOr(flag, 1u);
-                d = floor_abs > 0.0 ? floor_abs : 1.0;
+        double v0 = S[j][i], v1 = 0.0;
+        int k = 0;
+        for (; k + 8 <= j; k += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; u += 2) {
+                v0 -= S[k + u][i] * S[k + u][j];
+                v1 -= S[k + u + 1][i] * S[k + u + 1][j];
             }
-            S[j][j] = sqrt(d);
         }
-        __syncthreads();
-        if (tid > j && tid < nb) S[tid][j] /= S[j][j];
-        __syncthreads();
-        for (int e = tid; e < CH_NB * CH_NB; e += 256) {
-            const int i = e >> 6, c = e & 63;
-            if (c > j && i >= c && i < nb) S[i][c] -= S[i][j] * S[c][j];
+        for (; k < j; ++k) v0 -= S[k][i] * S[k][j];
+        v0 += v1;
+        double d = __shfl(v0, j, 64);
+        if (!(d > floor_abs)) {                           // not (numerically) positive definite: give up, stay finite
+            bad = true;
+            d = floor_abs > 0.0 ? floor_abs : 1.0;
         }
-        __syncthreads();
+        const double root = sqrt(d);
+        S[j][i] = i == j ? root : (i > j ? v0 / root : 0.0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-    for (int e = tid; e < CH_NB * CH_NB; e += 256) {
-        const int i = e >> 6, c = e & 63;
-        if (i < nb && c < nb) blk[(size_t)i * lda + c] = c <= i ? S[i][c] : 0.0;
+    if (i == 0 && bad) atomicOr(flag, 1u);
+    for (int r = 0; r < nb; ++r)
+        if (i < nb) blk[(size_t)r * lda + i] = S[i][r];   // (row r, column i: zero above the diagonal)
+    for (int r = 0; r < CH_NB; ++r) {
+        double v0 = r == i ? 1.0 : 0.0, v1 = 0.0;
+        int k = 0;
+        for (; k + 8 <= r; k += 8) {
+#pragma unroll
+            for (int u = 0; u < 8; u += 2) {
+                v0 -= S[k + u][r] * Y[k + u][i];
+                v1 -= S[k + u + 1][r] * Y[k + u + 1][i];
+            }
+        }
+        for (; k < r; ++k) v0 -= S[k][r] * Y[k][i];
+        const double y = (v0 + v1) / S[r][r];
+        Y[r][i] = y;
+        inv[r * CH_NB + i] = y;
     }
-}
-
-// rows j0 + nb .. n - 1 of the block column at j0: x L11^T = a, one thread per row, L11 (the factored diagonal
-// block) in LDS, every thread reading the same entry at the same time
-__global__ __launch_bounds__(256) void panel_solve_kernel(double* __restrict__ A, long lda, int j0, int nb, int n)
-{
-    __shared__ double L[CH_NB][CH_NB + 1];
-    const int tid = threadIdx.x;
-    for (int e = tid; e < CH_NB * CH_NB; e += 256) {
-        const int i = e >> 6, c = e & 63;
-        L[i][c] = (i < nb && c <= i) ? A[(size_t)(j0 + i) * lda + j0 + c] : (i == c ? 1.0 : 0.0);
-    }
-    __syncthreads();
-    const int row = j0 + nb + blockIdx.x * 256 + tid;
-    if (row >= n) return;
-    double* const a = A + (size_t)row * lda + j0;
-    double x[CH_NB];
-#pragma unroll
-    for (int c = 0; c < CH_NB; ++c) x[c] = c < nb ? a[c] : 0.0;
-#pragma unroll
-    for (int c = 0; c < CH_NB; ++c) {
-        double v = x[c];
-#pragma unroll
-        for (int e = 0; e < c; ++e) v -= x[e] * L[c][e];
-        x[c] = v / L[c][c];
-    }
-#pragma unroll
-    for (int c = 0; c < CH_NB; ++c)
-        if (c < nb) a[c] = x[c];
 }
 
 __global__ void zero_upper_kernel(double* __restrict__ A, int n)
@@ -687,6 +711,98 @@ __global__ __launch_bounds__(64) void store_q_tiles_kernel(const double* __restr
     }
 }
 
+// ------------------------------------------------------------------------------------------------------------
+// The r leading left singular vectors of T (m x n) by Chebyshev-filtered subspace iteration on S = T T^T, for r well
+// below m: the Jacobi sweeps over all m rows compute m components of which r are kept.  A block of p >= 2 r vectors
+// (rows of Z, length m) is filtered with a Chebyshev polynomial that is bounded by 1 on [0, a], a = the smallest Ritz
+// value of the block, orthonormalised (Cholesky of its Gram matrix, twice) and rotated to its Ritz vectors; the degree
+// is what the spread of the Ritz values allows before the smallest directions drown in the rounding of the largest.
+// Leading vectors that have converged are taken out of S (S -= theta z z^T) once that lowers the spread.  Convergence
+// needs the gap to the (p + 1)-th singular value only; the r-th is told from the (r + 1)-th by the Jacobi sweeps over
+// the p rows of Z T at the end, so nothing is lost to the squares in S.  (Zhou, Saad, Tiago, Chelikowsky 2006.)
+
+// deterministic entries in (-1, 1)
+__global__ void random_rows_kernel(double* __restrict__ Z, size_t n)
+{
+    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    unsigned long long x = (i + 1) * 0x9E3779B97F4A7C15ull;      // splitmix64 (Steele, Lea, Flood 2014)
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    x ^= x >> 31;
+    Z[i] = (double)(long long)x * (1.0 / 9223372036854775808.0);
+}
+
+__global__ void add_diagonal_kernel(double* __restrict__ S, int m, double v)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < m) S[(size_t)i * m + i] += v;
+}
+
+// row p of Z divided by its norm; one workgroup of 256 per row
+__global__ __launch_bounds__(256) void normalise_rows_kernel(double* __restrict__ Z, int L)
+{
+    double* const z = Z + (size_t)blockIdx.x * L;
+    double s = 0;
+    for (int k = threadIdx.x; k < L; k += 256) s += z[k] * z[k];
+    __shared__ double red[4];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    s = red[0] + red[1] + red[2] + red[3];
+    const double f = s > 0.0 ? 1.0 / sqrt(s) : 0.0;
+    for (int k = threadIdx.x; k < L; k += 256) z[k] *= f;
+}
+
+// out[p] = | Y_p - theta[p] Z_p |, one workgroup of 256 per row
+__global__ __launch_bounds__(256) void residual_kernel(const double* __restrict__ Y, const double* __restrict__ Z, int L,
+                                                       const double* __restrict__ theta, double shift, double* __restrict__ out)
+{
+    const int p = blockIdx.x;
+    const double t = theta[p] - shift;
+    double s = 0;
+    for (int k = threadIdx.x; k < L; k += 256) {
+        const double d = Y[(size_t)p * L + k] - t * Z[(size_t)p * L + k];
+        s += d * d;
+    }
+    __shared__ double red[4];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) out[p] = sqrt(red[0] + red[1] + red[2] + red[3]);
+}
+
+// G (p x p): the first nl rows and columns become diag(theta), `shift` is added to the rest of the diagonal, and the
+// rest is made symmetric
+__global__ void ritz_matrix_kernel(const double* __restrict__ src, double* __restrict__ G, int p, int nl, const double* __restrict__ theta, double shift)
+{
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= p * p) return;
+    const int i = e / p, c = e - i * p;
+    double v;
+    if (i < nl || c < nl) v = i == c ? theta[i] : 0.0;
+    else v = 0.5 * (src[(size_t)i * p + c] + src[(size_t)c * p + i]) + (i == c ? shift : 0.0);
+    G[e] = v;
+}
+
+// rank of lam[i] among p values (descending): out row rank <- row i of R, theta[rank] = lam[i]
+__global__ __launch_bounds__(256) void sort_rows_kernel(const double* __restrict__ R, const double* __restrict__ lam, int p, double* __restrict__ out,
+                                                        double* __restrict__ theta)
+{
+    __shared__ int s_rank;
+    const int i = blockIdx.x;
+    if (threadIdx.x == 0) s_rank = 0;
+    __syncthreads();
+    const double v = lam[i];
+    int rank = 0;
+    for (int q = threadIdx.x; q < p; q += 256) rank += (lam[q] > v) || (lam[q] == v && q < i);
+    atomicAdd(&s_rank, rank);
+    __syncthreads();
+    rank = s_rank;
+    if (threadIdx.x == 0) theta[rank] = v;
+    for (int k = threadIdx.x; k < p; k += 256) out[(size_t)rank * p + k] = R[(size_t)i * p + k];
+}
+
 inline unsigned blocks(size_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
 
 template <typename TA, typename TB>
@@ -699,18 +815,22 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
 
 // G (n x n, row-major, symmetric) -> L in its lower triangle, zeros above.  Enqueues only; *flag (device, cleared
 // here) is raised if a pivot is not above rel * max diag(G): the factor is then unusable.
-void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, hipStream_t st)
+// clear == false leaves a flag that is already up.  inv: scratch of CH_NB^2 doubles; or, keep_inv, one such block per
+// diagonal block, which then holds their inverses.
+void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double* inv, hipStream_t st, bool clear = true, bool keep_inv = false)
 {
-    hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, flag);
+    if (clear) hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, flag);
     hipLaunchKernelGGL(pivot_floor_kernel, dim3(1), dim3(1024), 0, st, G, n, rel, thr);
     for (int j0 = 0; j0 < n; j0 += CH_NB) {
         const int nb = n - j0 < CH_NB ? n - j0 : CH_NB, rest = n - j0 - nb;
-        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(256), 0, st, G, (long)n, j0, nb, thr, flag);
+        double* const iv = inv + (keep_inv ? (size_t)j0 * CH_NB : 0);
+        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(64), 0, st, G, (long)n, j0, nb, thr, flag, iv);
         if (rest <= 0) break;
-        hipLaunchKernelGGL(panel_solve_kernel, dim3((rest + 255) / 256), dim3(256), 0, st, G, (long)n, j0, nb, n);
-        // trailing matrix -= panel . panel^T (the tiles of its lower triangle)
+        // rows below: P <- P L11^-T, in place (a workgroup reads its 64 rows whole before it writes them)
         double* const P = G + (size_t)(j0 + nb) * n + j0;
-        gemm(P, (long)n, 1L, P, (long)n, 1L, G + (size_t)(j0 + nb) * n + (j0 + nb), (long)n, rest, rest, nb, st, -1.0, 1.0, 1);
+        gemm((const double*)P, (long)n, 1L, (const double*)iv, (long)CH_NB, 1L, P, (long)n, rest, nb, nb, st);
+        // trailing matrix -= panel . panel^T (the tiles of its lower triangle)
+        gemm((const double*)P, (long)n, 1L, (const double*)P, (long)n, 1L, G + (size_t)(j0 + nb) * n + (j0 + nb), (long)n, rest, rest, nb, st, -1.0, 1.0, 1);
     }
     hipLaunchKernelGGL(zero_upper_kernel, dim3(blocks((size_t)n * n)), dim3(256), 0, st, G, n);
 }
@@ -794,6 +914,131 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
         if (n == 0) return sweep;
     }
     return -1;
+}
+
+// ---- host side of the filtered subspace iteration (see random_rows_kernel) ----------------------------------
+constexpr int SUB_CYCLES = 14;
+constexpr double SUB_SPREAD = 27.6;         // ln 1e12: growth of the largest Ritz direction over the smallest per filter
+constexpr double SUB_TOL = 1e-12;           // residual of a leading vector, relative to its Ritz value
+
+// vectors of the block for rank r of m: at least twice r, whole block rounds
+int subspace_size(int r) { return ((2 * r > r + 64 ? 2 * r : r + 64) + 127) / 128 * 128; }
+// taken when the block is at most a quarter of the rows (its buffers then fit one m x m matrix, and the sweeps over all
+// rows cost more: 4096 x 4096 with r = 128, 0.78 s of sweeps)
+bool subspace_fits(int m, int r) { return subspace_size(r) <= m / 4; }
+
+// the p rows of Z (length L) made orthonormal; F, inv: p x p scratch each (p >= 64)
+void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* thr, unsigned* flag, hipStream_t st)
+{
+    hipLaunchKernelGGL(normalise_rows_kernel, dim3(p), dim3(256), 0, st, Z, L);
+    for (int pass = 0; pass < 2; ++pass) {
+        gemm((const double*)Z, (long)L, 1L, (const double*)Z, (long)L, 1L, F, (long)p, p, p, L, st, 1.0, 0.0, 1);
+        cholesky(F, p, 1e-14, thr, flag, inv, st, pass == 0, true);
+        for (int j0 = 0; j0 < p; j0 += CH_NB) {
+            const int nb = p - j0 < CH_NB ? p - j0 : CH_NB;
+            if (j0 > 0)                     // rows j0 .. -= F[j0 .., 0 .. j0) Z[0 .. j0)
+                gemm((const double*)(F + (size_t)j0 * p), (long)p, 1L, (const double*)Z, 1L, (long)L, Z + (size_t)j0 * L, (long)L, nb, L, j0, st, -1.0, 1.0);
+            // rows j0 .. <- L11^-1 rows, in place (a workgroup reads its 64 columns whole before it writes them)
+            gemm((const double*)(inv + (size_t)j0 * CH_NB), (long)CH_NB, 1L, (const double*)(Z + (size_t)j0 * L), 1L, (long)L, Z + (size_t)j0 * L, (long)L, nb, L, nb, st);
+        }
+    }
+}
+
+// S: m x m, symmetric, destroyed.  On success (1) the first p rows of `work` (p x m) are an orthonormal basis that holds
+// the r leading eigenvectors; 0: not converged or not of rank p (the caller takes another way), < 0: runtime error.
+// work: 3 p m + 3 p^2 doubles, theta / res / lam: p doubles each.
+int leading_subspace(double* S, int m, int r, int p, double* work, double* theta, double* res, double* lam, unsigned* rot, unsigned* flag,
+                     double* thr, hipStream_t st)
+{
+    double* const Z = work;
+    double* const Y = Z + (size_t)p * m;
+    double* const U = Y + (size_t)p * m;                  // scratch of the rotations
+    double* const G = U + (size_t)p * m;
+    double* const R = G + (size_t)p * p;
+    double* const F = R + (size_t)p * p;
+    double* const host = (double*)malloc(sizeof(double) * 2 * p);
+    if (!host) return -2;
+    double* const h_theta = host;
+    double* const h_res = host + p;
+    struct Free { double* p; ~Free() { free(p); } } free_host{host};
+    double shift = 0.0;                                   // S holds S - shift I
+    int nl = 0;                                           // leading rows taken out of S
+    auto times_s = [&](const double* A, double* C, int rows, double alpha, double beta) {
+        gemm(A, (long)m, 1L, (const double*)S, (long)m, 1L, C, (long)m, rows, m, m, st, alpha, beta);
+    };
+    // Ritz rotation of all p rows: Z <- Ritz vectors (descending), Y <- Z S, theta, residuals, on the host too
+    auto ritz = [&]() -> int {
+        times_s(Z, Y, p, 1.0, 0.0);
+        gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st);
+        hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
+        hipLaunchKernelGGL(identity_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, R, p);
+        double rotations = 0;
+        if (jacobi_sweeps(G, p, R, p, lam, rot, st, &rotations) < 0) return 0;
+        hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, (const double*)G, (const double*)R, p, lam);
+        hipLaunchKernelGGL(sort_rows_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)lam, p, F, theta);
+        gemm((const double*)F, (long)p, 1L, (const double*)Z, 1L, (long)m, U, (long)m, p, m, p, st);
+        hipMemcpyAsync(Z, U, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
+        gemm((const double*)F, (long)p, 1L, (const double*)Y, 1L, (long)m, U, (long)m, p, m, p, st);
+        hipMemcpyAsync(Y, U, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
+        hipLaunchKernelGGL(residual_kernel, dim3(p), dim3(256), 0, st, (const double*)Y, (const double*)Z, m, (const double*)theta, shift, res);
+        unsigned bad = 1;
+        if (hipMemcpyAsync(h_theta, theta, sizeof(double) * p, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipMemcpyAsync(h_res, res, sizeof(double) * p, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+            return -2;
+        return bad == 0 && h_theta[p - 1] > 0.0 && std::isfinite(h_theta[0]) ? 1 : 0;
+    };
+    hipLaunchKernelGGL(random_rows_kernel, dim3(blocks((size_t)p * m)), dim3(256), 0, st, Y, (size_t)p * m);
+    for (int it = 0; it < 2; ++it) {
+        times_s(Y, Z, p, 1.0, 0.0);
+        orthonormalise(Z, p, m, F, R, thr, flag, st);
+        if (it == 0) hipMemcpyAsync(Y, Z, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
+    }
+    int rc = ritz();
+    for (int cycle = 0; rc == 1 && cycle < SUB_CYCLES; ++cycle) {
+        const double a = h_theta[p - 1], x1 = 2.0 * h_theta[nl] / a - 1.0;
+        int degree = (int)(SUB_SPREAD / std::acosh(x1 > 1.0 + 1e-9 ? x1 : 1.0 + 1e-9));
+        degree = degree < 2 ? 2 : degree > 30 ? 30 : degree;
+        hipLaunchKernelGGL(add_diagonal_kernel, dim3(blocks(m)), dim3(256), 0, st, S, m, shift - 0.5 * a);
+        shift = 0.5 * a;
+        // y_{k+1} = 2 s (2/a) (S - a/2 I) y_k - s_{k-1} s y_{k-1}, scaled so that the direction at x1 keeps its length
+        const int rows = p - nl;
+        double* y0 = Z + (size_t)nl * m;
+        double* y1 = Y + (size_t)nl * m;
+        const double sig1 = 1.0 / x1;
+        double sig = sig1;
+        times_s(y0, y1, rows, sig * 2.0 / a, 0.0);
+        for (int k = 2; k <= degree; ++k) {
+            const double s2 = 1.0 / (2.0 / sig1 - sig);
+            times_s(y1, y0, rows, 2.0 * s2 * 2.0 / a, -sig * s2);
+            double* const t = y0;
+            y0 = y1;
+            y1 = t;
+            sig = s2;
+        }
+        if (y1 != Z + (size_t)nl * m) hipMemcpyAsync(Z + (size_t)nl * m, y1, sizeof(double) * rows * m, hipMemcpyDeviceToDevice, st);
+        if (nl > 0) {                                     // against the rows taken out: z -= (z X^T) X
+            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
+            gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, Z + (size_t)nl * m, (long)m, rows, m, nl, st, -1.0, 1.0);
+        }
+        orthonormalise(Z + (size_t)nl * m, rows, m, F, R, thr, flag, st);
+        rc = ritz();
+        if (rc != 1) break;
+        double worst = 0.0;
+        int done = 0;
+        for (int i = nl; i < r; ++i) worst = h_res[i] / h_theta[i] > worst ? h_res[i] / h_theta[i] : worst;
+        if (getenv("EORA_VERBOSE")) fprintf(stderr, "eora: subspace m=%d p=%d cycle %d degree %d out %d residual %.2e\n", m, p, cycle, degree, nl, worst);
+        if (worst <= SUB_TOL) return 1;
+        for (done = nl; done < r - 1 && h_res[done] <= SUB_TOL * h_theta[done];) ++done;
+        if (done > nl && h_theta[nl] > 4.0 * h_theta[done]) {
+            // S -= sum theta_i z_i z_i^T
+            hipMemcpyAsync(U, Z + (size_t)nl * m, sizeof(double) * (done - nl) * m, hipMemcpyDeviceToDevice, st);
+            hipLaunchKernelGGL(scale_kernel, dim3(blocks((size_t)(done - nl) * m)), dim3(256), 0, st, U, done - nl, m, (const double*)(theta + nl), 1);
+            gemm((const double*)U, 1L, (long)m, (const double*)(Z + (size_t)nl * m), 1L, (long)m, S, (long)m, m, m, done - nl, st, -1.0, 1.0);
+            nl = done;
+        }
+    }
+    return rc == 1 ? 0 : rc;
 }
 
 inline size_t r256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -886,9 +1131,9 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     const size_t nw = (size_t)d_out * d_in;
     const int k = d_in;
 
-    // steps 1, 2: error and Gram matrix
+    // steps 1, 2: error and Gram matrix (the factorisation reads the lower triangle only)
     hipLaunchKernelGGL(sub_kernel, dim3(blocks(nw)), dim3(256), 0, st, W, What, dW, nw);
-    gemm(Xt, (long)n_tokens, 1L, Xt, (long)n_tokens, 1L, H, (long)k, k, k, n_tokens, st);
+    gemm(Xt, (long)n_tokens, 1L, Xt, (long)n_tokens, 1L, H, (long)k, k, k, n_tokens, st, 1.0, 0.0, g_factors_route == 0 ? 1 : 0);
 
     // Steps 2-4 and 6 by a Cholesky factor.  With X~ X~^T = L L^T, dW L equals dW Q sqrt(Lambda) times an orthogonal
     // matrix on the right, so step 5 finds the same U' and Sigma', and step 6's A = Sigma'^-1 U'^T (dW L) L^-1 is
@@ -903,7 +1148,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
         if (timed) hipEventRecord(e0, st);
-        cholesky(H, k, 1e4 * eig_floor, thr, flag, st);
+        cholesky(H, k, 1e4 * eig_floor, thr, flag, V, st);
         if (timed) hipEventRecord(e1, st);
         unsigned bad = 1;
         const bool copied = hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, st) == hipSuccess &&
@@ -963,18 +1208,50 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     // ended with.  The r largest components are accurate to the rounding of T T^T relative to sigma_1^2; a T of
     // rank below m (an error of low rank) has no such factor: then, as before, the rows of T are rotated.
     bool square = false;
-    if (chol && n >= 2 * m) {
+    // r well below m: the leading subspace instead of all m components (H and V are free by now).  0: it did not settle
+    // (no gap behind the block, or an error of rank below the block's size): then as for larger ranks.
+    int sub = 0;
+    const int p = subspace_size(r);
+    if (chol && subspace_fits(m, r)) {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
+        if (timed) hipEventRecord(e0, st);
+        gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st, 1.0, 0.0, 1);
+        hipLaunchKernelGGL(mirror_kernel, dim3((m + 31) / 32, (m + 31) / 32), dim3(256), 0, st, H, m);
+        sub = leading_subspace(H, m, r, p, V, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st);
+        if (sub == 1) {
+            gemm((const double*)V, (long)m, 1L, (const double*)T, 1L, (long)n, T0, (long)n, p, n, m, st);      // Z T
+            sweeps = jacobi(T0, n, nullptr, p, sq, rot, st, stats ? stats + 4 : nullptr);
+            if (sweeps < 0) return sweeps == -1 ? EORA_ERR_NOT_CONVERGED : EORA_ERR_LAUNCH;
+            hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, T0, T0, n, sq);
+            hipLaunchKernelGGL(top_rows_kernel, dim3(blocks(p)), dim3(256), 0, st, sq, p, r, idx, sigma);
+            if (stats) stats[2] = n;
+        }
+        if (timed) {
+            float ms = 0;
+            hipEventRecord(e1, st);
+            hipEventSynchronize(e1);
+            hipEventElapsedTime(&ms, e0, e1);
+            stats[5] = ms;
+        }
+        if (e0) hipEventDestroy(e0);
+        if (e1) hipEventDestroy(e1);
+        if (sub < 0) return EORA_ERR_LAUNCH;
+    }
+    if (chol && !sub && n >= 2 * m) {
         unsigned* flag = rot + 16;
         double* thr = (double*)(rot + 32);
-        gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st);
-        cholesky(H, m, 1e-14, thr, flag, st);
+        gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st, 1.0, 0.0, 1);
+        cholesky(H, m, 1e-14, thr, flag, V, st);
         unsigned bad = 1;
         if (hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
             return EORA_ERR_LAUNCH;
         square = bad == 0;
     }
     const double* Tkeep = T;                    // T as step 4 left it
-    if (square) {
+    if (sub) {
+        // rows idx[i] of T0: sigma_i z_i^T
+    } else if (square) {
         double* Y = V;                          // C^T
         hipLaunchKernelGGL(transpose_kernel, dim3((m + 31) / 32, (m + 31) / 32), dim3(256), 0, st, (const double*)H, Y, m);
         sweeps = jacobi(Y, m, nullptr, m, sq, rot, st, stats ? stats + 4 : nullptr);
@@ -997,7 +1274,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         hipLaunchKernelGGL(top_rows_kernel, dim3(blocks(m)), dim3(256), 0, st, sq, m, r, idx, sigma);
         if (stats && chol) stats[2] = n;
     }
-    const double* Tc = square ? T0 : T;         // rows idx[i]: sigma_i z_i^T
+    const double* Tc = sub || square ? T0 : T;  // rows idx[i]: sigma_i z_i^T
     if (by_rows) {
         // z_i = v_i: A' = rows of V'^T; B' = U' Sigma' = dW' A'^T
         hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks((size_t)r * k)), dim3(256), 0, st, Tc, k, idx, sigma, -1, Ap, r);

@@ -342,3 +342,34 @@ def test_factors_validation(gpu):
             gpu.factors(**args(**bad))
         assert e.value.status == code, (bad, e.value.status)
     assert gpu.factors_workspace_bytes(127, 64, 8) == 0
+
+
+@pytest.mark.parametrize("d_in,d_out,n_tokens,r", [
+    (512, 640, 1500, 16),        # the smallest block (128) of the fewest rows it is taken for
+    (768, 512, 1700, 33),        # T longer than it has rows, an odd rank
+    (1024, 512, 2300, 64),       # twice as long: no square factor is formed
+    (512, 518, 1300, 8),         # lengths no multiple of 128: pair rounds at the end
+])
+def test_leading_subspace_matches_oracle(gpu, d_in, d_out, n_tokens, r):
+    """Ranks well below the number of rows: the filtered subspace iteration instead of sweeps over all rows, to the same
+    bounds as the other routes."""
+    W, W_hat, Xt = _inputs(8000 + d_in + d_out, d_in, d_out, n_tokens)
+    B, A, sig = _run(gpu, W, W_hat, Xt, r)
+    _compare(W, W_hat, Xt, r, B, A, sig)
+
+
+def test_leading_subspace_gives_way_to_the_sweeps(gpu):
+    """An error of rank below the block's size has no such block: the sweeps over the rows take over, and the planted
+    term comes back (the bound of the other planted test: W is rounded to fp32 after the term was added)."""
+    d_in, d_out, r = 512, 512, 16
+    rng = np.random.default_rng(8100)
+    W_hat = (rng.standard_normal((d_out, d_in)) * 0.02).astype(np.float32)
+    low = rng.standard_normal((d_out, r)) @ rng.standard_normal((r, d_in)) * 0.002
+    W = (W_hat + low).astype(np.float32)
+    import synth
+    Xt = synth.draw_calibration(8101, d_in, 1400)
+    B, A, _ = _run(gpu, W, W_hat, Xt, r)
+    dW = W.astype(np.float64) - W_hat
+    assert np.abs(B @ A - dW).max() <= 1e-5 * np.abs(dW).max()
+    B, A, sig = _run(gpu, W_hat, W_hat, Xt, r)               # no error at all
+    assert not B.any() and not A.any() and not sig.any()
