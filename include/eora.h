@@ -107,7 +107,8 @@ size_t eora_sp24q4_meta_bytes(int d_in, int d_out);                  /* d_out*(d
  * the size of the largest (M, r) serves smaller calls too.  For 5 .. 127 tokens the size also holds
  * 12 MiB (for d_in >= 16384 at least 4 * M * d_out floats): a call may cut its contraction into ranges
  * whose partial outputs are added, in a fixed order, by a second kernel of the same call.  A quantised
- * call with a smaller workspace (from about 3.3 MiB on) is served without that. */
+ * call with a smaller workspace (from about 3.3 MiB on) is served without that.  For 128 .. 1024 tokens the size
+ * holds 48 MiB for the same purpose, with the same fallback. */
 size_t eora_workspace_bytes(int M, int d_in, int d_out, int r);
 /* Size that lets eora_linear_q_group() serve n_members members in one pass also for M >= 128 (the
  * down-projections of all members then sit side by side in the scratch).  With a workspace of only

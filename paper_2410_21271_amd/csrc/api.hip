@@ -200,10 +200,42 @@ size_t prefill_scratch_bytes(int M, int d_in, int r, int n)
     return round256((size_t)M * n * r * 2) + (ks > 1 ? (size_t)ks * M * n * r * sizeof(float) : 0);
 }
 
+// room for the fp32 partial outputs of a prompt whose contraction is cut into parts (up to PREFILL_SPLIT_TOKENS tokens)
+constexpr size_t PREFILL_SPLIT_BYTES = 48u << 20;
+constexpr int PREFILL_SPLIT_TOKENS = 1024;
+
+// Parts of the main GEMM's contraction: a launch of few output tiles (128 tokens x 256 rows, one per compute unit) leaves
+// most of the chip idle for the length of a whole contraction (333 tokens of the 8B layer: 48 tiles of 32 steps for a
+// 4096 x 4096 linear).  The cheapest by rounds of 256 tiles, 1.6 us a step and 6 a tile, the parts' fp32 outputs written
+// and read at 4 TB/s and 5 us for the second launch (each measured on the 8B shapes).
+int pick_prefill_parts(int M, int d_in, int r, const eora_q_member* members, int n, size_t room)
+{
+    size_t rows = 0;
+    int tiles = 0;
+    for (int m = 0; m < n; ++m) {
+        rows += members[m].d_out;
+        tiles += (members[m].d_out + 255) / 256;
+    }
+    tiles *= (M + 127) / 128;
+    const int G = d_in / 128;
+    int best = 1;
+    float best_us = 1e30f;
+    for (int ks = 1; ks <= 8 && ks * 4 <= G + 3; ++ks) {
+        const float bytes = (float)ks * M * rows * 4;
+        if (ks > 1 && bytes > (float)room) break;
+        const float us = (float)((tiles * ks + 255) / 256) * (1.6f * ((G + ks - 1) / ks + r / 128) + 6.f) + (ks > 1 ? 5.f + bytes * 2.f / 4e6f : 0.f);
+        if (us < best_us) {
+            best_us = us;
+            best = ks;
+        }
+    }
+    return best;
+}
+
 // validated members that share x, as GEMMs: one launch for every member's t (the members' A side by side), one
 // for every member's y
 int launch_prefill_group(const void* x, const eora_q_member* members, int n, int M, int d_in, int r, int w_bits, int group,
-                         int fa, int fe, const int* adapter, int r_per, void* workspace, hipStream_t stream)
+                         int fa, int fe, const int* adapter, int r_per, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     _Float16* T = (_Float16*)((char*)workspace + WS_T);           // M x (n * r): member m owns columns m*r ..
     if (r > 0) {
@@ -233,8 +265,12 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
     p.M = M; p.K1 = d_in; p.K2 = r;
     p.ldx2 = n * r;
     p.n = n;
-    p.ksplit = 1;
+    const size_t at = WS_T + round256(prefill_scratch_bytes(M, d_in, r, n));      // partial outputs behind t's scratch
+    p.ksplit = M <= PREFILL_SPLIT_TOKENS && workspace_bytes > at ? pick_prefill_parts(M, d_in, r, members, n, workspace_bytes - at) : 1;
+    p.part = (float*)((char*)workspace + at);
     for (int m = 0; m < n; ++m) {
+        p.pcol[m] = p.ldp;
+        p.ldp += members[m].d_out;
         p.w[m] = members[m].qweight;
         p.w_scales[m] = (const _Float16*)members[m].scales;
         p.w_zeros[m] = (const uint32_t*)members[m].qzeros;
@@ -245,6 +281,7 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
         p.N[m] = members[m].d_out;
     }
     if (failed(launch_prefill(p, backbone_format(w_bits), r > 0 ? fe : S_NONE, stream), "prefill")) return EORA_ERR_LAUNCH;
+    if (p.ksplit > 1 && failed(launch_reduce_members(p, stream), "prefill sum")) return EORA_ERR_LAUNCH;
     return EORA_OK;
 }
 
@@ -297,6 +334,11 @@ size_t workspace_min_bytes(int M, int d_in, int d_out, int r)
     return WS_T + (M >= PREFILL_MIN_TOKENS ? prefill_scratch_bytes(M, d_in, r, 1) : sparse_split_bytes(M, d_in, d_out));
 }
 
+size_t workspace_group_min_bytes(int M, int d_in, int r, int n)
+{
+    return WS_T + (M >= PREFILL_MIN_TOKENS ? prefill_scratch_bytes(M, d_in, r, n) : 0);
+}
+
 }  // namespace
 
 extern "C" {
@@ -307,13 +349,15 @@ size_t eora_workspace_bytes(int M, int d_in, int d_out, int r)
     // partials of t for the small-M kernels, and t itself as fp16 M x r for the prefill GEMM
     // (and, for a 2:4 call with a long contraction at 5 .. 127 tokens, the partial outputs of its ranges)
     const size_t base = workspace_min_bytes(M, d_in, d_out, r), split = M > 4 && M < PREFILL_MIN_TOKENS ? WS_T + WIDE_SPLIT_BYTES : 0;
+    if (M >= PREFILL_MIN_TOKENS && M <= PREFILL_SPLIT_TOKENS) return round256(base) + PREFILL_SPLIT_BYTES;
     return base > split ? base : split;
 }
 
 size_t eora_workspace_bytes_group(int M, int d_in, int r, int n_members)
 {
     if (n_members < 1 || n_members > MAX_GROUP || check_backbone_shape(M, d_in, 16, r) != EORA_OK) return 0;
-    return WS_T + (M >= PREFILL_MIN_TOKENS ? prefill_scratch_bytes(M, d_in, r, n_members) : 0);
+    const size_t base = workspace_group_min_bytes(M, d_in, r, n_members);
+    return M >= PREFILL_MIN_TOKENS && M <= PREFILL_SPLIT_TOKENS ? round256(base) + PREFILL_SPLIT_BYTES : base;
 }
 
 int eora_workspace_init(void* workspace, size_t workspace_bytes, void* stream)
@@ -411,7 +455,7 @@ static int run_linear_q(const void* x, const eora_q_member& e, int M, int d_in, 
     const int d_out = e.d_out;
     if (M == 0) return EORA_OK;
 
-    if (prefill_fits(M, r, ab_bits)) return launch_prefill_group(x, &e, 1, M, d_in, r, w_bits, group, fa, fe, nullptr, 0, workspace, (hipStream_t)stream);
+    if (prefill_fits(M, r, ab_bits)) return launch_prefill_group(x, &e, 1, M, d_in, r, w_bits, group, fa, fe, nullptr, 0, workspace, workspace_bytes, (hipStream_t)stream);
 
     int nw = 0, nq = 0;
     if (small_kernel_fits(M, d_in, group, &nw, &nq))
@@ -503,7 +547,7 @@ int eora_linear_q_multi(const void* x, const void* qweight, const void* scales, 
     if (M == 0) return EORA_OK;
     // many tokens: the GEMM path, with t masked per row between its two launches
     if (prefill_fits(M, R, ab_bits))
-        return launch_prefill_group(x, &e, 1, M, d_in, R, w_bits, group, fa, fe, (const int*)adapter_of_row, r, workspace, (hipStream_t)stream);
+        return launch_prefill_group(x, &e, 1, M, d_in, R, w_bits, group, fa, fe, (const int*)adapter_of_row, r, workspace, workspace_bytes, (hipStream_t)stream);
     // one to four tokens: the decode kernel, with t masked where it is gathered
     int nw = 0, nq = 0;
     if (small_kernel_fits(M, d_in, group, &nw, &nq))
@@ -529,15 +573,17 @@ int eora_linear_q_group(const void* x, const eora_q_member* members, int n_membe
     if (small_kernel_fits(M, d_in, group, &nw, &nq) &&
         (r == 0 || (r / 16) * pick_kcn(M, d_in) * n_members <= HDR_FLAGS_PER_BLOCK))
         return launch_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, nw, nq, workspace, (hipStream_t)stream);
-    if (prefill_fits(M, r, ab_bits) && workspace_bytes >= eora_workspace_bytes_group(M, d_in, r, n_members))
-        return launch_prefill_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, nullptr, 0, workspace, (hipStream_t)stream);
+    if (prefill_fits(M, r, ab_bits) && workspace_bytes >= workspace_group_min_bytes(M, d_in, r, n_members))
+        return launch_prefill_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, nullptr, 0, workspace, workspace_bytes, (hipStream_t)stream);
     if (n_members >= 1) {
         int rows[MAX_GROUP] = {0, 0, 0, 0};
         for (int m = 0; m < n_members; ++m) rows[m] = members[m].d_out;
         if (stream_fits(M, d_in, group, r, backbone_format(w_bits), fa, rows, n_members))
             return launch_stream_group(x, members, n_members, M, d_in, r, w_bits, fa, fe, workspace, (hipStream_t)stream);
     }
-    if (n_members > 1 && M > 4 && M < PREFILL_MIN_TOKENS)
+    // one launch of the general kernel, as long as the members' t fits its region (64 tokens per group of token blocks)
+    if (n_members > 1 && M > 0 && !prefill_fits(M, r, ab_bits) &&
+        (size_t)n_members * (((M < CHUNK_TOKENS ? M : CHUNK_TOKENS) + 63) / 64) * 64 * r <= MAX_PART_ELEMS)
         return launch_wide_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, workspace, workspace_bytes, (hipStream_t)stream);
     for (int m = 0; m < n_members; ++m) {               // other shapes (or a workspace sized for one member): one after the other
         const int rc = run_linear_q(x, members[m], M, d_in, r, w_bits, group, ab_bits, fa, fe, workspace, workspace_bytes, stream);

@@ -171,8 +171,8 @@ struct PrefillArgs {
     int group;
     int ldx2;                 // row stride of the second segment's activations
     int M, K1, K2;
-    int ksplit;               // > 1: workgroup (tile, ks) contracts the ks-th part of K1 only and writes its
-    float* part;              //      fp32 tile to part[ks][M][ldp] (columns pcol ..) instead of y; no second segment then
+    int ksplit;               // > 1: workgroup (tile, ks) contracts the ks-th part of K1 only (the last one K2 too) and
+    float* part;              //      writes its fp32 tile to part[ks][M][ldp] (columns pcol ..) instead of y
     int ldp;
     int n;                    // members
     const void* w[MAX_GROUP];            // first segment's weight tiles (N rows, K1 columns)
@@ -193,6 +193,8 @@ hipError_t launch_prefill(const PrefillArgs& a, int fm, int fe2, hipStream_t str
 hipError_t launch_mask_t(void* T, const int* adapter, int M, int R, int r_per, hipStream_t stream);
 
 // T[i] = fp16(sum over ks, in order, of part[ks][i]), i < count (count % 4 == 0)
+// y of every member from the parts of a launch with ksplit > 1, in order
+hipError_t launch_reduce_members(const PrefillArgs& a, hipStream_t stream);
 hipError_t launch_reduce_parts(const float* part, void* T, size_t count, int ksplit, hipStream_t stream);
 
 hipError_t launch_unpack_q(const uint32_t* qweight, const uint32_t* qzeros, uint8_t* codes, uint8_t* zeros,

@@ -220,8 +220,9 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     const int h = (lane >> 4) & 1;
     const int Rl = R0 + 2 * wn + h < nblk ? R0 + 2 * wn + h : nblk - 1;   // the row block this lane supplies a row of, clamped to a valid one
     const int G1 = a.K1 / 128, G2 = EXT ? a.K2 / 128 : 0;
-    const int sb = EXT ? 0 : ks * (G1 / a.ksplit);               // this workgroup's steps: [sb, GT)
-    const int GT = EXT ? G1 + G2 : sb + G1 / a.ksplit;
+    // this workgroup's steps: [sb, se) of the first segment, and with the last part the second segment's, [se, GT)
+    const int sb = ks * G1 / a.ksplit, se = (ks + 1) * G1 / a.ksplit;
+    const int GT = EXT && ks == a.ksplit - 1 ? G1 + G2 : se;
     constexpr bool W16 = FM == S_F16;                             // first segment's weights are fp16 tiles
     unsigned char* const buf0 = eora_smem;
     unsigned char* const buf1 = eora_smem + PF_XS;
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     WPre<W16 ? S_Q4 : FM> wp[2];                                  // (unused for fp16 tiles)
     fetch_x(xr, sb);
     if constexpr (!W16) {
-        const int lastw = (EXT ? G1 : GT) - 1;
+        const int lastw = se - 1;
         load_wpre<FM>(wp[0], a, Rl, sb, lane);
         load_wpre<FM>(wp[1], a, Rl, sb + 1 < lastw ? sb + 1 : lastw, lane);
     }
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     // Operands of step s into bf.  First segment: decode of the prefetched tiles and the request for the
     // following step's (fp16 tiles are operands as they are: no prefetch copy).  Second segment: B's tiles.
     h8 bf[8];
-    const int last1 = (EXT ? G1 : GT) - 1;                        // last step of the first segment
+    const int last1 = se - 1;                                     // last step of the first segment
     auto prep_main = [&](auto par_tag, int s) {                   // par_tag: (s - sb) & 1
         constexpr int PAR = decltype(par_tag)::value ? 1 : 0;
         s = s < last1 ? s : last1;                                // past the end: the last one again, never used
@@ -274,6 +275,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     };
     auto prep_ext = [&](int s) {
         s = s < GT ? s : GT - 1;
+        s = s > G1 ? s : G1;                                      // (a part without the second segment: a valid step, never used)
         if constexpr (E16) {
             load_b_frags(bf, a.w2, a.K2, Rl, s - G1, lane);
         } else {                                                  // quantised B: a handful of steps, loaded and decoded in place
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
 #endif
 
     // ---- split contraction: this part's fp32 tile, 128-byte rows straight from the accumulators ------
-    if (!EXT && a.ksplit > 1) {
+    if (a.ksplit > 1) {
 #pragma unroll
         for (int mb = 0; mb < 4; ++mb)
 #pragma unroll
@@ -402,7 +404,7 @@ static hipError_t launch_pf(const PrefillArgs& a, hipStream_t stream)
     for (int m = 0; m < a.n; ++m) ntn += (a.N[m] + PF_BN - 1) / PF_BN;
     const int ntm = (a.M + PF_BM - 1) / PF_BM;
     note_launch("prefill FM=%d EXT=%d ksplit=%d n=%d FE=%d", FM, (int)EXT, a.ksplit, a.n, FE2);
-    hipLaunchKernelGGL(kern, dim3(ntn * ntm * (EXT ? 1 : a.ksplit)), dim3(PF_NT), PF_LDS, stream, a);
+    hipLaunchKernelGGL(kern, dim3(ntn * ntm * a.ksplit), dim3(PF_NT), PF_LDS, stream, a);
     return hipGetLastError();
 }
 
@@ -419,6 +421,35 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 hipError_t launch_reduce_parts(const float* part, void* T, size_t count, int ksplit, hipStream_t stream)
 {
     hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, stream, part, (_Float16*)T, count, ksplit);
+    return hipGetLastError();
+}
+
+// y of every member = fp16(sum over the parts, in order); eight columns per thread
+__global__ __launch_bounds__(256) void reduce_members_kernel(PrefillArgs a)
+{
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    const int per_row = a.ldp / 8;
+    const int m = (int)(i / per_row), c = 8 * (int)(i - (size_t)m * per_row);
+    if (m >= a.M) return;
+    const size_t stride = (size_t)a.M * a.ldp;
+    const float* p = a.part + (size_t)m * a.ldp + c;
+    f4 v0 = *(const f4*)p, v1 = *(const f4*)(p + 4);
+    for (int ks = 1; ks < a.ksplit; ++ks) {
+        v0 += *(const f4*)(p + ks * stride);
+        v1 += *(const f4*)(p + ks * stride + 4);
+    }
+    int mem = 0;
+#pragma unroll
+    for (int q = 1; q < MAX_GROUP; ++q)
+        if (q < a.n && c >= a.pcol[q]) mem = q;
+    _Float16* const y = (_Float16*)a.y[mem] + (size_t)m * a.ldy[mem] + (c - a.pcol[mem]);
+    *(h8*)y = h8{(_Float16)v0[0], (_Float16)v0[1], (_Float16)v0[2], (_Float16)v0[3], (_Float16)v1[0], (_Float16)v1[1], (_Float16)v1[2], (_Float16)v1[3]};
+}
+
+hipError_t launch_reduce_members(const PrefillArgs& a, hipStream_t stream)
+{
+    const size_t items = (size_t)a.M * a.ldp / 8;
+    hipLaunchKernelGGL(reduce_members_kernel, dim3((unsigned)((items + 255) / 256)), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
