@@ -664,7 +664,11 @@ static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
     a.nprod = a.r > 0 ? a.n * (a.r / 16) * kcn * a.ntg : 0;
     // The split of a workgroup and the parts S of the contraction: the cheapest by steps.  A step of 128 columns per range
     // costs STEP microseconds whatever the launch's size (LDS traffic and the barrier), a workgroup's start, hand-over of t
-    // and end about 9, the sum of the parts 8 more; workgroups beyond the chip's slots come in further rounds.  Measured
+    // and end about 9; workgroups beyond the chip's slots come in further rounds.  The sum of the parts: with three or four
+    // token blocks it grows with the parts and the output (fitted at 41 and 64 tokens, two to eight parts; against 8
+    // microseconds whatever the size: 41 x 4608 x 1200 W3 17.2 -> 15.1 us, 37 x 7296 x 2688 W3 21.1 -> 19.4, 64 x 4096 x 1024
+    // W4 17.9 -> 16.6, 64 x 14336 x 4096 W4 27.4 -> 27.5); with one or two the fit splits too much (24 x 4096 x 1024 W4
+    // 11.0 -> 12.8 us, 24 x 14336 x 4096 21.4 -> 22.7) and 8 stays.  Measured
     // on one-linear launches of 64 and 24 tokens, contractions of 4096 .. 14336 (down projection of the 8B layer, 64
     // tokens: two row blocks per workgroup and one part 46.9 us, eight and seven parts 27.3).
     static const int per[4] = {8, 4, 2, 1}, ranges[4] = {2, 2, 4, 8};
@@ -672,6 +676,7 @@ static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
     const float* const step_us = STEP[tb == 4 ? 2 : tb - 1];
     size_t rows = 0;
     for (int i = 0; i < a.n; ++i) rows += a.d_out[i];
+    const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
     int cfg = 0;
     float best = 1e30f;
     a.S = 1;
@@ -682,7 +687,7 @@ static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
         for (int S = 1; S <= 8; ++S) {
             if (S > 1 && (S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;
             const int rounds = (cons * S + a.nprod + slots - 1) / slots, tiles = (G + S - 1) / S;
-            const float t = rounds * (9.f + step_us[c] * ((tiles + ranges[c] - 1) / ranges[c])) + (S > 1 ? 8.f : 0.f);
+            const float t = rounds * (9.f + step_us[c] * ((tiles + ranges[c] - 1) / ranges[c])) + (S > 1 ? sum0 + sum_part * S : 0.f);
             if (t < best) {
                 best = t;
                 cfg = c;
