@@ -408,8 +408,8 @@ __global__ __launch_bounds__(1024) void pivot_floor_kernel(const double* __restr
 
 // The nb x nb diagonal block at (j0, j0), by one wavefront (no barriers: a wavefront's LDS operations are carried out in
 // order): lane i owns row i, the matrix is kept transposed in LDS (a row's entry of every lane in one access, the pivot
-// row's entry the same for all).  Unblocked, left-looking; the block's strict upper part is zeroed.  Then inv = L11^-1
-// (64 x 64, row-major; rows beyond nb those of the identity), lane c its column c, so that the rows below the block and
+// row's entry the same for all).  Unblocked, left-looking; the block's strict upper part is zeroed.  Then, unless inv is
+// null, inv = L11^-1 (always 64 x 64, row-major; rows beyond nb those of the identity), lane c its column c, so that the rows below the block and
 // the right-hand sides of a solve are products on the matrix cores (one thread per row with its 64 entries in scratch
 // memory took 297 us a panel; this kernel takes 94).
 __global__ __launch_bounds__(64) void potrf_block_kernel(double* __restrict__ A, long lda, int j0, int nb, const double* __restrict__ thr,
@@ -446,6 +446,7 @@ __global__ __launch_bounds__(64) void potrf_block_kernel(double* __restrict__ A,
     if (i == 0 && bad) atomicOr(flag, 1u);
     for (int r = 0; r < nb; ++r)
         if (i < nb) blk[(size_t)r * lda + i] = S[i][r];   // (row r, column i: zero above the diagonal)
+    if (!inv) return;
     for (int r = 0; r < CH_NB; ++r) {
         double v0 = r == i ? 1.0 : 0.0, v1 = 0.0;
         int k = 0;
@@ -815,8 +816,9 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
 
 // G (n x n, row-major, symmetric) -> L in its lower triangle, zeros above.  Enqueues only; *flag (device, cleared
 // here) is raised if a pivot is not above rel * max diag(G): the factor is then unusable.
-// clear == false leaves a flag that is already up.  inv: scratch of CH_NB^2 doubles; or, keep_inv, one such block per
-// diagonal block, which then holds their inverses.
+// clear == false leaves a flag that is already up.  inv: scratch of CH_NB^2 doubles, not touched when n <= CH_NB (a
+// matrix of one block has no rows below it; a scratch of n x n is then smaller than an inverse); or, keep_inv, one such
+// block per diagonal block, which then holds their inverses.
 void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double* inv, hipStream_t st, bool clear = true, bool keep_inv = false)
 {
     if (clear) hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, flag);
@@ -824,7 +826,7 @@ void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double*
     for (int j0 = 0; j0 < n; j0 += CH_NB) {
         const int nb = n - j0 < CH_NB ? n - j0 : CH_NB, rest = n - j0 - nb;
         double* const iv = inv + (keep_inv ? (size_t)j0 * CH_NB : 0);
-        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(64), 0, st, G, (long)n, j0, nb, thr, flag, iv);
+        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(64), 0, st, G, (long)n, j0, nb, thr, flag, keep_inv || rest > 0 ? iv : nullptr);
         if (rest <= 0) break;
         // rows below: P <- P L11^-T, in place (a workgroup reads its 64 rows whole before it writes them)
         double* const P = G + (size_t)(j0 + nb) * n + j0;

@@ -373,3 +373,30 @@ def test_leading_subspace_gives_way_to_the_sweeps(gpu):
     assert np.abs(B @ A - dW).max() <= 1e-5 * np.abs(dW).max()
     B, A, sig = _run(gpu, W_hat, W_hat, Xt, r)               # no error at all
     assert not B.any() and not A.any() and not sig.any()
+
+
+@pytest.mark.parametrize("d_in,d_out,r", [
+    (2, 2, 1), (16, 16, 4), (32, 32, 8),              # a d_in x d_in scratch is smaller than the inverse of a 64 x 64 block
+    (32, 64, 8), (48, 96, 16), (62, 124, 8),          # ... and a second factorisation (T twice as long as it has rows)
+    (64, 128, 16), (66, 132, 16), (66, 64, 16),       # one whole block; a block and a remainder of two
+    (128, 32, 8), (130, 62, 8),                       # the fewer rows on the other side
+])
+def test_small_sizes_stay_inside_the_workspace(gpu, d_in, d_out, r):
+    """Linears with a side of at most 64: the same bounds as the other sizes, and not a word beyond the workspace that
+    factors_workspace_bytes() asks for is written."""
+    import torch
+    rng = np.random.default_rng(8200 + d_in + d_out)
+    n_tokens = 4 * d_in + 40
+    W = (rng.standard_normal((d_out, d_in)) * 0.02).astype(np.float32)
+    W_hat = (np.round(W / 0.01) * 0.01).astype(np.float32)
+    Xt = (rng.standard_normal((d_in, n_tokens)) * np.exp(rng.uniform(-1.0, 1.0, d_in))[:, None]).astype(np.float32)
+    need, guard = gpu.factors_workspace_bytes(d_in, d_out, r), 65536
+    buf = torch.full((need + guard,), 0x5A, dtype=torch.uint8, device="cuda")
+    Wd, Whd, Xd = (torch.from_numpy(a).cuda() for a in (W, W_hat, Xt))
+    B = torch.full((d_out, r), float("nan"), dtype=torch.float64, device="cuda")
+    A = torch.full((r, d_in), float("nan"), dtype=torch.float64, device="cuda")
+    sig = torch.full((r,), float("nan"), dtype=torch.float64, device="cuda")
+    gpu.factors(Wd, Whd, Xd, B, A, sig, n_tokens, d_in, d_out, r, 1e-12, buf[:need])
+    torch.cuda.synchronize()
+    assert bool((buf[need:] == 0x5A).all())
+    _compare(W, W_hat, Xt, r, B.cpu().numpy(), A.cpu().numpy(), sig.cpu().numpy())
