@@ -143,6 +143,9 @@ void eora_debug_set_factors_route(int route);
  * (empty before the first launch), so that a test can assert that its shape reaches the instantiation it is
  * meant to cover.  Process-wide, not synchronised with concurrent callers.  Errors: EORA_ERR_NULL. */
 int eora_debug_last_launch(char* out, size_t capacity);
+/* HOST, test hook: the parts a prompt's GEMM would cut its contraction into with `room` bytes for their fp32 outputs
+ * (each part needs 4 * M * d_out; one linear, M >= 128; nothing is enqueued), or a negative status. */
+int eora_debug_prefill_parts(int M, int d_in, int d_out, int r, size_t room);
 /* Measurement probes, enqueued on `stream` like a forward call, for quoting a layer kernel's time against what
  * the device does with no arithmetic at all.  kind 0: an empty kernel of 256 workgroups (the launch floor; src
  * and bytes ignored).  kind 1: a kernel that only reads `bytes` bytes from src (DEVICE, 16-byte aligned;

@@ -60,6 +60,7 @@ def _load():
         "eora_debug_set_resident_min_blocks": (None, [ci]),
         "eora_debug_set_factors_route": (None, [ci]),
         "eora_debug_last_launch": (ci, [ctypes.c_char_p, sz]),
+        "eora_debug_prefill_parts": (ci, [ci, ci, ci, ci, sz]),
         "eora_debug_probe": (ci, [ci, vp, sz, vp, vp]),
         "eora_pack_q": (ci, [vp, vp, vp, ci, ci, ci, ci, vp, vp, vp]),
         "eora_pack_factor_f16": (ci, [vp, ci, ci, vp]),
@@ -98,7 +99,8 @@ EXPORTS = ["eora_status_string", "eora_qweight_bytes", "eora_qzeros_bytes", "eor
            "eora_linear_q_group", "eora_linear_sp24", "eora_unpack_q", "eora_dequant_q", "eora_expand_sp24",
            "eora_sp24q4_tiles_bytes", "eora_sp24q4_meta_bytes", "eora_pack_sp24q4", "eora_linear_sp24q4", "eora_expand_sp24q4",
            "eora_factors_workspace_bytes", "eora_factors", "eora_linear_q_multi", "eora_pack_factor_q3", "eora_factors_store_f16", "eora_factors_store_q", "eora_linear_sp24_group",
-           "eora_debug_last_launch", "eora_debug_probe", "eora_linear_q_static", "eora_debug_set_resident_min_blocks", "eora_debug_set_factors_route"]
+           "eora_debug_last_launch", "eora_debug_probe", "eora_linear_q_static", "eora_debug_set_resident_min_blocks", "eora_debug_set_factors_route",
+           "eora_debug_prefill_parts"]
 
 
 def status_string(status):
@@ -263,6 +265,11 @@ def debug_last_launch():
     buf = ctypes.create_string_buffer(160)
     _check(lib.eora_debug_last_launch(buf, len(buf)), "debug_last_launch")
     return buf.value.decode()
+
+
+def debug_prefill_parts(M, d_in, d_out, r, room):
+    """Parts a prompt's GEMM would cut its contraction into with `room` bytes for their outputs."""
+    return int(lib.eora_debug_prefill_parts(int(M), int(d_in), int(d_out), int(r), int(room)))
 
 
 def debug_probe(kind, src, nbytes, sink):

@@ -208,22 +208,16 @@ constexpr int PREFILL_SPLIT_TOKENS = 1024;
 // most of the chip idle for the length of a whole contraction (333 tokens of the 8B layer: 48 tiles of 32 steps for a
 // 4096 x 4096 linear).  The cheapest by rounds of 256 tiles, 1.6 us a step and 6 a tile, the parts' fp32 outputs written
 // and read at 4 TB/s and 5 us for the second launch (each measured on the 8B shapes).
-int pick_prefill_parts(int M, int d_in, int r, const eora_q_member* members, int n, size_t room)
+// room: bytes for the partial outputs; the parts never need more.  rows, tiles: of all members together.
+int pick_prefill_parts(int M, int d_in, int r, size_t rows, int tiles, size_t room)
 {
-    size_t rows = 0;
-    int tiles = 0;
-    for (int m = 0; m < n; ++m) {
-        rows += members[m].d_out;
-        tiles += (members[m].d_out + 255) / 256;
-    }
-    tiles *= (M + 127) / 128;
     const int G = d_in / 128;
     int best = 1;
     float best_us = 1e30f;
     for (int ks = 1; ks <= 8 && ks * 4 <= G + 3; ++ks) {
-        const float bytes = (float)ks * M * rows * 4;
-        if (ks > 1 && bytes > (float)room) break;
-        const float us = (float)((tiles * ks + 255) / 256) * (1.6f * ((G + ks - 1) / ks + r / 128) + 6.f) + (ks > 1 ? 5.f + bytes * 2.f / 4e6f : 0.f);
+        const size_t bytes = (size_t)ks * M * rows * sizeof(float);
+        if (ks > 1 && bytes > room) break;                // (whole numbers: a float would round the room up to the need)
+        const float us = (float)((tiles * ks + 255) / 256) * (1.6f * ((G + ks - 1) / ks + r / 128) + 6.f) + (ks > 1 ? 5.f + (float)bytes * 2.f / 4e6f : 0.f);
         if (us < best_us) {
             best_us = us;
             best = ks;
@@ -231,6 +225,8 @@ int pick_prefill_parts(int M, int d_in, int r, const eora_q_member* members, int
     }
     return best;
 }
+
+int prefill_tiles(int M, int d_out) { return ((d_out + 255) / 256) * ((M + 127) / 128); }
 
 // validated members that share x, as GEMMs: one launch for every member's t (the members' A side by side), one
 // for every member's y
@@ -266,7 +262,13 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
     p.ldx2 = n * r;
     p.n = n;
     const size_t at = WS_T + round256(prefill_scratch_bytes(M, d_in, r, n));      // partial outputs behind t's scratch
-    p.ksplit = M <= PREFILL_SPLIT_TOKENS && workspace_bytes > at ? pick_prefill_parts(M, d_in, r, members, n, workspace_bytes - at) : 1;
+    size_t rows = 0;
+    int tiles = 0;
+    for (int m = 0; m < n; ++m) {
+        rows += members[m].d_out;
+        tiles += prefill_tiles(M, members[m].d_out);
+    }
+    p.ksplit = M <= PREFILL_SPLIT_TOKENS && workspace_bytes > at ? pick_prefill_parts(M, d_in, r, rows, tiles, workspace_bytes - at) : 1;
     p.part = (float*)((char*)workspace + at);
     for (int m = 0; m < n; ++m) {
         p.pcol[m] = p.ldp;
@@ -407,6 +409,13 @@ int eora_debug_probe(int kind, const void* src, size_t bytes, void* sink, void* 
     if (bytes == 0 || bytes % 32768 || bytes / 32768 > 0x7fffffffull) return EORA_ERR_SHAPE;
     if (failed(launch_probe_stream(src, bytes, (uint32_t*)sink, (hipStream_t)stream), "probe (stream)")) return EORA_ERR_LAUNCH;
     return EORA_OK;
+}
+
+int eora_debug_prefill_parts(int M, int d_in, int d_out, int r, size_t room)
+{
+    const int rc = check_backbone_shape(M, d_in, d_out, r);
+    if (rc != EORA_OK) return rc;
+    return pick_prefill_parts(M, d_in, r, d_out, prefill_tiles(M, d_out), room);
 }
 
 int eora_debug_last_launch(char* out, size_t capacity)

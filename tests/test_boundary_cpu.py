@@ -229,3 +229,19 @@ def test_linear_sp24_group_validation_codes():
     assert call([fp, S(g, 0x1008, None, None, g, g, g, 32)]) == -4
     assert call([fp, fp], r=48) == -2 and call([fp, fp], ws=null) == -5 and call([fp, fp], ws_bytes=16) == -5
     assert call([fp, fp], M=0) == 0
+
+
+@pytest.mark.parametrize("M,d_in,d_out,r", [(333, 4096, 4096, 128), (128, 4096, 16384, 0), (640, 14336, 4096, 256),
+                                            (1024, 28672, 2048, 512), (1023, 28672, 1040, 128)])
+def test_parts_of_a_prompt_never_need_more_than_their_room(M, d_in, d_out, r):
+    """The fp32 outputs of the parts (4 * M * d_out bytes each) fit the room they are given to the byte, also where a
+    room of one byte too few, as a float, is the room itself."""
+    most = eora.debug_prefill_parts(M, d_in, d_out, r, 1 << 62)
+    assert most > 1
+    for parts in range(2, 9):
+        need = parts * 4 * M * d_out
+        for room in (need - 1, need - 16, need - 64, need, need + 1):
+            got = eora.debug_prefill_parts(M, d_in, d_out, r, room)
+            assert got == 1 or got * 4 * M * d_out <= room, (parts, room - need, got)
+    assert eora.debug_prefill_parts(M, d_in, d_out, r, most * 4 * M * d_out) == most
+    assert eora.debug_prefill_parts(M, d_in, d_out, r, 0) == 1
