@@ -30,8 +30,8 @@ constexpr int MAX_KCN = 8;                      // k-ranges of the down-projecti
 
 // Host-side record of the kernel instantiation the most recent layer launch of this process chose, read
 // back through eora_debug_last_launch() (tests assert that a shape reaches the instantiation it is meant to
-// cover).  `fmt` is a printf format for up to six ints and must be a string literal.  Not synchronised.
-void note_launch(const char* fmt, int a = 0, int b = 0, int c = 0, int d = 0, int e = 0, int f = 0, int g = 0);
+// cover).  `fmt` is a printf format for up to eight ints and must be a string literal.  Not synchronised.
+void note_launch(const char* fmt, int a = 0, int b = 0, int c = 0, int d = 0, int e = 0, int f = 0, int g = 0, int h = 0);
 
 // General kernel of the quantised backbone (wideq.hip): 5 and more tokens, and the shapes the decode kernel does not take.
 // x is shared through LDS by the wavefronts of a workgroup.  Up to four linears that read the same x in one launch.

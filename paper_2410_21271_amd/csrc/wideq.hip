@@ -9,10 +9,10 @@
 //    LDS, where the wavefronts of a range find their fragments.  With NWR = 1 a chunk belongs to one wavefront: one
 //    slot and no barrier (a wavefront's LDS operations are carried out in order); otherwise two slots and one barrier
 //    per step.
-//  - Stored tiles come straight into the registers of the wavefront that owns the row block, D steps ahead, with the
-//    row's group scale and zero-point word beside them.  Every stored tile is decoded once per workgroup and serves all
-//    TB token blocks.  All requests are unconditional plain loads (past the end: the last tile again, never used), so
-//    that the compiler's wait counts stay exact.
+//  - Stored tiles come straight into the registers of the wavefront that owns the row block, D steps ahead; the rows'
+//    group scales and zero-point words wait in LDS, put there before the first step.  Every stored tile is decoded once
+//    per workgroup and serves all TB token blocks.  All requests are unconditional plain loads (past the end: the last
+//    tile again, never used), so that the compiler's wait counts stay exact.
 //  - Arithmetic: integer codes minus zero-point exact in fp16, fp32 accumulation per 128 columns, scaled in fp32; t in
 //    fp32, split into a high and a low fp16 part for B's product.
 //  - Low-rank path: the launch's first workgroups are producers, one (16 rows of A) x (one of kcn ranges of the
@@ -249,7 +249,6 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
 #pragma unroll
     for (int i = 1; i < 4; ++i)
         if (i < a.n && bid >= a.first[i]) mem = i;
-    // workgroups that read the same stored tiles (the token groups of one row group) sit eight apart: same XCD, same L2
     const int RBs = wq_pick(a.d_out, mem) / 16;
     int rg = bid - wq_pick(a.first, mem), tg = 0, part_id = 0;
     if (a.S > 1 || ntg > 1) {
@@ -628,7 +627,9 @@ static hipError_t launch_wide_one(WideArgs a, hipStream_t stream)
         a.ycol[i] = i > 0 && i < a.n ? a.ycol[i - 1] + a.d_out[i - 1] : 0;
         if (i < a.n) total += (a.d_out[i] / 16 + NWR * RW - 1) / (NWR * RW) * a.ntg * a.S;
     }
-    note_launch("wide_q FM=%d FA=%d NWR=%d NWK=%d TB=%d n=%d", FM, a.fa, NWR, NWK, TB, a.n);
+    const int part_tiles = (G + a.S - 1) / a.S, segments = (part_tiles + a.seg - 1) / a.seg;         // of the longest part
+    if (a.S == 1 && segments == 1) note_launch("wide_q FM=%d FA=%d NWR=%d NWK=%d TB=%d n=%d", FM, a.fa, NWR, NWK, TB, a.n);
+    else note_launch("wide_q FM=%d FA=%d NWR=%d NWK=%d TB=%d parts=%d segments=%d n=%d", FM, a.fa, NWR, NWK, TB, a.S, segments, a.n);
     hipLaunchKernelGGL(kern, dim3(total), dim3(WQ_NT), lds, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || a.S == 1) return e;

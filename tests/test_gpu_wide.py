@@ -33,9 +33,9 @@ SHAPES = [
     (2, 16, 96, 64, 1152, 1040, 384),       # coarse groups that do not divide over the ranges
     (4, 16, 160, 65, 2688, 336, 2688),      # channel-wise, a second group of token blocks with one token
     (3, 3, 128, 127, 896, 144, 128),
-    (4, 16, 512, 24, 14336, 4096, 128),     # contraction cut into parts, B's sixteen tiles shared out
-    (3, 16, 96, 37, 7296, 2688, 128),       # parts of unequal length, fewer tiles of B than parts
-    (4, 16, 0, 48, 8320, 1024, 128),        # bare, cut
+    (4, 16, 512, 24, 14336, 4096, 128),     # whole contraction at the largest rank: t of two token blocks fills the LDS
+    (3, 16, 96, 37, 7296, 2688, 128),       # three token blocks, the last ragged
+    (4, 16, 0, 48, 8320, 1024, 128),        # bare
     (4, 16, 128, 2, 2176, 1536, 128),       # few tokens, a shape the decode kernel does not take
     (2, 4, 256, 16, 11008, 272, 128),
     (4, 16, 96, 300, 1024, 256, 128),       # many tokens with a rank the GEMM path does not take: two launches
@@ -55,6 +55,78 @@ def test_wide_edges(gpu, w_bits, ab_bits, r, M, d_in, d_out, group):
     assert gpu.workspace_error(ws) == 0
 
 
+def _parts(gpu):
+    """(parts of the contraction in different workgroups, segments of the longest part) of the last launch."""
+    s = gpu.debug_last_launch()
+    assert s.startswith("wide_q "), s
+    if "parts=" not in s:
+        return 1, 1
+    return int(s.split("parts=")[1].split()[0]), int(s.split("segments=")[1].split()[0])
+
+
+# w_bits, ab_bits, r, M, d_in, d_out, group
+CUT = [
+    (3, 16, 96, 37, 7296, 2688, 128),       # parts of unequal length, fewer tiles of B than parts
+    (4, 16, 0, 48, 8320, 1024, 128),        # bare
+    (4, 16, 512, 24, 8192, 512, 128),       # sixteen tiles of B shared out over the parts
+    (4, 4, 512, 40, 8192, 272, 128),        # 4-bit factors: four tiles of B, some parts without one; a ragged row group
+    (2, 4, 64, 24, 8192, 512, 8192),        # rank 64 in 4 bits: a single tile of B; channel-wise
+    (3, 3, 128, 33, 9344, 80, 128),         # 3-bit factors; 73 tiles over the parts
+    (4, 16, 64, 12, 16384, 64, 256),        # one token block
+    (2, 3, 128, 9, 17920, 96, 128),
+    (3, 4, 256, 5, 28672, 48, 256),
+    (4, 16, 128, 70, 14336, 256, 128),      # a second group of token blocks, ragged
+]
+
+
+@pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_out,group", CUT)
+def test_wide_cut_contraction(gpu, w_bits, ab_bits, r, M, d_in, d_out, group):
+    """The contraction in parts in different workgroups, summed by a second kernel: every share [g0, g1) of B's tiles."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q
+    c = QCase(9600 + M + d_out, d_in, d_out, M, r, w_bits, group=group, ab_bits=ab_bits, packer=gpu)
+    ws = gpu.new_workspace(M, d_in, d_out, r)
+    y = run_linear_q(c, ws=ws)
+    assert _parts(gpu)[0] > 1, gpu.debug_last_launch()
+    _check(y, c.oracle_y())
+    assert np.array_equal(y, run_linear_q(c, ws=ws))
+    assert gpu.workspace_error(ws) == 0
+
+
+def test_wide_cut_contraction_several_adapters(gpu):
+    from oracle import linear
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q_multi
+    M, n, r = 24, 4, 64
+    c = QCase(9650, 8192, 512, M, n * r, 4, packer=gpu)
+    sel = (np.arange(M) % (n + 1) - 1).astype(np.int32)
+    y = run_linear_q_multi(c, sel, r)
+    assert _parts(gpu)[0] > 1, gpu.debug_last_launch()
+    _check(y, linear.eora_linear_q_multi(c.x, c.o_qw, c.o_sc, c.o_qz, c.o_A, c.o_B, c.o_As, c.o_Bs, sel, M, c.d_in, c.d_out, r, n,
+                                         c.w_bits, c.group, c.ab_bits))
+
+
+@pytest.mark.parametrize("w_bits,r,M,d_in,group", [
+    (4, 32, 40, 53632, 128),                # 400 + 19 tiles; an odd number of groups: scales one by one
+    (3, 0, 35, 57344, 256),                 # 400 + 48 tiles of coarse groups, eight scales at a time
+    (2, 32, 64, 54272, 53 * 128),           # a group of 53 tiles across the border of the segments
+])
+def test_wide_scales_in_segments(gpu, w_bits, r, M, d_in, group):
+    """A contraction longer than the scales that fit the LDS (and a workspace without room for parts, which would be
+    shorter): segment after segment."""
+    import torch
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q
+    c = QCase(9700 + M, d_in, 48, M, r, w_bits, group=group, packer=gpu)
+    need = gpu.workspace_bytes(M, d_in, 48, r) - (12 << 20) + 4 * 4 * M * 48      # (a 2:4 call of that shape would put its parts there)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    gpu.workspace_init(ws)
+    y = run_linear_q(c, ws=ws)
+    assert _parts(gpu) == (1, 2), gpu.debug_last_launch()
+    _check(y, c.oracle_y())
+    assert gpu.workspace_error(ws) == 0
+
+
 def test_wide_group_of_four_ragged_members(gpu):
     from tests.cases import QCase
     from tests.gpu_util import run_linear_q_group
@@ -67,7 +139,9 @@ def test_wide_group_cut_contraction(gpu):
     from tests.cases import QCase
     from tests.gpu_util import run_linear_q_group
     cs = [QCase(9300 + i, 14336, d, 20, 64, 4, packer=gpu) for i, d in enumerate((1024, 1040))]
-    for c, y in zip(cs, run_linear_q_group(cs, cs[0].x)):
+    ys = run_linear_q_group(cs, cs[0].x)
+    assert _parts(gpu)[0] > 1, gpu.debug_last_launch()
+    for c, y in zip(cs, ys):
         _check(y, c.oracle_y(x=cs[0].x))
 
 
@@ -82,6 +156,9 @@ def test_smaller_workspace_still_serves(gpu):
     ws = torch.empty(small, dtype=torch.uint8, device="cuda")
     gpu.workspace_init(ws)
     _check(run_linear_q(c, ws=ws), c.oracle_y())
+    assert _parts(gpu)[0] == 1
+    _check(run_linear_q(c), c.oracle_y())
+    assert _parts(gpu)[0] > 1
     with pytest.raises(gpu.EoraError) as e:
         run_linear_q(c, ws=ws[: small - 256])
     assert e.value.status == -5
