@@ -110,22 +110,6 @@ __device__ __forceinline__ void decode_tile(const uint32_t (&w)[Fmt<FMT>::WORDS]
 }
 
 // ------------------------------------------------------------------------------------------------
-// Backbone: quads of four consecutive k-tiles, RB row blocks each.
-template <int FMT, int RB>
-struct Quad {
-    uint32_t w[RB][4][Fmt<FMT>::WORDS];
-    uint2 sc[RB];       // four fp16 scales (tiles 4q .. 4q+3) of the lane's row
-    uint32_t zq[RB];    // their four zero-points, one nibble each
-};
-
-struct Backbone {
-    const uint32_t* w;
-    const _Float16* scales;   // row-major d_out x NG
-    const uint32_t* zeros;    // row-major d_out x NGW words, nibble g%8 of word g/8
-    int G, NG, NGW, gdiv;
-};
-
-// ------------------------------------------------------------------------------------------------
 // Factor tiles (A in phase A with x, B in phase B with t): plain per-tile steps.
 struct Factor {
     const uint32_t* w;
