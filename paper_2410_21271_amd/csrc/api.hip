@@ -200,6 +200,23 @@ size_t prefill_scratch_bytes(int M, int d_in, int r, int n)
     return round256((size_t)M * n * r * 2) + (ks > 1 ? (size_t)ks * M * n * r * sizeof(float) : 0);
 }
 
+// the most that prefill_scratch_bytes() names for up to M tokens and ranks (n members: r = their sum) up to r: fewer tokens
+// or columns of t may be cut into more parts (a workspace of the size of the largest call serves smaller ones too)
+size_t prefill_scratch_most(int M, int d_in, int r)
+{
+    size_t parts = 0;
+    for (int m = 128, last = 0; !last && m <= 256 * 128; m += 128) {          // (beyond 256 tiles nothing is cut)
+        last = m >= M;
+        const int tokens = last ? M : m;
+        for (int q = 128; q < r + 128; q += 128) {
+            const int cols = q < r ? q : r, ks = pick_ksplit(tokens, d_in, cols);
+            const size_t need = ks > 1 ? (size_t)ks * tokens * cols * sizeof(float) : 0;
+            parts = need > parts ? need : parts;
+        }
+    }
+    return round256((size_t)M * r * 2) + parts;
+}
+
 // room for the fp32 partial outputs of a prompt whose contraction is cut into parts (up to PREFILL_SPLIT_TOKENS tokens)
 constexpr size_t PREFILL_SPLIT_BYTES = 48u << 20;
 constexpr int PREFILL_SPLIT_TOKENS = 1024;
@@ -268,7 +285,10 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
         rows += members[m].d_out;
         tiles += prefill_tiles(M, members[m].d_out);
     }
-    p.ksplit = M <= PREFILL_SPLIT_TOKENS && workspace_bytes > at ? pick_prefill_parts(M, d_in, r, rows, tiles, workspace_bytes - at) : 1;
+    // (never more than the room every workspace of the right size has: the order of the sums, and with it the bits of y, are
+    // then the same whatever larger size the workspace has)
+    const size_t room = workspace_bytes > at ? workspace_bytes - at : 0;
+    p.ksplit = M <= PREFILL_SPLIT_TOKENS ? pick_prefill_parts(M, d_in, r, rows, tiles, room < PREFILL_SPLIT_BYTES ? room : PREFILL_SPLIT_BYTES) : 1;
     p.part = (float*)((char*)workspace + at);
     for (int m = 0; m < n; ++m) {
         p.pcol[m] = p.ldp;
@@ -341,6 +361,14 @@ size_t workspace_group_min_bytes(int M, int d_in, int r, int n)
     return WS_T + (M >= PREFILL_MIN_TOKENS ? prefill_scratch_bytes(M, d_in, r, n) : 0);
 }
 
+// what a quantised call (r: the ranks of its members together) makes use of: t of the prefill GEMM and its parts, and the
+// room for partial outputs.  Never shrinks as M or r grows.
+size_t workspace_room(int M, int d_in, int r)
+{
+    if (M >= PREFILL_MIN_TOKENS) return WS_T + prefill_scratch_most(M, d_in, r) + PREFILL_SPLIT_BYTES;
+    return WS_T + (M > 4 ? WIDE_SPLIT_BYTES : 0);
+}
+
 }  // namespace
 
 extern "C" {
@@ -348,18 +376,17 @@ extern "C" {
 size_t eora_workspace_bytes(int M, int d_in, int d_out, int r)
 {
     if (check_backbone_shape(M, d_in, d_out, r) != EORA_OK) return 0;
-    // partials of t for the small-M kernels, and t itself as fp16 M x r for the prefill GEMM
-    // (and, for a 2:4 call with a long contraction at 5 .. 127 tokens, the partial outputs of its ranges)
-    const size_t base = workspace_min_bytes(M, d_in, d_out, r), split = M > 4 && M < PREFILL_MIN_TOKENS ? WS_T + WIDE_SPLIT_BYTES : 0;
-    if (M >= PREFILL_MIN_TOKENS && M <= PREFILL_SPLIT_TOKENS) return round256(base) + PREFILL_SPLIT_BYTES;
-    return base > split ? base : split;
+    // partials of t for the small-M kernels (and, for a 2:4 call with a long contraction at 5 .. 127 tokens, the partial
+    // outputs of its ranges); for more tokens what any smaller number asks for, too
+    const int few = M < PREFILL_MIN_TOKENS ? M : PREFILL_MIN_TOKENS - 1;
+    const size_t base = workspace_min_bytes(few, d_in, d_out, r), all = workspace_room(M, d_in, r);
+    return base > all ? base : all;
 }
 
 size_t eora_workspace_bytes_group(int M, int d_in, int r, int n_members)
 {
     if (n_members < 1 || n_members > MAX_GROUP || check_backbone_shape(M, d_in, 16, r) != EORA_OK) return 0;
-    const size_t base = workspace_group_min_bytes(M, d_in, r, n_members);
-    return M >= PREFILL_MIN_TOKENS && M <= PREFILL_SPLIT_TOKENS ? round256(base) + PREFILL_SPLIT_BYTES : base;
+    return workspace_room(M, d_in, n_members * r);
 }
 
 int eora_workspace_init(void* workspace, size_t workspace_bytes, void* stream)

@@ -245,3 +245,26 @@ def test_parts_of_a_prompt_never_need_more_than_their_room(M, d_in, d_out, r):
             assert got == 1 or got * 4 * M * d_out <= room, (parts, room - need, got)
     assert eora.debug_prefill_parts(M, d_in, d_out, r, most * 4 * M * d_out) == most
     assert eora.debug_prefill_parts(M, d_in, d_out, r, 0) == 1
+
+
+@pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (14336, 4096), (28672, 8192), (1152, 272)])
+def test_workspace_sizes_never_shrink_with_tokens_or_rank(d_in, d_out):
+    """A workspace of the size of the largest (M, r) serves smaller calls too, with everything they would have asked for
+    themselves: the sizes never shrink as M, r or the number of members grows, and hold 12 MiB for partial outputs from
+    five tokens and 48 MiB from 128 tokens on, beyond what the calls work with at least."""
+    least = eora.workspace_bytes(1, 128, 16, 0)
+    Ms = [1, 4, 5, 16, 64, 100, 127, 128, 129, 333, 1000, 1024, 1025, 2048, 2500, 4096, 4097, 4737, 5000, 8192, 9000, 20000, 40000, 100000]
+    rs = [0, 32, 64, 96, 128, 160, 256, 320, 384, 512]
+    sizes = [lambda M, r: eora.workspace_bytes(M, d_in, d_out, r)] + [
+        lambda M, r, n=n: eora.workspace_bytes_group(M, d_in, r, n) for n in (1, 2, 3, 4)]
+    for size in sizes:
+        table = np.array([[size(M, r) for r in rs] for M in Ms], dtype=np.int64)
+        assert (np.diff(table, axis=0) >= 0).all() and (np.diff(table, axis=1) >= 0).all()
+        assert (table[2] - least >= 0).all()
+    for a, b in zip(sizes[1:], sizes[2:]):
+        assert all(a(M, r) <= b(M, r) for M in Ms for r in rs)
+    for M in (5, 127, 128, 1024, 1025, 8192):
+        room = (12 << 20) if M < 128 else (48 << 20)
+        for size in sizes:
+            assert size(M, 0) >= room
+            assert size(M, 128) >= room + 2 * (M if M >= 128 else 0) * 128

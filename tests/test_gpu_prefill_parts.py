@@ -72,3 +72,31 @@ def test_few_token_group_of_a_general_shape_is_one_launch(gpu):
     assert gpu.debug_last_launch().endswith("n=2"), gpu.debug_last_launch()
     for c, y in zip(cs, ys):
         _check(y, c.oracle_y(x=cs[0].x))
+
+
+def test_workspace_of_a_long_prompt_serves_short_ones_alike(gpu):
+    """A workspace sized for the longest prompt gives shorter calls what one of their own size gives them: parts, and the
+    same bits.  Also for a group, and from 5 to 127 tokens."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q, run_linear_q_group
+    big = gpu.new_workspace(5000, 4096, 272, 128, n_members=2)
+    c = QCase(9950, 4096, 272, 333, 128, 4, packer=gpu)
+    y = run_linear_q(c, ws=big)
+    assert _parts(gpu) > 1
+    assert np.array_equal(y, run_linear_q(c))
+    _check(y, c.oracle_y())
+    cs = [QCase(9960 + i, 4096, d, 140, 128, 3, packer=gpu) for i, d in enumerate((272, 80))]
+    ys = run_linear_q_group(cs, cs[0].x, ws=big)
+    assert _parts(gpu) > 1
+    for a, b, q in zip(ys, run_linear_q_group(cs, cs[0].x), cs):
+        assert np.array_equal(a, b)
+        _check(a, q.oracle_y(x=cs[0].x))
+    w = [QCase(9970 + i, 8192, d, 40, 128, 4, packer=gpu) for i, d in enumerate((272, 80))]
+    import torch
+    only = torch.empty(gpu.workspace_bytes_group(40, 8192, 128, 2), dtype=torch.uint8, device="cuda")      # (the group size alone)
+    gpu.workspace_init(only)
+    for ws in (only, big):
+        ys = run_linear_q_group(w, w[0].x, ws=ws)
+        assert "parts=" in gpu.debug_last_launch(), gpu.debug_last_launch()
+        for y, q in zip(ys, w):
+            _check(y, q.oracle_y(x=w[0].x))
