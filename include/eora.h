@@ -104,8 +104,8 @@ size_t eora_sp24q4_meta_bytes(int d_in, int d_out);                  /* d_out*(d
  * first forward call on it; every forward call leaves it usable for the next, so no per-call
  * clearing (and nothing a HIP graph could not replay) is needed.  Calls that may overlap in time
  * (different streams) need different workspaces.  r == 0 still needs a workspace.  A workspace of
- * the size of the largest (M, r) serves smaller calls too (the size never shrinks as M or r grows).  From 5
- * tokens on the size also holds 12 MiB (for d_in >= 16384 at least 4 * min(M, 127) * d_out floats): a call may
+ * the size of the largest (M, r) serves smaller calls too (the size never shrinks as M or r grows).  The
+ * size also holds 12 MiB (for 5 tokens and more and d_in >= 16384 at least 4 * min(M, 127) * d_out floats): a call may
  * cut its contraction into ranges whose partial outputs are added, in a fixed order, by a second kernel of the
  * same call.  From 128 tokens on it holds 48 MiB for the same purpose.  A quantised call with a smaller
  * workspace (about 3.3 MiB, and from 128 tokens on M * r halves and their partial sums, are needed at least) is

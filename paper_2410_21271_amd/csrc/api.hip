@@ -366,7 +366,7 @@ size_t workspace_group_min_bytes(int M, int d_in, int r, int n)
 size_t workspace_room(int M, int d_in, int r)
 {
     if (M >= PREFILL_MIN_TOKENS) return WS_T + prefill_scratch_most(M, d_in, r) + PREFILL_SPLIT_BYTES;
-    return WS_T + (M > 4 ? WIDE_SPLIT_BYTES : 0);
+    return WS_T + WIDE_SPLIT_BYTES;                       // (1 .. 4 tokens too: shapes the decode kernel does not take)
 }
 
 }  // namespace
