@@ -650,63 +650,102 @@ static hipError_t launch_wide_cfg(const WideArgs& a, int cfg, hipStream_t stream
     }
 }
 
-template <int FM>
-static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
+// The split of a launch: token blocks of a workgroup, its row blocks and ranges (configuration 0..3), parts of the contraction
+struct WidePlan { int tb, cfg, S; };
+
+// k-ranges of t: a producer's eight wavefronts take four chunks each (one range at d_in 4096: with two the consumers of a
+// gate+up launch at 64 tokens lose more to the producers' compute units than t arrives earlier, 33.3 -> 37.4 us)
+static int wide_kcn(const WideArgs& a, int tb)
 {
-    const int yblocks = (a.M + 15) / 16;
-    const int tb = yblocks >= 3 ? 4 : yblocks;
-    a.ntg = (yblocks + tb - 1) / tb;
-    const int G = a.d_in / 128;
-    // k-ranges of t: a producer's eight wavefronts take four chunks each (one range at d_in 4096: with two the consumers
-    // of a gate+up launch at 64 tokens lose more to the producers' compute units than t arrives earlier, 33.3 -> 37.4 us)
+    const int G = a.d_in / 128, ntg = ((a.M + 15) / 16 + tb - 1) / tb;
     int kcn = (G + 31) / 32;
-    while (kcn > 1 && (size_t)a.n * a.ntg * tb * 16 * kcn * a.r > a.tpair_count) --kcn;
-    a.kcn = kcn;
-    a.nprod = a.r > 0 ? a.n * (a.r / 16) * kcn * a.ntg : 0;
-    // The split of a workgroup and the parts S of the contraction: the cheapest by steps.  A step of 128 columns per range
-    // costs STEP microseconds whatever the launch's size (LDS traffic and the barrier), a workgroup's start, hand-over of t
-    // and end about 9; workgroups beyond the chip's slots come in further rounds.  The sum of the parts: with three or four
-    // token blocks it grows with the parts and the output (fitted at 41 and 64 tokens, two to eight parts; against 8
-    // microseconds whatever the size: 41 x 4608 x 1200 W3 17.2 -> 15.1 us, 37 x 7296 x 2688 W3 21.1 -> 19.4, 64 x 4096 x 1024
-    // W4 17.9 -> 16.6, 64 x 14336 x 4096 W4 27.4 -> 27.5); with one or two the fit splits too much (24 x 4096 x 1024 W4
-    // 11.0 -> 12.8 us, 24 x 14336 x 4096 21.4 -> 22.7) and 8 stays.  Measured
-    // on one-linear launches of 64 and 24 tokens, contractions of 4096 .. 14336 (down projection of the 8B layer, 64
-    // tokens: two row blocks per workgroup and one part 46.9 us, eight and seven parts 27.3).
+    while (kcn > 1 && (size_t)a.n * ntg * tb * 16 * kcn * a.r > a.tpair_count) --kcn;
+    return kcn;
+}
+
+static WidePlan wide_plan(const WideArgs& a)
+{
+    // The cheapest by steps.  A step of 128 columns per range costs STEP microseconds whatever the launch's size (LDS
+    // traffic and the barrier), a workgroup's start, hand-over of t and end about 9; workgroups beyond the chip's slots come
+    // in further rounds.  The sum of the parts: with three or four token blocks it grows with the parts and the output
+    // (fitted at 41 and 64 tokens, two to eight parts; against 8 microseconds whatever the size: 64 x 14336 x 4096 W4
+    // 27.4 -> 27.5 us, 80 x 11008 x 4096 bare 26.0); with one or two the fit splits too much (24 x 14336 x 4096
+    // 21.4 -> 22.7) and 8 stays.  Measured on one-linear launches of 64 and 24 tokens, contractions of 4096 .. 14336 (down
+    // projection of the 8B layer, 64 tokens: two row blocks per workgroup and one part 46.9 us, eight and seven parts 27.3).
     static const int per[4] = {8, 4, 2, 1}, ranges[4] = {2, 2, 4, 8};
     static const float STEP[3][4] = {{0.5f, 0.4f, 0.45f, 0.6f}, {0.85f, 0.55f, 0.65f, 1.2f}, {1.2f, 0.85f, 1.3f, 2.8f}};
-    const float* const step_us = STEP[tb == 4 ? 2 : tb - 1];
+    const int yblocks = (a.M + 15) / 16, G = a.d_in / 128;
     size_t rows = 0;
     for (int i = 0; i < a.n; ++i) rows += a.d_out[i];
-    const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
-    int cfg = 0;
-    float best = 1e30f;
-    a.S = 1;
-    for (int c = 0; c < 4; ++c) {
+    auto workgroups = [&](int tb, int c, int S) {
+        const int ntg = (yblocks + tb - 1) / tb;
         int cons = 0;
-        for (int i = 0; i < a.n; ++i) cons += (a.d_out[i] / 16 + per[c] - 1) / per[c] * a.ntg;
+        for (int i = 0; i < a.n; ++i) cons += (a.d_out[i] / 16 + per[c] - 1) / per[c] * ntg;
+        return cons * S + (a.r > 0 ? a.n * (a.r / 16) * wide_kcn(a, tb) * ntg : 0);
+    };
+    WidePlan best{yblocks >= 3 ? 4 : yblocks, 0, 1};
+    const int tb = best.tb;
+    const float* const step_us = STEP[tb == 4 ? 2 : tb - 1];
+    const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
+    float best_us = 1e30f;
+    for (int c = 0; c < 4; ++c) {
         const int slots = tb == 1 && c < 3 ? 512 : 256;   // workgroups the chip holds (registers)
         for (int S = 1; S <= 8; ++S) {
             if (S > 1 && (S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;
-            const int rounds = (cons * S + a.nprod + slots - 1) / slots, tiles = (G + S - 1) / S;
+            const int rounds = (workgroups(tb, c, S) + slots - 1) / slots, tiles = (G + S - 1) / S;
             const float t = rounds * (9.f + step_us[c] * ((tiles + ranges[c] - 1) / ranges[c])) + (S > 1 ? sum0 + sum_part * S : 0.f);
-            if (t < best) {
-                best = t;
-                cfg = c;
-                a.S = S;
+            if (t < best_us) {
+                best_us = t;
+                best = WidePlan{tb, c, S};
             }
         }
     }
+    // Small launches: fewer token blocks per workgroup, each group of them with workgroups of its own that read the same
+    // stored tiles (from L2), where the whole launch then still has one workgroup per compute unit or less and at most
+    // sixteen steps.  A step with one token block is a third as long as with four and the tiles are not what bounds such a
+    // launch (33 x 4096 x 1024 W4, rank 64: four token blocks 15.5 us, two 10.0, one 8.0; 64 x 4096 x 4096 W4, 4-bit
+    // factors: 18.8, 15.8, 15.8; 24 x 4096 x 1024 W3 bare: two 8.3, one 7.0; 48 x 2688 x 2688 W4 bare: 11.2, 8.3, 7.2).
+    // With more steps or a second round the tiles' second reading and decoding shows (100 x 7296 x 2688 W3 bare: four
+    // token blocks in three parts 18.6 us, two 22.1; 33 x 4096 x 11008 W4: 21.3, one 25.6), and with eight row blocks per
+    // workgroup it is no gain (48 x 4096 x 14336 W3: 23.0, two 23.8).  Fixed costs and steps in microseconds from 172
+    // shapes of 3 .. 256 tokens, every split of each timed: on average 0.89 of the time of the splits above, none slower.
+    static const float FIXED[2] = {4.5f, 5.5f}, LOW_RANK = 1.8f;
+    static const float BARE_LESS = 2.5f, TWO_LESS = 2.f;  // what the 9 above has too much without a low-rank term, with two token blocks
+    static const float SMALL_STEP[2][4] = {{0.f, 0.5f, 0.55f, 0.6f}, {0.f, 0.5f, 0.8f, 1.2f}};
+    if (a.r == 0) best_us -= BARE_LESS;
+    if (tb == 2) best_us -= TWO_LESS;
+    for (int t = 1; t < tb; t *= 2)
+        for (int c = 1; c < 4; ++c) {
+            const int steps = (G + ranges[c] - 1) / ranges[c];
+            if (steps > 16 || workgroups(t, c, 1) > 256) continue;
+            const float us = FIXED[t - 1] + (a.r > 0 ? LOW_RANK : 0.f) + SMALL_STEP[t - 1][c] * steps;
+            if (us < best_us) {
+                best_us = us;
+                best = WidePlan{t, c, 1};
+            }
+        }
+    return best;
+}
+
+template <int FM>
+static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
+{
+    const WidePlan p = wide_plan(a);
+    a.ntg = ((a.M + 15) / 16 + p.tb - 1) / p.tb;
+    a.kcn = wide_kcn(a, p.tb);
+    a.nprod = a.r > 0 ? a.n * (a.r / 16) * a.kcn * a.ntg : 0;
+    a.S = p.S;
     if (a.r > 0) {
-        switch (tb) {
-            case 1: return launch_wide_cfg<FM, 1, true>(a, cfg, stream);
-            case 2: return launch_wide_cfg<FM, 2, true>(a, cfg, stream);
-            default: return launch_wide_cfg<FM, 4, true>(a, cfg, stream);
+        switch (p.tb) {
+            case 1: return launch_wide_cfg<FM, 1, true>(a, p.cfg, stream);
+            case 2: return launch_wide_cfg<FM, 2, true>(a, p.cfg, stream);
+            default: return launch_wide_cfg<FM, 4, true>(a, p.cfg, stream);
         }
     }
-    switch (tb) {
-        case 1: return launch_wide_cfg<FM, 1, false>(a, cfg, stream);
-        case 2: return launch_wide_cfg<FM, 2, false>(a, cfg, stream);
-        default: return launch_wide_cfg<FM, 4, false>(a, cfg, stream);
+    switch (p.tb) {
+        case 1: return launch_wide_cfg<FM, 1, false>(a, p.cfg, stream);
+        case 2: return launch_wide_cfg<FM, 2, false>(a, p.cfg, stream);
+        default: return launch_wide_cfg<FM, 4, false>(a, p.cfg, stream);
     }
 }
 

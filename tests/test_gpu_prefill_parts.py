@@ -91,9 +91,9 @@ def test_workspace_of_a_long_prompt_serves_short_ones_alike(gpu):
     for a, b, q in zip(ys, run_linear_q_group(cs, cs[0].x), cs):
         assert np.array_equal(a, b)
         _check(a, q.oracle_y(x=cs[0].x))
-    w = [QCase(9970 + i, 8192, d, 40, 128, 4, packer=gpu) for i, d in enumerate((272, 80))]
+    w = [QCase(9970 + i, 16640, d, 40, 128, 4, packer=gpu) for i, d in enumerate((272, 80))]
     import torch
-    only = torch.empty(gpu.workspace_bytes_group(40, 8192, 128, 2), dtype=torch.uint8, device="cuda")      # (the group size alone)
+    only = torch.empty(gpu.workspace_bytes_group(40, 16640, 128, 2) + 4 * 4 * 40 * 272, dtype=torch.uint8, device="cuda")      # (and what a 2:4 call of a member would ask for)
     gpu.workspace_init(only)
     for ws in (only, big):
         ys = run_linear_q_group(w, w[0].x, ws=ws)

@@ -66,16 +66,16 @@ def _parts(gpu):
 
 # w_bits, ab_bits, r, M, d_in, d_out, group
 CUT = [
-    (3, 16, 96, 37, 7296, 2688, 128),       # parts of unequal length, fewer tiles of B than parts
-    (4, 16, 0, 48, 8320, 1024, 128),        # bare
-    (4, 16, 512, 24, 8192, 512, 128),       # sixteen tiles of B shared out over the parts
-    (4, 4, 512, 40, 8192, 272, 128),        # 4-bit factors: four tiles of B, some parts without one; a ragged row group
-    (2, 4, 64, 24, 8192, 512, 8192),        # rank 64 in 4 bits: a single tile of B; channel-wise
-    (3, 3, 128, 33, 9344, 80, 128),         # 3-bit factors; 73 tiles over the parts
+    (3, 16, 96, 37, 17024, 784, 128),       # parts of unequal length, fewer tiles of B than parts
+    (4, 16, 0, 48, 16768, 1024, 128),       # bare
+    (4, 16, 512, 24, 16640, 512, 128),      # sixteen tiles of B shared out over the parts
+    (4, 4, 512, 40, 16640, 272, 128),       # 4-bit factors: four tiles of B, some parts without one; a ragged row group
+    (2, 4, 64, 24, 16640, 512, 16640),      # rank 64 in 4 bits: a single tile of B; channel-wise
+    (3, 3, 128, 33, 17408, 80, 128),        # 3-bit factors
     (4, 16, 64, 12, 16384, 64, 256),        # one token block
     (2, 3, 128, 9, 17920, 96, 128),
     (3, 4, 256, 5, 28672, 48, 256),
-    (4, 16, 128, 70, 14336, 256, 128),      # a second group of token blocks, ragged
+    (4, 16, 128, 70, 16640, 256, 128),      # a second group of token blocks, ragged
 ]
 
 
@@ -98,7 +98,7 @@ def test_wide_cut_contraction_several_adapters(gpu):
     from tests.cases import QCase
     from tests.gpu_util import run_linear_q_multi
     M, n, r = 24, 4, 64
-    c = QCase(9650, 8192, 512, M, n * r, 4, packer=gpu)
+    c = QCase(9650, 16640, 512, M, n * r, 4, packer=gpu)
     sel = (np.arange(M) % (n + 1) - 1).astype(np.int32)
     y = run_linear_q_multi(c, sel, r)
     assert _parts(gpu)[0] > 1, gpu.debug_last_launch()
@@ -156,12 +156,49 @@ def test_smaller_workspace_still_serves(gpu):
     ws = torch.empty(small, dtype=torch.uint8, device="cuda")
     gpu.workspace_init(ws)
     _check(run_linear_q(c, ws=ws), c.oracle_y())
-    assert _parts(gpu)[0] == 1
-    _check(run_linear_q(c), c.oracle_y())
-    assert _parts(gpu)[0] > 1
     with pytest.raises(gpu.EoraError) as e:
         run_linear_q(c, ws=ws[: small - 256])
     assert e.value.status == -5
+
+
+def test_smaller_workspace_leaves_the_contraction_whole(gpu):
+    """The same linear with and without room for partial outputs: in parts, and whole."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q
+    c = QCase(9420, 14336, 1024, 40, 128, 4, packer=gpu)
+    ws = gpu.new_workspace(40, 14336, 1024, 128)
+    _check(run_linear_q(c, ws=ws), c.oracle_y())
+    assert _parts(gpu)[0] > 1
+    _check(run_linear_q(c, ws=ws[: ws.numel() - 256]), c.oracle_y())
+    assert _parts(gpu)[0] == 1
+
+
+# M, d_in, d_outs, r, w_bits, ab_bits, token blocks and row groups of a workgroup
+FEWER_BLOCKS = [
+    (33, 4096, (1024,), 64, 4, 16, 1, 1),                # three groups of one token block, the last with one token
+    (24, 1152, (272,), 0, 3, 16, 1, 1),                  # two groups
+    (48, 2688, (2688,), 0, 4, 16, 1, 2),                 # two row blocks
+    (40, 2048, (4080,), 32, 2, 16, 1, 4),                # four, the last row group ragged
+    (127, 2048, (528,), 128, 4, 4, 1, 2),                # eight groups
+    (100, 2048, (2688,), 128, 4, 3, 2, 4),               # four groups of two token blocks, one token block in the last
+    (64, 4096, (4096, 1024, 1024), 128, 4, 16, 2, 4),    # a group of members
+    (256, 1024, (528,), 96, 4, 16, 1, 4),                # sixteen groups: the most of a launch
+]
+
+
+@pytest.mark.parametrize("M,d_in,d_outs,r,w_bits,ab_bits,tb,nwr", FEWER_BLOCKS)
+def test_wide_small_launches_take_fewer_token_blocks(gpu, M, d_in, d_outs, r, w_bits, ab_bits, tb, nwr):
+    """Small launches: several groups of one or two token blocks, each with workgroups and producers of its own."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q_group
+    cs = [QCase(9430 + i + M, d_in, d, M, r, w_bits, ab_bits=ab_bits, packer=gpu) for i, d in enumerate(d_outs)]
+    ws = gpu.new_workspace(M, d_in, max(d_outs), r, n_members=len(cs))
+    ys = run_linear_q_group(cs, cs[0].x, ws=ws)
+    assert " NWR=%d " % nwr in gpu.debug_last_launch() and " TB=%d " % tb in gpu.debug_last_launch(), gpu.debug_last_launch()
+    for c, y, y2 in zip(cs, ys, run_linear_q_group(cs, cs[0].x, ws=ws)):
+        _check(y, c.oracle_y(x=cs[0].x))
+        assert np.array_equal(y, y2)
+    assert gpu.workspace_error(ws) == 0
 
 
 def test_infinities_stay_in_their_token(gpu):

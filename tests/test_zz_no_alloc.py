@@ -65,7 +65,7 @@ def test_static_workspace_entry_point_kernel_families(gpu, w_bits, ab_bits, r, M
     (4, 16, 128, 3, 14336, 4096),      # three and four tokens of a contraction the decode kernel takes for two
     (3, 16, 32, 4, 14336, 4096),
     (4, 16, 0, 2, 28672, 2048),
-    (4, 4, 128, 24, 8192, 512),
+    (4, 4, 128, 24, 16640, 512),
 ])
 def test_static_workspace_entry_point_cut_contraction(gpu, w_bits, ab_bits, r, M, d_in, d_out):
     """Both entry points cut such a contraction, so their sums are taken in one order and agree bit for bit."""
