@@ -606,8 +606,9 @@ int eora_linear_q_group(const void* x, const eora_q_member* members, int n_membe
         if (rc != EORA_OK) return rc;
     }
     int nw = 0, nq = 0;
-    if (small_kernel_fits(M, d_in, group, &nw, &nq) &&
-        (r == 0 || (r / 16) * pick_kcn(M, d_in) * n_members <= HDR_FLAGS_PER_BLOCK))
+    // one to four tokens: every group of shapes the decode kernel takes (it hands t over in tagged pairs alone, without the
+    // header's flags; four members of rank 512 in four ranges fill half of the pairs' region)
+    if (small_kernel_fits(M, d_in, group, &nw, &nq))
         return launch_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, nw, nq, workspace, (hipStream_t)stream);
     if (prefill_fits(M, r, ab_bits) && workspace_bytes >= workspace_group_min_bytes(M, d_in, r, n_members))
         return launch_prefill_group(x, members, n_members, M, d_in, r, w_bits, group, fa, fe, nullptr, 0, workspace, workspace_bytes, (hipStream_t)stream);

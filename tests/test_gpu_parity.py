@@ -148,6 +148,28 @@ def test_group_of_layers_sharing_x(gpu, w_bits, ab_bits, r, M, d_in, d_outs):
 
 
 @pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_outs", [
+    (4, 16, 512, 1, 4096, (1024, 256, 272)),        # three members at the largest rank
+    (4, 16, 512, 4, 2048, (64, 16, 48, 32)),        # four
+    (3, 4, 384, 2, 4096, (272, 64, 64)),
+    (4, 4, 512, 3, 4096, (1024, 1024, 1024, 1024)),
+    (3, 16, 256, 1, 14336, (64, 48, 16, 32)),       # more k-ranges of t for a long contraction
+])
+def test_group_of_large_ranks_is_one_decode_launch(gpu, w_bits, ab_bits, r, M, d_in, d_outs):
+    """One to four tokens at ranks whose members have more than 512 units of t together in eight ranges: the decode kernel
+    all the same, in one launch, with the bits of separate calls."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q, run_linear_q_group
+    cases = [QCase(540 + 7 * i + d_in + r, d_in, d, M, r, w_bits, ab_bits=ab_bits, packer=gpu) for i, d in enumerate(d_outs)]
+    x = cases[0].x
+    ys = run_linear_q_group(cases, x)
+    last = gpu.debug_last_launch()
+    assert last.startswith("small ") and " n=%d " % len(d_outs) in last, last
+    for c, y in zip(cases, ys):
+        _check(y, c.oracle_y(x=x))
+        assert np.array_equal(y, run_linear_q(c, x=x))
+
+
+@pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_outs", [
     (4, 16, 128, 16, 4096, (4096, 1024, 1024)),     # query / key / value at sixteen tokens
     (3, 4, 64, 37, 2048, (2048, 512)),              # three token blocks (ragged), 4-bit factors of rank 64
     (4, 16, 128, 64, 4096, (14336, 14336)),         # gate / up at 64 tokens
