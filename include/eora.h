@@ -104,8 +104,8 @@ size_t eora_sp24q4_meta_bytes(int d_in, int d_out);                  /* d_out*(d
  * first forward call on it; every forward call leaves it usable for the next, so no per-call
  * clearing (and nothing a HIP graph could not replay) is needed.  Calls that may overlap in time
  * (different streams) need different workspaces.  r == 0 still needs a workspace.  A workspace of
- * the size of the largest (M, r) serves smaller calls too (the size never shrinks as M or r grows).  The
- * size also holds 12 MiB (for 5 tokens and more and d_in >= 16384 at least 4 * min(M, 127) * d_out floats): a call may
+ * the size of the largest (M, r) serves smaller calls too (the size never shrinks as M or r grows).  From 5
+ * tokens on the size also holds 12 MiB (for d_in >= 16384 at least 4 * min(M, 127) * d_out floats): a call may
  * cut its contraction into ranges whose partial outputs are added, in a fixed order, by a second kernel of the
  * same call.  From 128 tokens on it holds 48 MiB for the same purpose.  A quantised call with a smaller
  * workspace (about 3.3 MiB, and from 128 tokens on M * r halves and their partial sums, are needed at least) is
@@ -229,10 +229,10 @@ int eora_linear_q_static(const void* x, const void* qweight, const void* scales,
  * gate / up projections, of a decoder layer (the paper compensates every linear of the model the
  * same way, Sec. 3; which of them share an input is the transformer's structure).  Member m is an
  * eora_linear_q layer of its own (own weights, factors, output and d_out); M, d_in, r, w_bits,
- * group and ab_bits are common.  For one to four tokens and group == 128 this is one launch, which
+ * group and ab_bits are common.  For one to four tokens this is one launch (up to d_in 32768), which
  * pays the launch and the hand-over of x.A^T once, with results bit-identical to n_members separate
- * eora_linear_q calls.  For 5 .. 127 tokens it is one launch too when the members together have enough
- * rows to fill the chip, and for M >= 128 (fp16 factors, r % 128 == 0, or r == 0) the members' rows
+ * eora_linear_q calls.  For 5 .. 127 tokens it is one launch too (a call whose contraction is cut adds
+ * a second), and for M >= 128 (fp16 factors, r % 128 == 0, or r == 0) the members' rows
  * form one GEMM, which keeps narrow members (d_out = 1024) from leaving most of the chip idle; in
  * these two cases sums may be split differently than in a separate call (results agree to rounding,
  * and are the same from run to run).  Other shapes run the members one after the other.

@@ -132,6 +132,13 @@ int launch_wide_group(const void* x, const eora_q_member* members, int n, int M,
         a.spin_limit = g_spin_limit;
         a.adapter = adapter ? adapter + m0 : nullptr;
         a.r_per = r_per;
+        if (!wide_q_shares_launch(a)) {                   // (at most four tokens: the only chunk)
+            for (int m = 0; m < n; ++m) {
+                const int rc = launch_wide_group(x, &members[m], 1, M, d_in, r, w_bits, group, fa, fe, workspace, workspace_bytes, stream, adapter, r_per);
+                if (rc != EORA_OK) return rc;
+            }
+            return EORA_OK;
+        }
         if (failed(launch_wide_q(a, backbone_format(w_bits), stream), "linear_q (wide)")) return EORA_ERR_LAUNCH;
     }
     return EORA_OK;
@@ -366,7 +373,7 @@ size_t workspace_group_min_bytes(int M, int d_in, int r, int n)
 size_t workspace_room(int M, int d_in, int r)
 {
     if (M >= PREFILL_MIN_TOKENS) return WS_T + prefill_scratch_most(M, d_in, r) + PREFILL_SPLIT_BYTES;
-    return WS_T + WIDE_SPLIT_BYTES;                       // (1 .. 4 tokens too: shapes the decode kernel does not take)
+    return WS_T + (M > 4 ? WIDE_SPLIT_BYTES : 0);
 }
 
 }  // namespace

@@ -68,6 +68,9 @@ struct WideArgs {
     int seg;                            // tiles of a row block whose scales sit in LDS at a time
 };
 hipError_t launch_wide_q(const WideArgs& a, int fm, hipStream_t stream);
+// Whether these members may be one launch: with one to four tokens only where their sums are then taken as in separate
+// calls (more tokens: always).
+bool wide_q_shares_launch(const WideArgs& a);
 
 // Kernel for 5 .. 16 tokens with x resident in LDS (stream.hip): one workgroup of 16 wavefronts per compute unit keeps
 // the whole x (d_in <= 4096) and finishes every output tile it starts; t is handed over as tagged pairs.

@@ -141,14 +141,15 @@ __device__ __forceinline__ void wq_up_load(const Factor& fb, const int (&R)[RW],
     }
 }
 
-template <int FE, int TB, int RW, int NWK>
-__device__ __forceinline__ void wq_up(const Factor& fb, const int (&R)[RW], int wk, int tbs, int plane, int lane,
+// tiles g0 + first, + STRIDE, ... < g1; have: the first one's words are in bw already
+template <int FE, int TB, int RW, int STRIDE>
+__device__ __forceinline__ void wq_up(const Factor& fb, const int (&R)[RW], int first, bool have, int tbs, int plane, int lane,
                                       uint32_t (&bw)[RW][4], _Float16 (&bs)[RW], int g0, int g1, f4 (&acc)[RW][TB])
 {
     constexpr int KT = Fmt<FE>::KT, NMF = KT / 32, W = Fmt<FE>::WORDS;
     const int n = lane & 15, j = lane >> 4;
-    for (int g = g0 + wk; g < g1; g += NWK) {
-        if (g != g0 + wk) wq_up_load<FE, RW>(fb, R, g, lane, bw, bs);
+    for (int g = g0 + first; g < g1; g += STRIDE) {
+        if (g != g0 + first || !have) wq_up_load<FE, RW>(fb, R, g, lane, bw, bs);
 #pragma unroll
         for (int rw = 0; rw < RW; ++rw) {
             uint32_t w[W];
@@ -173,10 +174,16 @@ __device__ __forceinline__ void wq_up(const Factor& fb, const int (&R)[RW], int 
     }
 }
 
-template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK>
+// ONE_ORDER (one to four tokens): sums in an order that no split of the workgroup changes, so that a linear in a group's
+// launch and alone has the same bits.  There are eight partial sums whatever NWK is, tile k of the backbone and of B going
+// to number k modulo 8: a wavefront takes tiles wk, wk + NWK, ..., turn and turn about into its 8 / NWK accumulators.  They
+// are added as ((0+4)+(2+6))+((1+5)+(3+7)).
+template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK, bool ONE_ORDER>
 __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kernel(WideArgs a)
 {
     static_assert(NWR * NWK == WQ_NW, "eight wavefronts");
+    static_assert(!ONE_ORDER || TB == 1, "one token block");
+    constexpr int NV = ONE_ORDER ? 8 / NWK : 1;           // accumulators per wavefront and output tile
     constexpr int SLOT = TB * 4096;                       // bytes: 16 TB tokens x 128 columns
     constexpr int NSLOT = NWR == 1 ? 1 : 2;
     constexpr int XN = (4 * TB) / NWR > 0 ? (4 * TB) / NWR : 1;      // 1 KiB pieces of a chunk per wavefront
@@ -290,11 +297,14 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
         xdst[i] = wq_xdst(wr + i * NWR, lane);
     }
     u4 xr[PX][XN];
-    f4 acc[RW][TB];
+    f4 accs[NV][RW][TB];
+    f4 (&acc)[RW][TB] = accs[0];
 #pragma unroll
-    for (int rw = 0; rw < RW; ++rw)
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-        for (int tb = 0; tb < TB; ++tb) acc[rw][tb] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int rw = 0; rw < RW; ++rw)
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) accs[v][rw][tb] = f4{0.f, 0.f, 0.f, 0.f};
     int poff[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) poff[t] = wq_frag(n, 4 * j + t);
@@ -308,10 +318,13 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
     // the contraction in segments of at most a.seg tiles (one for every usual shape): their scales fit the LDS
     for (int ga = ga0; ga < ga1; ga += a.seg) {
     const int gl = ga1 - ga < a.seg ? ga1 - ga : a.seg;
-    const int ka = ga + gl * wk / NWK, len = ga + gl * (wk + 1) / NWK - ka;   // this range's
+    // this range's tiles: consecutive ones, or (ONE_ORDER) every NWK-th
+    const int ka = ONE_ORDER ? ga + wk : ga + gl * wk / NWK;
+    const int len = ONE_ORDER ? (gl - wk + NWK - 1) / NWK : ga + gl * (wk + 1) / NWK - ka;       // (gl + NWK - 1 >= wk)
+    constexpr int STRIDE = ONE_ORDER ? NWK : 1;
     const int steps = (gl + NWK - 1) / NWK;
     auto tile_at = [&](int s) {                           // tile (= chunk of x) of step s of this range
-        const int k = ka + (s < len ? s : (len > 0 ? len - 1 : 0));
+        const int k = ka + STRIDE * (s < len ? s : (len > 0 ? len - 1 : 0));
         return k < G - 1 ? k : G - 1;
     };
     auto load_tile = [&](Pre& p, int rw, int s) {
@@ -398,7 +411,7 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
         if (s < len) {                                    // uniform over the wavefront; no global load inside
             h8 b[RW][4];
             f4 part[RW][TB];
-            const int grp = group_of(ka + s), zs = 4 * (grp & 7);
+            const int grp = group_of(ka + STRIDE * s), zs = 4 * (grp & 7);
             const int lrow = wr * RW * 16 + n;
             float sc[RW];
 #pragma unroll
@@ -419,7 +432,7 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
 #pragma unroll
             for (int rw = 0; rw < RW; ++rw) {
 #pragma unroll
-                for (int tb = 0; tb < TB; ++tb) acc[rw][tb] += sc[rw] * part[rw][tb];
+                for (int tb = 0; tb < TB; ++tb) accs[i % NV][rw][tb] += sc[rw] * part[rw][tb];
             }
         }
         asm volatile("" ::: "memory");
@@ -514,16 +527,27 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
                 }
                 if (!good_all) atomicOr(&a.hdr[HDR_ERROR], 1u);       // never expected: producers do not wait
                 __syncthreads();
-                if (a.fe == S_F16) wq_up<S_F16, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
-                else if (a.fe == S_Q4S128) wq_up<S_Q4S128, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
-                else if (a.fe == S_Q4S64) wq_up<S_Q4S64, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
-                else wq_up<S_Q3S128, TB, RW, NWK>(fb, R, wk, tbs, plane, lane, bw, bs, g0, g1, acc);
+                auto up = [&](auto fmt) {
+                    constexpr int FE = decltype(fmt)::value;
+#pragma unroll
+                    for (int v = 0; v < NV; ++v)          // (every NWK-th tile is this wavefront's)
+                        wq_up<FE, TB, RW, NV * NWK>(fb, R, wk + NWK * v, v == 0, tbs, plane, lane, bw, bs, g0, g1, accs[v]);
+                };
+                if (a.fe == S_F16) up(std::integral_constant<int, S_F16>{});
+                else if (a.fe == S_Q4S128) up(std::integral_constant<int, S_Q4S128>{});
+                else if (a.fe == S_Q4S64) up(std::integral_constant<int, S_Q4S64>{});
+                else up(std::integral_constant<int, S_Q3S128>{});
                 __syncthreads();                          // t has been used: the LDS is reused below
             }
         }
     }
 
     // ---- add the ranges' accumulators in a fixed order, convert, store ---------------------------------------
+    if constexpr (NV > 1) {
+#pragma unroll
+        for (int rw = 0; rw < RW; ++rw)
+            acc[rw][0] = NV == 2 ? accs[0][rw][0] + accs[NV / 2][rw][0] : (accs[0][rw][0] + accs[NV / 2][rw][0]) + (accs[1][rw][0] + accs[NV - 1][rw][0]);
+    }
     // through LDS as [range][token][row], so that a thread adds and stores eight consecutive rows of a token (rows of
     // 4 bytes more than a multiple of 16 banks keep the four token rows of a store apart)
     constexpr int RS = ROWS + 4;
@@ -548,11 +572,31 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
         const int m = m0 + tok, o = rg * ROWS + r8;
         if (m >= a.M || o >= d_out) continue;
         const float* p = red + (size_t)tok * RS + r8;
-        f4 v0 = *(const f4*)p, v1 = *(const f4*)(p + 4);
+        f4 v0, v1;
+        if constexpr (ONE_ORDER) {
+            f4 sums[2][NWK];
 #pragma unroll
-        for (int k2 = 1; k2 < NWK; ++k2) {
-            v0 += *(const f4*)(p + (size_t)k2 * 16 * TB * RS);
-            v1 += *(const f4*)(p + (size_t)k2 * 16 * TB * RS + 4);
+            for (int k2 = 0; k2 < NWK; ++k2) {
+                sums[0][k2] = *(const f4*)(p + (size_t)k2 * 16 * RS);
+                sums[1][k2] = *(const f4*)(p + (size_t)k2 * 16 * RS + 4);
+            }
+#pragma unroll
+            for (int w2 = NWK / 2; w2 > 0; w2 /= 2)       // halves apart
+#pragma unroll
+                for (int k2 = 0; k2 < w2; ++k2) {
+                    sums[0][k2] += sums[0][k2 + w2];
+                    sums[1][k2] += sums[1][k2 + w2];
+                }
+            v0 = sums[0][0];
+            v1 = sums[1][0];
+        } else {
+            v0 = *(const f4*)p;
+            v1 = *(const f4*)(p + 4);
+#pragma unroll
+            for (int k2 = 1; k2 < NWK; ++k2) {
+                v0 += *(const f4*)(p + (size_t)k2 * 16 * TB * RS);
+                v1 += *(const f4*)(p + (size_t)k2 * 16 * TB * RS + 4);
+            }
         }
         if (a.S > 1) {
             float* const q = a.ypart + (size_t)a.S * a.M * wq_pick(a.ycol, mem) + ((size_t)part_id * a.M + m) * d_out + o;
@@ -597,7 +641,7 @@ __global__ __launch_bounds__(256) void wide_q_sum_kernel(WideArgs a)
 }
 
 // ------------------------------------------------------------------------------------------------
-template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK>
+template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK, bool ONE_ORDER>
 static hipError_t launch_wide_one(WideArgs a, hipStream_t stream)
 {
     constexpr int NSLOT = NWR == 1 ? 1 : 2;
@@ -616,7 +660,7 @@ static hipError_t launch_wide_one(WideArgs a, hipStream_t stream)
     lds = lds > red ? lds : red;
     if (LOWRANK) lds = lds > prod ? lds : prod;
     if (LOWRANK) lds = lds > t ? lds : t;
-    auto kern = wide_q_kernel<FM, TB, RW, NWR, NWK, LOWRANK>;
+    auto kern = wide_q_kernel<FM, TB, RW, NWR, NWK, LOWRANK, ONE_ORDER>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -639,14 +683,17 @@ static hipError_t launch_wide_one(WideArgs a, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <int FM, int TB, bool LOWRANK>
+template <int FM, int TB, bool LOWRANK, bool ONE_ORDER = false>
 static hipError_t launch_wide_cfg(const WideArgs& a, int cfg, hipStream_t stream)
 {
+    if constexpr (!ONE_ORDER) {                           // (its eight row blocks' eighths do not fit 128 registers)
+        if (cfg == 0) return launch_wide_one<FM, TB, 2, 4, 2, LOWRANK, false>(a, stream);
+    }
     switch (cfg) {
-        case 0: return launch_wide_one<FM, TB, 2, 4, 2, LOWRANK>(a, stream);
-        case 1: return launch_wide_one<FM, TB, 1, 4, 2, LOWRANK>(a, stream);
-        case 2: return launch_wide_one<FM, TB, 1, 2, 4, LOWRANK>(a, stream);
-        default: return launch_wide_one<FM, TB, 1, 1, 8, LOWRANK>(a, stream);
+        case 1: return launch_wide_one<FM, TB, 1, 4, 2, LOWRANK, ONE_ORDER>(a, stream);
+        case 2: return launch_wide_one<FM, TB, 1, 2, 4, LOWRANK, ONE_ORDER>(a, stream);
+        case 3: return launch_wide_one<FM, TB, 1, 1, 8, LOWRANK, ONE_ORDER>(a, stream);
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -688,10 +735,11 @@ static WidePlan wide_plan(const WideArgs& a)
     const float* const step_us = STEP[tb == 4 ? 2 : tb - 1];
     const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
     float best_us = 1e30f;
-    for (int c = 0; c < 4; ++c) {
+    for (int c = a.M <= 4 ? 1 : 0; c < 4; ++c) {
         const int slots = tb == 1 && c < 3 ? 512 : 256;   // workgroups the chip holds (registers)
         for (int S = 1; S <= 8; ++S) {
-            if (S > 1 && (S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;
+            // (one to four tokens stay whole: the parts would depend on the rows, and with them the order of the sums)
+            if (S > 1 && (a.M <= 4 || S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;
             const int rounds = (workgroups(tb, c, S) + slots - 1) / slots, tiles = (G + S - 1) / S;
             const float t = rounds * (9.f + step_us[c] * ((tiles + ranges[c] - 1) / ranges[c])) + (S > 1 ? sum0 + sum_part * S : 0.f);
             if (t < best_us) {
@@ -727,6 +775,19 @@ static WidePlan wide_plan(const WideArgs& a)
     return best;
 }
 
+// One to four tokens: every split takes the sums in one order (ONE_ORDER above), so that a group's results are those of
+// separate calls bit for bit.  That needs scales in one segment in every split (the largest workgroup holds those of 296
+// tiles) and, in a group, t in as many ranges as a member alone has them.
+static bool wide_one_order(const WideArgs& a) { return a.M <= 4 && a.S == 1 && a.d_in <= 256 * 128; }
+
+bool wide_q_shares_launch(const WideArgs& a)
+{
+    if (a.n == 1 || a.M > 4) return true;
+    WideArgs one = a;
+    one.n = 1;
+    return a.d_in <= 256 * 128 && wide_kcn(a, 1) == wide_kcn(one, 1);
+}
+
 template <int FM>
 static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
 {
@@ -735,6 +796,7 @@ static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
     a.kcn = wide_kcn(a, p.tb);
     a.nprod = a.r > 0 ? a.n * (a.r / 16) * a.kcn * a.ntg : 0;
     a.S = p.S;
+    if (wide_one_order(a)) return a.r > 0 ? launch_wide_cfg<FM, 1, true, true>(a, p.cfg, stream) : launch_wide_cfg<FM, 1, false, true>(a, p.cfg, stream);
     if (a.r > 0) {
         switch (p.tb) {
             case 1: return launch_wide_cfg<FM, 1, true>(a, p.cfg, stream);

@@ -169,6 +169,28 @@ def test_group_of_large_ranks_is_one_decode_launch(gpu, w_bits, ab_bits, r, M, d
         assert np.array_equal(y, run_linear_q(c, x=x))
 
 
+@pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_outs,group", [
+    (3, 16, 96, 2, 2688, (2688, 896, 896), 128),    # alone, the members would all be split alike; together, with fewer ranges
+    (4, 16, 128, 1, 1152, (6448, 2160), 128),       # alone, they would be split differently
+    (4, 16, 0, 4, 14336, (4096, 1024), 128),        # one of them in parts
+    (4, 4, 128, 3, 1024, (1024, 1024, 1024), 128),
+    (2, 16, 64, 2, 2048, (2064, 272), 256),         # coarse groups: not a shape of the decode kernel either
+    (4, 16, 512, 4, 40960, (32, 48, 16, 64), 128),  # four members' t in fewer ranges than one's
+])
+def test_group_of_general_shapes_with_few_tokens_equals_separate_calls(gpu, w_bits, ab_bits, r, M, d_in, d_outs, group):
+    """One to four tokens of shapes the decode kernel does not take: bit for bit what separate calls give, whether the
+    members share a launch or not."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q, run_linear_q_group
+    cases = [QCase(560 + 7 * i + d_in + r, d_in, d, M, r, w_bits, group=group, ab_bits=ab_bits, packer=gpu) for i, d in enumerate(d_outs)]
+    x = cases[0].x
+    ys = run_linear_q_group(cases, x)
+    assert gpu.debug_last_launch().startswith("wide_q "), gpu.debug_last_launch()
+    for c, y in zip(cases, ys):
+        _check(y, c.oracle_y(x=x))
+        assert np.array_equal(y, run_linear_q(c, x=x))
+
+
 @pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_outs", [
     (4, 16, 128, 16, 4096, (4096, 1024, 1024)),     # query / key / value at sixteen tokens
     (3, 4, 64, 37, 2048, (2048, 512)),              # three token blocks (ragged), 4-bit factors of rank 64

@@ -67,16 +67,17 @@ def test_static_workspace_entry_point_kernel_families(gpu, w_bits, ab_bits, r, M
     (4, 16, 0, 2, 28672, 2048),
     (4, 4, 128, 24, 16640, 512),
 ])
-def test_static_workspace_entry_point_cut_contraction(gpu, w_bits, ab_bits, r, M, d_in, d_out):
-    """Both entry points cut such a contraction, so their sums are taken in one order and agree bit for bit."""
+def test_static_workspace_entry_point_long_contraction(gpu, w_bits, ab_bits, r, M, d_in, d_out):
+    """Both entry points cut such a contraction from five tokens on, and neither below, whatever room there is: their sums
+    are taken in one order and agree bit for bit."""
     from oracle import linear
     from tests.cases import QCase
     from tests.gpu_util import run_linear_q
     c = QCase(90 + M, d_in, d_out, M, r, w_bits, ab_bits=ab_bits, packer=gpu)
     y = _static(gpu, c)
-    assert "parts=" in gpu.debug_last_launch(), gpu.debug_last_launch()
+    assert ("parts=" in gpu.debug_last_launch()) == (M > 4), gpu.debug_last_launch()
     assert np.array_equal(y, run_linear_q(c))
-    assert "parts=" in gpu.debug_last_launch(), gpu.debug_last_launch()
+    assert ("parts=" in gpu.debug_last_launch()) == (M > 4), gpu.debug_last_launch()
     assert linear.y_error(y, c.oracle_y()) <= TOL
 
 
