@@ -439,8 +439,7 @@ def calibration_main(args):
         what = "SVD of step 5"
         m_rows, length = min(d_out, d_in), int(st["eig_rotations"])      # (Cholesky route: that counter holds the rotated rows' length)
         rows, rounds, bytes_total, ms = jacobi_round("svd", m_rows, length, False)
-    block = -(-max(2 * r, r + 64) // 128) * 128       # vectors of the subspace iteration that replaces the SVD's sweeps for small ranks
-    if st["eig_rows"] == 0 and block <= min(d_in, d_out) // 4:
+    if st["subspace_cycles"] > 0:                     # the subspace iteration replaced the sweeps over all rows
         # bound by fp64 matrix products: Gram matrix (one triangle), its factor, dW times it, the r leading components, A
         lo, hi = min(d_in, d_out), max(d_in, d_out)
         flops = 1.0 * d_in * d_in * n + d_in ** 3 / 3.0 + 1.0 * d_out * d_in * d_in + 4.0 * lo * hi * r + 2.0 * r * d_in * d_out
@@ -465,7 +464,7 @@ def calibration_main(args):
                higher_is_better=False, scaling="weak", vs_baseline=None, dtype="f64", data="synthetic",
                config=dict(workload=args.workload, gram_route="cholesky" if st["eig_rows"] == 0 else "eigendecomposition",
                            eig_sweeps=st["eig_sweeps"], eig_seconds=round(st["eig_ms"] / 1e3, 4),
-                           svd_sweeps=st["svd_sweeps"], svd_seconds=round(st["svd_ms"] / 1e3, 4)),
+                           subspace_cycles=st["subspace_cycles"], svd_sweeps=st["svd_sweeps"], svd_seconds=round(st["svd_ms"] / 1e3, 4)),
                roofline=roofline)
     if not args.no_cpu_baseline:
         from oracle import calibrate

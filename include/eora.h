@@ -345,15 +345,16 @@ size_t eora_factors_workspace_bytes(int d_in, int d_out, int r);
  * Jacobi iteration.  The SVD of step 5 is such an iteration too, over all rows, or, on the Cholesky route and for ranks well
  * below the number of rows (a block of max(2 r, r + 64) vectors, rounded up to 128, at most a quarter of min(d_in, d_out)),
  * over the rows of a block that holds the r leading components, found by a Chebyshev-filtered subspace iteration (which
- * gives way to the sweeps over all rows where it does not settle).  The call SYNCHRONISES `stream` once
+ * gives way to the sweeps over all rows where it does not settle: an error of rank below the block's size, or a spread
+ * of singular values beyond about 1e7).  The call SYNCHRONISES `stream` once
  * after the factorisation, once per sweep and per cycle of the subspace iteration and before returning, and allocates
  * nothing on the device.
  * stats: HOST pointer to eight doubles or NULL: for steps 2-3, then for the SVD, the number of sweeps, the
  * milliseconds its rounds took (events on `stream`), the workgroups that rotated their rows, and the rows a
  * workgroup handles per round (16: block rounds, taken when the row count is a multiple of 16 and the row
  * lengths are multiples of 128; 2: pair rounds).  (With the subspace iteration: the sweeps over its block, and the
- * milliseconds of all of step 5.)  The Cholesky route reports, in place of the first four, 0 sweeps,
- * its milliseconds, the length of the rows the SVD's sweeps rotated, and 0.  That length is min(d_in, d_out) when the
+ * milliseconds of all of step 5.)  The Cholesky route reports, in place of the first four, the cycles of the subspace
+ * iteration (0: not taken; negative: so many, and it gave way to the sweeps over all rows), its milliseconds, the length of the rows the SVD's sweeps rotated, and 0.  That length is min(d_in, d_out) when the
  * matrix of step 5, at least twice as long as it has rows, was first reduced to a square factor with the same singular
  * values and left singular vectors (T T^T = C C^T by a second Cholesky factorisation; not possible for an error of
  * rank below min(d_in, d_out)), else max(d_in, d_out).

@@ -365,7 +365,8 @@ def factors(W_f32, W_hat_f32, Xt_f32, B_f64, A_f64, sigma_f64, n_tokens, d_in, d
     _check(lib.eora_factors(_dp(W_f32), _dp(W_hat_f32), _dp(Xt_f32), n_tokens, d_in, d_out, r, float(eig_floor),
                             _dp(B_f64), _dp(A_f64), _dp(sigma_f64), _dp(workspace), ws_bytes, _stream(), st), "factors")
     if stats:
-        return dict(eig_sweeps=int(st[0]), eig_ms=st[1], eig_rotations=st[2], eig_rows=int(st[3]),
+        chol = int(st[3]) == 0                            # (the Cholesky route reports the subspace iteration's cycles instead of sweeps)
+        return dict(eig_sweeps=0 if chol else int(st[0]), subspace_cycles=int(st[0]) if chol else 0, eig_ms=st[1], eig_rotations=st[2], eig_rows=int(st[3]),
                     svd_sweeps=int(st[4]), svd_ms=st[5], svd_rotations=st[6], svd_rows=int(st[7]))
 
 

@@ -718,9 +718,17 @@ __global__ __launch_bounds__(64) void store_q_tiles_kernel(const double* __restr
 // (rows of Z, length m) is filtered with a Chebyshev polynomial that is bounded by 1 on [0, a], a = the smallest Ritz
 // value of the block, orthonormalised (Cholesky of its Gram matrix, twice) and rotated to its Ritz vectors; the degree
 // is what the spread of the Ritz values allows before the smallest directions drown in the rounding of the largest.
-// Leading vectors that have converged are taken out of S (S -= theta z z^T) once that lowers the spread.  Convergence
-// needs the gap to the (p + 1)-th singular value only; the r-th is told from the (r + 1)-th by the Jacobi sweeps over
-// the p rows of Z T at the end, so nothing is lost to the squares in S.  (Zhou, Saad, Tiago, Chelikowsky 2006.)
+// Leading vectors that have converged are taken out once that lowers the spread.  Convergence needs the gap to the
+// (p + 1)-th singular value only; the r-th is told from the (r + 1)-th by the Jacobi sweeps over the p rows of Z T at the
+// end.  (Zhou, Saad, Tiago, Chelikowsky 2006.)
+//  - A locked vector keeps an error of SUB_TOL of its own Ritz value, which couples it to the others.  That coupling stays
+//    inside the block and the sweeps at the end undo it, so it is no residual of theirs: Y = Z S is taken orthogonal to the
+//    locked rows.  (Counted, it held inputs whose outlier channels are 60 times the rest or more above SUB_TOL for good.)
+//  - S has the rounding of sigma_1^2 in every entry: a direction of sigma_r is off by about 1e-16 (sigma_1 / sigma_r)^2.
+//    As long as the spread of the Ritz values is at most SUB_DOWNDATE the locked vectors are taken out of S itself (that
+//    error is then below SUB_TOL); beyond, out of T, and S is formed again (T - X^T (X T) has the rounding of sigma_1 only).
+//    Largest angle between the r leading vectors and the block, numpy model, 1024 rows, r = 32 and 100, outliers 60 to 3000
+//    times the rest: 2e-12, at a spread sigma_1 / sigma_r of 3110.
 
 // deterministic entries in (-1, 1)
 __global__ void random_rows_kernel(double* __restrict__ Z, size_t n)
@@ -922,6 +930,7 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
 constexpr int SUB_CYCLES = 14;
 constexpr double SUB_SPREAD = 27.6;         // ln 1e12: growth of the largest Ritz direction over the smallest per filter
 constexpr double SUB_TOL = 1e-12;           // residual of a leading vector, relative to its Ritz value
+constexpr double SUB_DOWNDATE = 1e4;        // spread of the Ritz values up to which S is updated instead of formed again
 
 // vectors of the block for rank r of m: at least twice r, whole block rounds
 int subspace_size(int r) { return ((2 * r > r + 64 ? 2 * r : r + 64) + 127) / 128 * 128; }
@@ -946,11 +955,18 @@ void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* thr
     }
 }
 
-// S: m x m, symmetric, destroyed.  On success (1) the first p rows of `work` (p x m) are an orthonormal basis that holds
-// the r leading eigenvectors; 0: not converged or not of rank p (the caller takes another way), < 0: runtime error.
-// work: 3 p m + 3 p^2 doubles, theta / res / lam: p doubles each.
-int leading_subspace(double* S, int m, int r, int p, double* work, double* theta, double* res, double* lam, unsigned* rot, unsigned* flag,
-                     double* thr, hipStream_t st)
+// S = T T^T (both triangles) of T, m x n
+void row_products(const double* T, int m, int n, double* S, hipStream_t st)
+{
+    gemm(T, (long)n, 1L, T, (long)n, 1L, S, (long)m, m, m, n, st, 1.0, 0.0, 1);
+    hipLaunchKernelGGL(mirror_kernel, dim3((m + 31) / 32, (m + 31) / 32), dim3(256), 0, st, S, m);
+}
+
+// T: m x n.  On success (1) the first p rows of `work` (p x m) are an orthonormal basis that holds the r leading left
+// singular vectors of T; 0: not converged or not of rank p (the caller takes another way), < 0: runtime error.
+// S: m x m, T1: m x n, XT: r x n, work: 3 p m + 3 p^2 doubles, theta / res / lam: p doubles each.  *cycles: filters applied.
+int leading_subspace(const double* T, int m, int n, int r, int p, double* S, double* T1, double* XT, double* work, double* theta, double* res,
+                     double* lam, unsigned* rot, unsigned* flag, double* thr, hipStream_t st, int* cycles)
 {
     double* const Z = work;
     double* const Y = Z + (size_t)p * m;
@@ -964,13 +980,21 @@ int leading_subspace(double* S, int m, int r, int p, double* work, double* theta
     double* const h_res = host + p;
     struct Free { double* p; ~Free() { free(p); } } free_host{host};
     double shift = 0.0;                                   // S holds S - shift I
-    int nl = 0;                                           // leading rows taken out of S
+    int nl = 0;                                           // leading rows taken out
+    *cycles = 0;
+    row_products(T, m, n, S, st);
+    // rows of A (`rows` x m) minus their components in the locked rows; F: p x p scratch
+    auto against_locked = [&](double* A, int rows) {
+        gemm((const double*)A, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
+        gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, A, (long)m, rows, m, nl, st, -1.0, 1.0);
+    };
     auto times_s = [&](const double* A, double* C, int rows, double alpha, double beta) {
         gemm(A, (long)m, 1L, (const double*)S, (long)m, 1L, C, (long)m, rows, m, m, st, alpha, beta);
     };
     // Ritz rotation of all p rows: Z <- Ritz vectors (descending), Y <- Z S, theta, residuals, on the host too
     auto ritz = [&]() -> int {
         times_s(Z, Y, p, 1.0, 0.0);
+        if (nl > 0) against_locked(Y + (size_t)nl * m, p - nl);
         gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st);
         hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
         hipLaunchKernelGGL(identity_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, R, p);
@@ -996,8 +1020,10 @@ int leading_subspace(double* S, int m, int r, int p, double* work, double* theta
         orthonormalise(Z, p, m, F, R, thr, flag, st);
         if (it == 0) hipMemcpyAsync(Y, Z, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
     }
-    int rc = ritz();
+    int rc = ritz(), stalled = 0;
+    double before = 1.0;
     for (int cycle = 0; rc == 1 && cycle < SUB_CYCLES; ++cycle) {
+        *cycles = cycle + 1;
         const double a = h_theta[p - 1], x1 = 2.0 * h_theta[nl] / a - 1.0;
         int degree = (int)(SUB_SPREAD / std::acosh(x1 > 1.0 + 1e-9 ? x1 : 1.0 + 1e-9));
         degree = degree < 2 ? 2 : degree > 30 ? 30 : degree;
@@ -1019,10 +1045,7 @@ int leading_subspace(double* S, int m, int r, int p, double* work, double* theta
             sig = s2;
         }
         if (y1 != Z + (size_t)nl * m) hipMemcpyAsync(Z + (size_t)nl * m, y1, sizeof(double) * rows * m, hipMemcpyDeviceToDevice, st);
-        if (nl > 0) {                                     // against the rows taken out: z -= (z X^T) X
-            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
-            gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, Z + (size_t)nl * m, (long)m, rows, m, nl, st, -1.0, 1.0);
-        }
+        if (nl > 0) against_locked(Z + (size_t)nl * m, rows);
         orthonormalise(Z + (size_t)nl * m, rows, m, F, R, thr, flag, st);
         rc = ritz();
         if (rc != 1) break;
@@ -1032,7 +1055,20 @@ int leading_subspace(double* S, int m, int r, int p, double* work, double* theta
         if (getenv("EORA_VERBOSE")) fprintf(stderr, "eora: subspace m=%d p=%d cycle %d degree %d out %d residual %.2e\n", m, p, cycle, degree, nl, worst);
         if (worst <= SUB_TOL) return 1;
         for (done = nl; done < r - 1 && h_res[done] <= SUB_TOL * h_theta[done];) ++done;
-        if (done > nl && h_theta[nl] > 4.0 * h_theta[done]) {
+        // two cycles that do not halve the residual, with nothing to take out: it does not settle
+        const bool lock = done > nl && h_theta[nl] > 4.0 * h_theta[done];
+        stalled = lock || worst <= 0.5 * before ? 0 : stalled + 1;
+        before = worst;
+        if (stalled == 2) return 0;
+        if (lock && h_theta[0] > SUB_DOWNDATE * h_theta[r - 1]) {
+            // T1 = T - X^T (X T), S = T1 T1^T
+            gemm((const double*)Z, (long)m, 1L, T, 1L, (long)n, XT, (long)n, done, n, m, st);
+            hipLaunchKernelGGL(copy_kernel, dim3(blocks((size_t)m * n)), dim3(256), 0, st, T, T1, (size_t)m * n);
+            gemm((const double*)Z, 1L, (long)m, (const double*)XT, 1L, (long)n, T1, (long)n, m, n, done, st, -1.0, 1.0);
+            row_products(T1, m, n, S, st);
+            shift = 0.0;
+            nl = done;
+        } else if (lock) {
             // S -= sum theta_i z_i z_i^T
             hipMemcpyAsync(U, Z + (size_t)nl * m, sizeof(double) * (done - nl) * m, hipMemcpyDeviceToDevice, st);
             hipLaunchKernelGGL(scale_kernel, dim3(blocks((size_t)(done - nl) * m)), dim3(256), 0, st, U, done - nl, m, (const double*)(theta + nl), 1);
@@ -1218,9 +1254,9 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
         if (timed) hipEventRecord(e0, st);
-        gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st, 1.0, 0.0, 1);
-        hipLaunchKernelGGL(mirror_kernel, dim3((m + 31) / 32, (m + 31) / 32), dim3(256), 0, st, H, m);
-        sub = leading_subspace(H, m, r, p, V, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st);
+        int cycles = 0;
+        sub = leading_subspace(T, m, n, r, p, H, T0, by_rows ? Ap : Bn, V, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st, &cycles);
+        if (stats) stats[0] = sub == 1 ? cycles : -cycles;
         if (sub == 1) {
             gemm((const double*)V, (long)m, 1L, (const double*)T, 1L, (long)n, T0, (long)n, p, n, m, st);      // Z T
             sweeps = jacobi(T0, n, nullptr, p, sq, rot, st, stats ? stats + 4 : nullptr);

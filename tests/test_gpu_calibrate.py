@@ -358,6 +358,46 @@ def test_leading_subspace_matches_oracle(gpu, d_in, d_out, n_tokens, r):
     _compare(W, W_hat, Xt, r, B, A, sig)
 
 
+def _factors_with_stats(eora, W, W_hat, Xt, r):
+    import torch
+    d_out, d_in = W.shape
+    Wd, Whd, Xd = (torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda() for a in (W, W_hat, Xt))
+    B = torch.full((d_out, r), float("nan"), dtype=torch.float64, device="cuda")
+    A = torch.full((r, d_in), float("nan"), dtype=torch.float64, device="cuda")
+    sig = torch.full((r,), float("nan"), dtype=torch.float64, device="cuda")
+    ws = torch.empty(eora.factors_workspace_bytes(d_in, d_out, r), dtype=torch.uint8, device="cuda")
+    st = eora.factors(Wd, Whd, Xd, B, A, sig, Xt.shape[1], d_in, d_out, r, 1e-12, ws, stats=True)
+    return B.cpu().numpy(), A.cpu().numpy(), sig.cpu().numpy(), st
+
+
+@pytest.mark.parametrize("d_in,d_out,r", [(1024, 1024, 32), (768, 1024, 16), (1024, 640, 11), (512, 640, 4)])
+@pytest.mark.parametrize("scale", [1.0, 20.0, 60.0, 100.0, 300.0, 1000.0])
+def test_leading_subspace_settles_for_any_outliers(gpu, d_in, d_out, r, scale):
+    """Outlier channels up to a thousand times the rest: the leading components differ in size by as much, and the
+    iteration still ends in a few cycles (ranks below, at and above the number of outliers)."""
+    import synth
+    W, W_hat, _ = _inputs(8300 + d_in + d_out, d_in, d_out, 16)
+    Xt = synth.draw_calibration(8301, d_in, 3 * d_in, outlier_scale=scale)
+    B, A, sig, st = _factors_with_stats(gpu, W, W_hat, Xt, r)
+    assert 0 < st["subspace_cycles"] <= 6, st
+    _compare(W, W_hat, Xt, r, B, A, sig)
+
+
+def test_leading_subspace_without_a_gap(gpu):
+    """A flat spectrum: orthonormal activations and an error whose singular values fall from 1.2 to 1, so that nothing
+    sets the block apart from what is behind it."""
+    import torch
+    d_in, d_out, r = 512, 512, 16
+    rng = np.random.default_rng(8400)
+    U, V = (np.linalg.qr(rng.standard_normal((512, 512)))[0] for _ in range(2))
+    W = ((U * np.linspace(1.2, 1.0, 512)) @ V).astype(np.float32)
+    Xt = np.linalg.qr(rng.standard_normal((1400, d_in)))[0].T.astype(np.float32).copy()
+    W_hat = np.zeros_like(W)
+    B, A, sig, st = _factors_with_stats(gpu, W, W_hat, Xt, r)
+    assert st["subspace_cycles"] != 0, st
+    _compare(W, W_hat, Xt, r, B, A, sig)
+
+
 def test_leading_subspace_gives_way_to_the_sweeps(gpu):
     """An error of rank below the block's size has no such block: the sweeps over the rows take over, and the planted
     term comes back (the bound of the other planted test: W is rounded to fp32 after the term was added)."""
