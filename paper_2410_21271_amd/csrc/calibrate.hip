@@ -983,19 +983,15 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     int nl = 0;                                           // leading rows taken out
     *cycles = 0;
     row_products(T, m, n, S, st);
-    // rows of A (`rows` x m) minus their components in the locked rows; F: p x p scratch
-    auto against_locked = [&](double* A, int rows) {
-        gemm((const double*)A, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
-        gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, A, (long)m, rows, m, nl, st, -1.0, 1.0);
-    };
     auto times_s = [&](const double* A, double* C, int rows, double alpha, double beta) {
         gemm(A, (long)m, 1L, (const double*)S, (long)m, 1L, C, (long)m, rows, m, m, st, alpha, beta);
     };
     // Ritz rotation of all p rows: Z <- Ritz vectors (descending), Y <- Z S, theta, residuals, on the host too
     auto ritz = [&]() -> int {
         times_s(Z, Y, p, 1.0, 0.0);
-        if (nl > 0) against_locked(Y + (size_t)nl * m, p - nl);
         gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st);
+        if (nl > 0)                                       // Y orthogonal to the locked rows: their products with it are F's first columns
+            gemm((const double*)(F + (size_t)nl * p), (long)p, 1L, (const double*)Z, 1L, (long)m, Y + (size_t)nl * m, (long)m, p - nl, m, nl, st, -1.0, 1.0);
         hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
         hipLaunchKernelGGL(identity_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, R, p);
         double rotations = 0;
@@ -1045,7 +1041,10 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
             sig = s2;
         }
         if (y1 != Z + (size_t)nl * m) hipMemcpyAsync(Z + (size_t)nl * m, y1, sizeof(double) * rows * m, hipMemcpyDeviceToDevice, st);
-        if (nl > 0) against_locked(Z + (size_t)nl * m, rows);
+        if (nl > 0) {                                     // against the rows taken out: z -= (z X^T) X
+            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
+            gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, Z + (size_t)nl * m, (long)m, rows, m, nl, st, -1.0, 1.0);
+        }
         orthonormalise(Z + (size_t)nl * m, rows, m, F, R, thr, flag, st);
         rc = ritz();
         if (rc != 1) break;
