@@ -995,7 +995,8 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
         hipLaunchKernelGGL(identity_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, R, p);
         double rotations = 0;
-        if (jacobi_sweeps(G, p, R, p, lam, rot, st, &rotations) < 0) return 0;
+        const int swept = jacobi_sweeps(G, p, R, p, lam, rot, st, &rotations);
+        if (swept < 0) return swept == -1 ? 0 : -2;       // (a runtime error is not "did not settle")
         hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, (const double*)G, (const double*)R, p, lam);
         hipLaunchKernelGGL(sort_rows_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)lam, p, F, theta);
         gemm((const double*)F, (long)p, 1L, (const double*)Z, 1L, (long)m, U, (long)m, p, m, p, st);
