@@ -814,6 +814,12 @@ __global__ __launch_bounds__(256) void sort_rows_kernel(const double* __restrict
 
 inline unsigned blocks(size_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
 
+// (a launch like the others: its error is the call's, where an unchecked copy's would be lost)
+void copy_doubles(const double* src, double* dst, size_t n, hipStream_t st)
+{
+    hipLaunchKernelGGL(copy_kernel, dim3(blocks(n)), dim3(256), 0, st, src, dst, n);
+}
+
 template <typename TA, typename TB>
 void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
           hipStream_t st, double alpha = 1.0, double beta = 0.0, int lower = 0)
@@ -1000,9 +1006,9 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, (const double*)G, (const double*)R, p, lam);
         hipLaunchKernelGGL(sort_rows_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)lam, p, F, theta);
         gemm((const double*)F, (long)p, 1L, (const double*)Z, 1L, (long)m, U, (long)m, p, m, p, st);
-        hipMemcpyAsync(Z, U, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
+        copy_doubles(U, Z, (size_t)p * m, st);
         gemm((const double*)F, (long)p, 1L, (const double*)Y, 1L, (long)m, U, (long)m, p, m, p, st);
-        hipMemcpyAsync(Y, U, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
+        copy_doubles(U, Y, (size_t)p * m, st);
         hipLaunchKernelGGL(residual_kernel, dim3(p), dim3(256), 0, st, (const double*)Y, (const double*)Z, m, (const double*)theta, shift, res);
         unsigned bad = 1;
         if (hipMemcpyAsync(h_theta, theta, sizeof(double) * p, hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -1015,7 +1021,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     for (int it = 0; it < 2; ++it) {
         times_s(Y, Z, p, 1.0, 0.0);
         orthonormalise(Z, p, m, F, R, thr, flag, st);
-        if (it == 0) hipMemcpyAsync(Y, Z, sizeof(double) * p * m, hipMemcpyDeviceToDevice, st);
+        if (it == 0) copy_doubles(Z, Y, (size_t)p * m, st);
     }
     int rc = ritz(), stalled = 0;
     double before = 1.0;
@@ -1041,7 +1047,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
             y1 = t;
             sig = s2;
         }
-        if (y1 != Z + (size_t)nl * m) hipMemcpyAsync(Z + (size_t)nl * m, y1, sizeof(double) * rows * m, hipMemcpyDeviceToDevice, st);
+        if (y1 != Z + (size_t)nl * m) copy_doubles(y1, Z + (size_t)nl * m, (size_t)rows * m, st);
         if (nl > 0) {                                     // against the rows taken out: z -= (z X^T) X
             gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
             gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, Z + (size_t)nl * m, (long)m, rows, m, nl, st, -1.0, 1.0);
@@ -1063,14 +1069,14 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         if (lock && h_theta[0] > SUB_DOWNDATE * h_theta[r - 1]) {
             // T1 = T - X^T (X T), S = T1 T1^T
             gemm((const double*)Z, (long)m, 1L, T, 1L, (long)n, XT, (long)n, done, n, m, st);
-            hipLaunchKernelGGL(copy_kernel, dim3(blocks((size_t)m * n)), dim3(256), 0, st, T, T1, (size_t)m * n);
+            copy_doubles(T, T1, (size_t)m * n, st);
             gemm((const double*)Z, 1L, (long)m, (const double*)XT, 1L, (long)n, T1, (long)n, m, n, done, st, -1.0, 1.0);
             row_products(T1, m, n, S, st);
             shift = 0.0;
             nl = done;
         } else if (lock) {
             // S -= sum theta_i z_i z_i^T
-            hipMemcpyAsync(U, Z + (size_t)nl * m, sizeof(double) * (done - nl) * m, hipMemcpyDeviceToDevice, st);
+            copy_doubles(Z + (size_t)nl * m, U, (size_t)(done - nl) * m, st);
             hipLaunchKernelGGL(scale_kernel, dim3(blocks((size_t)(done - nl) * m)), dim3(256), 0, st, U, done - nl, m, (const double*)(theta + nl), 1);
             gemm((const double*)U, 1L, (long)m, (const double*)(Z + (size_t)nl * m), 1L, (long)m, S, (long)m, m, m, done - nl, st, -1.0, 1.0);
             nl = done;
@@ -1303,7 +1309,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         hipLaunchKernelGGL(iota_kernel, dim3(blocks(r)), dim3(256), 0, st, idx, r);
         if (stats) stats[2] = m;                // (Cholesky route: the length of the rows the SVD's sweeps rotated)
     } else {
-        hipLaunchKernelGGL(copy_kernel, dim3(blocks(nw)), dim3(256), 0, st, T, T0, nw);
+        copy_doubles(T, T0, nw, st);
         Tkeep = T0;
         // step 5: rows of T -> sigma_i z_i^T
         sweeps = jacobi(T, n, nullptr, m, sq, rot, st, stats ? stats + 4 : nullptr);
