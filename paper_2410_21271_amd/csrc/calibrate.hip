@@ -291,10 +291,10 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 // v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS sixteen k at a time, the next sixteen on their way
 // from memory meanwhile.  LDS rows of 18 doubles: a stage's sixteen k of a row are written together, and the sixteen rows
 // of a fragment start in different banks.
+// C may be A or B where a workgroup reads all it needs of it before it writes (one tile of rows or columns): no __restrict__.
 constexpr int GM_ST = 18;
 template <typename TA, typename TB>
-__global__ __launch_bounds__(256) void gemm_kernel(const TA* __restrict__ A, long ai, long ak, const TB* __restrict__ B,
-                                                   long bj, long bk, double* C, long ldc, int M, int N, int K,
+__global__ __launch_bounds__(256) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
                                                    double alpha, double beta, int lower)
 {
     __shared__ double As[2][64 * GM_ST], Bs[2][64 * GM_ST];
