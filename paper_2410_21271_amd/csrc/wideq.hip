@@ -60,11 +60,12 @@ __device__ __forceinline__ int wq_xdst(int i, int lane)
 __device__ __forceinline__ int wq_frag(int n, int p) { return (n * 16 + (p ^ n)) * 16; }
 
 // ---- producer: one block of A, one range of the contraction, TB token blocks -------------------------------------------
-template <int FA, int TB>
+// FEW: one to four tokens, the first 1 KiB piece of a chunk alone
+template <int FA, int TB, bool FEW>
 __device__ __forceinline__ void wq_produce(const WideArgs& a, const void* A, const _Float16* A_scales, int rho, int m0, int ka, int len,
                                            unsigned char* xs, int lane, f4 (&acc)[TB])
 {
-    constexpr int NT = 128 / Fmt<FA>::KT, NMF = Fmt<FA>::KT / 32;
+    constexpr int NT = 128 / Fmt<FA>::KT, NMF = Fmt<FA>::KT / 32, NP = FEW ? 1 : 4 * TB;
     const int n = lane & 15, j = lane >> 4;
     const Factor fa{(const uint32_t*)A, A_scales, a.d_in / Fmt<FA>::KT};
     const int last = a.d_in / 128 - 1;
@@ -73,7 +74,7 @@ __device__ __forceinline__ void wq_produce(const WideArgs& a, const void* A, con
         return k < last ? k : last;
     };
     FTile<FA> at[2][NT];
-    u4 xr[4 * TB];
+    u4 xr[NP];
     auto load_a = [&](FTile<FA> (&t)[NT], int s) {
         const int k = tile_at(s);
 #pragma unroll
@@ -82,7 +83,7 @@ __device__ __forceinline__ void wq_produce(const WideArgs& a, const void* A, con
     auto load_x = [&](int s) {
         const _Float16* p = a.x + (size_t)tile_at(s) * 128;
 #pragma unroll
-        for (int i = 0; i < 4 * TB; ++i) xr[i] = *(const u4*)(p + wq_xrow(a, m0, i, lane));
+        for (int i = 0; i < NP; ++i) xr[i] = *(const u4*)(p + wq_xrow(a, m0, i, lane));
     };
     load_x(0);
     load_a(at[0], 0);
@@ -93,7 +94,7 @@ __device__ __forceinline__ void wq_produce(const WideArgs& a, const void* A, con
             const int s = s0 + h;
             if (s < len) {
 #pragma unroll
-                for (int i = 0; i < 4 * TB; ++i) *(u4*)(xs + wq_xdst(i, lane)) = xr[i];
+                for (int i = 0; i < NP; ++i) *(u4*)(xs + wq_xdst(i, lane)) = xr[i];
                 load_x(s + 1);
                 asm volatile("" ::: "memory");            // (the fragments read below were written by other lanes of this wavefront)
                 if constexpr (FA == S_F16) {
@@ -179,14 +180,18 @@ __device__ __forceinline__ void wq_up(const Factor& fb, const int (&R)[RW], int 
 // to number k modulo 8: a wavefront takes tiles wk, wk + NWK, ..., turn and turn about into its 8 / NWK accumulators.  They
 // are added as ((0+4)+(2+6))+((1+5)+(3+7)).
 template <int FM, int TB, int RW, int NWR, int NWK, bool LOWRANK, bool ONE_ORDER>
-__global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kernel(WideArgs a)
+__global__ __launch_bounds__(WQ_NT, TB == 1 && (NWR > 1 || (ONE_ORDER && LOWRANK)) ? 4 : 2) void wide_q_kernel(WideArgs a)
 {
     static_assert(NWR * NWK == WQ_NW, "eight wavefronts");
     static_assert(!ONE_ORDER || TB == 1, "one token block");
     constexpr int NV = ONE_ORDER ? 8 / NWK : 1;           // accumulators per wavefront and output tile
     constexpr int SLOT = TB * 4096;                       // bytes: 16 TB tokens x 128 columns
     constexpr int NSLOT = NWR == 1 ? 1 : 2;
-    constexpr int XN = (4 * TB) / NWR > 0 ? (4 * TB) / NWR : 1;      // 1 KiB pieces of a chunk per wavefront
+    // 1 KiB pieces of a chunk (four token rows each) per wavefront.  With one to four tokens the first piece is all there is,
+    // and the others' places in LDS keep whatever they hold: rows of a matrix product that nobody reads.  (Two row blocks
+    // with 3-bit and 2-bit codes: one piece alone makes the compiler spill.)  The registers saved let two workgroups of one
+    // row block share a compute unit: 14336 x 4096 W4, three tokens 20.3 -> 15.7 us, 1024 x 1024, one token 5.7 -> 5.2.
+    constexpr int XN = ONE_ORDER && (NWR == 1 || FM == S_Q4) ? 1 : (4 * TB) / NWR;
     constexpr int PX = XN > 8 ? 1 : 2;                    // steps between a request for x and its LDS write
     constexpr int D = RW >= 4 ? 2 : 4;                    // steps between a request for a stored tile and its use
     static_assert((4 * TB) % NWR == 0, "the pieces of a chunk divide evenly over a range's wavefronts");
@@ -219,9 +224,9 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && NWR > 1 ? 4 : 2) void wide_q_kern
             const void* A = wq_pick(a.A, mem);
             const _Float16* As = wq_pick(a.A_scales, mem);
             unsigned char* xs = eora_smem + wave * SLOT;
-            if (a.fa == S_F16) wq_produce<S_F16, TB>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
-            else if (a.fa == S_Q4S128) wq_produce<S_Q4S128, TB>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
-            else wq_produce<S_Q3S128, TB>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
+            if (a.fa == S_F16) wq_produce<S_F16, TB, ONE_ORDER>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
+            else if (a.fa == S_Q4S128) wq_produce<S_Q4S128, TB, ONE_ORDER>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
+            else wq_produce<S_Q3S128, TB, ONE_ORDER>(a, A, As, rho, m0, ka, kb - ka, xs, lane, acc);
             if (tid == 0) {
                 s_epoch = epoch_v;
                 arrive(epoch_v, a.hdr, bid);
@@ -736,7 +741,7 @@ static WidePlan wide_plan(const WideArgs& a)
     const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
     float best_us = 1e30f;
     for (int c = a.M <= 4 ? 1 : 0; c < 4; ++c) {
-        const int slots = tb == 1 && c < 3 ? 512 : 256;   // workgroups the chip holds (registers)
+        const int slots = tb == 1 && (c < 3 || (a.M <= 4 && a.r > 0)) ? 512 : 256;          // workgroups the chip holds (registers)
         for (int S = 1; S <= 8; ++S) {
             // (one to four tokens stay whole: the parts would depend on the rows, and with them the order of the sums)
             if (S > 1 && (a.M <= 4 || S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;

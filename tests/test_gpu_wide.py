@@ -201,6 +201,31 @@ def test_wide_small_launches_take_fewer_token_blocks(gpu, M, d_in, d_outs, r, w_
     assert gpu.workspace_error(ws) == 0
 
 
+@pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_out,group,nwr", [
+    (4, 4, 64, 1, 1024, 1024, 128, 1),
+    (3, 16, 32, 4, 128, 48, 128, 4),                     # a single tile: one range without one
+    (2, 3, 128, 3, 1664, 1040, 128, 1),
+    (4, 16, 0, 3, 1152, 16, 1152, 1),                    # bare, channel-wise
+    (4, 16, 96, 2, 1152, 9232, 128, 2),                  # two row blocks, the last row group ragged
+    (3, 4, 128, 4, 640, 9216, 128, 2),
+    (2, 16, 0, 1, 384, 9232, 128, 2),
+    (4, 16, 32, 2, 384, 24592, 128, 4),                  # four, the last row group ragged
+    (3, 3, 128, 4, 256, 24576, 128, 4),
+    (4, 16, 64, 3, 34816, 32, 128, 1),                   # longer than one order is kept for
+])
+def test_wide_few_tokens(gpu, w_bits, ab_bits, r, M, d_in, d_out, group, nwr):
+    """One to four tokens: four of a token block's sixteen rows are all that is read, with every split of a workgroup."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q
+    c = QCase(9900 + M + d_out, d_in, d_out, M, r, w_bits, group=group, ab_bits=ab_bits, packer=gpu)
+    ws = gpu.new_workspace(M, d_in, d_out, r)
+    y = run_linear_q(c, ws=ws)
+    assert " NWR=%d " % nwr in gpu.debug_last_launch() and _parts(gpu) == (1, 1), gpu.debug_last_launch()
+    _check(y, c.oracle_y())
+    assert np.array_equal(y, run_linear_q(c, ws=ws))
+    assert gpu.workspace_error(ws) == 0
+
+
 def test_infinities_stay_in_their_token(gpu):
     """A token with an infinite activation does not disturb the others, whatever ranges and token blocks they share."""
     from tests.cases import QCase
