@@ -449,15 +449,8 @@ def calibration_main(args):
     else:
         us_round = 1e3 * ms / rounds
         kernel = "Jacobi round of the %s (%d rows of length %d per workgroup)" % (what, rows, length)
-        traffic = None                                    # HBM bytes per round from the committed counter runs, if they are of this kernel
-        tpath = os.path.join(ROOT, "profiles", "factors_traffic.json")
-        if os.path.exists(tpath):
-            with open(tpath) as f:
-                rec = json.load(f).get(args.workload)
-            if isinstance(rec, dict) and rec.get("kernel") == kernel:
-                traffic = rec.get("bytes")
         roofline = dict(bound="hbm", achieved=round(bytes_total / rounds / us_round / 1e3, 1), peak=HBM_PEAK_GBS, unit="GB/s",
-                        frac=round(bytes_total / rounds / us_round / 1e3 / HBM_PEAK_GBS, 4), traffic=traffic, kernel=kernel,
+                        frac=round(bytes_total / rounds / us_round / 1e3 / HBM_PEAK_GBS, 4), traffic=None, kernel=kernel,
                         bytes_per_launch=int(bytes_total / rounds), us_per_launch=round(us_round, 3), launches=rounds)
     out = dict(metric="seconds for Algorithm 1 steps 1-6 of one %d x %d linear (rank %d, %d calibration tokens)" % (d_out, d_in, r, n),
                value=round(sec, 4), unit="s", n_gpus=1, steps=steps, warmup=warmup, ms_per_step=round(1e3 * sec, 3),

@@ -79,7 +79,7 @@ typedef enum {
     EORA_ERR_SHAPE = -2,       /* a size violates the constraints listed at the function */
     EORA_ERR_UNSUPPORTED = -3, /* w_bits / ab_bits / group value not implemented */
     EORA_ERR_ALIGN = -4,       /* a device pointer is not 16-byte aligned */
-    EORA_ERR_WORKSPACE = -5,   /* workspace missing or smaller than eora_workspace_bytes() */
+    EORA_ERR_WORKSPACE = -5,   /* workspace missing or smaller than the call works with at least */
     EORA_ERR_LAUNCH = -6,      /* the HIP runtime refused a launch (hipGetLastError) */
     EORA_ERR_VALUE = -7,       /* host packer: a code / zero-point / position is out of range */
     EORA_ERR_TIMEOUT = -8,     /* eora_workspace_error: a bounded in-kernel wait expired (results invalid) */
@@ -345,8 +345,8 @@ size_t eora_factors_workspace_bytes(int d_in, int d_out, int r);
  * Jacobi iteration.  The SVD of step 5 is such an iteration too, over all rows, or, on the Cholesky route and for ranks well
  * below the number of rows (a block of max(2 r, r + 64) vectors, rounded up to 128, at most a quarter of min(d_in, d_out)),
  * over the rows of a block that holds the r leading components, found by a Chebyshev-filtered subspace iteration (which
- * gives way to the sweeps over all rows where it does not settle: an error of rank below the block's size, or a spread
- * of singular values beyond about 1e7).  The call SYNCHRONISES `stream` once
+ * gives way to the sweeps over all rows where it does not settle: an error of rank below the block's size, or a
+ * largest singular value some thousand times the block's smallest).  The call SYNCHRONISES `stream` once
  * after the factorisation, once per sweep and per cycle of the subspace iteration and before returning, and allocates
  * nothing on the device.
  * stats: HOST pointer to eight doubles or NULL: for steps 2-3, then for the SVD, the number of sweeps, the
