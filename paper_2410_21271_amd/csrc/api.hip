@@ -132,7 +132,7 @@ int launch_wide_group(const void* x, const eora_q_member* members, int n, int M,
         a.spin_limit = g_spin_limit;
         a.adapter = adapter ? adapter + m0 : nullptr;
         a.r_per = r_per;
-        if (!wide_q_shares_launch(a)) {                   // (at most four tokens: the only chunk)
+        if (M <= 4 && !wide_q_shares_launch(a)) {         // (a longer call's last launch may have as few tokens: it promises no bits)
             for (int m = 0; m < n; ++m) {
                 const int rc = launch_wide_group(x, &members[m], 1, M, d_in, r, w_bits, group, fa, fe, workspace, workspace_bytes, stream, adapter, r_per);
                 if (rc != EORA_OK) return rc;

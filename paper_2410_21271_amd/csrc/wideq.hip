@@ -704,6 +704,7 @@ static hipError_t launch_wide_cfg(const WideArgs& a, int cfg, hipStream_t stream
 
 // The split of a launch: token blocks of a workgroup, its row blocks and ranges (configuration 0..3), parts of the contraction
 struct WidePlan { int tb, cfg, S; };
+constexpr int ONE_ORDER_D_IN = 256 * 128;                  // longest contraction of the kernel that takes all sums in one order
 
 // k-ranges of t: a producer's eight wavefronts take four chunks each (one range at d_in 4096: with two the consumers of a
 // gate+up launch at 64 tokens lose more to the producers' compute units than t arrives earlier, 33.3 -> 37.4 us)
@@ -741,7 +742,8 @@ static WidePlan wide_plan(const WideArgs& a)
     const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
     float best_us = 1e30f;
     for (int c = a.M <= 4 ? 1 : 0; c < 4; ++c) {
-        const int slots = tb == 1 && (c < 3 || (a.M <= 4 && a.r > 0)) ? 512 : 256;          // workgroups the chip holds (registers)
+        // workgroups the chip holds (registers)
+        const int slots = tb == 1 && (c < 3 || (a.M <= 4 && a.r > 0 && a.d_in <= ONE_ORDER_D_IN)) ? 512 : 256;
         for (int S = 1; S <= 8; ++S) {
             // (one to four tokens stay whole: the parts would depend on the rows, and with them the order of the sums)
             if (S > 1 && (a.M <= 4 || S * ranges[c] > G || (size_t)S * a.M * rows > a.ypart_count)) break;
@@ -783,14 +785,14 @@ static WidePlan wide_plan(const WideArgs& a)
 // One to four tokens: every split takes the sums in one order (ONE_ORDER above), so that a group's results are those of
 // separate calls bit for bit.  That needs scales in one segment in every split (the largest workgroup holds those of 296
 // tiles) and, in a group, t in as many ranges as a member alone has them.
-static bool wide_one_order(const WideArgs& a) { return a.M <= 4 && a.S == 1 && a.d_in <= 256 * 128; }
+static bool wide_one_order(const WideArgs& a) { return a.M <= 4 && a.S == 1 && a.d_in <= ONE_ORDER_D_IN; }
 
 bool wide_q_shares_launch(const WideArgs& a)
 {
     if (a.n == 1 || a.M > 4) return true;
     WideArgs one = a;
     one.n = 1;
-    return a.d_in <= 256 * 128 && wide_kcn(a, 1) == wide_kcn(one, 1);
+    return a.d_in <= ONE_ORDER_D_IN && wide_kcn(a, 1) == wide_kcn(one, 1);
 }
 
 template <int FM>

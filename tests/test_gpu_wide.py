@@ -226,6 +226,16 @@ def test_wide_few_tokens(gpu, w_bits, ab_bits, r, M, d_in, d_out, group, nwr):
     assert gpu.workspace_error(ws) == 0
 
 
+@pytest.mark.parametrize("M,d_outs,r", [(257, (272,), 96), (259, (272, 144, 16), 96), (515, (48, 32), 160)])
+def test_wide_last_launch_of_few_tokens(gpu, M, d_outs, r):
+    """Ranks the GEMM path does not take: launches of 256 tokens, the last with one to three."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q_group
+    cs = [QCase(9990 + i, 640, d, M, r, 4, packer=gpu) for i, d in enumerate(d_outs)]
+    for c, y in zip(cs, run_linear_q_group(cs, cs[0].x)):
+        _check(y, c.oracle_y(x=cs[0].x))
+
+
 def test_infinities_stay_in_their_token(gpu):
     """A token with an infinite activation does not disturb the others, whatever ranges and token blocks they share."""
     from tests.cases import QCase
