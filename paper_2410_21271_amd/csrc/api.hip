@@ -228,29 +228,43 @@ size_t prefill_scratch_most(int M, int d_in, int r)
 constexpr size_t PREFILL_SPLIT_BYTES = 48u << 20;
 constexpr int PREFILL_SPLIT_TOKENS = 1024;
 
-// Parts of the main GEMM's contraction: a launch of few output tiles (128 tokens x 256 rows, one per compute unit) leaves
-// most of the chip idle for the length of a whole contraction (333 tokens of the 8B layer: 48 tiles of 32 steps for a
-// 4096 x 4096 linear).  The cheapest by rounds of 256 tiles, 1.6 us a step and 6 a tile, the parts' fp32 outputs written
-// and read at 4 TB/s and 5 us for the second launch (each measured on the 8B shapes).
-// room: bytes for the partial outputs; the parts never need more.  rows, tiles: of all members together.
-int pick_prefill_parts(int M, int d_in, int r, size_t rows, int tiles, size_t room)
+// Tokens per workgroup (64 tm) and parts of the main GEMM's contraction.  A workgroup is 64 tm tokens x 256 rows, one per
+// compute unit.  More tokens share the decoding of a weight, but a launch of few output tiles leaves most of the chip idle for
+// the length of a contraction (333 tokens of the 8B layer: 32 tiles for a 4096 x 4096 linear), and tokens that are not there
+// cost as much as others.  The cheapest by rounds of 256 workgroups: 1.08, 1.36, 1.60 us a step of 64 columns for tm = 2, 3, 4
+// (8192 tokens x 28672 rows, d_in 4096: 1926, 1652, 1466 us) and 5 a tile; the parts' fp32 outputs written and read at 4 TB/s
+// and 5 us for the second launch.
+// room: bytes for the partial outputs; the parts never need more.  d_out: the members' rows.
+struct PrefillPlan {
+    int tm, parts;
+};
+PrefillPlan pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
 {
+    static const float step_us[5] = {0.f, 0.f, 1.08f, 1.36f, 1.60f};
     const int G = d_in / 128;
-    int best = 1;
+    size_t rows = 0;
+    int row_tiles = 0;
+    for (int m = 0; m < n; ++m) {
+        rows += d_out[m];
+        row_tiles += (d_out[m] + 255) / 256;
+    }
+    PrefillPlan best{2, 1};
     float best_us = 1e30f;
-    for (int ks = 1; ks <= 8 && ks * 4 <= G + 3; ++ks) {
+    for (int ks = 1; ks <= 8 && (ks == 1 || (M <= PREFILL_SPLIT_TOKENS && ks * 4 <= G + 3)); ++ks) {
         const size_t bytes = (size_t)ks * M * rows * sizeof(float);
         if (ks > 1 && bytes > room) break;                // (whole numbers: a float would round the room up to the need)
-        const float us = (float)((tiles * ks + 255) / 256) * (1.6f * ((G + ks - 1) / ks + r / 128) + 6.f) + (ks > 1 ? 5.f + (float)bytes * 2.f / 4e6f : 0.f);
-        if (us < best_us) {
-            best_us = us;
-            best = ks;
+        for (int tm = 2; tm <= 4; ++tm) {
+            const size_t wgs = (size_t)row_tiles * ((M + 64 * tm - 1) / (64 * tm)) * ks;
+            const float us = (float)((wgs + 255) / 256) * (step_us[tm] * (2 * ((G + ks - 1) / ks) + (r + 63) / 64) + 5.f) +
+                             (ks > 1 ? 5.f + (float)bytes * 2.f / 4e6f : 0.f);
+            if (us < best_us) {
+                best_us = us;
+                best = {tm, ks};
+            }
         }
     }
     return best;
 }
-
-int prefill_tiles(int M, int d_out) { return ((d_out + 255) / 256) * ((M + 127) / 128); }
 
 // validated members that share x, as GEMMs: one launch for every member's t (the members' A side by side), one
 // for every member's y
@@ -267,6 +281,7 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
         p.ksplit = pick_ksplit(M, d_in, n * r);
         p.part = (float*)((char*)workspace + WS_T + round256((size_t)M * n * r * 2));
         p.ldp = n * r;
+        p.tm = 2;                                                 // (few output tiles)
         for (int m = 0; m < n; ++m) {
             p.w[m] = members[m].A;
             p.w_scales[m] = (const _Float16*)members[m].A_scales;
@@ -286,16 +301,14 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
     p.ldx2 = n * r;
     p.n = n;
     const size_t at = WS_T + round256(prefill_scratch_bytes(M, d_in, r, n));      // partial outputs behind t's scratch
-    size_t rows = 0;
-    int tiles = 0;
-    for (int m = 0; m < n; ++m) {
-        rows += members[m].d_out;
-        tiles += prefill_tiles(M, members[m].d_out);
-    }
+    int d_outs[MAX_GROUP] = {0, 0, 0, 0};
+    for (int m = 0; m < n; ++m) d_outs[m] = members[m].d_out;
     // (never more than the room every workspace of the right size has: the order of the sums, and with it the bits of y, are
     // then the same whatever larger size the workspace has)
     const size_t room = workspace_bytes > at ? workspace_bytes - at : 0;
-    p.ksplit = M <= PREFILL_SPLIT_TOKENS ? pick_prefill_parts(M, d_in, r, rows, tiles, room < PREFILL_SPLIT_BYTES ? room : PREFILL_SPLIT_BYTES) : 1;
+    const PrefillPlan plan = pick_prefill(M, d_in, r, d_outs, n, room < PREFILL_SPLIT_BYTES ? room : PREFILL_SPLIT_BYTES);
+    p.ksplit = plan.parts;
+    p.tm = plan.tm;
     p.part = (float*)((char*)workspace + at);
     for (int m = 0; m < n; ++m) {
         p.pcol[m] = p.ldp;
@@ -449,7 +462,7 @@ int eora_debug_prefill_parts(int M, int d_in, int d_out, int r, size_t room)
 {
     const int rc = check_backbone_shape(M, d_in, d_out, r);
     if (rc != EORA_OK) return rc;
-    return pick_prefill_parts(M, d_in, r, d_out, prefill_tiles(M, d_out), room);
+    return pick_prefill(M, d_in, r, &d_out, 1, room).parts;
 }
 
 int eora_debug_last_launch(char* out, size_t capacity)

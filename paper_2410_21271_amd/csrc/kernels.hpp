@@ -177,6 +177,7 @@ struct PrefillArgs {
     int ksplit;               // > 1: workgroup (tile, ks) contracts the ks-th part of K1 only (the last one K2 too) and
     float* part;              //      writes its fp32 tile to part[ks][M][ldp] (columns pcol ..) instead of y
     int ldp;
+    int tm;                   // blocks of 32 tokens per wavefront: 64 tm tokens x 256 rows per workgroup
     int n;                    // members
     const void* w[MAX_GROUP];            // first segment's weight tiles (N rows, K1 columns)
     const _Float16* w_scales[MAX_GROUP];

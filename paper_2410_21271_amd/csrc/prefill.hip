@@ -5,407 +5,552 @@
 // launch of the same kernel with A as the weight operand (fp16 M x r into scratch): recomputing it
 // per output tile would cost r / 128 times the backbone's MFMA work.
 //
-// Workgroup: 8 wavefronts, tile = 128 tokens x 256 output rows, contraction in steps of 128 (one
-// quantisation group); each wavefront owns all 128 tokens x 32 rows = 4 accumulator blocks of
-// v_mfma_f32_32x32x16_f16, the instruction with the highest sustained rate here (measured with
-// register-only loops: 2.2 PFLOP/s against 1.9 for the 16x16x32 form).  Its operand layout is:
-// lane l holds 8 consecutive k (8*(l/32) ..) of token / output row l%32; result register v of lane l
-// is token 8*(v/4) + 4*(l/32) + v%4, output row l%32 (checked on the device against a host matmul).
-//   - Weights never touch LDS.  The stored tiles (16 rows x 128 columns, lane (n, j) = row n, columns
-//     32j .. 32j+31, tiles.hpp) feed this MFMA as well: lane l = n + 16*h + 32*kg of the wavefront loads,
-//     for jp = 0, 1, the 16 bytes of stored lane (n, 2*jp + kg) of the tile of its row block h; word
-//     t of that load decodes to the operand of the k-slice (jp, t): columns 32*(2jp+kg) + 8t .. +7 of
-//     output row 16*h + n of the wavefront's 32.  Every wavefront loads its own two tiles one step
-//     ahead, decodes them to the exact integers code - zero and multiplies by the fp16 group scale
-//     (one fp16 rounding of scale*(code-zero), relative error <= 2^-11 per weight; scaling the
-//     accumulators per group instead would cost as many VALU cycles as the group's MFMAs).  Every
-//     weight is decoded exactly once per workgroup, and LDS carries only x.
-//   - x: the 128 x 128 slab is read with coalesced 16-byte loads (256 bytes per token row) into
-//     registers two steps ahead and written one step ahead to the other of two LDS buffers as MFMA
-//     operand fragments (32 tokens x 16 columns = 1 KiB, one ds_read_b128 each; an XOR of the token
-//     slot with the slice number keeps both the scattered writes and the reads free of bank
-//     conflicts): one barrier per step.
-//   - The two wavefronts of a SIMD (w and w + 4) run the two halves of a step, decode (VALU) and
-//     contraction (MFMA), in opposite order, so that the two pipes are busy at the same time.
-// One workgroup per compute unit (two wavefronts per SIMD, at most 256 registers).  The epilogue
-// transposes through LDS so that y is written in 128-byte rows.
+// Workgroup: 8 wavefronts (2 along the tokens x 4 along the rows), tile = 64 TM tokens x 256 rows, contraction in steps of 64
+// columns; a wavefront owns 32 TM tokens x 64 rows as blocks of v_mfma_f32_16x16x32_f16 (A: 16 rows of weights, B: 16 tokens;
+// lane l holds columns 8 (l / 16) .. + 7 of row / token l % 16, result register v is row 4 (l / 16) + v of token l % 16).
+//
+// What bounds it is the card's power: with all compute units busy the clock falls to 1.3 .. 1.8 GHz, and the time follows the
+// energy of the work more than its cycles.  Register-only loops over normally distributed activations and dequantised weights
+// run at 2.02 PFLOP/s with 16x16x32 and at 1.75 with 32x32x16 (with zeros both reach 2.4), so the smaller form is taken; the
+// library's GEMM reaches 1.47 on fp16 weights of the size below.  8192 tokens x 28672 rows, d_in 4096, 4 bits: 1466 us
+// (1.31 PFLOP/s); the kernel before this one (128 x 256 tiles, 32x32x16, weights decoded into the registers of each
+// wavefront, x read from LDS once per 32 rows) 1850 us.
+//   - 256 tokens (TM = 4) share the decoding of a weight and the reading of x by 256 rows: 1926, 1652, 1466 us with 128, 192
+//     and 256.  More does not fit: 128 accumulator registers of 256, and three slabs of x next to two of weights in LDS.
+//   - Weights: every lane decodes 32 of them a step (one stored lane's words; exact integers code - zero, times the fp16 scale
+//     of the group: one rounding, relative error <= 2^-11 per weight) and writes them to LDS as four 16-byte chunks, between
+//     the MFMAs of the step before; the words are requested two steps ahead.
+//   - x goes from memory to LDS without passing registers, one step ahead (through registers and ds_write: 1600 us).
+//   - Both slabs are rows of 64 columns with the 16-byte chunks of a row XOR-ed by half the row's number: reads and writes
+//     of 16 bytes per lane are served in groups of 16 lanes {0-3, 12-15, 20-23, 24-27}, ..., and none has two lanes on a bank.
+//   - A step has one barrier.  The last quarter of its MFMAs is carried out behind it, under the first LDS reads of the next.
+//   - Requests for x are spread over the step (all at once, every wavefront waits for 350 cycles to get rid of them: 1572 us
+//     instead of 1542), and a wavefront's priority falls as it gets through the step: left to age, wavefronts 0..3 run ahead
+//     of those they share a SIMD with and idle for a third of the step at the barrier (1502 us instead of 1466).
+//   - Scales come eight groups at a time (16 bytes per row): one by one their lines cost as many bytes of L2 as x does.
 #include "segments.hpp"
 
 namespace eora {
 
-typedef float f16v __attribute__((ext_vector_type(16)));
 
-// one member of a launch, as the helpers below see it
-struct PfView {
-    const _Float16* x;
-    int ldx;
-    const void* w;
-    const _Float16* w_scales;
-    const uint32_t* w_zeros;
-    int group;
-    const _Float16* x2;
-    int ldx2;
-    const void* w2;
-    const _Float16* w2_scales;
-    void* y;
-    int ldy;
-    int M, N, K1, K2;
-    int ksplit;
-    float* part;
-    int ldp, pcol;
+constexpr int PF_BN = 256;                            // output rows per workgroup
+constexpr int PF_NW = 8, PF_NT = PF_NW * 64;          // wavefronts: 2 along the tokens x 4 along the rows
+constexpr int PF_WS = PF_BN * 128;                    // one slab of weights: 256 rows x 64 columns fp16
+constexpr int pf_bm(int tm) { return 64 * tm; }       // tokens per workgroup: TM blocks of 32 per wavefront
+constexpr int pf_lds(int tm) { return 3 * pf_bm(tm) * 128 + 2 * PF_WS; }      // three slabs of x, two of weights
+
+#define PF_SCHED() __builtin_amdgcn_sched_barrier(0)
+// A slab in LDS is rows of 64 columns (128 bytes); the 16-byte chunk c of row R sits at slot c ^ ((R >> 1) & 7).
+__device__ __forceinline__ int pf_slot(int row, int c) { return row * 128 + ((c ^ ((row >> 1) & 7)) << 4); }
+
+// Scales and zero-points of the lane's row: those of eight consecutive groups where a row's allow 16-byte loads, else of one.
+struct WScale {
+    uint32_t s[4], z;
 };
 
-constexpr int PF_BM = 128, PF_BN = 256;
-constexpr int PF_NW = 8, PF_NT = PF_NW * 64;         // wavefronts: 2 (tokens) x 4 (rows)
-constexpr int PF_XS = 32 * 1024;                      // one x slab: 4 token blocks x 8 slices x 1 KiB
-constexpr int PF_LDS = 2 * PF_XS;                     // the two x slabs; the epilogue's staging tiles (40 KiB) reuse them
+// Loads whose address is a uniform base and a 32-bit offset per lane: buffer instructions take both as they are (with plain
+// pointers the compiler keeps 64-bit addresses per lane, and the kernel does not fit its registers).  The offsets are
+// clamped to valid rows by the caller; the descriptor checks nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pf_rsrc(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -1, 0x00027000);
+}
 
-__device__ __forceinline__ f16v mfma32(h8 a, h8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+template <int WORDS>
+__device__ __forceinline__ void pf_load(uint32_t (&w)[WORDS], __amdgpu_buffer_rsrc_t r, uint32_t lane_off, uint32_t off)
+{
+    typedef uint32_t u3 __attribute__((ext_vector_type(3)));
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    if constexpr (WORDS == 4) {
+        const u4 v = __builtin_amdgcn_raw_buffer_load_b128(r, lane_off, off, 0);
+        w[0] = v[0]; w[1] = v[1]; w[2] = v[2]; w[3] = v[3];
+    } else if constexpr (WORDS == 3) {
+        const u3 v = __builtin_amdgcn_raw_buffer_load_b96(r, lane_off, off, 0);
+        w[0] = v[0]; w[1] = v[1]; w[2] = v[2];
+    } else {
+        const u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, lane_off, off, 0);
+        w[0] = v[0]; w[1] = v[1];
+    }
+}
 
-// weights of one 128-wide step for the wavefront's two pairs of row blocks, exactly as loaded: nothing
-// here is touched before decode_wpre(), a whole step later (any arithmetic on a loaded value at load
-// time would make the wavefront wait for the request it has just issued)
+// 64 chunks of 16 bytes from memory straight into 1 KiB of LDS, lane after lane: from rsrc + lane_off + OFF to lds + OFF.
+// The compiler does not know of the request: it counts in vmcnt all the same, so the compiler's own waits only get longer,
+// and whoever reads the bytes waits for them (pf_arrived) before the barrier in front of the reads.
+template <int OFF>
+__device__ __forceinline__ void pf_load_lds(u4 rsrc, uint32_t lane_off, uint32_t lds)
+{
+    static_assert(OFF >= 0 && OFF < 4096 && OFF % 16 == 0, "");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen offset:%3 lds" : : "s"(lds), "v"(lane_off), "s"(rsrc), "i"(OFF) : "memory", "m0");
+}
+// everything but the NEWER last requests is there
+template <int NEWER>
+__device__ __forceinline__ void pf_arrived()
+{
+    static_assert(NEWER <= 4, "");
+    if constexpr (NEWER == 0) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+    else if constexpr (NEWER == 1) asm volatile("s_waitcnt vmcnt(1)" : : : "memory");
+    else if constexpr (NEWER == 2) asm volatile("s_waitcnt vmcnt(2)" : : : "memory");
+    else if constexpr (NEWER == 3) asm volatile("s_waitcnt vmcnt(3)" : : : "memory");
+    else asm volatile("s_waitcnt vmcnt(4)" : : : "memory");
+}
+template <int V> struct PfInt { static constexpr int value = V; };
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void pf_for(F&& f)
+{
+    if constexpr (I < N) {
+        f(PfInt<I>{});
+        pf_for<N, I + 1>(f);
+    }
+}
+
+// Stored words of one step of 64 columns, as loaded: the lane owns row (lane & 31) of the wavefront's 32 rows and the
+// chunks 4q .. 4q+3 of the step, q = lane >> 5 (fp16 tiles: chunks 2i + q).
 template <int FMT>
-struct WPre {
-    uint32_t w[2][Fmt<FMT>::WORDS];                   // [jp]
-    uint32_t zraw;                                    // the word that holds the group's zero-point nibble
-    uint32_t sraw;                                    // fp16 scale bits, zero-extended
-    int zshift;                                       // 4 * (group index % 8)
+struct WReg {
+    uint32_t w[FMT == S_Q4S64 ? 4 : Fmt<FMT>::WORDS];
 };
 template <>
-struct WPre<S_F16> {
-    u4 v[8];                                          // [slice]: four tiles of 32 columns = eight slices of 16
+struct WReg<S_F16> {
+    u4 v[4];
 };
 
-// Rl: the row block (2*wn + h, clamped) whose row n this lane supplies.  tiles / scales / zeros / K / group: the
-// segment's stored operand (first segment: the backbone, or A for the down-projection launch; second: B).
+// One segment's stored operand, seen from a lane: everything is relative to the workgroup's first row block.
+struct WSeg {
+    __amdgpu_buffer_rsrc_t tiles;                     // from the workgroup's first row block
+    __amdgpu_buffer_rsrc_t scales;                    // from its first row
+    __amdgpu_buffer_rsrc_t zeros;
+    int K;
+    uint32_t tile_off, scale_off, zero_off;           // the lane's byte offsets
+    uint32_t gdiv, gmagic;                            // tiles of 128 columns per quantisation group, and ceil(2^32 / gdiv)
+    int ng;                                           // groups per row
+    bool by8;                                         // scales and zero-points eight groups at a time
+};
+
+// rb: the lane's row block, relative and clamped to a valid one
 template <int FMT>
-__device__ __forceinline__ void load_wpre_from(WPre<FMT>& r, const void* tiles, const _Float16* scales, const uint32_t* zeros,
-                                               int K, int group, int Rl, int g, int lane)
+__device__ __forceinline__ void place_w(WSeg& a, int rb, int lane)
 {
-    const int n = lane & 15, kg = lane >> 5;
-    constexpr int WORDS = Fmt<FMT>::WORDS;
-    const int G = K / 128;
-    const int NG = Fmt<FMT>::ASYM ? K / group : G, grp = Fmt<FMT>::ASYM ? (g * 128) / group : g;
-    r.zshift = 4 * (grp & 7);
-    const uint32_t* tile = (const uint32_t*)tiles + ((size_t)Rl * G + g) * 64 * WORDS;
-#pragma unroll
-    for (int jp = 0; jp < 2; ++jp) load_words<WORDS>(r.w[jp], tile + (16 * (2 * jp + kg) + n) * WORDS);
-    const size_t row = (size_t)Rl * 16 + n;
-    r.sraw = ((const uint16_t*)scales)[row * NG + grp];
-    if constexpr (Fmt<FMT>::ASYM) r.zraw = zeros[row * ((NG + 7) / 8) + (grp >> 3)];
+    const int n = lane & 15, q = lane >> 5;
+    if constexpr (FMT == S_F16) a.tile_off = (uint32_t)(rb * (a.K / 32) * 64 + 16 * q + n) * 16u;
+    else if constexpr (FMT == S_Q4S64) a.tile_off = (uint32_t)(rb * 64 + 32 * q + n) * 8u;
+    else a.tile_off = (uint32_t)(rb * (a.K / 128) * 64 + 16 * q + n) * (4u * Fmt<FMT>::WORDS);
+    a.scale_off = (uint32_t)(rb * 16 + n) * a.ng * 2u;
+    a.zero_off = (uint32_t)(rb * 16 + n) * ((a.ng + 7) / 8) * 4u;
+    a.by8 = FMT != S_Q4S64 && a.gdiv == 1 && a.ng % 8 == 0;
 }
 
+// step s: columns 64 s .. 64 s + 63 of the segment
 template <int FMT>
-__device__ __forceinline__ void load_wpre(WPre<FMT>& r, const PfView& a, int Rl, int g, int lane)
+__device__ __forceinline__ void load_w(WReg<FMT>& r, const WSeg& a, int s)
 {
-    load_wpre_from<FMT>(r, a.w, a.w_scales, a.w_zeros, a.K1, a.group, Rl, g, lane);
-}
-
-// decode to operands bf[slice], slice = 4*jp + t, scale folded in fp16
-template <int FMT>
-__device__ __forceinline__ void decode_wpre(const WPre<FMT>& r, h8 (&bf)[8])
-{
-    const uint32_t z = Fmt<FMT>::ASYM ? (r.zraw >> r.zshift) & 0xFu : 8u;       // (symmetric formats carry their constant themselves)
-    const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)r.sraw);
-    const h8 s = {sc, sc, sc, sc, sc, sc, sc, sc};
+    if constexpr (FMT == S_F16) {                     // chunk 2 i + q: tile 2 s + i / 2, its columns 8 (2 (i % 2) + q) ..
+        const int nt = a.K / 32;
 #pragma unroll
-    for (int jp = 0; jp < 2; ++jp) {
-        h8 b[4];
-        decode_tile<FMT>(r.w[jp], z, b);
-#pragma unroll
-        for (int t = 0; t < 4; ++t) bf[4 * jp + t] = b[t] * s;
+        for (int i = 0; i < 4; ++i) {
+            int t = 2 * s + (i >> 1);
+            t = t < nt ? t : nt - 1;
+            r.v[i] = __builtin_amdgcn_raw_buffer_load_b128(a.tiles, a.tile_off, (uint32_t)(t * 64 + 32 * (i & 1)) * 16u, 0);
+        }
+    } else if constexpr (FMT == S_Q4S64) {            // one tile of 64 columns: two stored lanes of two words
+        uint32_t v[2][2];
+        pf_load<2>(v[0], a.tiles, a.tile_off, 0);
+        pf_load<2>(v[1], a.tiles, a.tile_off, 16 * 8);
+        r.w[0] = v[0][0]; r.w[1] = v[0][1]; r.w[2] = v[1][0]; r.w[3] = v[1][1];
+    } else {
+        pf_load<Fmt<FMT>::WORDS>(r.w, a.tiles, a.tile_off, (uint32_t)((s >> 1) * 64 + 32 * (s & 1)) * (4u * Fmt<FMT>::WORDS));
     }
 }
 
-// fp16 tiles (A for the down-projection launch, B in the second segment) straight into operands
-__device__ __forceinline__ void load_b_frags(h8 (&bf)[8], const void* __restrict__ tiles, int K, int Rl, int step, int lane)
+template <int FMT>
+__device__ __forceinline__ void load_scale(WScale& r, const WSeg& a, int s)
 {
-    const int n = lane & 15, kg = lane >> 5;
-    const u4* p = (const u4*)tiles + ((size_t)Rl * (K / 32) + 4 * step) * 64 + n;
-#pragma unroll
-    for (int f = 0; f < 8; ++f) bf[f] = __builtin_bit_cast(h8, p[(f >> 1) * 64 + 16 * (2 * (f & 1) + kg)]);
-}
-
-// x slab of one step: thread tid owns the 16-byte chunks c = tid + 256*i, i = 0..7; chunk c is token row
-// c / 16 of the tile and columns 8*(c % 16) .. +7 of the step (coalesced: 256 bytes per row).
-constexpr int PF_XC = 2048 / PF_NT;                   // 16-byte chunks of the slab per thread
-__device__ __forceinline__ void load_x(u4 (&v)[PF_XC], const _Float16* __restrict__ act, int ld, int M, int m0, int col0, int tid)
-{
-#pragma unroll
-    for (int i = 0; i < PF_XC; ++i) {
-        const int c = tid + PF_NT * i;
-        int row = m0 + (c >> 4);
-        row = row < M ? row : M - 1;                  // rows beyond M re-read the last row; never stored
-        v[i] = *(const u4*)(act + (size_t)row * ld + col0 + 8 * (c & 15));
-    }
-}
-
-// The operand (token block tb of 32, slice f) holds for lane (token slot, kg) the eight columns that the
-// weight operand of slice f holds for kg: chunk kc = 4*(2*jp + kg) + t, f = 4*jp + t, for a quantised
-// tile (quarter_major); chunk kc = 4*tile + 2*s + kg, f = 2*tile + s, for four fp16 tiles.  The token slot
-// is XOR-ed with 2*f + kg: the 16 lanes that write one token row's chunks, and the 16 lanes of a read
-// that differ in token, then hit 16 different bank groups.
-__device__ __forceinline__ int x_slot(int tb, int f, int kg, int tr) { return ((tb * 8 + f) * 64 + 32 * kg + (tr ^ (2 * f + kg))) * 16; }
-
-__device__ __forceinline__ void store_x(const u4 (&v)[PF_XC], unsigned char* buf, bool quarter_major, int tid)
-{
-#pragma unroll
-    for (int i = 0; i < PF_XC; ++i) {
-        const int c = tid + PF_NT * i;
-        const int row = c >> 4, kc = c & 15;
-        const int f = quarter_major ? ((kc >> 3) << 2) | (kc & 3) : kc >> 1;
-        const int kg = quarter_major ? (kc >> 2) & 1 : kc & 1;
-        *(u4*)(buf + x_slot(row >> 5, f, kg, row & 31)) = v[i];
-    }
-}
-
-// The activation fragments of slice f + 2 are requested from LDS right after the MFMAs of slice f have been
-// issued (two register sets): left to itself the compiler keeps two fragments and waits for each pair of
-// LDS reads right before the two MFMAs that use them, and the LDS latency, not the MFMA pipe, then sets the
-// pace of this phase.
-__device__ __forceinline__ void contract_step(f16v (&acc)[4], const h8 (&bf)[8], const unsigned char* buf, int lane)
-{
-    const int tr = lane & 31, kg = lane >> 5;
-    h8 af[2][4];
-#pragma unroll
-    for (int f = 0; f < 2; ++f)
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) af[f][mb] = *(const h8*)(buf + x_slot(mb, f, kg, tr));
-#pragma unroll
-    for (int f = 0; f < 8; ++f) {
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb) acc[mb] = mfma32(af[f & 1][mb], bf[f], acc[mb]);
-        if (f + 2 < 8) {
-#pragma unroll
-            for (int mb = 0; mb < 4; ++mb) af[f & 1][mb] = *(const h8*)(buf + x_slot(mb, f + 2, kg, tr));
+    if constexpr (FMT != S_F16) {
+        const uint32_t g = s >> 1;
+        if (a.by8) {
+            const u4 v = __builtin_amdgcn_raw_buffer_load_b128(a.scales, a.scale_off, (g & ~7u) * 2u, 0);
+            r.s[0] = v[0]; r.s[1] = v[1]; r.s[2] = v[2]; r.s[3] = v[3];
+            if constexpr (Fmt<FMT>::ASYM) r.z = __builtin_amdgcn_raw_buffer_load_b32(a.zeros, a.zero_off, (g >> 3) * 4u, 0);
+        } else {
+            const uint32_t grp = a.gdiv == 1 ? g : __umulhi(g, a.gmagic);
+            r.s[0] = __builtin_amdgcn_raw_buffer_load_b16(a.scales, a.scale_off, grp * 2u, 0);
+            if constexpr (Fmt<FMT>::ASYM) r.z = __builtin_amdgcn_raw_buffer_load_b32(a.zeros, a.zero_off, (grp >> 3) * 4u, 0);
         }
     }
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);            // LDS reads of slices 0 and 1
-#pragma unroll
-    for (int f = 0; f < 6; ++f) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);        // the MFMAs of slice f
-        __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);        // the LDS reads of slice f + 2
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
 }
 
-template <bool V> struct PfFlag { static constexpr bool value = V; };
+// whether step s is the first that the values loaded before it do not cover
+template <int FMT>
+__device__ __forceinline__ bool scale_due(const WSeg& a, int s) { return FMT != S_F16 && (s & (a.by8 ? 15 : 1)) == 0; }
+
+template <int FMT>
+__device__ __forceinline__ void pick_scale(const WScale& r, const WSeg& a, int s, uint32_t& sraw, uint32_t& z)
+{
+    sraw = 0;
+    z = FMT == S_Q3S128 ? 4u : 8u;
+    if constexpr (FMT != S_F16) {
+        const uint32_t g = s >> 1, grp = a.by8 || a.gdiv == 1 ? g : __umulhi(g, a.gmagic);
+        const uint32_t s0 = r.s[0], s1 = r.s[1], s2 = r.s[2], s3 = r.s[3];
+        const uint32_t o = a.by8 ? g & 7 : 0, lo = o & 2 ? s1 : s0, hi = o & 2 ? s3 : s2;
+        sraw = (o & 4 ? hi : lo) >> (16 * (o & 1));
+        if constexpr (Fmt<FMT>::ASYM) z = (r.z >> (4 * (grp & 7))) & 0xFu;
+    }
+}
+
+// the four pairs of three-bit codes that form fragment T (columns 8T .. 8T + 7 of the lane's 32)
+template <int T>
+__device__ __forceinline__ h8 dq3_frag(const uint32_t (&d)[3], uint32_t z)
+{
+    const h2 eighth = {(_Float16)0.125f, (_Float16)0.125f}, sixtyfourth = {(_Float16)0.015625f, (_Float16)0.015625f};
+    const uint32_t magic = in_vgpr(MAGIC);
+    Frag f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int p = 4 * T + e;
+        if (p == 15) {
+            uint32_t last = and_or(d[0] >> 15, 0x00010001u, magic);
+            last = and_or(d[1] >> 14, 0x00020002u, last);
+            last = and_or(d[2] >> 13, 0x00040004u, last);
+            f.p[e] = as_h2(last) - as_h2(k1024(z));
+        } else {
+            const int o = p % 5;
+            const uint32_t w = o < 3 ? d[p / 5] : d[p / 5] >> 9;
+            if (o % 3 == 0) f.p[e] = as_h2(and_or(w, 0x00070007u, magic)) - as_h2(k1024(z));
+            else if (o % 3 == 1) f.p[e] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00380038u, magic)), eighth, -as_h2(k128(z)));
+            else f.p[e] = __builtin_elementwise_fma(as_h2(and_or(w, 0x01C001C0u, magic)), sixtyfourth, -as_h2(k16(z)));
+        }
+    }
+    return f.v;
+}
+
+// two-bit codes: fragment T is half of word T / 2
+template <int T>
+__device__ __forceinline__ h8 dq2_frag(const uint32_t (&d)[2], uint32_t z)
+{
+    const h2 quarter = {(_Float16)0.25f, (_Float16)0.25f}, sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f};
+    const h2 sixtyfourth = {(_Float16)0.015625f, (_Float16)0.015625f};
+    const uint32_t magic = in_vgpr(MAGIC), w = T & 1 ? d[T / 2] >> 8 : d[T / 2];
+    Frag f;
+    f.p[0] = as_h2(and_or(w, 0x00030003u, magic)) - as_h2(k1024(z));
+    f.p[1] = __builtin_elementwise_fma(as_h2(and_or(w, 0x000C000Cu, magic)), quarter, -as_h2(0x5C005C00u | (z * 0x00040004u)));
+    f.p[2] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00300030u, magic)), sixteenth, -as_h2(k64(z)));
+    f.p[3] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00C000C0u, magic)), sixtyfourth, -as_h2(k16(z)));
+    return f.v;
+}
+
+// fragment T (of four) of the lane's chunks into the slab; the group's scale is folded in (one fp16 rounding per weight).
+// wl: the lane's first chunk in the slab
+template <int FMT, int T>
+__device__ __forceinline__ void store_w(const WReg<FMT>& r, uint32_t sraw, uint32_t z, uint32_t wl, bool valid = true)
+{
+    if constexpr (FMT == S_F16) {
+        u4 v = r.v[T];
+        if (!valid) v = u4{0u, 0u, 0u, 0u};
+        *(u4*)(eora_smem + (wl ^ (T << 5))) = v;
+    } else {
+        const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)sraw);
+        const h8 s = {sc, sc, sc, sc, sc, sc, sc, sc};
+        h8 b;
+        if constexpr (FMT == S_Q3 || FMT == S_Q3S128) b = dq3_frag<T>(r.w, z);
+        else if constexpr (FMT == S_Q2) b = dq2_frag<T>(r.w, z);
+        else b = dq4_word(r.w[T], k1024(z), k64(z));
+        *(h8*)(eora_smem + (wl ^ (T << 4))) = b * s;
+    }
+}
 
 // FM: format of the first segment's weights (S_Q4, S_Q3, S_Q2 asymmetric; S_Q4S128, S_Q3S128, S_F16 for the
-// down-projection launch).  FE2: S_NONE, or the format of a second segment's tiles (B: S_F16, S_Q4S128, S_Q3S128):
-// the kernel then continues over a
-// second segment of fp16 tiles (B) with its own activations (t).
-template <int FM, int FE2>
+// down-projection launch).  FE2: S_NONE, or the format of a second segment's tiles (B): the kernel then continues over a
+// second segment with its own activations (t).  TM: blocks of 32 tokens per wavefront.
+template <int FM, int FE2, int TM>
 __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
 {
     constexpr bool EXT = FE2 != S_NONE;
-    constexpr bool E16 = FE2 == S_F16 || FE2 == S_NONE;           // second segment's tiles are fp16 (or there is none)
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int wn = wave;                                          // this wavefront's 128 tokens x 32 rows of the 128 x 256 tile
-    int ntn = 0;                                                  // column tiles of all members
+    constexpr int BM = pf_bm(TM), XS = BM * 128, FX = EXT ? FE2 : S_F16;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    int ntn = 0;                                                  // row tiles of all members
     for (int m = 0; m < ga.n; ++m) ntn += (ga.N[m] + PF_BN - 1) / PF_BN;
-    const int ntm = (ga.M + PF_BM - 1) / PF_BM;
+    const int ntm = (ga.M + BM - 1) / BM;
     const int tile_id = blockIdx.x % (ntn * ntm), ks = blockIdx.x / (ntn * ntm);     // ks > 0 only with ksplit > 1
-    const int m0 = (tile_id / ntn) * PF_BM;
-    int nt = tile_id % ntn, mem = 0;                              // column tile within its member
+    const int m0 = (tile_id / ntn) * BM;
+    int nt = tile_id % ntn, mem = 0;                              // row tile within its member
     while (mem + 1 < ga.n && nt >= (ga.N[mem] + PF_BN - 1) / PF_BN) {
         nt -= (ga.N[mem] + PF_BN - 1) / PF_BN;
         ++mem;
     }
-    const PfView a{ga.x, ga.ldx, ga.w[mem], ga.w_scales[mem], ga.w_zeros[mem], ga.group, ga.x2[mem], ga.ldx2, ga.w2[mem], ga.w2_scales[mem],
-                   ga.y[mem], ga.ldy[mem], ga.M, ga.N[mem], ga.K1, ga.K2, ga.ksplit, ga.part, ga.ldp, ga.pcol[mem]};
-    const int R0 = nt * (PF_BN / 16);
-    const int nblk = a.N / 16;
-    const int h = (lane >> 4) & 1;
-    const int Rl = R0 + 2 * wn + h < nblk ? R0 + 2 * wn + h : nblk - 1;   // the row block this lane supplies a row of, clamped to a valid one
-    const int G1 = a.K1 / 128, G2 = EXT ? a.K2 / 128 : 0;
+    const int M = ga.M, N = ga.N[mem], K1 = ga.K1, K2 = ga.K2;
+    const int R0 = nt * (PF_BN / 16), nblk = N / 16;
+    int rb = 2 * wave + ((lane >> 4) & 1);                        // the row block this lane supplies a row of, clamped to a valid one
+    rb = R0 + rb < nblk ? rb : nblk - 1 - R0;
+    const int H1 = K1 / 64, H2 = EXT ? (K2 + 63) / 64 : 0;
     // this workgroup's steps: [sb, se) of the first segment, and with the last part the second segment's, [se, GT)
-    const int sb = ks * G1 / a.ksplit, se = (ks + 1) * G1 / a.ksplit;
-    const int GT = EXT && ks == a.ksplit - 1 ? G1 + G2 : se;
-    constexpr bool W16 = FM == S_F16;                             // first segment's weights are fp16 tiles
-    unsigned char* const buf0 = eora_smem;
-    unsigned char* const buf1 = eora_smem + PF_XS;
+    const int sb = 2 * (ks * (H1 / 2) / ga.ksplit), se = 2 * ((ks + 1) * (H1 / 2) / ga.ksplit);
+    const int GT = EXT && ks == ga.ksplit - 1 ? H1 + H2 : se;
 
-    f16v acc[4];                                                  // token blocks of 32
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) acc[i][q] = 0.f;
-
-    // x slab of step s into registers (steps past the end re-read the last one; never stored)
-    auto fetch_x = [&](u4 (&v)[PF_XC], int s) {
-        s = s < GT ? s : GT - 1;
-        if (EXT && s >= G1) load_x(v, a.x2, a.ldx2, a.M, m0, (s - G1) * 128, tid);
-        else load_x(v, a.x, a.ldx, a.M, m0, s * 128, tid);
-    };
-    u4 xr[PF_XC];
-    // the stored tiles of two steps are in flight: one step (about 2 us) is less than a memory round trip
-    // under load.  Step sb + i uses set i & 1 (the loops below are unrolled in pairs: no run-time index).
-    WPre<W16 ? S_Q4 : FM> wp[2];                                  // (unused for fp16 tiles)
-    fetch_x(xr, sb);
-    if constexpr (!W16) {
-        const int lastw = se - 1;
-        load_wpre<FM>(wp[0], a, Rl, sb, lane);
-        load_wpre<FM>(wp[1], a, Rl, sb + 1 < lastw ? sb + 1 : lastw, lane);
+    WSeg w1;
+    w1.K = K1;
+    w1.gdiv = Fmt<FM>::ASYM ? ga.group / 128 : 1;
+    w1.gmagic = w1.gdiv > 1 ? (uint32_t)((0x100000000ull + w1.gdiv - 1) / w1.gdiv) : 0u;
+    w1.ng = K1 / 128 / (int)w1.gdiv;
+    w1.tiles = pf_rsrc((const uint32_t*)ga.w[mem] + (size_t)R0 * (K1 / Fmt<FM>::KT) * 64 * Fmt<FM>::WORDS);
+    w1.scales = pf_rsrc((const uint16_t*)ga.w_scales[mem] + (size_t)R0 * 16 * w1.ng);
+    w1.zeros = pf_rsrc(ga.w_zeros[mem] + (size_t)R0 * 16 * ((w1.ng + 7) / 8));
+    place_w<FM>(w1, rb, lane);
+    WSeg w2;
+    if constexpr (EXT) {
+        w2.K = K2;
+        w2.gdiv = 1;
+        w2.gmagic = 0;
+        w2.ng = FX == S_Q4S64 ? 1 : K2 / 128;
+        w2.tiles = pf_rsrc((const uint32_t*)ga.w2[mem] + (size_t)R0 * (K2 / Fmt<FX>::KT) * 64 * Fmt<FX>::WORDS);
+        w2.scales = pf_rsrc((const uint16_t*)ga.w2_scales[mem] + (size_t)R0 * 16 * w2.ng);
+        place_w<FX>(w2, rb, lane);
     }
-    store_x(xr, buf0, !W16, tid);
-    fetch_x(xr, sb + 1);                                          // xr always holds the slab of the step after the one in LDS
+
+    // x: a request is eight rows of 64 columns; wavefront w brings rows 8 TM w .. of the slab.  Lane l is row l / 8 of them, and the
+    // chunk that belongs into slot l % 8 of that row.  Rows beyond M re-read the last one (never stored).
+    constexpr int W0 = 3 * XS;                                    // LDS: three slabs of x, two of weights
+    int xrow[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int row = 8 * (TM * wave + i) + (lane >> 3);
+        xrow[i] = m0 + row < M ? row : M - 1 - m0;
+    }
+    // chunk of request i: (l % 8) ^ ((row / 2) % 8), row / 2 = 4 (TM w + i) + l / 16
+    const int xc = 8 * ((lane & 7) ^ (lane >> 4));
+    // the lane's byte offsets in the rows of x, shifted so that request I may name offset 1024 I on both sides
+    uint32_t xo[TM];
+    auto place_x = [&](int ld) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) xo[i] = (uint32_t)(xrow[i] * ld + (xc ^ (((TM * wave + i) & 1) << 5))) * 2u + 1024u * (TM - 1 - i);
+    };
+    const uint32_t xlds = TM * wave * 1024;
+    auto x_base = [&](const _Float16* p, int ld) __attribute__((always_inline)) {     // of the segment's first step
+        return (uint64_t)(p + (size_t)m0 * ld) - 1024u * (TM - 1);
+    };
+    auto load_x = [&](auto itag, uint64_t at, uint32_t buf) __attribute__((always_inline)) {
+        constexpr int I = decltype(itag)::value;
+        pf_load_lds<1024 * I>(u4{(uint32_t)at, (uint32_t)(at >> 32), 0xffffffffu, 0x00027000u}, xo[I], buf + xlds);
+    };
+
+    constexpr int NX = 2 * TM;                                    // blocks of 16 tokens per wavefront; 4 blocks of 16 rows
+    f4 acc[NX][4];
+#pragma unroll
+    for (int i = 0; i < NX; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][e] = f4{0.f, 0.f, 0.f, 0.f};
+
+    // operand fragments: 16 rows x 32 columns, lane l row l % 16, columns 8 (l / 16) .. of the half step
+    const uint32_t fo = pf_slot(lane & 15, lane >> 4);
+    const uint32_t xf = fo + (wave & 1) * (BM / 2) * 128, wf = W0 + fo + (wave >> 1) * 64 * 128;
+    h8 fx[4], fw[2][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) fx[i] = h8{};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) fw[0][e] = fw[1][e] = h8{};
+
+    WReg<FM> wp[2];                                               // stored words of step sb + i in wp[i % 2], two steps ahead
+    WScale sc;                                                    // the block's groups behind the one in use, the next one lowest
+    uint32_t zsh = 0;                                             // where the next one's zero-point is
+    uint32_t sraw = 0, z = 8;                                     // the group in use
+    auto load_block = [&](int s) __attribute__((always_inline)) {
+        load_scale<FM>(sc, w1, s);
+        if (Fmt<FM>::ASYM && !w1.by8) zsh = 4 * ((w1.gdiv == 1 ? (uint32_t)s >> 1 : __umulhi((uint32_t)s >> 1, w1.gmagic)) & 7);
+    };
+    auto next_group = [&]() __attribute__((always_inline)) {
+        if constexpr (FM != S_F16) {
+            sraw = sc.s[0];
+            z = Fmt<FM>::ASYM ? (sc.z >> zsh) & 0xFu : (FM == S_Q3S128 ? 4u : 8u);
+            asm volatile("" : "+v"(sraw), "+v"(z));               // (formed here: a later request replaces what they come from)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) sc.s[i] = __builtin_amdgcn_alignbit(sc.s[i + 1], sc.s[i], 16);
+            sc.s[3] >>= 16;
+            if constexpr (Fmt<FM>::ASYM) sc.z >>= 4;
+        }
+    };
+    const int row32 = lane & 31, q = lane >> 5;
+    const uint32_t wd = W0 + wave * 32 * 128 + pf_slot(row32, FM == S_F16 ? q : 4 * q);
+    uint32_t xb = 0;                                              // LDS offset of the current step's slab of x
+    auto turn3 = [](uint32_t b) __attribute__((always_inline)) { return b == 2 * XS ? 0u : b + XS; };
+
+    place_x(ga.ldx);
+    uint64_t xat = x_base(ga.x, ga.ldx) + (uint64_t)sb * 128;
+    pf_for<TM>([&](auto i) __attribute__((always_inline)) { load_x(i, xat, 0); });
+    load_w<FM>(wp[0], w1, sb);
+    load_block(sb);
+    pf_for<TM>([&](auto i) __attribute__((always_inline)) { load_x(i, xat + 128, XS); });
+    load_w<FM>(wp[1], w1, sb + 1);
+    pf_arrived<0>();
+    if constexpr (FM != S_F16)
+        if (w1.by8)                                               // (a part that begins within eight groups)
+            for (int e = 0; e < ((sb >> 1) & 7); ++e) next_group();
+    next_group();
+    pf_for<4>([&](auto t) __attribute__((always_inline)) { store_w<FM, decltype(t)::value>(wp[0], sraw, z, wd); });
+    load_w<FM>(wp[0], w1, sb + 2 < se ? sb + 2 : se - 1);
     __syncthreads();
+    xat += 256;                                                   // the step after next's
 
-#ifdef EORA_TIMELINE
-    long long tl[5] = {0, 0, 0, 0, 0}, tl0 = clock64(), tlstart = tl0;
-#define PF_STAMP(i) do { const long long now = clock64(); tl[i] += now - tl0; tl0 = now; } while (0)
-#else
-#define PF_STAMP(i) do { } while (0)
-#endif
-    // Operands of step s into bf.  First segment: decode of the prefetched tiles and the request for the
-    // following step's (fp16 tiles are operands as they are: no prefetch copy).  Second segment: B's tiles.
-    h8 bf[8];
-    const int last1 = se - 1;                                     // last step of the first segment
-    auto prep_main = [&](auto par_tag, int s) {                   // par_tag: (s - sb) & 1
-        constexpr int PAR = decltype(par_tag)::value ? 1 : 0;
-        s = s < last1 ? s : last1;                                // past the end: the last one again, never used
-        if constexpr (W16) {
-            load_b_frags(bf, a.w, a.K1, Rl, s, lane);
-        } else {
-            decode_wpre<FM>(wp[PAR], bf);
-            load_wpre<FM>(wp[PAR], a, Rl, s + 2 < last1 ? s + 2 : last1, lane);
-        }
-    };
-    auto prep_ext = [&](int s) {
-        s = s < GT ? s : GT - 1;
-        s = s > G1 ? s : G1;                                      // (a part without the second segment: a valid step, never used)
-        if constexpr (E16) {
-            load_b_frags(bf, a.w2, a.K2, Rl, s - G1, lane);
-        } else {                                                  // quantised B: a handful of steps, loaded and decoded in place
-            WPre<E16 ? S_Q4S128 : FE2> wb;
-            load_wpre_from<E16 ? S_Q4S128 : FE2>(wb, a.w2, a.w2_scales, nullptr, a.K2, 128, Rl, s - G1, lane);
-            decode_wpre<E16 ? S_Q4S128 : FE2>(wb, bf);
-        }
-    };
-    // The two wavefronts that share a SIMD (w and w + 4) run the two halves of a step in opposite order,
-    // so that one decodes (VALU) while the other contracts (MFMA): wavefronts 0..3 decode step s at the
-    // top of iteration s, wavefronts 4..7 decoded it at the bottom of iteration s - 1.  Measured with
-    // both in the same order: the second decoder waits for the first, and its MFMAs then run alone.
-    // Each order, and each kind of operand preparation, gets a loop of its own under wavefront-uniform
-    // branches: with "if (late)" or "if (second segment)" inside one loop the compiler no longer knows how
-    // many requests follow the one it needs and waits for all of them, i.e. for the x slab requested a
-    // moment ago, at every decode.
-    auto step = [&](auto late_tag, auto ext_tag, auto par_tag, int s) {     // par_tag: (s - sb) & 1
-        constexpr bool LATE = decltype(late_tag)::value, EXTP = decltype(ext_tag)::value, PAR = decltype(par_tag)::value;
-        PF_STAMP(4);
-        unsigned char* const cur = ((s - sb) & 1) ? buf1 : buf0;
-        unsigned char* const nxt = ((s - sb) & 1) ? buf0 : buf1;
-        if constexpr (!LATE) {
-            if constexpr (EXTP) prep_ext(s);
-            else prep_main(PfFlag<PAR>{}, s);
-            // nothing crosses this point: left alone, the scheduler sinks the requests for the next step's
-            // weights below the MFMAs, and the next step then starts by waiting for them
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        PF_STAMP(0);
-        contract_step(acc, bf, cur, lane);
-#ifdef EORA_TIMELINE
-        __builtin_amdgcn_sched_barrier(0);
-        PF_STAMP(1);
-#endif
-        // the next step's slab goes to the other buffer (free since the barrier of the step before)
-        store_x(xr, nxt, !((EXT && s + 1 >= G1) ? E16 : W16), tid);      // the fragment order follows the weight operand's
-        fetch_x(xr, s + 2);
-        if constexpr (LATE) {
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (EXTP) prep_ext(s + 1);
-            else prep_main(PfFlag<!PAR>{}, s + 1);
-        }
-#ifdef EORA_TIMELINE
-        __builtin_amdgcn_sched_barrier(0);
-        PF_STAMP(2);
-#endif
-        __syncthreads();
-        PF_STAMP(3);
-    };
-    const int s1 = last1 + 1;                                     // first step of the second segment (= GT without one)
-    // steps [from, to) in pairs, so that the parity of a step is known at compile time
-    auto run = [&](auto late_tag, auto ext_tag, int from, int to) {
-        int s = from;
-        if ((s - sb) & 1) {
-            if (s < to) step(late_tag, ext_tag, PfFlag<true>{}, s);
-            ++s;
-        }
-        for (; s + 1 < to; s += 2) {
-            step(late_tag, ext_tag, PfFlag<false>{}, s);
-            step(late_tag, ext_tag, PfFlag<true>{}, s + 1);
-        }
-        if (s < to) step(late_tag, ext_tag, PfFlag<false>{}, s);
-    };
-    if (__builtin_amdgcn_readfirstlane(wave) >= PF_NW / 2) {
-        prep_main(PfFlag<false>{}, sb);
-        if constexpr (EXT) {
-            run(PfFlag<true>{}, PfFlag<false>{}, sb, s1 - 1);
-            run(PfFlag<true>{}, PfFlag<true>{}, s1 - 1, GT);
-        } else {
-            run(PfFlag<true>{}, PfFlag<false>{}, sb, GT);
-        }
-    } else {
-        run(PfFlag<false>{}, PfFlag<false>{}, sb, s1);
-        if constexpr (EXT) run(PfFlag<false>{}, PfFlag<true>{}, s1, GT);
-    }
-#ifdef EORA_TIMELINE
-    if ((blockIdx.x == 0 || blockIdx.x == 700) && lane == 0)
-        printf("wg %d wave %d: decode+wload %lld  contract %lld  storex+fetch %lld  barrier %lld  loop-top %lld  total %lld (clock64 ticks, %d steps)\n",
-               (int)blockIdx.x, wave, tl[0], tl[1], tl[2], tl[3], tl[4], clock64() - tlstart, GT - sb);
-#endif
-
-    // ---- split contraction: this part's fp32 tile, 128-byte rows straight from the accumulators ------
-    if (a.ksplit > 1) {
+    // A step is 2 NX units of four MFMAs: block i of 16 tokens times the four blocks of 16 rows, for either half h of the
+    // step's columns.  The fragments of four units are in registers; a unit's place is refilled right after its MFMAs.  The
+    // last four units of a step are carried out behind its barrier, while the first reads of the next step are on their way.
+    constexpr int U = 2 * NX;
+    auto unit = [&](auto utag, auto rtag, auto wtag) __attribute__((always_inline)) {   // rtag: whether there is something to read behind it
+        constexpr int u = decltype(utag)::value, h = u / NX, i = u % NX;
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
+        for (int e = 0; e < 4; ++e) acc[i][e] = mfma16(fw[h][e], fx[u & 3], acc[i][e]);
+        if constexpr (decltype(rtag)::value) {
+            constexpr int v = (u + 4) % U;                        // (behind the barrier: the next step's)
+            fx[u & 3] = *(const h8*)(eora_smem + ((xf + xb) ^ ((v / NX) << 6)) + (v % NX) * 2048);
+            // the other half's rows: for the second half in turn over the first, for the next step's first half behind the barrier
+            constexpr int f = h == 0 ? (NX == 8 ? (i % 2 ? -1 : i / 2) : NX - 4 <= i ? i - (NX - 4) : -1) : i - (NX - 4);
+            if constexpr (f >= 0) fw[h ^ 1][f] = *(const h8*)(eora_smem + (wf ^ ((h ^ 1) << 6)) + decltype(wtag)::value * PF_WS + f * 2048);
+        }
+    };
+    // One step (its weights are in slab PAR).  MAIN: it and the two behind it are the first segment's.  Otherwise what there is
+    // to bring is found out step by step.
+    WReg<FX> we;
+    WScale se2;
+    auto step = [&](auto main_tag, auto par_tag, int s) __attribute__((always_inline)) {
+        constexpr bool MAIN = decltype(main_tag)::value != 0;
+        constexpr int PAR = decltype(par_tag)::value, NXT = PAR ^ 1;
+        __builtin_amdgcn_s_setprio(3);
+        pf_for<4>([&](auto xtag) __attribute__((always_inline)) {
+            unit(PfInt<U - 4 + decltype(xtag)::value>{}, PfInt<1>{}, PfInt<PAR>{});
+            PF_SCHED();
+        });
+        const bool main1 = MAIN || s + 1 < se, ext1 = EXT && !MAIN && s + 1 >= se && s + 1 < GT;
+        const bool main2 = MAIN || s + 2 < se, ext2 = EXT && !MAIN && s + 2 >= se && s + 2 < GT;
+        // the next step's x, requested a step ago, and its stored words (those of the step behind it are the last request)
+        pf_arrived<MAIN ? (FM == S_F16 ? 4 : 1) : 0>();
+        if constexpr (FM == S_F16) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + 32 * mb + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const int o = (R0 + 2 * wn) * 16 + (lane & 31);
-                if (m < a.M && o < a.N) a.part[((size_t)ks * a.M + m) * a.ldp + a.pcol + o] = acc[mb][v];
+            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(wp[NXT].v[i]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < (int)(sizeof(wp[NXT].w) / 4); ++i) asm volatile("" : "+v"(wp[NXT].w[i]));
+        }
+        if (main1 && PAR == 1) next_group();
+        if (main2 && PAR == 0 && scale_due<FM>(w1, s + 2)) load_block(s + 2);
+        if constexpr (EXT && !MAIN) {
+            if (ext1) {                                           // (a handful of steps: all at once)
+                const uint32_t wx = W0 + wave * 32 * 128 + pf_slot(row32, FX == S_F16 ? q : 4 * q) + NXT * PF_WS;
+                const bool valid = FX != S_F16 || 2 * (s + 1 - H1) + 1 < K2 / 32;
+                uint32_t sraw2, z2;
+                pick_scale<FX>(se2, w2, s + 1 - H1, sraw2, z2);
+                store_w<FX, 0>(we, sraw2, z2, wx);
+                store_w<FX, 1>(we, sraw2, z2, wx);
+                store_w<FX, 2>(we, sraw2, z2, wx, valid);
+                store_w<FX, 3>(we, sraw2, z2, wx, valid);
             }
+            if (s + 2 == se && GT > se) {                         // from here on x is t
+                place_x(ga.ldx2);
+                xat = x_base(ga.x2[mem], ga.ldx2);
+            }
+            if (ext2) {
+                load_w<FX>(we, w2, s + 2 - H1);
+                if (scale_due<FX>(w2, s + 2 - H1)) load_scale<FX>(se2, w2, s + 2 - H1);
+            }
+        }
+        const uint32_t xnew = turn3(turn3(xb));
+        PF_SCHED();
+        pf_for<U - 4>([&](auto xtag) __attribute__((always_inline)) {
+            constexpr int x = decltype(xtag)::value, PER = (U - 4) / 4;
+            if constexpr (x % 4 == 0) __builtin_amdgcn_s_setprio(2 - x / 4);
+            unit(PfInt<x>{}, PfInt<1>{}, PfInt<PAR>{});
+            // x of the step after next goes where the step before this one had its own (everyone has left it at the barrier);
+            // one request at a time: a compute unit takes in 64 bytes a cycle, and a wavefront that asks for more at once waits
+            if constexpr (x % PER == 0 && x / PER < TM)
+                if (main2 || ext2) load_x(PfInt<x / PER>{}, xat, xnew);
+            if constexpr (x % PER == PER - 1) {
+                constexpr int T = x / PER;
+                if (main1) store_w<FM, T>(wp[NXT], sraw, z, wd + NXT * PF_WS);
+            }
+            PF_SCHED();
+        });
+        if constexpr (MAIN) load_w<FM>(wp[NXT], w1, s + 3 < se ? s + 3 : se - 1);
+        xat += 128;
+        xb = turn3(xb);
+        __syncthreads();
+    };
+    for (int s = sb; s < se - 2; s += 2) {
+        step(PfInt<1>{}, PfInt<0>{}, s);
+        step(PfInt<1>{}, PfInt<1>{}, s + 1);
+    }
+    for (int s = se - 2; s < GT; s += 2) {
+        step(PfInt<0>{}, PfInt<0>{}, s);
+        if (s + 1 < GT) step(PfInt<0>{}, PfInt<1>{}, s + 1);
+    }
+    pf_for<4>([&](auto xtag) __attribute__((always_inline)) { unit(PfInt<U - 4 + decltype(xtag)::value>{}, PfInt<0>{}, PfInt<0>{}); });
+
+    // ---- epilogue: wavefront-private staging of 32 tokens x 64 rows, so that y is written in 128-byte rows ----------
+    // result register v of lane l: row 4 (l / 16) + v of the block's 16, token l % 16
+    const int tok0 = m0 + (wave & 1) * (BM / 2), o0 = R0 * 16 + (wave >> 1) * 64;
+    const int tr = lane & 15, kg = lane >> 4;
+    if (ga.ksplit > 1) {                                          // split contraction: this part's fp32 tile
+        constexpr int TS = 68;                                    // floats per token row in the staging tile (64 + pad)
+        float* const tile = (float*)eora_smem + wave * 32 * TS;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) *(f4*)(tile + (16 * b + tr) * TS + 16 * e + 4 * kg) = acc[2 * i + b][e];
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const int tok = 4 * it + (lane >> 4), c = 4 * (lane & 15);
+                const int m = tok0 + 32 * i + tok, o = o0 + c;
+                const f4 v = *(const f4*)(tile + tok * TS + c);
+                if (m < M && o < N) *(f4*)(ga.part + ((size_t)ks * M + m) * ga.ldp + ga.pcol[mem] + o) = v;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
         return;
     }
-    // ---- epilogue: fp32 -> fp16, transpose through LDS, 128-byte row stores ----------------------------
-    // (wavefront-private staging tiles of 64 tokens, two passes: 40 KiB, so that the kernel's LDS stays at the
-    // two x slabs and two workgroups fit a compute unit)
-    constexpr int TS = 40;                                        // halves per token row in the staging tile (32 + pad)
-    _Float16* tile = (_Float16*)eora_smem + wave * 64 * TS;
+    constexpr int TS = 72;                                        // halves per token row in the staging tile (64 + pad)
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    _Float16* const tile = (_Float16*)eora_smem + wave * 32 * TS;
 #pragma unroll
-    for (int pass = 0; pass < 2; ++pass) {
-        if (pass) __syncthreads();                                // (keeps the two passes of a wavefront apart in program order)
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-        for (int mb2 = 0; mb2 < 2; ++mb2)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                tile[(32 * mb2 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * TS + (lane & 31)] = (_Float16)acc[2 * pass + mb2][v];
-        __syncthreads();
+            for (int e = 0; e < 4; ++e) {
+                const f4 a = acc[2 * i + b][e];
+                *(h4*)(tile + (16 * b + tr) * TS + 16 * e + 4 * kg) = h4{(_Float16)a[0], (_Float16)a[1], (_Float16)a[2], (_Float16)a[3]};
+            }
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
-            const int tok = 16 * it + (lane >> 2), chunk = lane & 3;  // 64-byte rows: four 16-byte chunks
-            const int m = m0 + 64 * pass + tok, o = (R0 + 2 * wn) * 16 + chunk * 8;
-            const u4 v = *(const u4*)(tile + tok * TS + chunk * 8);
-            if (m < a.M && o < a.N) *(u4*)((_Float16*)a.y + (size_t)m * a.ldy + o) = v;
+            const int tok = 8 * it + (lane >> 3), c = 8 * (lane & 7);
+            const int m = tok0 + 32 * i + tok, o = o0 + c;
+            const u4 v = *(const u4*)(tile + tok * TS + c);
+            if (m < M && o < N) *(u4*)((_Float16*)ga.y[mem] + (size_t)m * ga.ldy[mem] + o) = v;
         }
+        __builtin_amdgcn_wave_barrier();
     }
+}
+
+template <int FM, int FE2, int TM>
+static hipError_t launch_pf_tile(const PrefillArgs& a, hipStream_t stream)
+{
+    auto kern = prefill_kernel<FM, FE2, TM>;
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, pf_lds(TM));
+    if (e != hipSuccess) return e;
+    int ntn = 0;
+    for (int m = 0; m < a.n; ++m) ntn += (a.N[m] + PF_BN - 1) / PF_BN;
+    const int ntm = (a.M + pf_bm(TM) - 1) / pf_bm(TM);
+    note_launch("prefill FM=%d EXT=%d ksplit=%d n=%d FE=%d", FM, (int)(FE2 != S_NONE), a.ksplit, a.n, FE2);
+    hipLaunchKernelGGL(kern, dim3(ntn * ntm * a.ksplit), dim3(PF_NT), pf_lds(TM), stream, a);
+    return hipGetLastError();
 }
 
 template <int FM, int FE2>
 static hipError_t launch_pf(const PrefillArgs& a, hipStream_t stream)
 {
-    constexpr bool EXT = FE2 != S_NONE;
-    auto kern = prefill_kernel<FM, FE2>;
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, PF_LDS);
-    if (e != hipSuccess) return e;
-    int ntn = 0;
-    for (int m = 0; m < a.n; ++m) ntn += (a.N[m] + PF_BN - 1) / PF_BN;
-    const int ntm = (a.M + PF_BM - 1) / PF_BM;
-    note_launch("prefill FM=%d EXT=%d ksplit=%d n=%d FE=%d", FM, (int)EXT, a.ksplit, a.n, FE2);
-    hipLaunchKernelGGL(kern, dim3(ntn * ntm * a.ksplit), dim3(PF_NT), PF_LDS, stream, a);
-    return hipGetLastError();
+    if constexpr (FM == S_Q4 || FM == S_Q3 || FM == S_Q2) {       // (A's formats: the launch for t alone, always two blocks)
+        if (a.tm == 4) return launch_pf_tile<FM, FE2, 4>(a, stream);
+        if (a.tm == 3) return launch_pf_tile<FM, FE2, 3>(a, stream);
+    }
+    return a.tm == 2 ? launch_pf_tile<FM, FE2, 2>(a, stream) : hipErrorInvalidValue;
 }
 
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restrict__ part, _Float16* __restrict__ T, size_t count, int ksplit)
