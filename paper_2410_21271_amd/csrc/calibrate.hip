@@ -19,6 +19,7 @@
 
 #include <hip/hip_runtime.h>
 #include <cmath>
+#include <type_traits>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -135,9 +136,39 @@ __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H
 // result register v holds D[i = 4 v + g][j = n].
 typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int BJ_NT = 512, BJ_NW = BJ_NT / 64;
-constexpr int BJ_INNER_SWEEPS = 2;      // (of the 16 x 16 matrix per round: what two leave is finished in the next sweep)
+constexpr int BJ_INNER_SWEEPS = 1;      // (of the 16 x 16 matrix per round: what one leaves is finished in the next sweep; as many sweeps over
+                                        //  the rows as with two, 12 us a round of 256 rows instead of 16)
 
 __device__ __forceinline__ d4 mfma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
+__device__ __forceinline__ double rcp_approx(double v) { return __builtin_amdgcn_rcp(v); }
+__device__ __forceinline__ double rsq_approx(double v) { return __builtin_amdgcn_rsq(v); }
+
+// 1 / sqrt(v) to the last bits but one: two Newton steps on the machine's approximation
+__device__ __forceinline__ double rsq_newton(double v)
+{
+    double y = rsq_approx(v);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) y = fma(0.5 * y, fma(-v * y, y, 1.0), y);
+    return y;
+}
+
+// Cosine and sine of the plane rotation that makes [a c; c b] diagonal.  The 30 steps of a 16 x 16 matrix are a chain in which
+// each waits for these values, and the library's division and square root are some 30 dependent instructions each.  The
+// angle may be off in its last bits (what it leaves of c the next sweep finds), the rotation may not: cosine and sine come
+// from one t, so their squares add to 1 to rounding whatever t is.
+__device__ __forceinline__ void jacobi_angle(double a, double b, double c, double& co, double& si)
+{
+    const double d = b - a, h = c + c, rh = rcp_approx(h), q0 = d * rh;
+    double zeta = fma(fma(-h, q0, d), rh, q0);
+    zeta = fmin(fmax(zeta, -1e100), 1e100);               // (c that is next to nothing: no infinities further on)
+    const double az = fabs(zeta), w = fma(az, az, 1.0), root = w * rsq_approx(w);
+    double t = rcp_approx(az + root);                     // the smaller root of t^2 + 2 |zeta| t - 1
+    t = fma(-fma(t, t + 2.0 * az, -1.0), 0.5 * rcp_approx(t + az), t);
+    t = copysign(t, zeta);
+    co = rsq_newton(fma(t, t, 1.0));
+    si = co * t;
+}
 
 // rows <- J^T rows for the 16 rows (block P, block Q) of X (row length len, a multiple of 128)
 __device__ __forceinline__ void apply_rotation(double* __restrict__ X, int len, int P, int Q, const double (*J)[17], int wave,
@@ -222,54 +253,53 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
     }
     __syncthreads();
     // ---- S = J D J^T by two-sided Jacobi: eight disjoint pairs per step, fifteen steps per sweep.  One wavefront does it
-    // alone (its LDS operations are carried out in order; three workgroup barriers per step cost more than they shared out)
+    // alone (its LDS operations are carried out in order; three workgroup barriers per step cost more than they shared out).
+    // Lane (i, j) owns the 2 x 2 block of S in the rows of pair i and the columns of pair j, forms both pairs' rotations by
+    // itself and applies them from either side at once, and turns rows 2 i, 2 i + 1 of J's columns of pair j: one round through
+    // LDS per step (the chain of reads, rotation and writes is what a round of the rows waits for).
     if (wave == 0) {
+        const int pi = lane >> 3, pj = lane & 7;
+        auto due = [&](double a, double b, double c) { return a > abs_floor && b > abs_floor && fabs(c) > tol * (a * rsq_approx(a)) * (b * rsq_approx(b)); };
+        bool some = false;                            // whether any of the 120 pairs is to be rotated (in the last sweeps most rounds have none)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int r = (lane >> 4) + 4 * e, c = lane & 15;
+            some = some || (r < c && due(S[r][r], S[c][c], S[r][c]));
+        }
         bool rotated = false;
-        for (int sweep = 0; sweep < BJ_INNER_SWEEPS; ++sweep) {
+        for (int sweep = 0; sweep < BJ_INNER_SWEEPS && __any(some); ++sweep) {
             bool any = false;
             for (int step = 0; step < 15; ++step) {
-                double co = 1.0, si = 0.0;
-                int p = 0, q = 0;
-                {                                     // lane -> pair lane % 8 (eight lanes the same pair)
-                    const int t = lane & 7;
-                    if (t == 0) {
-                        p = step;
-                        q = 15;
-                    } else {
-                        p = step + t;
-                        p = p >= 15 ? p - 15 : p;
-                        q = step + 15 - t;
-                        q = q >= 15 ? q - 15 : q;
-                    }
-                    const double a = S[p][p], b = S[q][q], c = S[p][q];
-                    if (a > abs_floor && b > abs_floor && fabs(c) > tol * sqrt(a) * sqrt(b)) {
-                        const double zeta = (b - a) / (2.0 * c);
-                        const double t2 = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                        co = 1.0 / sqrt(1.0 + t2 * t2);
-                        si = co * t2;
-                    }
-                }
-                if (!__any(si != 0.0)) continue;      // uniform: nothing to rotate in this step
+                auto pair = [&](int t, int& p, int& q) {
+                    p = t == 0 ? step : step + t >= 15 ? step + t - 15 : step + t;
+                    q = t == 0 ? 15 : step + 15 - t >= 15 ? step - t : step + 15 - t;
+                };
+                int p0, q0, p1, q1;
+                pair(pi, p0, q0);
+                pair(pj, p1, q1);
+                const double a0 = S[p0][p0], b0 = S[q0][q0], c0 = S[p0][q0], a1 = S[p1][p1], b1 = S[q1][q1], c1 = S[p1][q1];
+                const double spp = S[p0][p1], spq = S[p0][q1], sqp = S[q0][p1], sqq = S[q0][q1];
+                const double jp0 = J[2 * pi][p1], jq0 = J[2 * pi][q1], jp1 = J[2 * pi + 1][p1], jq1 = J[2 * pi + 1][q1];
+                double co0, si0, co1, si1;
+                jacobi_angle(a0, b0, c0, co0, si0);
+                jacobi_angle(a1, b1, c1, co1, si1);
+                const bool on0 = due(a0, b0, c0), on1 = due(a1, b1, c1);
+                co0 = on0 ? co0 : 1.0;
+                si0 = on0 ? si0 : 0.0;
+                co1 = on1 ? co1 : 1.0;
+                si1 = on1 ? si1 : 0.0;
+                if (!__any(on1)) continue;            // uniform: nothing to rotate in this step
                 any = true;
-                // rows of S and columns of J: lane -> pair lane % 8, columns (rows of J) lane / 8 and lane / 8 + 8
-                const int c0 = lane >> 3;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int c = c0 + 8 * h;
-                    const double a = S[p][c], b = S[q][c], u = J[c][p], w = J[c][q];
-                    S[p][c] = co * a - si * b;
-                    S[q][c] = si * a + co * b;
-                    J[c][p] = co * u - si * w;
-                    J[c][q] = si * u + co * w;
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {         // columns of S
-                    const int r = c0 + 8 * h;
-                    const double a = S[r][p], b = S[r][q];
-                    S[r][p] = co * a - si * b;
-                    S[r][q] = si * a + co * b;
-                }
+                const double tpp = co0 * spp - si0 * sqp, tqp = si0 * spp + co0 * sqp;      // rows
+                const double tpq = co0 * spq - si0 * sqq, tqq = si0 * spq + co0 * sqq;
+                S[p0][p1] = co1 * tpp - si1 * tpq;                                          // columns
+                S[p0][q1] = si1 * tpp + co1 * tpq;
+                S[q0][p1] = co1 * tqp - si1 * tqq;
+                S[q0][q1] = si1 * tqp + co1 * tqq;
+                J[2 * pi][p1] = co1 * jp0 - si1 * jq0;
+                J[2 * pi][q1] = si1 * jp0 + co1 * jq0;
+                J[2 * pi + 1][p1] = co1 * jp1 - si1 * jq1;
+                J[2 * pi + 1][q1] = si1 * jp1 + co1 * jq1;
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             }
             if (!any) break;
@@ -286,90 +316,162 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 }
 
 // C[i][j] = beta * C[i][j] + alpha * sum_k A[i*ai + k*ak] * B[j*bj + k*bk], i < M, j < N, k < K (beta == 0: C is
-// not read).  lower != 0: only the tiles that touch the lower triangle (j0 <= i0) are computed (symmetric updates).
-// Bound by the fp64 matrix cores: 64 x 64 outputs per workgroup, 32 x 32 per wavefront as 2 x 2 blocks of
-// v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS sixteen k at a time, the next sixteen on their way
-// from memory meanwhile.  LDS rows of 18 doubles: a stage's sixteen k of a row are written together, and the sixteen rows
-// of a fragment start in different banks.
+// not read).  shape: GM_LOWER, only the tiles that touch the lower triangle (j0 <= i0) are computed (symmetric updates);
+// GM_B_LOWER, B[j][k] is zero for k < j (a lower triangle): the contraction begins at the tile's first column.
+// Bound by the fp64 matrix cores: 64 x 64 outputs per workgroup, a quarter per wavefront as 2 x 2 blocks of
+// v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS 32 k at a time.  256 rows x 4096 are one workgroup per
+// compute unit, so one wavefront per SIMD, and a stage lasts 0.9 us: its operands are requested two stages ahead (256 x 4096 x
+// 4096: 166 us, 52 TFLOP/s; 16 k and one stage ahead took 277).  The Gram matrix of 4096 x 8192: 3.7 ms (4.6).  Tiles of 128
+// halve the operand traffic but leave fewer of them to share out (4.4 ms).  LDS rows of 34 doubles: the sixteen rows of a
+// fragment start in different banks.
+// part: null, or room for gridDim.z partial products, each over its share of k (gemm_sum_kernel adds them).
 // C may be A or B where a workgroup reads all it needs of it before it writes (one tile of rows or columns): no __restrict__.
-constexpr int GM_ST = 18;
-template <typename TA, typename TB>
-__global__ __launch_bounds__(256) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
-                                                   double alpha, double beta, int lower)
+// a value at a uniform address and an offset of the lane's own, in bytes (a buffer load takes both as they are)
+template <typename T>
+__device__ __forceinline__ T load_at(const T* base, uint32_t off)
 {
-    __shared__ double As[2][64 * GM_ST], Bs[2][64 * GM_ST];
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, -1, 0x00027000);
+    if constexpr (sizeof(T) == 8) {
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        return __builtin_bit_cast(T, (u2)__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    } else {
+        return __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    }
+}
+enum { GM_FULL = 0, GM_LOWER = 1, GM_B_LOWER = 2 };
+constexpr int GM_TILE = 64, GM_KT = 32;
+template <typename TA, typename TB>
+__global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
+                                                   double alpha, double beta, int shape, double* part)
+{
+    constexpr int TILE = GM_TILE, KT = GM_KT, ST = KT + 2, E = TILE * KT / 256, FR = TILE / 32;
+    __shared__ double As[2][TILE * ST], Bs[2][TILE * ST];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
-    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-    if (lower && j0 > i0) return;
-    const int wi = 32 * (wave & 1), wj = 32 * (wave >> 1);
-    // this thread's four elements of a stage: consecutive threads along whichever index is contiguous in memory
-    auto place = [&](long stride_k, int e, int& row, int& kk) {
-        if (stride_k == 1) {
-            kk = tid & 15;
-            row = (tid >> 4) + 16 * e;
+    const int i0 = blockIdx.y * TILE, j0 = blockIdx.x * TILE;
+    if (shape == GM_LOWER && j0 > i0) return;
+    const int wi = TILE / 2 * (wave & 1), wj = TILE / 2 * (wave >> 1);
+    const int stages = (K + KT - 1) / KT, parts = gridDim.z, z = blockIdx.z;
+    const int first = shape == GM_B_LOWER ? j0 / KT : 0;
+    const int sb = first + (int)((long)(stages - first) * z / parts), se = first + (int)((long)(stages - first) * (z + 1) / parts);
+    // This thread's elements of a stage: consecutive threads along whichever index is contiguous in memory.  A lane's offsets
+    // (32 bits: within a tile) stay the same, the tile's address moves; rows beyond the last one re-read it, never stored.
+    int row_a[E], row_b[E];
+    uint32_t off_a[E], off_b[E];
+    const int k_a = ak == 1 ? tid % KT : tid / TILE, k_b = bk == 1 ? tid % KT : tid / TILE;
+    const int dk_a = ak == 1 ? 0 : 256 / TILE, dk_b = bk == 1 ? 0 : 256 / TILE;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int ra_ = ak == 1 ? tid / KT + 256 / KT * e : tid % TILE, rb_ = bk == 1 ? tid / KT + 256 / KT * e : tid % TILE;
+        row_a[e] = i0 + ra_ < M ? ra_ : M - 1 - i0;
+        row_b[e] = j0 + rb_ < N ? rb_ : N - 1 - j0;
+        off_a[e] = (uint32_t)(row_a[e] * ai + (k_a + dk_a * e) * ak) * (uint32_t)sizeof(TA);
+        off_b[e] = (uint32_t)(row_b[e] * bj + (k_b + dk_b * e) * bk) * (uint32_t)sizeof(TB);
+    }
+    const int la = ak == 1 ? tid / KT * ST + k_a : tid % TILE * ST + k_a, sa = ak == 1 ? 256 / KT * ST : 256 / TILE;
+    const int lb = bk == 1 ? tid / KT * ST + k_b : tid % TILE * ST + k_b, sbk = bk == 1 ? 256 / KT * ST : 256 / TILE;
+    const TA* const A0 = A + (size_t)i0 * ai;
+    const TB* const B0 = B + (size_t)j0 * bj;
+    TA ra[2][E];
+    TB rb[2][E];
+    auto fetch = [&](int set, int st) __attribute__((always_inline)) {
+        const int k0 = st * KT;
+        if (k0 + KT <= K) {
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                ra[set][e] = load_at(A0 + (size_t)k0 * ak, off_a[e]);
+                rb[set][e] = load_at(B0 + (size_t)k0 * bk, off_b[e]);
+            }
         } else {
-            row = tid & 63;
-            kk = (tid >> 6) + 4 * e;
+#pragma unroll
+            for (int e = 0; e < E; ++e) {
+                const int ka = k0 + k_a + dk_a * e, kb = k0 + k_b + dk_b * e;
+                ra[set][e] = A0[(size_t)row_a[e] * ai + (size_t)(ka < K ? ka : K - 1) * ak];
+                rb[set][e] = B0[(size_t)row_b[e] * bj + (size_t)(kb < K ? kb : K - 1) * bk];
+                if (ka >= K) ra[set][e] = 0;
+                if (kb >= K) rb[set][e] = 0;
+            }
         }
     };
-    TA ra[4];
-    TB rb[4];
-    auto fetch = [&](int k0) {
+    auto stage = [&](int set, int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            int row, kk;
-            place(ak, e, row, kk);
-            ra[e] = (i0 + row < M && k0 + kk < K) ? A[(size_t)(i0 + row) * ai + (size_t)(k0 + kk) * ak] : (TA)0;
-            place(bk, e, row, kk);
-            rb[e] = (j0 + row < N && k0 + kk < K) ? B[(size_t)(j0 + row) * bj + (size_t)(k0 + kk) * bk] : (TB)0;
+        for (int e = 0; e < E; ++e) {
+            As[buf][la + sa * e] = (double)ra[set][e];
+            Bs[buf][lb + sbk * e] = (double)rb[set][e];
         }
     };
-    auto stage = [&](int buf) {
+    d4 acc[FR][FR];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            int row, kk;
-            place(ak, e, row, kk);
-            As[buf][row * GM_ST + kk] = (double)ra[e];
-            place(bk, e, row, kk);
-            Bs[buf][row * GM_ST + kk] = (double)rb[e];
-        }
-    };
-    d4 acc[2][2] = {{{0, 0, 0, 0}, {0, 0, 0, 0}}, {{0, 0, 0, 0}, {0, 0, 0, 0}}};
-    fetch(0);
-    stage(0);
-    __syncthreads();
-    for (int k0 = 0, buf = 0; k0 < K; k0 += 16, buf ^= 1) {
-        if (k0 + 16 < K) fetch(k0 + 16);
+    for (int e = 0; e < FR; ++e)
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            double a[2], b[2];
+        for (int f = 0; f < FR; ++f) acc[e][f] = d4{0, 0, 0, 0};
+    auto contract = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                a[e] = As[buf][(wi + 16 * e + n) * GM_ST + 4 * kk + g];
-                b[e] = Bs[buf][(wj + 16 * e + n) * GM_ST + 4 * kk + g];
+        for (int kk = 0; kk < KT / 4; ++kk) {
+            double a[FR], b[FR];
+#pragma unroll
+            for (int e = 0; e < FR; ++e) {
+                a[e] = As[buf][(wi + 16 * e + n) * ST + 4 * kk + g];
+                b[e] = Bs[buf][(wj + 16 * e + n) * ST + 4 * kk + g];
             }
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
+            for (int e = 0; e < FR; ++e)
 #pragma unroll
-                for (int f = 0; f < 2; ++f) acc[e][f] = mfma64(a[e], b[f], acc[e][f]);
+                for (int f = 0; f < FR; ++f) acc[e][f] = mfma64(a[e], b[f], acc[e][f]);
         }
-        if (k0 + 16 < K) stage(buf ^ 1);      // (everyone left that buffer at the barrier of the stage before)
+    };
+    // Stage sb + i waits in LDS buffer i % 2 and, two stages ahead, in register set i % 2 (stages past the end: the last one, not
+    // used).  No branch in the loop touches the accumulators: where paths meet the compiler copies them.
+    if (sb < se) {
+        fetch(0, sb);
+        stage(0, 0);
+        fetch(1, sb + 1 < se ? sb + 1 : se - 1);
         __syncthreads();
+        int s = sb;
+        for (; s + 1 < se; s += 2) {
+            fetch(0, s + 2 < se ? s + 2 : se - 1);
+            contract(0);
+            stage(1, 1);
+            __syncthreads();
+            fetch(1, s + 3 < se ? s + 3 : se - 1);
+            contract(1);
+            stage(0, 0);
+            __syncthreads();
+        }
+        if (s < se) contract(0);
     }
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int e = 0; e < FR; ++e)
 #pragma unroll
-        for (int f = 0; f < 2; ++f)
+        for (int f = 0; f < FR; ++f)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int gi = i0 + wi + 16 * e + 4 * v + g, gj = j0 + wj + 16 * f + n;
                 if (gi < M && gj < N) {
-                    double c = alpha * acc[e][f][v];
-                    if (beta != 0.0) c += beta * C[(size_t)gi * ldc + gj];
-                    C[(size_t)gi * ldc + gj] = c;
+                    if (part) {
+                        part[((size_t)z * M + gi) * N + gj] = acc[e][f][v];
+                    } else {
+                        double c = alpha * acc[e][f][v];
+                        if (beta != 0.0) c += beta * C[(size_t)gi * ldc + gj];
+                        C[(size_t)gi * ldc + gj] = c;
+                    }
                 }
             }
+}
+
+// C = beta * C + alpha * (the partial products, in order); lower: where their tiles of 64 touch the lower triangle
+__global__ __launch_bounds__(256) void gemm_sum_kernel(const double* __restrict__ part, int parts, double* __restrict__ C, long ldc, int M, int N, double alpha,
+                                                       double beta, int lower)
+{
+    const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (e >= (size_t)M * N) return;
+    const int i = (int)(e / N), j = (int)(e - (size_t)i * N);
+    if (lower && j / 64 > i / 64) return;
+    double v = 0.0;
+    for (int z = 0; z < parts; ++z) v += part[(size_t)z * M * N + e];
+    double c = alpha * v;
+    if (beta != 0.0) c += beta * C[(size_t)i * ldc + j];
+    C[(size_t)i * ldc + j] = c;
 }
 
 // the strict upper triangle of an n x n matrix from the lower one
@@ -406,61 +508,151 @@ __global__ __launch_bounds__(1024) void pivot_floor_kernel(const double* __restr
     if (threadIdx.x == 0) thr[0] = rel * red[0];
 }
 
-// The nb x nb diagonal block at (j0, j0), by one wavefront (no barriers: a wavefront's LDS operations are carried out in
-// order): lane i owns row i, the matrix is kept transposed in LDS (a row's entry of every lane in one access, the pivot
-// row's entry the same for all).  Unblocked, left-looking; the block's strict upper part is zeroed.  Then, unless inv is
-// null, inv = L11^-1 (always 64 x 64, row-major; rows beyond nb those of the identity), lane c its column c, so that the rows below the block and
-// the right-hand sides of a solve are products on the matrix cores (one thread per row with its 64 entries in scratch
-// memory took 297 us a panel; this kernel takes 94).
-__global__ __launch_bounds__(64) void potrf_block_kernel(double* __restrict__ A, long lda, int j0, int nb, const double* __restrict__ thr,
+// The nb x nb diagonal block at (j0, j0), by one workgroup, as 4 x 4 blocks of 16 (rows beyond nb: those of the identity).  A
+// block on the diagonal is factored in the registers of one wavefront, lane i % 16 its row i (right-looking, the column's entries passed by DPP), and inverted there, lane c column c; the blocks
+// below and the trailing ones are products on the matrix cores.  The block's strict upper part is zeroed.  Then, unless
+// inv is null, inv = L11^-1 (always 64 x 64, row-major), blockwise on the matrix cores too, so that the rows below the
+// block and the right-hand sides of a solve are products.  Bound by the chain of 64 pivots.  (Left-looking over the whole 64
+// columns by one wavefront, two LDS reads per multiplication: 94 us; now 21.)
+// the value of lane LANE of the caller's row of 16 lanes
+template <int LANE>
+__device__ __forceinline__ double row_value(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_mov_dpp((int)(unsigned)u, 0x150 + LANE, 0xF, 0xF, true);
+    const unsigned hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), 0x150 + LANE, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unrolled(F&& f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        unrolled<N, I + 1>(f);
+    }
+}
+
+__global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A, long lda, int j0, int nb, const double* __restrict__ thr,
                                                          unsigned* __restrict__ flag, double* __restrict__ inv)
 {
-    __shared__ double S[CH_NB][CH_NB], Y[CH_NB][CH_NB];   // S[k][i] = entry (i, k); Y[k][c] = entry (k, c) of the inverse
-    const int i = threadIdx.x;
+    // S: the matrix; once a column of blocks is done, the blocks of the inverse below the diagonal go to the mirrored places
+    // above it (block (i, j) of the inverse, i > j, at block (j, i), not transposed).  D: inverses of the diagonal blocks.
+    __shared__ double S[CH_NB][CH_NB + 2], D[4][16][18];
+    __shared__ int s_bad;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, g = lane >> 4;
     double* const blk = A + (size_t)j0 * lda + j0;
-    for (int r = 0; r < CH_NB; ++r) S[i][r] = (r < nb && i <= r) ? blk[(size_t)r * lda + i] : (i == r ? 1.0 : 0.0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    const double floor_abs = thr[0];
-    bool bad = false;
-    for (int j = 0; j < nb; ++j) {
-        double v0 = S[j][i], v1 = 0.0;
-        int k = 0;
-        for (; k + 8 <= j; k += 8) {
+    {
+        double v[16];
+        const int c = lane < nb ? lane : 0;
 #pragma unroll
-            for (int u = 0; u < 8; u += 2) {
-                v0 -= S[k + u][i] * S[k + u][j];
-                v1 -= S[k + u + 1][i] * S[k + u + 1][j];
-            }
+        for (int e = 0; e < 16; ++e) {
+            const int r = wave + 4 * e;
+            v[e] = blk[(size_t)(r < nb ? r : 0) * lda + c];
         }
-        for (; k < j; ++k) v0 -= S[k][i] * S[k][j];
-        v0 += v1;
-        double d = __shfl(v0, j, 64);
-        if (!(d > floor_abs)) {                           // not (numerically) positive definite: give up, stay finite
-            bad = true;
-            d = floor_abs > 0.0 ? floor_abs : 1.0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int r = wave + 4 * e;
+            S[r][lane] = r < nb && lane <= r ? v[e] : (lane == r ? 1.0 : 0.0);
         }
-        const double root = sqrt(d);
-        S[j][i] = i == j ? root : (i > j ? v0 / root : 0.0);
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-    if (i == 0 && bad) atomicOr(flag, 1u);
-    for (int r = 0; r < nb; ++r)
-        if (i < nb) blk[(size_t)r * lda + i] = S[i][r];   // (row r, column i: zero above the diagonal)
-    if (!inv) return;
-    for (int r = 0; r < CH_NB; ++r) {
-        double v0 = r == i ? 1.0 : 0.0, v1 = 0.0;
-        int k = 0;
-        for (; k + 8 <= r; k += 8) {
+    if (tid == 0) s_bad = 0;
+    const double floor_abs = thr[0];
+    __syncthreads();
+#pragma unroll 1
+    for (int jb = 0; jb < 4; ++jb) {
+        if (wave == 0) {
+            bool bad = false;
+            double a[16], rinv[16];
 #pragma unroll
-            for (int u = 0; u < 8; u += 2) {
-                v0 -= S[k + u][r] * Y[k + u][i];
-                v1 -= S[k + u + 1][r] * Y[k + u + 1][i];
+            for (int c = 0; c < 16; ++c) a[c] = S[16 * jb + n][16 * jb + c];
+            unrolled<16>([&](auto jt) __attribute__((always_inline)) {
+                constexpr int j = decltype(jt)::value;
+                double d = row_value<j>(a[j]);
+                const bool low = 16 * jb + j < nb && !(d > floor_abs);       // not (numerically) positive definite: give up, stay finite
+                bad = bad || low;
+                d = low ? (floor_abs > 0.0 ? floor_abs : 1.0) : d;
+                const double y = rsq_newton(d);
+                double root = d * y;
+                root = fma(fma(-root, root, d), 0.5 * y, root);
+                rinv[j] = y;
+                a[j] = n == j ? root : a[j] * y;
+                unrolled<15 - j>([&](auto kt) __attribute__((always_inline)) {
+                    constexpr int k = j + 1 + decltype(kt)::value;
+                    a[k] = fma(-a[j], row_value<k>(a[j]), a[k]);
+                });
+            });
+            double y[16];
+            unrolled<16>([&](auto rt) __attribute__((always_inline)) {
+                constexpr int r = decltype(rt)::value;
+                double v = r == n ? 1.0 : 0.0;
+                unrolled<r>([&](auto kt) __attribute__((always_inline)) {
+                    constexpr int k = decltype(kt)::value;
+                    v = fma(-row_value<r>(a[k]), y[k], v);
+                });
+                y[r] = v * rinv[r];
+            });
+            if (lane < 16) {
+#pragma unroll
+                for (int c = 0; c < 16; ++c) {
+                    S[16 * jb + n][16 * jb + c] = c <= n ? a[c] : 0.0;
+                    D[jb][c][n] = y[c];
+                }
             }
+            if (lane == 0 && bad) s_bad = 1;
         }
-        for (; k < r; ++k) v0 -= S[k][r] * Y[k][i];
-        const double y = (v0 + v1) / S[r][r];
-        Y[r][i] = y;
-        inv[r * CH_NB + i] = y;
+        __syncthreads();
+        for (int ib = jb + 1 + wave; ib < 4; ib += 4) {   // block below: times L11^-T
+            d4 x = {0, 0, 0, 0};
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) x = mfma64(S[16 * ib + n][16 * jb + 4 * kk + g], D[jb][n][4 * kk + g], x);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[16 * ib + 4 * v + g][16 * jb + n] = x[v];
+        }
+        __syncthreads();
+        int turn = 0;
+        for (int ib = jb + 1; ib < 4; ++ib)
+            for (int kb = jb + 1; kb <= ib; ++kb) {
+                if ((turn++ & 3) != wave) continue;
+                d4 c;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) c[v] = S[16 * ib + 4 * v + g][16 * kb + n];
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk) c = mfma64(-S[16 * ib + n][16 * jb + 4 * kk + g], S[16 * kb + n][16 * jb + 4 * kk + g], c);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) S[16 * ib + 4 * v + g][16 * kb + n] = c[v];
+            }
+        __syncthreads();
+    }
+    if (tid == 0 && s_bad) atomicOr(flag, 1u);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int r = wave + 4 * e;
+        if (r < nb && lane < nb) blk[(size_t)r * lda + lane] = lane <= r ? S[r][lane] : 0.0;
+    }
+    if (!inv) return;
+    // X(i, j) = -D(i) sum over j <= k < i of L(i, k) X(k, j): the three diagonals of blocks below the main one in turn, a block a
+    // wavefront (the places above the diagonal they go to are zeros that nobody reads as L any more)
+    __syncthreads();
+    for (int dist = 1; dist < 4; ++dist) {
+        const int j = wave, i = wave + dist;
+        if (i < 4) {
+            d4 w = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+            for (int k = j; k < i; ++k)
+#pragma unroll
+                for (int kk = 0; kk < 4; ++kk)
+                    w = mfma64(S[16 * i + n][16 * k + 4 * kk + g], k == j ? D[j][4 * kk + g][n] : S[16 * j + 4 * kk + g][16 * k + n], w);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) x = mfma64(D[i][n][4 * kk + g], w[kk], x);      // (register kk of w is row 4 kk + g: the operand)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[16 * j + 4 * v + g][16 * i + n] = -x[v];
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+        const int r = wave + 4 * e, bi = r >> 4, bj = lane >> 4;
+        const double below = S[16 * bj + (r & 15)][16 * bi + n], diag = D[bi][r & 15][n];
+        inv[r * CH_NB + lane] = bi < bj ? 0.0 : bi == bj ? diag : below;
     }
 }
 
@@ -820,12 +1012,26 @@ void copy_doubles(const double* src, double* dst, size_t n, hipStream_t st)
     hipLaunchKernelGGL(copy_kernel, dim3(blocks(n)), dim3(256), 0, st, src, dst, n);
 }
 
+// scratch (room for `room` doubles): where there are few tiles and a long contraction the compute units share the contraction
+// (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are added in order.
 template <typename TA, typename TB>
 void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
-          hipStream_t st, double alpha = 1.0, double beta = 0.0, int lower = 0)
+          hipStream_t st, double alpha = 1.0, double beta = 0.0, int shape = GM_FULL, double* scratch = nullptr, size_t room = 0)
 {
-    hipLaunchKernelGGL((gemm_kernel<TA, TB>), dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, A, ai, ak, B, bj, bk, C,
-                       ldc, M, N, K, alpha, beta, lower);
+    const int ti = (M + 63) / 64, tj = (N + 63) / 64, tiles = shape == GM_LOWER ? ti * (ti + 1) / 2 : ti * tj;
+    if (scratch && tiles <= 64 && K >= 512 && shape != GM_B_LOWER) {
+        size_t parts = 256 / tiles;
+        if (parts > (size_t)K / 128) parts = K / 128;     // at least four stages each
+        if (parts > room / ((size_t)M * N)) parts = room / ((size_t)M * N);
+        if (parts > 1) {
+            hipLaunchKernelGGL((gemm_kernel<TA, TB>), dim3(tj, ti, (unsigned)parts), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta,
+                               shape, scratch);
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3(blocks((size_t)M * N)), dim3(256), 0, st, (const double*)scratch, (int)parts, C, ldc, M, N, alpha, beta,
+                               shape == GM_LOWER);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((gemm_kernel<TA, TB>), dim3(tj, ti), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, (double*)nullptr);
 }
 
 // G (n x n, row-major, symmetric) -> L in its lower triangle, zeros above.  Enqueues only; *flag (device, cleared
@@ -840,13 +1046,13 @@ void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double*
     for (int j0 = 0; j0 < n; j0 += CH_NB) {
         const int nb = n - j0 < CH_NB ? n - j0 : CH_NB, rest = n - j0 - nb;
         double* const iv = inv + (keep_inv ? (size_t)j0 * CH_NB : 0);
-        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(64), 0, st, G, (long)n, j0, nb, thr, flag, keep_inv || rest > 0 ? iv : nullptr);
+        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(256), 0, st, G, (long)n, j0, nb, thr, flag, keep_inv || rest > 0 ? iv : nullptr);
         if (rest <= 0) break;
         // rows below: P <- P L11^-T, in place (a workgroup reads its 64 rows whole before it writes them)
         double* const P = G + (size_t)(j0 + nb) * n + j0;
         gemm((const double*)P, (long)n, 1L, (const double*)iv, (long)CH_NB, 1L, P, (long)n, rest, nb, nb, st);
         // trailing matrix -= panel . panel^T (the tiles of its lower triangle)
-        gemm((const double*)P, (long)n, 1L, (const double*)P, (long)n, 1L, G + (size_t)(j0 + nb) * n + (j0 + nb), (long)n, rest, rest, nb, st, -1.0, 1.0, 1);
+        gemm((const double*)P, (long)n, 1L, (const double*)P, (long)n, 1L, G + (size_t)(j0 + nb) * n + (j0 + nb), (long)n, rest, rest, nb, st, -1.0, 1.0, GM_LOWER);
     }
     hipLaunchKernelGGL(zero_upper_kernel, dim3(blocks((size_t)n * n)), dim3(256), 0, st, G, n);
 }
@@ -944,12 +1150,12 @@ int subspace_size(int r) { return ((2 * r > r + 64 ? 2 * r : r + 64) + 127) / 12
 // rows cost more: 4096 x 4096 with r = 128, 0.78 s of sweeps)
 bool subspace_fits(int m, int r) { return subspace_size(r) <= m / 4; }
 
-// the p rows of Z (length L) made orthonormal; F, inv: p x p scratch each (p >= 64)
-void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* thr, unsigned* flag, hipStream_t st)
+// the p rows of Z (length L) made orthonormal; F, inv: p x p scratch each (p >= 64), scratch: `room` doubles
+void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* scratch, size_t room, double* thr, unsigned* flag, hipStream_t st)
 {
     hipLaunchKernelGGL(normalise_rows_kernel, dim3(p), dim3(256), 0, st, Z, L);
     for (int pass = 0; pass < 2; ++pass) {
-        gemm((const double*)Z, (long)L, 1L, (const double*)Z, (long)L, 1L, F, (long)p, p, p, L, st, 1.0, 0.0, 1);
+        gemm((const double*)Z, (long)L, 1L, (const double*)Z, (long)L, 1L, F, (long)p, p, p, L, st, 1.0, 0.0, GM_LOWER, scratch, room);
         cholesky(F, p, 1e-14, thr, flag, inv, st, pass == 0, true);
         for (int j0 = 0; j0 < p; j0 += CH_NB) {
             const int nb = p - j0 < CH_NB ? p - j0 : CH_NB;
@@ -964,7 +1170,7 @@ void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* thr
 // S = T T^T (both triangles) of T, m x n
 void row_products(const double* T, int m, int n, double* S, hipStream_t st)
 {
-    gemm(T, (long)n, 1L, T, (long)n, 1L, S, (long)m, m, m, n, st, 1.0, 0.0, 1);
+    gemm(T, (long)n, 1L, T, (long)n, 1L, S, (long)m, m, m, n, st, 1.0, 0.0, GM_LOWER);
     hipLaunchKernelGGL(mirror_kernel, dim3((m + 31) / 32, (m + 31) / 32), dim3(256), 0, st, S, m);
 }
 
@@ -995,7 +1201,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     // Ritz rotation of all p rows: Z <- Ritz vectors (descending), Y <- Z S, theta, residuals, on the host too
     auto ritz = [&]() -> int {
         times_s(Z, Y, p, 1.0, 0.0);
-        gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st);
+        gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st, 1.0, 0.0, GM_FULL, U, (size_t)p * m);
         if (nl > 0)                                       // Y orthogonal to the locked rows: their products with it are F's first columns
             gemm((const double*)(F + (size_t)nl * p), (long)p, 1L, (const double*)Z, 1L, (long)m, Y + (size_t)nl * m, (long)m, p - nl, m, nl, st, -1.0, 1.0);
         hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
@@ -1020,7 +1226,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     hipLaunchKernelGGL(random_rows_kernel, dim3(blocks((size_t)p * m)), dim3(256), 0, st, Y, (size_t)p * m);
     for (int it = 0; it < 2; ++it) {
         times_s(Y, Z, p, 1.0, 0.0);
-        orthonormalise(Z, p, m, F, R, thr, flag, st);
+        orthonormalise(Z, p, m, F, R, U, (size_t)p * m, thr, flag, st);
         if (it == 0) copy_doubles(Z, Y, (size_t)p * m, st);
     }
     int rc = ritz(), stalled = 0;
@@ -1049,10 +1255,10 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         }
         if (y1 != Z + (size_t)nl * m) copy_doubles(y1, Z + (size_t)nl * m, (size_t)rows * m, st);
         if (nl > 0) {                                     // against the rows taken out: z -= (z X^T) X
-            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st);
+            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st, 1.0, 0.0, GM_FULL, U, (size_t)p * m);
             gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, Z + (size_t)nl * m, (long)m, rows, m, nl, st, -1.0, 1.0);
         }
-        orthonormalise(Z + (size_t)nl * m, rows, m, F, R, thr, flag, st);
+        orthonormalise(Z + (size_t)nl * m, rows, m, F, R, U, (size_t)p * m, thr, flag, st);
         rc = ritz();
         if (rc != 1) break;
         double worst = 0.0;
@@ -1177,7 +1383,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
 
     // steps 1, 2: error and Gram matrix (the factorisation reads the lower triangle only)
     hipLaunchKernelGGL(sub_kernel, dim3(blocks(nw)), dim3(256), 0, st, W, What, dW, nw);
-    gemm(Xt, (long)n_tokens, 1L, Xt, (long)n_tokens, 1L, H, (long)k, k, k, n_tokens, st, 1.0, 0.0, g_factors_route == 0 ? 1 : 0);
+    gemm(Xt, (long)n_tokens, 1L, Xt, (long)n_tokens, 1L, H, (long)k, k, k, n_tokens, st, 1.0, 0.0, g_factors_route == 0 ? GM_LOWER : GM_FULL);
 
     // Steps 2-4 and 6 by a Cholesky factor.  With X~ X~^T = L L^T, dW L equals dW Q sqrt(Lambda) times an orthogonal
     // matrix on the right, so step 5 finds the same U' and Sigma', and step 6's A = Sigma'^-1 U'^T (dW L) L^-1 is
@@ -1228,7 +1434,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     if (by_rows) {
         if (chol) {
             // T = dW L (d_out x k): T[o][j] = sum_i dW[o][i] L[i][j]
-            gemm(dW, (long)k, 1L, H, 1L, (long)k, T, (long)k, d_out, k, k, st);
+            gemm(dW, (long)k, 1L, H, 1L, (long)k, T, (long)k, d_out, k, k, st, 1.0, 0.0, GM_B_LOWER);
         } else {
             // T[o][j] = root[j] * sum_i dW[o][i] V[j][i]
             gemm(dW, (long)k, 1L, V, (long)k, 1L, T, (long)k, d_out, k, k, st);
@@ -1285,7 +1491,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     if (chol && !sub && n >= 2 * m) {
         unsigned* flag = rot + 16;
         double* thr = (double*)(rot + 32);
-        gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st, 1.0, 0.0, 1);
+        gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st, 1.0, 0.0, GM_LOWER);
         cholesky(H, m, 1e-14, thr, flag, V, st);
         unsigned bad = 1;
         if (hipMemcpyAsync(&bad, flag, sizeof(bad), hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
