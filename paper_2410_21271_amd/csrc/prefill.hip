@@ -196,47 +196,6 @@ __device__ __forceinline__ void pick_scale(const WScale& r, const WSeg& a, int s
     }
 }
 
-// the four pairs of three-bit codes that form fragment T (columns 8T .. 8T + 7 of the lane's 32)
-template <int T>
-__device__ __forceinline__ h8 dq3_frag(const uint32_t (&d)[3], uint32_t z)
-{
-    const h2 eighth = {(_Float16)0.125f, (_Float16)0.125f}, sixtyfourth = {(_Float16)0.015625f, (_Float16)0.015625f};
-    const uint32_t magic = in_vgpr(MAGIC);
-    Frag f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int p = 4 * T + e;
-        if (p == 15) {
-            uint32_t last = and_or(d[0] >> 15, 0x00010001u, magic);
-            last = and_or(d[1] >> 14, 0x00020002u, last);
-            last = and_or(d[2] >> 13, 0x00040004u, last);
-            f.p[e] = as_h2(last) - as_h2(k1024(z));
-        } else {
-            const int o = p % 5;
-            const uint32_t w = o < 3 ? d[p / 5] : d[p / 5] >> 9;
-            if (o % 3 == 0) f.p[e] = as_h2(and_or(w, 0x00070007u, magic)) - as_h2(k1024(z));
-            else if (o % 3 == 1) f.p[e] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00380038u, magic)), eighth, -as_h2(k128(z)));
-            else f.p[e] = __builtin_elementwise_fma(as_h2(and_or(w, 0x01C001C0u, magic)), sixtyfourth, -as_h2(k16(z)));
-        }
-    }
-    return f.v;
-}
-
-// two-bit codes: fragment T is half of word T / 2
-template <int T>
-__device__ __forceinline__ h8 dq2_frag(const uint32_t (&d)[2], uint32_t z)
-{
-    const h2 quarter = {(_Float16)0.25f, (_Float16)0.25f}, sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const h2 sixtyfourth = {(_Float16)0.015625f, (_Float16)0.015625f};
-    const uint32_t magic = in_vgpr(MAGIC), w = T & 1 ? d[T / 2] >> 8 : d[T / 2];
-    Frag f;
-    f.p[0] = as_h2(and_or(w, 0x00030003u, magic)) - as_h2(k1024(z));
-    f.p[1] = __builtin_elementwise_fma(as_h2(and_or(w, 0x000C000Cu, magic)), quarter, -as_h2(0x5C005C00u | (z * 0x00040004u)));
-    f.p[2] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00300030u, magic)), sixteenth, -as_h2(k64(z)));
-    f.p[3] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00C000C0u, magic)), sixtyfourth, -as_h2(k16(z)));
-    return f.v;
-}
-
 // fragment T (of four) of the lane's chunks into the slab; the group's scale is folded in (one fp16 rounding per weight).
 // wl: the lane's first chunk in the slab
 template <int FMT, int T>
@@ -249,11 +208,7 @@ __device__ __forceinline__ void store_w(const WReg<FMT>& r, uint32_t sraw, uint3
     } else {
         const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)sraw);
         const h8 s = {sc, sc, sc, sc, sc, sc, sc, sc};
-        h8 b;
-        if constexpr (FMT == S_Q3 || FMT == S_Q3S128) b = dq3_frag<T>(r.w, z);
-        else if constexpr (FMT == S_Q2) b = dq2_frag<T>(r.w, z);
-        else b = dq4_word(r.w[T], k1024(z), k64(z));
-        *(h8*)(eora_smem + (wl ^ (T << 4))) = b * s;
+        *(h8*)(eora_smem + (wl ^ (T << 4))) = decode_frag<T>(r.w, z) * s;
     }
 }
 

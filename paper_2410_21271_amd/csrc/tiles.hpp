@@ -128,6 +128,56 @@ __device__ __forceinline__ void dq3_lane(uint32_t d0, uint32_t d1, uint32_t d2, 
     }
 }
 
+// the four pairs of three-bit codes that form fragment T (columns 8T .. 8T + 7 of the lane's 32)
+template <int T>
+__device__ __forceinline__ h8 dq3_frag(const uint32_t (&d)[3], uint32_t z)
+{
+    const h2 eighth = {(_Float16)0.125f, (_Float16)0.125f}, sixtyfourth = {(_Float16)0.015625f, (_Float16)0.015625f};
+    const uint32_t magic = in_vgpr(MAGIC);
+    Frag f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int p = 4 * T + e;
+        if (p == 15) {
+            uint32_t last = and_or(d[0] >> 15, 0x00010001u, magic);
+            last = and_or(d[1] >> 14, 0x00020002u, last);
+            last = and_or(d[2] >> 13, 0x00040004u, last);
+            f.p[e] = as_h2(last) - as_h2(k1024(z));
+        } else {
+            const int o = p % 5;
+            const uint32_t w = o < 3 ? d[p / 5] : d[p / 5] >> 9;
+            if (o % 3 == 0) f.p[e] = as_h2(and_or(w, 0x00070007u, magic)) - as_h2(k1024(z));
+            else if (o % 3 == 1) f.p[e] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00380038u, magic)), eighth, -as_h2(k128(z)));
+            else f.p[e] = __builtin_elementwise_fma(as_h2(and_or(w, 0x01C001C0u, magic)), sixtyfourth, -as_h2(k16(z)));
+        }
+    }
+    return f.v;
+}
+
+// two-bit codes: fragment T is half of word T / 2
+template <int T>
+__device__ __forceinline__ h8 dq2_frag(const uint32_t (&d)[2], uint32_t z)
+{
+    const h2 quarter = {(_Float16)0.25f, (_Float16)0.25f}, sixteenth = {(_Float16)0.0625f, (_Float16)0.0625f};
+    const h2 sixtyfourth = {(_Float16)0.015625f, (_Float16)0.015625f};
+    const uint32_t magic = in_vgpr(MAGIC), w = T & 1 ? d[T / 2] >> 8 : d[T / 2];
+    Frag f;
+    f.p[0] = as_h2(and_or(w, 0x00030003u, magic)) - as_h2(k1024(z));
+    f.p[1] = __builtin_elementwise_fma(as_h2(and_or(w, 0x000C000Cu, magic)), quarter, -as_h2(0x5C005C00u | (z * 0x00040004u)));
+    f.p[2] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00300030u, magic)), sixteenth, -as_h2(k64(z)));
+    f.p[3] = __builtin_elementwise_fma(as_h2(and_or(w, 0x00C000C0u, magic)), sixtyfourth, -as_h2(k16(z)));
+    return f.v;
+}
+
+// fragment T (columns 8T .. 8T + 7) of the lane's 32 columns of a tile of 2, 3 or 4 words: code - z
+template <int T, int WORDS>
+__device__ __forceinline__ h8 decode_frag(const uint32_t (&w)[WORDS], uint32_t z)
+{
+    if constexpr (WORDS == 3) return dq3_frag<T>(w, z);
+    else if constexpr (WORDS == 2) return dq2_frag<T>(w, z);
+    else return dq4_word(w[T], k1024(z), k64(z));
+}
+
 // ------------------------------------------------------------------------------------------------
 // Codes as fp16 SUBNORMALS (decode kernel for one to four tokens).  A b-bit code left in place at bit p
 // (p + b <= 10) of a 16-bit half, everything else masked off, IS the fp16 subnormal code * 2^(p-24): one AND per

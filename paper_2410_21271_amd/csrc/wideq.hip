@@ -193,6 +193,12 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && (NWR > 1 || (ONE_ORDER && LOWRANK
     // row block share a compute unit: 14336 x 4096 W4, three tokens 20.3 -> 15.7 us, 1024 x 1024, one token 5.7 -> 5.2.
     constexpr int XN = ONE_ORDER && (NWR == 1 || FM == S_Q4) ? 1 : (4 * TB) / NWR;
     constexpr int PX = XN > 8 ? 1 : 2;                    // steps between a request for x and its LDS write
+    // Two and more token blocks, wavefronts that share x through LDS: the next chunk's writes and the requests for the one behind it are
+    // spread over the step (a compute unit takes in 64 bytes a cycle; all at once they hold a wavefront up for 270 .. 640 cycles
+    // of 2900), fragments are read a quarter of a step ahead, and a wavefront's priority falls as it gets through the step (by
+    // age alone the older of a SIMD's two runs ahead and waits at the barrier).  64 tokens, bare: 28672 x 4096 W4 30.6 -> 27.8 us,
+    // 4096 x 4096 10.2 -> 9.5.  With one token block the writes come too late that way (14336 x 1152, ten tokens 6.4 -> 6.7).
+    constexpr bool SPREAD = NWR > 1 && TB > 1;
     constexpr int D = RW >= 4 ? 2 : 4;                    // steps between a request for a stored tile and its use
     static_assert((4 * TB) % NWR == 0, "the pieces of a chunk divide evenly over a range's wavefronts");
     __shared__ uint32_t s_epoch;
@@ -403,9 +409,11 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && (NWR > 1 || (ONE_ORDER && LOWRANK
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own LDS writes of chunk s done
             __builtin_amdgcn_s_barrier();                 // chunk s is visible, everyone has left the other slot
             xs = xk + (i & 1) * SLOT;
+            if constexpr (!SPREAD) {
 #pragma unroll
-            for (int q = 0; q < XN; ++q) *(u4*)(xk + ((i + 1) & 1) * SLOT + xdst[q]) = xr[(i + 1) % PX][q];
-            load_x(xr[(i + 1) % PX], s + 1 + PX);
+                for (int q = 0; q < XN; ++q) *(u4*)(xk + ((i + 1) & 1) * SLOT + xdst[q]) = xr[(i + 1) % PX][q];
+                load_x(xr[(i + 1) % PX], s + 1 + PX);
+            }
         } else {
 #pragma unroll
             for (int q = 0; q < XN; ++q) *(u4*)(xk + xdst[q]) = xr[i % PX][q];
@@ -413,7 +421,66 @@ __global__ __launch_bounds__(WQ_NT, TB == 1 && (NWR > 1 || (ONE_ORDER && LOWRANK
         }
         asm volatile("" ::: "memory");                    // (fragments are read by other lanes than the ones that wrote them)
         __builtin_amdgcn_sched_barrier(0);
-        if (s < len) {                                    // uniform over the wavefront; no global load inside
+        if constexpr (SPREAD) {
+            // (a step past the range's end goes through the motions with a valid chunk and tile of the segment; nothing of it is added)
+            f4 part[RW][TB];
+            h8 b[2][RW], xf[2][TB];
+            uint32_t z[RW];
+            float sc[RW];
+            const int grp = group_of(tile_at(s)), zs = 4 * (grp & 7);
+            const int lrow = wr * RW * 16 + n;
+#pragma unroll
+            for (int rw = 0; rw < RW; ++rw) {
+                sc[rw] = (float)__builtin_bit_cast(_Float16, m_sc[(grp - g_lo) * ROWS + lrow + 16 * rw]);
+                z[rw] = m_zq[((grp >> 3) - z_lo) * ROWS + lrow + 16 * rw];
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb) part[rw][tb] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int tb = 0; tb < TB; ++tb) xf[0][tb] = *(const h8*)(xs + tb * 4096 + poff[0]);
+#pragma unroll
+            for (int rw = 0; rw < RW; ++rw) {
+                z[rw] = (z[rw] >> zs) & 0xFu;
+                b[0][rw] = decode_frag<0>(pre[i][rw].w, z[rw]);
+            }
+            // quarter t: its MFMAs, and between them the decoding and the fragments of the next one and a share of x
+            auto quarter = [&](auto ttag) __attribute__((always_inline)) {
+                constexpr int t = decltype(ttag)::value;
+                if constexpr (t < 3) {
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) xf[(t + 1) & 1][tb] = *(const h8*)(xs + tb * 4096 + poff[t + 1]);
+                }
+#pragma unroll
+                for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+                    for (int rw = 0; rw < RW; ++rw) part[rw][tb] = mfma16(xf[t & 1][tb], b[t & 1][rw], part[rw][tb]);
+                if constexpr (t < 3) {
+#pragma unroll
+                    for (int rw = 0; rw < RW; ++rw) b[(t + 1) & 1][rw] = decode_frag<t + 1>(pre[i][rw].w, z[rw]);
+                }
+#pragma unroll
+                for (int q = XN * t / 4; q < XN * (t + 1) / 4; ++q) {
+                    *(u4*)(xk + ((i + 1) & 1) * SLOT + xdst[q]) = xr[(i + 1) % PX][q];
+                    xr[(i + 1) % PX][q] = *(const u4*)(a.x + (size_t)tile_at(s + 1 + PX) * 128 + xsrc[q]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            __builtin_amdgcn_s_setprio(3);
+            quarter(std::integral_constant<int, 0>{});
+            __builtin_amdgcn_s_setprio(2);
+            quarter(std::integral_constant<int, 1>{});
+            __builtin_amdgcn_s_setprio(1);
+            quarter(std::integral_constant<int, 2>{});
+            __builtin_amdgcn_s_setprio(0);
+            quarter(std::integral_constant<int, 3>{});
+            if (s < len) {                                // uniform over the wavefront; no global load inside
+#pragma unroll
+                for (int rw = 0; rw < RW; ++rw) {
+#pragma unroll
+                    for (int tb = 0; tb < TB; ++tb) accs[i % NV][rw][tb] += sc[rw] * part[rw][tb];
+                }
+            }
+        } else if (s < len) {                             // uniform over the wavefront; no global load inside
             h8 b[RW][4];
             f4 part[RW][TB];
             const int grp = group_of(ka + STRIDE * s), zs = 4 * (grp & 7);
