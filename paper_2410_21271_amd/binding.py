@@ -7,6 +7,9 @@ import ctypes
 import os
 
 import numpy as np
+# torch must own the process's HIP runtime: loading it first makes libeora.so bind to the same libamdhip64 (same soname)
+# instead of bringing in a second runtime whose streams and device pointers would be foreign to torch's.
+import torch as _torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libeora.so")
@@ -37,10 +40,6 @@ def _load():
     if not os.path.exists(_LIB_PATH):
         raise ImportError("libeora.so is not built: run `python paper_2410_21271_amd/build.py` "
                           "(there is no CPU fallback)")
-    # torch must own the process's HIP runtime: loading it first makes libeora.so bind to the same
-    # libamdhip64 (same soname) instead of bringing in a second runtime whose streams and device
-    # pointers would be foreign to torch's.
-    import torch  # noqa: F401
     L = ctypes.CDLL(_LIB_PATH)
     vp, ci, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
     sig = {
@@ -227,13 +226,24 @@ def pack_sp24q4(codes, pos, zeros, scales, group):
 
 
 # ------------------------------------------------------------------ device entry points (torch tensors as memory)
+# A call of one small linear takes the GPU 5 us, so that what the host does per call shows: pointers go to ctypes as plain
+# integers (None: a null pointer) and the stream comes without the Stream object that torch.cuda.current_stream() builds
+# (one 1024 x 1024 linear, one token, called directly: 9.3 us with c_void_p objects and Stream, 5.6 now).
+_get_device, _raw_stream = _torch._C._cuda_getDevice, _torch._C._cuda_getCurrentRawStream
+
+
 def _dp(t):
-    return ctypes.c_void_p(0 if t is None else t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _nbytes(t):
+    return 0 if t is None else t.numel() * t.element_size()
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if not _torch.cuda.is_initialized():
+        return _torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
 
 
 def workspace_init(workspace):
@@ -283,19 +293,17 @@ def workspace_bytes_group(M, d_in, r, n_members):
 
 def new_workspace(M, d_in, d_out, r, n_members=1):
     """Allocate (torch, device memory only) and initialise a workspace for the forward calls."""
-    import torch
     nbytes = max(workspace_bytes(M, d_in, d_out, r), workspace_bytes_group(M, d_in, r, n_members))
-    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    ws = _torch.empty(nbytes, dtype=_torch.uint8, device="cuda")
     workspace_init(ws)
     return ws
 
 
 def linear_q(x, qweight, scales, qzeros, A, B, A_scales, B_scales, y, M, d_in, d_out, r, w_bits, group, ab_bits,
              workspace):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.eora_linear_q(_dp(x), _dp(qweight), _dp(scales), _dp(qzeros), _dp(A), _dp(B), _dp(A_scales),
                              _dp(B_scales), _dp(y), M, d_in, d_out, r, w_bits, group, ab_bits,
-                             _dp(workspace), ws_bytes, _stream()), "linear_q")
+                             _dp(workspace), _nbytes(workspace), _stream()), "linear_q")
 
 
 def linear_q_static(x, qweight, scales, qzeros, A, B, A_scales, B_scales, y, M, d_in, d_out, r, w_bits, group, ab_bits):
@@ -310,21 +318,18 @@ def linear_q_group(x, members, M, d_in, r, w_bits, group, ab_bits, workspace):
     for e, m in zip(arr, members):
         (e.qweight, e.scales, e.qzeros, e.A, e.B, e.A_scales, e.B_scales, e.y) = [_dp(t) for t in m[:8]]
         e.d_out = m[8]
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.eora_linear_q_group(_dp(x), arr, len(members), M, d_in, r, w_bits, group, ab_bits,
-                                   _dp(workspace), ws_bytes, _stream()), "linear_q_group")
+                                   _dp(workspace), _nbytes(workspace), _stream()), "linear_q_group")
 
 
 def linear_sp24(x, values, indices, A, B, y, M, d_in, d_out, r, workspace):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.eora_linear_sp24(_dp(x), _dp(values), _dp(indices), _dp(A), _dp(B), _dp(y), M, d_in, d_out, r,
-                                _dp(workspace), ws_bytes, _stream()), "linear_sp24")
+                                _dp(workspace), _nbytes(workspace), _stream()), "linear_sp24")
 
 
 def linear_sp24q4(x, qtiles, qmeta, A, B, y, M, d_in, d_out, r, workspace):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.eora_linear_sp24q4(_dp(x), _dp(qtiles), _dp(qmeta), _dp(A), _dp(B), _dp(y),
-                                  M, d_in, d_out, r, _dp(workspace), ws_bytes, _stream()), "linear_sp24q4")
+                                  M, d_in, d_out, r, _dp(workspace), _nbytes(workspace), _stream()), "linear_sp24q4")
 
 
 def unpack_q(qweight, qzeros, codes_u8, zeros_u8, d_in, d_out, w_bits, group):
@@ -347,10 +352,9 @@ def expand_sp24q4(qtiles, qmeta, W_f32, d_in, d_out):
 
 def linear_q_multi(x, qweight, scales, qzeros, A_all, B_all, A_scales, B_scales, adapter_of_row, y, M, d_in, d_out, r,
                    n_adapters, w_bits, group, ab_bits, workspace):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     _check(lib.eora_linear_q_multi(_dp(x), _dp(qweight), _dp(scales), _dp(qzeros), _dp(A_all), _dp(B_all), _dp(A_scales),
                                    _dp(B_scales), _dp(adapter_of_row), _dp(y), M, d_in, d_out, r, n_adapters, w_bits, group,
-                                   ab_bits, _dp(workspace), ws_bytes, _stream()), "linear_q_multi")
+                                   ab_bits, _dp(workspace), _nbytes(workspace), _stream()), "linear_q_multi")
 
 
 # ------------------------------------------------------------------ calibration (Alg. 1 steps 1-6)
@@ -360,10 +364,9 @@ def factors_workspace_bytes(d_in, d_out, r):
 
 def factors(W_f32, W_hat_f32, Xt_f32, B_f64, A_f64, sigma_f64, n_tokens, d_in, d_out, r, eig_floor, workspace, stats=False):
     """stats=True returns the eight counters of eora_factors' `stats` argument as a dict."""
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     st = (ctypes.c_double * 8)() if stats else None
     _check(lib.eora_factors(_dp(W_f32), _dp(W_hat_f32), _dp(Xt_f32), n_tokens, d_in, d_out, r, float(eig_floor),
-                            _dp(B_f64), _dp(A_f64), _dp(sigma_f64), _dp(workspace), ws_bytes, _stream(), st), "factors")
+                            _dp(B_f64), _dp(A_f64), _dp(sigma_f64), _dp(workspace), _nbytes(workspace), _stream(), st), "factors")
     if stats:
         chol = int(st[3]) == 0                            # (the Cholesky route reports the subspace iteration's cycles instead of sweeps)
         return dict(eig_sweeps=0 if chol else int(st[0]), subspace_cycles=int(st[0]) if chol else 0, eig_ms=st[1], eig_rotations=st[2], eig_rows=int(st[3]),
@@ -371,15 +374,13 @@ def factors(W_f32, W_hat_f32, Xt_f32, B_f64, A_f64, sigma_f64, n_tokens, d_in, d
 
 
 def factors_store_f16(B_f64, A_f64, d_in, d_out, r, balance, A_tiles, B_tiles, scratch):
-    nbytes = 0 if scratch is None else scratch.numel() * scratch.element_size()
     _check(lib.eora_factors_store_f16(_dp(B_f64), _dp(A_f64), d_in, d_out, r, int(bool(balance)), _dp(A_tiles), _dp(B_tiles),
-                                      _dp(scratch), nbytes, _stream()), "factors_store_f16")
+                                      _dp(scratch), _nbytes(scratch), _stream()), "factors_store_f16")
 
 
 def factors_store_q(B_f64, A_f64, d_in, d_out, r, ab_bits, balance, A_q, A_scales, B_q, B_scales, scratch):
-    nbytes = 0 if scratch is None else scratch.numel() * scratch.element_size()
     _check(lib.eora_factors_store_q(_dp(B_f64), _dp(A_f64), d_in, d_out, r, ab_bits, int(bool(balance)), _dp(A_q), _dp(A_scales),
-                                    _dp(B_q), _dp(B_scales), _dp(scratch), nbytes, _stream()), "factors_store_q")
+                                    _dp(B_q), _dp(B_scales), _dp(scratch), _nbytes(scratch), _stream()), "factors_store_q")
 
 
 def linear_sp24_group(x, members, M, d_in, r, workspace):
@@ -387,5 +388,4 @@ def linear_sp24_group(x, members, M, d_in, r, workspace):
     arr = (SpMember * len(members))()
     for i, (values, indices, qtiles, qmeta, A, B, y, d_out) in enumerate(members):
         arr[i] = SpMember(*(None if t is None else t.data_ptr() for t in (values, indices, qtiles, qmeta, A, B, y)), int(d_out))
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib.eora_linear_sp24_group(_dp(x), arr, len(members), M, d_in, r, _dp(workspace), ws_bytes, _stream()), "linear_sp24_group")
+    _check(lib.eora_linear_sp24_group(_dp(x), arr, len(members), M, d_in, r, _dp(workspace), _nbytes(workspace), _stream()), "linear_sp24_group")
