@@ -224,23 +224,47 @@ size_t prefill_scratch_most(int M, int d_in, int r)
     return round256((size_t)M * r * 2) + parts;
 }
 
-// room for the fp32 partial outputs of a prompt whose contraction is cut into parts (up to PREFILL_SPLIT_TOKENS tokens)
+// room for the fp32 partial outputs of a prompt whose contraction is cut into parts
 constexpr size_t PREFILL_SPLIT_BYTES = 48u << 20;
-constexpr int PREFILL_SPLIT_TOKENS = 1024;
+
+// Parts of the launch for t that are taken: pick_ksplit's eight and a divisor of the groups leave long contractions with few
+// tokens long chains of steps (333 tokens, rank 128, d_in 14336: 24 workgroups of 28 steps, 28 us).  The cheapest by rounds
+// of 256 workgroups, 0.9 us a step of 64 columns and 5 a workgroup, the parts written and read at 2 TB/s and 4 us for their
+// sum, as far as the workspace has room for the parts (it always has it for pick_ksplit's).  The parts cost more than the two
+// kernels show, because the caches are written back between them: 2048 tokens, rank 256, d_in 14336 in 8 parts 262 us a call
+// with the main GEMM, in 14 (which 4 TB/s would take) 267, and the kernels' own times say the opposite.
+int pick_t_parts(int M, int d_in, int r, int n, size_t room)
+{
+    const int G = d_in / 128, tiles = ((M + 127) / 128) * n * ((r + 255) / 256), least = pick_ksplit(M, d_in, n * r);
+    int best = least;
+    float best_us = 1e30f;
+    for (int ks = 1; ks <= G && ks <= 64; ++ks) {
+        const size_t bytes = ks > 1 ? (size_t)ks * M * n * r * sizeof(float) : 0;
+        if (ks > least && bytes > room) break;
+        const int steps = 2 * ((G + ks - 1) / ks);
+        const float us = (float)((tiles * ks + 255) / 256) * (0.9f * steps + 5.f) + (ks > 1 ? 4.f + (float)bytes * 2.f / 2e6f : 0.f);
+        if (us < best_us) {
+            best_us = us;
+            best = ks;
+        }
+    }
+    return best;
+}
 
 // Tokens per workgroup (64 tm) and parts of the main GEMM's contraction.  A workgroup is 64 tm tokens x 256 rows, one per
 // compute unit.  More tokens share the decoding of a weight, but a launch of few output tiles leaves most of the chip idle for
 // the length of a contraction (333 tokens of the 8B layer: 32 tiles for a 4096 x 4096 linear), and tokens that are not there
-// cost as much as others.  The cheapest by rounds of 256 workgroups: 1.08, 1.36, 1.60 us a step of 64 columns for tm = 2, 3, 4
-// (8192 tokens x 28672 rows, d_in 4096: 1926, 1652, 1466 us) and 5 a tile; the parts' fp32 outputs written and read at 4 TB/s
-// and 5 us for the second launch.
+// cost as much as others.  The cheapest by rounds of 256 workgroups: 1.05, 1.25, 1.5 us a step of 64 columns for tm = 2, 3, 4
+// and 8 a tile; the parts' fp32 outputs written and read at 8 TB/s (they stay in the caches) and 5 us for the second launch.
+// Measured: 333 tokens x 14336 -> 4096, tm = 2 in five parts 58.4 + 5.6 us, tm = 3 in eight 47.7 + 7.4; 333 x 4096 -> 28672, tm = 3
+// 87.1; 8192 x 4096 -> 28672 (the card's power decides, and costs a tenth more each) 1926, 1652, 1466 us.
 // room: bytes for the partial outputs; the parts never need more.  d_out: the members' rows.
 struct PrefillPlan {
     int tm, parts;
 };
 PrefillPlan pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
 {
-    static const float step_us[5] = {0.f, 0.f, 1.08f, 1.36f, 1.60f};
+    static const float step_us[5] = {0.f, 0.f, 1.05f, 1.25f, 1.5f};
     const int G = d_in / 128;
     size_t rows = 0;
     int row_tiles = 0;
@@ -250,13 +274,13 @@ PrefillPlan pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     }
     PrefillPlan best{2, 1};
     float best_us = 1e30f;
-    for (int ks = 1; ks <= 8 && (ks == 1 || (M <= PREFILL_SPLIT_TOKENS && ks * 4 <= G + 3)); ++ks) {
+    for (int ks = 1; ks <= 8 && (ks == 1 || ks * 4 <= G + 3); ++ks) {
         const size_t bytes = (size_t)ks * M * rows * sizeof(float);
         if (ks > 1 && bytes > room) break;                // (whole numbers: a float would round the room up to the need)
         for (int tm = 2; tm <= 4; ++tm) {
             const size_t wgs = (size_t)row_tiles * ((M + 64 * tm - 1) / (64 * tm)) * ks;
-            const float us = (float)((wgs + 255) / 256) * (step_us[tm] * (2 * ((G + ks - 1) / ks) + (r + 63) / 64) + 5.f) +
-                             (ks > 1 ? 5.f + (float)bytes * 2.f / 4e6f : 0.f);
+            const float us = (float)((wgs + 255) / 256) * (step_us[tm] * (2 * ((G + ks - 1) / ks) + r / 64) + 8.f) +
+                             (ks > 1 ? 5.f + (float)bytes * 2.f / 8e6f : 0.f);
             if (us < best_us) {
                 best_us = us;
                 best = {tm, ks};
@@ -278,8 +302,12 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
         p.group = 128;
         p.M = M; p.K1 = d_in;
         p.n = n;
-        p.ksplit = pick_ksplit(M, d_in, n * r);
-        p.part = (float*)((char*)workspace + WS_T + round256((size_t)M * n * r * 2));
+        // room: what is left behind t, as far as every workspace of the right size has it (the bits of t are then the same
+        // whatever larger size it has); the main GEMM's parts come after the sum of these and may overwrite them
+        const size_t own = WS_T + round256((size_t)M * n * r * 2), least = prefill_scratch_bytes(M, d_in, r, n) - round256((size_t)M * n * r * 2);
+        const size_t left = workspace_bytes - own, most = least + PREFILL_SPLIT_BYTES;
+        p.ksplit = pick_t_parts(M, d_in, r, n, left < most ? left : most);
+        p.part = (float*)((char*)workspace + own);
         p.ldp = n * r;
         p.tm = 2;                                                 // (few output tiles)
         for (int m = 0; m < n; ++m) {

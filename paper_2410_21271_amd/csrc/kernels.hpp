@@ -177,7 +177,7 @@ struct PrefillArgs {
     int ksplit;               // > 1: workgroup (tile, ks) contracts the ks-th part of K1 only (the last one K2 too) and
     float* part;              //      writes its fp32 tile to part[ks][M][ldp] (columns pcol ..) instead of y
     int ldp;
-    int tm;                   // blocks of 32 tokens per wavefront: 64 tm tokens x 256 rows per workgroup
+    int tm;                   // 2, 3 or 4: 64 tm tokens x 256 rows per workgroup
     int n;                    // members
     const void* w[MAX_GROUP];            // first segment's weight tiles (N rows, K1 columns)
     const _Float16* w_scales[MAX_GROUP];
@@ -193,6 +193,7 @@ struct PrefillArgs {
 
 // fm: format of the first segment's weights; fe2: S_NONE, or the format of the second segment's tiles
 hipError_t launch_prefill(const PrefillArgs& a, int fm, int fe2, hipStream_t stream);
+hipError_t launch_prefill128(const PrefillArgs& a, int fm, int fe2, hipStream_t stream);      // (tm == 2)
 // T (fp16 M x R, R adapters' ranks together): zero wherever a column does not belong to adapter[m]'s r_per columns
 hipError_t launch_mask_t(void* T, const int* adapter, int M, int R, int r_per, hipStream_t stream);
 

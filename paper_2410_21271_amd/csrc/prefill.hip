@@ -2,8 +2,9 @@
 // d_in (backbone, dequantised on the way) and then over r (B's tiles with t = x.A^T as the
 // activation) into the same fp32 accumulators (Sec. 3 forward equation, Alg. 1 step 7; the fusion of
 // B's product into the backbone's output follows Sec. 4.5 / App. A.6).  t itself is a first, small
-// launch of the same kernel with A as the weight operand (fp16 M x r into scratch): recomputing it
-// per output tile would cost r / 128 times the backbone's MFMA work.
+// launch with A as the weight operand (fp16 M x r into scratch): recomputing it per output tile would
+// cost r / 128 times the backbone's MFMA work.  That launch, and launches of few output tiles, take the
+// kernel of prefill128.hip; this one has 128, 192 or 256 tokens per workgroup.
 //
 // Workgroup: 8 wavefronts (2 along the tokens x 4 along the rows), tile = 64 TM tokens x 256 rows, contraction in steps of 64
 // columns; a wavefront owns 32 TM tokens x 64 rows as blocks of v_mfma_f32_16x16x32_f16 (A: 16 rows of weights, B: 16 tokens;
@@ -86,12 +87,9 @@ __device__ __forceinline__ void pf_load_lds(u4 rsrc, uint32_t lane_off, uint32_t
 template <int NEWER>
 __device__ __forceinline__ void pf_arrived()
 {
-    static_assert(NEWER <= 4, "");
+    static_assert(NEWER <= 1, "");
     if constexpr (NEWER == 0) asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-    else if constexpr (NEWER == 1) asm volatile("s_waitcnt vmcnt(1)" : : : "memory");
-    else if constexpr (NEWER == 2) asm volatile("s_waitcnt vmcnt(2)" : : : "memory");
-    else if constexpr (NEWER == 3) asm volatile("s_waitcnt vmcnt(3)" : : : "memory");
-    else asm volatile("s_waitcnt vmcnt(4)" : : : "memory");
+    else asm volatile("s_waitcnt vmcnt(1)" : : : "memory");
 }
 template <int V> struct PfInt { static constexpr int value = V; };
 template <int N, int I = 0, typename F>
@@ -107,7 +105,7 @@ __device__ __forceinline__ void pf_for(F&& f)
 // chunks 4q .. 4q+3 of the step, q = lane >> 5 (fp16 tiles: chunks 2i + q).
 template <int FMT>
 struct WReg {
-    uint32_t w[FMT == S_Q4S64 ? 4 : Fmt<FMT>::WORDS];
+    uint32_t w[Fmt<FMT>::WORDS];
 };
 template <>
 struct WReg<S_F16> {
@@ -132,11 +130,10 @@ __device__ __forceinline__ void place_w(WSeg& a, int rb, int lane)
 {
     const int n = lane & 15, q = lane >> 5;
     if constexpr (FMT == S_F16) a.tile_off = (uint32_t)(rb * (a.K / 32) * 64 + 16 * q + n) * 16u;
-    else if constexpr (FMT == S_Q4S64) a.tile_off = (uint32_t)(rb * 64 + 32 * q + n) * 8u;
     else a.tile_off = (uint32_t)(rb * (a.K / 128) * 64 + 16 * q + n) * (4u * Fmt<FMT>::WORDS);
     a.scale_off = (uint32_t)(rb * 16 + n) * a.ng * 2u;
     a.zero_off = (uint32_t)(rb * 16 + n) * ((a.ng + 7) / 8) * 4u;
-    a.by8 = FMT != S_Q4S64 && a.gdiv == 1 && a.ng % 8 == 0;
+    a.by8 = a.gdiv == 1 && a.ng % 8 == 0;
 }
 
 // step s: columns 64 s .. 64 s + 63 of the segment
@@ -144,18 +141,9 @@ template <int FMT>
 __device__ __forceinline__ void load_w(WReg<FMT>& r, const WSeg& a, int s)
 {
     if constexpr (FMT == S_F16) {                     // chunk 2 i + q: tile 2 s + i / 2, its columns 8 (2 (i % 2) + q) ..
-        const int nt = a.K / 32;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int t = 2 * s + (i >> 1);
-            t = t < nt ? t : nt - 1;
-            r.v[i] = __builtin_amdgcn_raw_buffer_load_b128(a.tiles, a.tile_off, (uint32_t)(t * 64 + 32 * (i & 1)) * 16u, 0);
-        }
-    } else if constexpr (FMT == S_Q4S64) {            // one tile of 64 columns: two stored lanes of two words
-        uint32_t v[2][2];
-        pf_load<2>(v[0], a.tiles, a.tile_off, 0);
-        pf_load<2>(v[1], a.tiles, a.tile_off, 16 * 8);
-        r.w[0] = v[0][0]; r.w[1] = v[0][1]; r.w[2] = v[1][0]; r.w[3] = v[1][1];
+        for (int i = 0; i < 4; ++i)
+            r.v[i] = __builtin_amdgcn_raw_buffer_load_b128(a.tiles, a.tile_off, (uint32_t)((2 * s + (i >> 1)) * 64 + 32 * (i & 1)) * 16u, 0);
     } else {
         pf_load<Fmt<FMT>::WORDS>(r.w, a.tiles, a.tile_off, (uint32_t)((s >> 1) * 64 + 32 * (s & 1)) * (4u * Fmt<FMT>::WORDS));
     }
@@ -199,12 +187,10 @@ __device__ __forceinline__ void pick_scale(const WScale& r, const WSeg& a, int s
 // fragment T (of four) of the lane's chunks into the slab; the group's scale is folded in (one fp16 rounding per weight).
 // wl: the lane's first chunk in the slab
 template <int FMT, int T>
-__device__ __forceinline__ void store_w(const WReg<FMT>& r, uint32_t sraw, uint32_t z, uint32_t wl, bool valid = true)
+__device__ __forceinline__ void store_w(const WReg<FMT>& r, uint32_t sraw, uint32_t z, uint32_t wl)
 {
     if constexpr (FMT == S_F16) {
-        u4 v = r.v[T];
-        if (!valid) v = u4{0u, 0u, 0u, 0u};
-        *(u4*)(eora_smem + (wl ^ (T << 5))) = v;
+        *(u4*)(eora_smem + (wl ^ (T << 5))) = r.v[T];
     } else {
         const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)sraw);
         const h8 s = {sc, sc, sc, sc, sc, sc, sc, sc};
@@ -212,9 +198,8 @@ __device__ __forceinline__ void store_w(const WReg<FMT>& r, uint32_t sraw, uint3
     }
 }
 
-// FM: format of the first segment's weights (S_Q4, S_Q3, S_Q2 asymmetric; S_Q4S128, S_Q3S128, S_F16 for the
-// down-projection launch).  FE2: S_NONE, or the format of a second segment's tiles (B): the kernel then continues over a
-// second segment with its own activations (t).  TM: blocks of 32 tokens per wavefront.
+// FM: format of the backbone (S_Q4, S_Q3, S_Q2).  FE2: S_NONE, or the format of a second segment's tiles (B): the kernel then
+// continues over a second segment with its own activations (t).  TM: blocks of 32 tokens per wavefront.
 template <int FM, int FE2, int TM>
 __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
 {
@@ -235,14 +220,14 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     const int R0 = nt * (PF_BN / 16), nblk = N / 16;
     int rb = 2 * wave + ((lane >> 4) & 1);                        // the row block this lane supplies a row of, clamped to a valid one
     rb = R0 + rb < nblk ? rb : nblk - 1 - R0;
-    const int H1 = K1 / 64, H2 = EXT ? (K2 + 63) / 64 : 0;
+    const int H1 = K1 / 64, H2 = EXT ? K2 / 64 : 0;
     // this workgroup's steps: [sb, se) of the first segment, and with the last part the second segment's, [se, GT)
     const int sb = 2 * (ks * (H1 / 2) / ga.ksplit), se = 2 * ((ks + 1) * (H1 / 2) / ga.ksplit);
     const int GT = EXT && ks == ga.ksplit - 1 ? H1 + H2 : se;
 
     WSeg w1;
     w1.K = K1;
-    w1.gdiv = Fmt<FM>::ASYM ? ga.group / 128 : 1;
+    w1.gdiv = ga.group / 128;
     w1.gmagic = w1.gdiv > 1 ? (uint32_t)((0x100000000ull + w1.gdiv - 1) / w1.gdiv) : 0u;
     w1.ng = K1 / 128 / (int)w1.gdiv;
     w1.tiles = pf_rsrc((const uint32_t*)ga.w[mem] + (size_t)R0 * (K1 / Fmt<FM>::KT) * 64 * Fmt<FM>::WORDS);
@@ -254,7 +239,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
         w2.K = K2;
         w2.gdiv = 1;
         w2.gmagic = 0;
-        w2.ng = FX == S_Q4S64 ? 1 : K2 / 128;
+        w2.ng = K2 / 128;
         w2.tiles = pf_rsrc((const uint32_t*)ga.w2[mem] + (size_t)R0 * (K2 / Fmt<FX>::KT) * 64 * Fmt<FX>::WORDS);
         w2.scales = pf_rsrc((const uint16_t*)ga.w2_scales[mem] + (size_t)R0 * 16 * w2.ng);
         place_w<FX>(w2, rb, lane);
@@ -308,21 +293,19 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     uint32_t sraw = 0, z = 8;                                     // the group in use
     auto load_block = [&](int s) __attribute__((always_inline)) {
         load_scale<FM>(sc, w1, s);
-        if (Fmt<FM>::ASYM && !w1.by8) zsh = 4 * ((w1.gdiv == 1 ? (uint32_t)s >> 1 : __umulhi((uint32_t)s >> 1, w1.gmagic)) & 7);
+        if (!w1.by8) zsh = 4 * ((w1.gdiv == 1 ? (uint32_t)s >> 1 : __umulhi((uint32_t)s >> 1, w1.gmagic)) & 7);
     };
     auto next_group = [&]() __attribute__((always_inline)) {
-        if constexpr (FM != S_F16) {
-            sraw = sc.s[0];
-            z = Fmt<FM>::ASYM ? (sc.z >> zsh) & 0xFu : (FM == S_Q3S128 ? 4u : 8u);
-            asm volatile("" : "+v"(sraw), "+v"(z));               // (formed here: a later request replaces what they come from)
+        sraw = sc.s[0];
+        z = (sc.z >> zsh) & 0xFu;
+        asm volatile("" : "+v"(sraw), "+v"(z));                   // (formed here: a later request replaces what they come from)
 #pragma unroll
-            for (int i = 0; i < 3; ++i) sc.s[i] = __builtin_amdgcn_alignbit(sc.s[i + 1], sc.s[i], 16);
-            sc.s[3] >>= 16;
-            if constexpr (Fmt<FM>::ASYM) sc.z >>= 4;
-        }
+        for (int i = 0; i < 3; ++i) sc.s[i] = __builtin_amdgcn_alignbit(sc.s[i + 1], sc.s[i], 16);
+        sc.s[3] >>= 16;
+        sc.z >>= 4;
     };
     const int row32 = lane & 31, q = lane >> 5;
-    const uint32_t wd = W0 + wave * 32 * 128 + pf_slot(row32, FM == S_F16 ? q : 4 * q);
+    const uint32_t wd = W0 + wave * 32 * 128 + pf_slot(row32, 4 * q);
     uint32_t xb = 0;                                              // LDS offset of the current step's slab of x
     auto turn3 = [](uint32_t b) __attribute__((always_inline)) { return b == 2 * XS ? 0u : b + XS; };
 
@@ -334,9 +317,8 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     pf_for<TM>([&](auto i) __attribute__((always_inline)) { load_x(i, xat + 128, XS); });
     load_w<FM>(wp[1], w1, sb + 1);
     pf_arrived<0>();
-    if constexpr (FM != S_F16)
-        if (w1.by8)                                               // (a part that begins within eight groups)
-            for (int e = 0; e < ((sb >> 1) & 7); ++e) next_group();
+    if (w1.by8)                                                   // (a part that begins within eight groups)
+        for (int e = 0; e < ((sb >> 1) & 7); ++e) next_group();
     next_group();
     pf_for<4>([&](auto t) __attribute__((always_inline)) { store_w<FM, decltype(t)::value>(wp[0], sraw, z, wd); });
     load_w<FM>(wp[0], w1, sb + 2 < se ? sb + 2 : se - 1);
@@ -355,7 +337,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
             constexpr int v = (u + 4) % U;                        // (behind the barrier: the next step's)
             fx[u & 3] = *(const h8*)(eora_smem + ((xf + xb) ^ ((v / NX) << 6)) + (v % NX) * 2048);
             // the other half's rows: for the second half in turn over the first, for the next step's first half behind the barrier
-            constexpr int f = h == 0 ? (NX == 8 ? (i % 2 ? -1 : i / 2) : NX - 4 <= i ? i - (NX - 4) : -1) : i - (NX - 4);
+            constexpr int f = h == 0 && NX == 8 ? (i % 2 ? -1 : i / 2) : i - (NX - 4);
             if constexpr (f >= 0) fw[h ^ 1][f] = *(const h8*)(eora_smem + (wf ^ ((h ^ 1) << 6)) + decltype(wtag)::value * PF_WS + f * 2048);
         }
     };
@@ -374,26 +356,20 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
         const bool main1 = MAIN || s + 1 < se, ext1 = EXT && !MAIN && s + 1 >= se && s + 1 < GT;
         const bool main2 = MAIN || s + 2 < se, ext2 = EXT && !MAIN && s + 2 >= se && s + 2 < GT;
         // the next step's x, requested a step ago, and its stored words (those of the step behind it are the last request)
-        pf_arrived<MAIN ? (FM == S_F16 ? 4 : 1) : 0>();
-        if constexpr (FM == S_F16) {
+        pf_arrived<MAIN ? 1 : 0>();
 #pragma unroll
-            for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(wp[NXT].v[i]));
-        } else {
-#pragma unroll
-            for (int i = 0; i < (int)(sizeof(wp[NXT].w) / 4); ++i) asm volatile("" : "+v"(wp[NXT].w[i]));
-        }
+        for (int i = 0; i < Fmt<FM>::WORDS; ++i) asm volatile("" : "+v"(wp[NXT].w[i]));
         if (main1 && PAR == 1) next_group();
         if (main2 && PAR == 0 && scale_due<FM>(w1, s + 2)) load_block(s + 2);
         if constexpr (EXT && !MAIN) {
             if (ext1) {                                           // (a handful of steps: all at once)
                 const uint32_t wx = W0 + wave * 32 * 128 + pf_slot(row32, FX == S_F16 ? q : 4 * q) + NXT * PF_WS;
-                const bool valid = FX != S_F16 || 2 * (s + 1 - H1) + 1 < K2 / 32;
                 uint32_t sraw2, z2;
                 pick_scale<FX>(se2, w2, s + 1 - H1, sraw2, z2);
                 store_w<FX, 0>(we, sraw2, z2, wx);
                 store_w<FX, 1>(we, sraw2, z2, wx);
-                store_w<FX, 2>(we, sraw2, z2, wx, valid);
-                store_w<FX, 3>(we, sraw2, z2, wx, valid);
+                store_w<FX, 2>(we, sraw2, z2, wx);
+                store_w<FX, 3>(we, sraw2, z2, wx);
             }
             if (s + 2 == se && GT > se) {                         // from here on x is t
                 place_x(ga.ldx2);
@@ -501,19 +477,29 @@ static hipError_t launch_pf_tile(const PrefillArgs& a, hipStream_t stream)
 template <int FM, int FE2>
 static hipError_t launch_pf(const PrefillArgs& a, hipStream_t stream)
 {
-    if constexpr (FM == S_Q4 || FM == S_Q3 || FM == S_Q2) {       // (A's formats: the launch for t alone, always two blocks)
-        if (a.tm == 4) return launch_pf_tile<FM, FE2, 4>(a, stream);
-        if (a.tm == 3) return launch_pf_tile<FM, FE2, 3>(a, stream);
+    switch (a.tm) {
+        case 2: return launch_pf_tile<FM, FE2, 2>(a, stream);
+        case 3: return launch_pf_tile<FM, FE2, 3>(a, stream);
+        case 4: return launch_pf_tile<FM, FE2, 4>(a, stream);
+        default: return hipErrorInvalidValue;
     }
-    return a.tm == 2 ? launch_pf_tile<FM, FE2, 2>(a, stream) : hipErrorInvalidValue;
 }
 
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restrict__ part, _Float16* __restrict__ T, size_t count, int ksplit)
 {
     const size_t i = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
     if (i >= count) return;
+    // fixed order; eight parts' loads at a time on their way (one by one, 32 parts of 1 MiB take 15 us)
     f4 v = *(const f4*)(part + i);
-    for (int ks = 1; ks < ksplit; ++ks) v += *(const f4*)(part + ks * count + i);      // fixed order
+    int ks = 1;
+    for (; ks + 8 <= ksplit; ks += 8) {
+        f4 w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[e] = *(const f4*)(part + (ks + e) * count + i);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v += w[e];
+    }
+    for (; ks < ksplit; ++ks) v += *(const f4*)(part + ks * count + i);
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     *(h4*)(T + i) = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
 }
@@ -568,13 +554,17 @@ static hipError_t launch_pf_ext(const PrefillArgs& a, int fe2, hipStream_t strea
 // fe2: S_NONE, or the format of the second segment's tiles
 hipError_t launch_prefill(const PrefillArgs& a, int fm, int fe2, hipStream_t stream)
 {
+    // 128 tokens: with (nearly) all compute units busy the card's power decides, and the 16x16x32 MFMAs of this kernel win
+    // (2048 tokens x 4096 -> 4096, 256 workgroups: 88.7 us a call against 91.4); with fewer the shorter steps of the other one
+    int wgs = 0;
+    for (int m = 0; m < a.n; ++m) wgs += (a.N[m] + PF_BN - 1) / PF_BN;
+    wgs *= (a.M + 127) / 128 * a.ksplit;
+    const bool backbone = fm == S_Q4 || fm == S_Q3 || fm == S_Q2;
+    if (a.tm == 2 && !(backbone && wgs > 248)) return launch_prefill128(a, fm, fe2, stream);
     switch (fm) {
         case S_Q4: return launch_pf_ext<S_Q4>(a, fe2, stream);
         case S_Q3: return launch_pf_ext<S_Q3>(a, fe2, stream);
         case S_Q2: return launch_pf_ext<S_Q2>(a, fe2, stream);
-        case S_Q4S128: return fe2 != S_NONE ? hipErrorInvalidValue : launch_pf<S_Q4S128, S_NONE>(a, stream);
-        case S_Q3S128: return fe2 != S_NONE ? hipErrorInvalidValue : launch_pf<S_Q3S128, S_NONE>(a, stream);
-        case S_F16: return fe2 != S_NONE ? hipErrorInvalidValue : launch_pf<S_F16, S_NONE>(a, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -28,6 +28,10 @@ def gpu():
     (4, 16, 128, 128, 128, (16,), 128),               # 128 tokens, the smallest launch
     (2, 4, 128, 255, 2048, (272, 16), 1024),          # 128 tokens, groups of eight tiles
     (3, 3, 128, 130, 3072, (528,), 128),              # parts that begin within eight groups
+    (4, 16, 128, 200, 14336, (272,), 128),            # t in many parts, the last of them shorter
+    (3, 4, 256, 131, 8320, (16, 272), 128),           # the same for two members, 65 groups
+    (4, 16, 128, 1500, 2048, (528,), 128),            # parts beyond 1024 tokens
+    (2, 16, 128, 2047, 256, (4096,), 128),            # 128 tokens, every compute unit busy, the last token missing
 ])
 def test_prefill_tiles(gpu, w_bits, ab_bits, r, M, d_in, d_outs, group):
     from oracle import linear
