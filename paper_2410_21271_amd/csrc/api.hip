@@ -296,17 +296,21 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
                          int fa, int fe, const int* adapter, int r_per, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     _Float16* T = (_Float16*)((char*)workspace + WS_T);           // M x (n * r): member m owns columns m*r ..
+    // room for partial outputs: what is left behind t, as far as every workspace of the right size has it (the order of the
+    // sums, and with it the bits of t and y, is then the same whatever larger size it has).  t's parts are there first, and
+    // after their sum those of the main GEMM (2048 tokens, rank 256, 14336 -> 4096: two parts of 128 workgroups with 256 tokens
+    // need the bytes of both, 265 -> 238 us).  A workspace that ends with t's own least parts has no room for the others: the
+    // contraction stays whole, as for every call with a workspace of the least size
+    const size_t t_bytes = round256((size_t)M * n * r * 2), own = WS_T + t_bytes;
+    const size_t least = prefill_scratch_bytes(M, d_in, r, n) - t_bytes, most = least + PREFILL_SPLIT_BYTES;
+    const size_t left = workspace_bytes > own ? workspace_bytes - own : 0, room = left < most ? left : most;
     if (r > 0) {
         PrefillArgs p{};
         p.x = (const _Float16*)x; p.ldx = d_in;
         p.group = 128;
         p.M = M; p.K1 = d_in;
         p.n = n;
-        // room: what is left behind t, as far as every workspace of the right size has it (the bits of t are then the same
-        // whatever larger size it has); the main GEMM's parts come after the sum of these and may overwrite them
-        const size_t own = WS_T + round256((size_t)M * n * r * 2), least = prefill_scratch_bytes(M, d_in, r, n) - round256((size_t)M * n * r * 2);
-        const size_t left = workspace_bytes - own, most = least + PREFILL_SPLIT_BYTES;
-        p.ksplit = pick_t_parts(M, d_in, r, n, left < most ? left : most);
+        p.ksplit = pick_t_parts(M, d_in, r, n, room);
         p.part = (float*)((char*)workspace + own);
         p.ldp = n * r;
         p.tm = 2;                                                 // (few output tiles)
@@ -328,16 +332,12 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
     p.M = M; p.K1 = d_in; p.K2 = r;
     p.ldx2 = n * r;
     p.n = n;
-    const size_t at = WS_T + round256(prefill_scratch_bytes(M, d_in, r, n));      // partial outputs behind t's scratch
     int d_outs[MAX_GROUP] = {0, 0, 0, 0};
     for (int m = 0; m < n; ++m) d_outs[m] = members[m].d_out;
-    // (never more than the room every workspace of the right size has: the order of the sums, and with it the bits of y, are
-    // then the same whatever larger size the workspace has)
-    const size_t room = workspace_bytes > at ? workspace_bytes - at : 0;
-    const PrefillPlan plan = pick_prefill(M, d_in, r, d_outs, n, room < PREFILL_SPLIT_BYTES ? room : PREFILL_SPLIT_BYTES);
+    const PrefillPlan plan = pick_prefill(M, d_in, r, d_outs, n, left > round256(least) ? room : 0);
     p.ksplit = plan.parts;
     p.tm = plan.tm;
-    p.part = (float*)((char*)workspace + at);
+    p.part = (float*)((char*)workspace + own);
     for (int m = 0; m < n; ++m) {
         p.pcol[m] = p.ldp;
         p.ldp += members[m].d_out;

@@ -31,6 +31,7 @@ def gpu():
     (4, 16, 128, 200, 14336, (272,), 128),            # t in many parts, the last of them shorter
     (3, 4, 256, 131, 8320, (16, 272), 128),           # the same for two members, 65 groups
     (4, 16, 128, 1500, 2048, (528,), 128),            # parts beyond 1024 tokens
+    (4, 16, 256, 1700, 8192, (4112,), 128),           # parts that take the room of t's parts as well
     (2, 16, 128, 2047, 256, (4096,), 128),            # 128 tokens, every compute unit busy, the last token missing
 ])
 def test_prefill_tiles(gpu, w_bits, ab_bits, r, M, d_in, d_outs, group):
