@@ -340,7 +340,16 @@ __device__ __forceinline__ T load_at(const T* base, uint32_t off)
 }
 enum { GM_FULL = 0, GM_LOWER = 1, GM_B_LOWER = 2 };
 constexpr int GM_TILE = 64, GM_KT = 32;
-template <typename TA, typename TB>
+
+// Whether every byte that a lane reads of a stage of an operand lies within 32 bits of the tile's address there (with one of the strides
+// 1, the other the length of a row: up to 2^32 / 63 / 4 = 17 million calibration tokens).  Beyond, gemm_kernel's FAR instance takes
+// 64-bit indices throughout.
+inline bool near_offsets(long row_stride, long k_stride, size_t size)
+{
+    return ((size_t)(GM_TILE - 1) * row_stride + (size_t)(GM_KT - 1) * k_stride + 1) * size <= 0xFFFFFFFFull;
+}
+
+template <typename TA, typename TB, bool FAR>
 __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
                                                    double alpha, double beta, int shape, double* part)
 {
@@ -351,11 +360,12 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
     const int i0 = blockIdx.y * TILE, j0 = blockIdx.x * TILE;
     if (shape == GM_LOWER && j0 > i0) return;
     const int wi = TILE / 2 * (wave & 1), wj = TILE / 2 * (wave >> 1);
-    const int stages = (K + KT - 1) / KT, parts = gridDim.z, z = blockIdx.z;
+    const int stages = (K - 1) / KT + 1, parts = gridDim.z, z = blockIdx.z;
     const int first = shape == GM_B_LOWER ? j0 / KT : 0;
     const int sb = first + (int)((long)(stages - first) * z / parts), se = first + (int)((long)(stages - first) * (z + 1) / parts);
     // This thread's elements of a stage: consecutive threads along whichever index is contiguous in memory.  A lane's offsets
-    // (32 bits: within a tile) stay the same, the tile's address moves; rows beyond the last one re-read it, never stored.
+    // (32 bits, where near_offsets says that they fit) stay the same, the tile's address moves; rows beyond the last one re-read
+    // it, never stored.
     int row_a[E], row_b[E];
     uint32_t off_a[E], off_b[E];
     const int k_a = ak == 1 ? tid % KT : tid / TILE, k_b = bk == 1 ? tid % KT : tid / TILE;
@@ -376,7 +386,7 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
     TB rb[2][E];
     auto fetch = [&](int set, int st) __attribute__((always_inline)) {
         const int k0 = st * KT;
-        if (k0 + KT <= K) {
+        if (!FAR && K - k0 >= KT) {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
                 ra[set][e] = load_at(A0 + (size_t)k0 * ak, off_a[e]);
@@ -385,11 +395,11 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
         } else {
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                const int ka = k0 + k_a + dk_a * e, kb = k0 + k_b + dk_b * e;
-                ra[set][e] = A0[(size_t)row_a[e] * ai + (size_t)(ka < K ? ka : K - 1) * ak];
-                rb[set][e] = B0[(size_t)row_b[e] * bj + (size_t)(kb < K ? kb : K - 1) * bk];
-                if (ka >= K) ra[set][e] = 0;
-                if (kb >= K) rb[set][e] = 0;
+                const int at_a = k_a + dk_a * e, at_b = k_b + dk_b * e, left = K - k0;      // (k0 + 31 may be beyond 31 bits)
+                ra[set][e] = A0[(size_t)row_a[e] * ai + (size_t)(at_a < left ? k0 + at_a : K - 1) * ak];
+                rb[set][e] = B0[(size_t)row_b[e] * bj + (size_t)(at_b < left ? k0 + at_b : K - 1) * bk];
+                if (at_a >= left) ra[set][e] = 0;
+                if (at_b >= left) rb[set][e] = 0;
             }
         }
     };
@@ -1019,20 +1029,25 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
           hipStream_t st, double alpha = 1.0, double beta = 0.0, int shape = GM_FULL, double* scratch = nullptr, size_t room = 0)
 {
     const int ti = (M + 63) / 64, tj = (N + 63) / 64, tiles = shape == GM_LOWER ? ti * (ti + 1) / 2 : ti * tj;
+    auto kern = gemm_kernel<TA, TB, false>;
+    // (fp64 operands are matrices of at most MAX_DIM columns.  An instance of its own: tested in the kernel instead, a call at
+    // 4096 x 4096 takes 46.5 ms instead of 46.1)
+    if constexpr (std::is_same_v<TA, float>)
+        if (!near_offsets(ai, ak, sizeof(TA)) || !near_offsets(bj, bk, sizeof(TB))) kern = gemm_kernel<TA, TB, true>;
     if (scratch && tiles <= 64 && K >= 512 && shape != GM_B_LOWER) {
         size_t parts = 256 / tiles;
         if (parts > (size_t)K / 128) parts = K / 128;     // at least four stages each
         if (parts > room / ((size_t)M * N)) parts = room / ((size_t)M * N);
         if (parts > 1) {
-            hipLaunchKernelGGL((gemm_kernel<TA, TB>), dim3(tj, ti, (unsigned)parts), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta,
-                               shape, scratch);
+            hipLaunchKernelGGL(kern, dim3(tj, ti, (unsigned)parts), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, scratch);
             hipLaunchKernelGGL(gemm_sum_kernel, dim3(blocks((size_t)M * N)), dim3(256), 0, st, (const double*)scratch, (int)parts, C, ldc, M, N, alpha, beta,
                                shape == GM_LOWER);
             return;
         }
     }
-    hipLaunchKernelGGL((gemm_kernel<TA, TB>), dim3(tj, ti), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, (double*)nullptr);
+    hipLaunchKernelGGL(kern, dim3(tj, ti), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, (double*)nullptr);
 }
+static_assert(((size_t)(GM_TILE - 1) * MAX_DIM + GM_KT) * sizeof(double) <= 0xFFFFFFFFull, "fp64 operands have near offsets");
 
 // G (n x n, row-major, symmetric) -> L in its lower triangle, zeros above.  Enqueues only; *flag (device, cleared
 // here) is raised if a pivot is not above rel * max diag(G): the factor is then unusable.
@@ -1341,6 +1356,8 @@ int check_shape(int n_tokens, int d_in, int d_out, int r)
 using namespace eora;
 
 extern "C" void eora_debug_set_factors_route(int route) { g_factors_route = route == 1 ? 1 : 0; }
+
+extern "C" int eora_debug_factors_near(int n_tokens) { return near_offsets(n_tokens, 1, sizeof(float)) ? 1 : 0; }
 
 extern "C" size_t eora_factors_workspace_bytes(int d_in, int d_out, int r)
 {

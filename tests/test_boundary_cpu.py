@@ -268,3 +268,12 @@ def test_workspace_sizes_never_shrink_with_tokens_or_rank(d_in, d_out):
         for size in sizes:
             assert size(M, 0) >= room
             assert size(M, 128) >= room + 2 * (M if M >= 128 else 0) * 128
+
+
+def test_calibration_tokens_beyond_32_bit_offsets():
+    """A tile of the Gram product spans 64 rows of n_tokens floats: 32-bit byte offsets are taken only as long as row 63's last
+    byte has one."""
+    assert eora.debug_factors_near(1) and eora.debug_factors_near(8192)
+    for n in (17_043_000, 17_043_521, 17_043_522, 17_100_000, 2 ** 31 - 1):
+        assert eora.debug_factors_near(n) == (4 * (63 * n + 31 + 1) <= 2 ** 32 - 1), n
+    assert eora.debug_factors_near(17_043_000) and not eora.debug_factors_near(17_043_522)

@@ -32,3 +32,35 @@ def test_factors_of_ragged_shapes(gpu, d_in, d_out, n_tokens, r):
     W, W_hat, Xt = _inputs(7100 + d_in + d_out, d_in, d_out, n_tokens, group=d_in)
     B, A, sig = _run(gpu, W, W_hat, Xt, r)
     _compare(W, W_hat, Xt, r, B, A, sig)
+
+
+@pytest.mark.parametrize("n_tokens", [17_043_000, 17_100_008])
+def test_factors_of_more_tokens_than_32_bit_offsets_reach(gpu, n_tokens):
+    """64 channels x some 17 million tokens on both sides of the limit: row 63 of the activations begins 4.3 GB behind row 0.  Against
+    the same factors from a Gram matrix that torch sums in fp64 (4096 partial sums of the same products: relative error some
+    1e-14, the bound 1e-9 on the singular values as above)."""
+    import torch
+    d, r = 64, 4
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X = torch.empty(d, n_tokens, dtype=torch.float32, device="cuda")
+    for i in range(d):
+        X[i].normal_(generator=g)
+        X[i] *= 1.0 + 0.1 * i
+    W = torch.randn(d, d, generator=g, device="cuda") * 0.02
+    W_hat = (W * 16).round() / 16
+    G = torch.zeros(d, d, dtype=torch.float64, device="cuda")
+    for part in X.split(n_tokens // 64 + 1, dim=1):
+        P = part.double()
+        G += P @ P.T.contiguous()
+    L = np.linalg.cholesky(G.cpu().numpy())
+    dW = (W.double() - W_hat.double()).cpu().numpy()
+    U, s, _ = np.linalg.svd(dW @ L)
+    f64 = dict(dtype=torch.float64, device="cuda")
+    B, A, sig = torch.empty(d, r, **f64), torch.empty(r, d, **f64), torch.empty(r, **f64)
+    ws = torch.empty(gpu.factors_workspace_bytes(d, d, r), dtype=torch.uint8, device="cuda")
+    gpu.factors(W, W_hat, X, B, A, sig, n_tokens, d, d, r, 1e-12, ws)
+    assert np.allclose(sig.cpu().numpy(), s[:r], rtol=1e-9, atol=0)
+    want = U[:, :r] @ (U[:, :r].T @ dW)                      # B'A = U' U'^T dW
+    got = (B @ A).cpu().numpy()
+    assert np.linalg.norm(got - want) <= 1e-8 * np.linalg.norm(want)
