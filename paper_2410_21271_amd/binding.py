@@ -229,8 +229,10 @@ def pack_sp24q4(codes, pos, zeros, scales, group):
 # ------------------------------------------------------------------ device entry points (torch tensors as memory)
 # A call of one small linear takes the GPU 5 us, so that what the host does per call shows: pointers go to ctypes as plain
 # integers (None: a null pointer) and the stream comes without the Stream object that torch.cuda.current_stream() builds
-# (one 1024 x 1024 linear, one token, called directly: 9.3 us with c_void_p objects and Stream, 5.6 now).
-_get_device, _raw_stream = _torch._C._cuda_getDevice, _torch._C._cuda_getCurrentRawStream
+# (one 1024 x 1024 linear, one token, called directly: 9.3 us with c_void_p objects and Stream, 5.6 now).  The two functions are
+# private ones of torch and a torch without a GPU backend has neither: the host packers and size queries do without, and a
+# device call then takes the public way.
+_get_device, _raw_stream = (getattr(_torch._C, n, None) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream"))
 
 
 def _dp(t):
@@ -245,6 +247,11 @@ def _stream():
     if not _torch.cuda.is_initialized():
         return _torch.cuda.current_stream().cuda_stream
     return _raw_stream(_get_device())
+
+
+if _get_device is None or _raw_stream is None:
+    def _stream():
+        return _torch.cuda.current_stream().cuda_stream
 
 
 def workspace_init(workspace):

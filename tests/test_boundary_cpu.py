@@ -277,3 +277,27 @@ def test_calibration_tokens_beyond_32_bit_offsets():
     for n in (17_043_000, 17_043_521, 17_043_522, 17_100_000, 2 ** 31 - 1):
         assert eora.debug_factors_near(n) == (4 * (63 * n + 31 + 1) <= 2 ** 32 - 1), n
     assert eora.debug_factors_near(17_043_000) and not eora.debug_factors_near(17_043_522)
+
+
+def test_import_without_torchs_private_stream_functions():
+    """Host packers and size queries need no GPU: they work with a torch that lacks the private functions behind the current
+    stream, and the stream of a device call then comes from torch.cuda.current_stream()."""
+    import subprocess
+    import sys
+    code = """
+import types
+import torch
+for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+    if hasattr(torch._C, name):
+        delattr(torch._C, name)
+import numpy as np
+import paper_2410_21271_amd as eora
+from paper_2410_21271_amd import binding
+assert eora.qweight_bytes(256, 32, 4) == 256 * 32 // 2
+assert eora.pack_factor_f16(np.zeros((16, 32), dtype=np.float16)).size > 0
+torch.cuda.current_stream = lambda: types.SimpleNamespace(cuda_stream=77)
+torch.cuda.is_initialized = lambda: True
+assert binding._stream() == 77
+"""
+    p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert p.returncode == 0, p.stderr[-2000:]
