@@ -61,6 +61,8 @@ def _load():
         "eora_debug_factors_near": (ci, [ci]),
         "eora_debug_last_launch": (ci, [ctypes.c_char_p, sz]),
         "eora_debug_prefill_parts": (ci, [ci, ci, ci, ci, sz]),
+        "eora_debug_prefill_plan": (ci, [ci, ci, ctypes.POINTER(ci), ci, ci, sz, ctypes.POINTER(ci)]),
+        "eora_debug_last_prefill": (ci, [ctypes.c_char_p, sz]),
         "eora_debug_probe": (ci, [ci, vp, sz, vp, vp]),
         "eora_pack_q": (ci, [vp, vp, vp, ci, ci, ci, ci, vp, vp, vp]),
         "eora_pack_factor_f16": (ci, [vp, ci, ci, vp]),
@@ -100,7 +102,7 @@ EXPORTS = ["eora_status_string", "eora_qweight_bytes", "eora_qzeros_bytes", "eor
            "eora_sp24q4_tiles_bytes", "eora_sp24q4_meta_bytes", "eora_pack_sp24q4", "eora_linear_sp24q4", "eora_expand_sp24q4",
            "eora_factors_workspace_bytes", "eora_factors", "eora_linear_q_multi", "eora_pack_factor_q3", "eora_factors_store_f16", "eora_factors_store_q", "eora_linear_sp24_group",
            "eora_debug_last_launch", "eora_debug_probe", "eora_linear_q_static", "eora_debug_set_resident_min_blocks", "eora_debug_set_factors_route",
-           "eora_debug_prefill_parts", "eora_debug_factors_near"]
+           "eora_debug_prefill_parts", "eora_debug_factors_near", "eora_debug_prefill_plan", "eora_debug_last_prefill"]
 
 
 def status_string(status):
@@ -293,6 +295,20 @@ def debug_last_launch():
 def debug_prefill_parts(M, d_in, d_out, r, room):
     """Parts a prompt's GEMM would cut its contraction into with `room` bytes for their outputs."""
     return int(lib.eora_debug_prefill_parts(int(M), int(d_in), int(d_out), int(r), int(room)))
+
+
+def debug_prefill_plan(M, d_in, d_outs, r, workspace_nbytes):
+    """(tokens per workgroup, parts, parts of the down-projection, kernel for few tiles) of a prompt; host only, nothing is enqueued."""
+    rows, plan = (ctypes.c_int * len(d_outs))(*d_outs), (ctypes.c_int * 4)()
+    _check(lib.eora_debug_prefill_plan(int(M), int(d_in), rows, len(d_outs), int(r), int(workspace_nbytes), plan), "debug_prefill_plan")
+    return plan[0], plan[1], plan[2], bool(plan[3])
+
+
+def debug_last_prefill():
+    """Kernel and tokens per workgroup of the most recent prompt's GEMM (a string)."""
+    buf = ctypes.create_string_buffer(160)
+    _check(lib.eora_debug_last_prefill(buf, len(buf)), "debug_last_prefill")
+    return buf.value.decode()
 
 
 def debug_probe(kind, src, nbytes, sink):

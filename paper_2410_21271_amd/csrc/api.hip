@@ -17,6 +17,12 @@ LaunchNote g_last_launch = {nullptr, {0, 0, 0, 0, 0, 0, 0, 0}};
 
 void note_launch(const char* fmt, int a, int b, int c, int d, int e, int f, int g, int h) { g_last_launch = {fmt, {a, b, c, d, e, f, g, h}}; }
 
+namespace {
+LaunchNote g_last_prefill = {nullptr, {0, 0, 0, 0, 0, 0, 0, 0}};
+}  // namespace
+
+void note_prefill(const char* fmt, int tokens) { g_last_prefill = {fmt, {tokens, 0, 0, 0, 0, 0, 0, 0}}; }
+
 }  // namespace eora
 
 namespace {
@@ -259,10 +265,10 @@ int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 // Measured: 333 tokens x 14336 -> 4096, tm = 2 in five parts 58.4 + 5.6 us, tm = 3 in eight 47.7 + 7.4; 333 x 4096 -> 28672, tm = 3
 // 87.1; 8192 x 4096 -> 28672 (the card's power decides, and costs a tenth more each) 1926, 1652, 1466 us.
 // room: bytes for the partial outputs; the parts never need more.  d_out: the members' rows.
-struct PrefillPlan {
+struct PrefillTiles {
     int tm, parts;
 };
-PrefillPlan pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
+PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
 {
     static const float step_us[5] = {0.f, 0.f, 1.05f, 1.25f, 1.5f};
     const int G = d_in / 128;
@@ -272,7 +278,7 @@ PrefillPlan pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
         rows += d_out[m];
         row_tiles += (d_out[m] + 255) / 256;
     }
-    PrefillPlan best{2, 1};
+    PrefillTiles best{2, 1};
     float best_us = 1e30f;
     for (int ks = 1; ks <= 8 && (ks == 1 || ks * 4 <= G + 3); ++ks) {
         const size_t bytes = (size_t)ks * M * rows * sizeof(float);
@@ -290,30 +296,57 @@ PrefillPlan pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     return best;
 }
 
+// What the launches of a prompt do with a workspace of so many bytes (n linears of d_out[..] rows that share x)
+struct PrefillPlan {
+    int tm, parts, t_parts;
+    bool by128;               // tm == 2: the kernel of prefill128.hip
+    size_t own;               // where the fp32 parts begin
+};
+PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t workspace_bytes)
+{
+    PrefillPlan p;
+    // room for partial outputs: what is left behind t, as far as every workspace of the right size has it (the order of the
+    // sums, and with it the bits of t and y, is then the same whatever larger size it has).  t's parts are there first, and
+    // after their sum those of the main GEMM (2048 tokens, rank 256, 14336 -> 4096: two parts of 128 workgroups with 256 tokens
+    // need the bytes of both, 265 -> 238 us).  A workspace that ends with t's own least parts has no room for the others: the
+    // contraction stays whole, as for every call with a workspace of the least size
+    const size_t t_bytes = round256((size_t)M * n * r * 2);
+    p.own = WS_T + t_bytes;
+    const size_t least = prefill_scratch_bytes(M, d_in, r, n) - t_bytes, most = least + PREFILL_SPLIT_BYTES;
+    const size_t left = workspace_bytes > p.own ? workspace_bytes - p.own : 0, room = left < most ? left : most;
+    p.t_parts = r > 0 ? pick_t_parts(M, d_in, r, n, room) : 1;
+    const PrefillTiles t = pick_prefill(M, d_in, r, d_out, n, left > round256(least) ? room : 0);
+    p.tm = t.tm;
+    p.parts = t.parts;
+    // 128 tokens: with (nearly) all compute units busy the card's power decides, and the 16x16x32 MFMAs of prefill.hip win
+    // (2048 tokens x 4096 -> 4096, 256 workgroups: 88.7 us a call against 91.4); with fewer the shorter steps of prefill128.hip
+    size_t wgs = 0;
+    for (int m = 0; m < n; ++m) wgs += (d_out[m] + 255) / 256;
+    wgs *= (size_t)((M + 127) / 128) * p.parts;
+    p.by128 = p.tm == 2 && wgs <= 248;
+    return p;
+}
+
 // validated members that share x, as GEMMs: one launch for every member's t (the members' A side by side), one
 // for every member's y
 int launch_prefill_group(const void* x, const eora_q_member* members, int n, int M, int d_in, int r, int w_bits, int group,
                          int fa, int fe, const int* adapter, int r_per, void* workspace, size_t workspace_bytes, hipStream_t stream)
 {
     _Float16* T = (_Float16*)((char*)workspace + WS_T);           // M x (n * r): member m owns columns m*r ..
-    // room for partial outputs: what is left behind t, as far as every workspace of the right size has it (the order of the
-    // sums, and with it the bits of t and y, is then the same whatever larger size it has).  t's parts are there first, and
-    // after their sum those of the main GEMM (2048 tokens, rank 256, 14336 -> 4096: two parts of 128 workgroups with 256 tokens
-    // need the bytes of both, 265 -> 238 us).  A workspace that ends with t's own least parts has no room for the others: the
-    // contraction stays whole, as for every call with a workspace of the least size
-    const size_t t_bytes = round256((size_t)M * n * r * 2), own = WS_T + t_bytes;
-    const size_t least = prefill_scratch_bytes(M, d_in, r, n) - t_bytes, most = least + PREFILL_SPLIT_BYTES;
-    const size_t left = workspace_bytes > own ? workspace_bytes - own : 0, room = left < most ? left : most;
+    int d_outs[MAX_GROUP] = {0, 0, 0, 0};
+    for (int m = 0; m < n; ++m) d_outs[m] = members[m].d_out;
+    const PrefillPlan plan = plan_prefill(M, d_in, r, d_outs, n, workspace_bytes);
     if (r > 0) {
         PrefillArgs p{};
         p.x = (const _Float16*)x; p.ldx = d_in;
         p.group = 128;
         p.M = M; p.K1 = d_in;
         p.n = n;
-        p.ksplit = pick_t_parts(M, d_in, r, n, room);
-        p.part = (float*)((char*)workspace + own);
+        p.ksplit = plan.t_parts;
+        p.part = (float*)((char*)workspace + plan.own);
         p.ldp = n * r;
-        p.tm = 2;                                                 // (few output tiles)
+        p.tm = 2;
+        p.by128 = true;                                           // (few output tiles)
         for (int m = 0; m < n; ++m) {
             p.w[m] = members[m].A;
             p.w_scales[m] = (const _Float16*)members[m].A_scales;
@@ -332,12 +365,10 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
     p.M = M; p.K1 = d_in; p.K2 = r;
     p.ldx2 = n * r;
     p.n = n;
-    int d_outs[MAX_GROUP] = {0, 0, 0, 0};
-    for (int m = 0; m < n; ++m) d_outs[m] = members[m].d_out;
-    const PrefillPlan plan = pick_prefill(M, d_in, r, d_outs, n, left > round256(least) ? room : 0);
     p.ksplit = plan.parts;
     p.tm = plan.tm;
-    p.part = (float*)((char*)workspace + own);
+    p.by128 = plan.by128;
+    p.part = (float*)((char*)workspace + plan.own);
     for (int m = 0; m < n; ++m) {
         p.pcol[m] = p.ldp;
         p.ldp += members[m].d_out;
@@ -493,10 +524,26 @@ int eora_debug_prefill_parts(int M, int d_in, int d_out, int r, size_t room)
     return pick_prefill(M, d_in, r, &d_out, 1, room).parts;
 }
 
-int eora_debug_last_launch(char* out, size_t capacity)
+int eora_debug_prefill_plan(int M, int d_in, const int* d_out, int n_members, int r, size_t workspace_bytes, int* plan)
+{
+    if (!d_out || !plan) return EORA_ERR_NULL;
+    if (n_members < 1 || n_members > MAX_GROUP) return EORA_ERR_SHAPE;
+    for (int m = 0; m < n_members; ++m) {
+        const int rc = check_backbone_shape(M, d_in, d_out[m], r);
+        if (rc != EORA_OK) return rc;
+    }
+    if (M < PREFILL_MIN_TOKENS || r % 128) return EORA_ERR_SHAPE;
+    const PrefillPlan p = plan_prefill(M, d_in, r, d_out, n_members, workspace_bytes);
+    plan[0] = 64 * p.tm;
+    plan[1] = p.parts;
+    plan[2] = p.t_parts;
+    plan[3] = p.by128;
+    return EORA_OK;
+}
+
+static int write_note(const LaunchNote& n, char* out, size_t capacity)
 {
     if (!out || capacity == 0) return EORA_ERR_NULL;
-    const LaunchNote n = g_last_launch;
     if (!n.fmt) {
         out[0] = 0;
         return EORA_OK;
@@ -504,6 +551,10 @@ int eora_debug_last_launch(char* out, size_t capacity)
     snprintf(out, capacity, n.fmt, n.v[0], n.v[1], n.v[2], n.v[3], n.v[4], n.v[5], n.v[6], n.v[7]);
     return EORA_OK;
 }
+
+int eora_debug_last_launch(char* out, size_t capacity) { return write_note(g_last_launch, out, capacity); }
+
+int eora_debug_last_prefill(char* out, size_t capacity) { return write_note(g_last_prefill, out, capacity); }
 
 // every check of one quantised layer; nothing is enqueued
 static int validate_linear_q(const void* x, const eora_q_member& e, int M, int d_in, int r, int w_bits, int group,

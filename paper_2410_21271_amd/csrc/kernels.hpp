@@ -32,6 +32,7 @@ constexpr int MAX_KCN = 8;                      // k-ranges of the down-projecti
 // back through eora_debug_last_launch() (tests assert that a shape reaches the instantiation it is meant to
 // cover).  `fmt` is a printf format for up to eight ints and must be a string literal.  Not synchronised.
 void note_launch(const char* fmt, int a = 0, int b = 0, int c = 0, int d = 0, int e = 0, int f = 0, int g = 0, int h = 0);
+void note_prefill(const char* fmt, int tokens);      // which of the kernels for many tokens, and its tokens per workgroup
 
 // General kernel of the quantised backbone (wideq.hip): 5 and more tokens, and the shapes the decode kernel does not take.
 // x is shared through LDS by the wavefronts of a workgroup.  Up to four linears that read the same x in one launch.
@@ -178,6 +179,7 @@ struct PrefillArgs {
     float* part;              //      writes its fp32 tile to part[ks][M][ldp] (columns pcol ..) instead of y
     int ldp;
     int tm;                   // 2, 3 or 4: 64 tm tokens x 256 rows per workgroup
+    bool by128;               // (tm == 2) the kernel of prefill128.hip
     int n;                    // members
     const void* w[MAX_GROUP];            // first segment's weight tiles (N rows, K1 columns)
     const _Float16* w_scales[MAX_GROUP];

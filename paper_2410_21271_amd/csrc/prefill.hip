@@ -470,6 +470,7 @@ static hipError_t launch_pf_tile(const PrefillArgs& a, hipStream_t stream)
     for (int m = 0; m < a.n; ++m) ntn += (a.N[m] + PF_BN - 1) / PF_BN;
     const int ntm = (a.M + pf_bm(TM) - 1) / pf_bm(TM);
     note_launch("prefill FM=%d EXT=%d ksplit=%d n=%d FE=%d", FM, (int)(FE2 != S_NONE), a.ksplit, a.n, FE2);
+    note_prefill("prefill tokens=%d", pf_bm(TM));
     hipLaunchKernelGGL(kern, dim3(ntn * ntm * a.ksplit), dim3(PF_NT), pf_lds(TM), stream, a);
     return hipGetLastError();
 }
@@ -554,13 +555,7 @@ static hipError_t launch_pf_ext(const PrefillArgs& a, int fe2, hipStream_t strea
 // fe2: S_NONE, or the format of the second segment's tiles
 hipError_t launch_prefill(const PrefillArgs& a, int fm, int fe2, hipStream_t stream)
 {
-    // 128 tokens: with (nearly) all compute units busy the card's power decides, and the 16x16x32 MFMAs of this kernel win
-    // (2048 tokens x 4096 -> 4096, 256 workgroups: 88.7 us a call against 91.4); with fewer the shorter steps of the other one
-    int wgs = 0;
-    for (int m = 0; m < a.n; ++m) wgs += (a.N[m] + PF_BN - 1) / PF_BN;
-    wgs *= (a.M + 127) / 128 * a.ksplit;
-    const bool backbone = fm == S_Q4 || fm == S_Q3 || fm == S_Q2;
-    if (a.tm == 2 && !(backbone && wgs > 248)) return launch_prefill128(a, fm, fe2, stream);
+    if (a.by128) return launch_prefill128(a, fm, fe2, stream);
     switch (fm) {
         case S_Q4: return launch_pf_ext<S_Q4>(a, fe2, stream);
         case S_Q3: return launch_pf_ext<S_Q3>(a, fe2, stream);

@@ -381,6 +381,7 @@ static hipError_t launch_p1(const PrefillArgs& a, hipStream_t stream)
     for (int m = 0; m < a.n; ++m) ntn += (a.N[m] + P1_BN - 1) / P1_BN;
     const int ntm = (a.M + P1_BM - 1) / P1_BM;
     note_launch("prefill FM=%d EXT=%d ksplit=%d n=%d FE=%d", FM, (int)EXT, a.ksplit, a.n, FE2);
+    note_prefill("prefill128 tokens=%d", P1_BM);
     hipLaunchKernelGGL(kern, dim3(ntn * ntm * a.ksplit), dim3(P1_NT), P1_LDS, stream, a);
     return hipGetLastError();
 }
@@ -399,6 +400,7 @@ static hipError_t launch_p1_ext(const PrefillArgs& a, int fe2, hipStream_t strea
 
 hipError_t launch_prefill128(const PrefillArgs& a, int fm, int fe2, hipStream_t stream)
 {
+    if (a.tm != 2) return hipErrorInvalidValue;
     switch (fm) {
         case S_Q4: return launch_p1_ext<S_Q4>(a, fe2, stream);
         case S_Q3: return launch_p1_ext<S_Q3>(a, fe2, stream);
