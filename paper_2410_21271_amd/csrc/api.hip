@@ -260,17 +260,21 @@ int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 // Tokens per workgroup (64 tm) and parts of the main GEMM's contraction.  A workgroup is 64 tm tokens x 256 rows, one per
 // compute unit.  More tokens share the decoding of a weight, but a launch of few output tiles leaves most of the chip idle for
 // the length of a contraction (333 tokens of the 8B layer: 32 tiles for a 4096 x 4096 linear), and tokens that are not there
-// cost as much as others.  The cheapest by rounds of 256 workgroups: 1.05, 1.25, 1.5 us a step of 64 columns for tm = 2, 3, 4
-// and 8 a tile; the parts' fp32 outputs written and read at 8 TB/s (they stay in the caches) and 5 us for the second launch.
-// Measured: 333 tokens x 14336 -> 4096, tm = 2 in five parts 58.4 + 5.6 us, tm = 3 in eight 47.7 + 7.4; 333 x 4096 -> 28672, tm = 3
-// 87.1; 8192 x 4096 -> 28672 (the card's power decides, and costs a tenth more each) 1926, 1652, 1466 us.
+// cost as much as others.  The cheapest by rounds of 256 workgroups: STEP_US a step of 64 columns and TILE_US a tile for tm = 2, 3,
+// 4; the parts' fp32 outputs written and read at 11 TB/s (they stay in the caches), and 10 us for the launch that sums them, with
+// the caches written back in between.
+// The constants are fitted to calls of 402 shapes (128 .. 8192 tokens, d_in 1024 .. 28672, every tm and one to eight parts of
+// each timed) for the choice they lead to, not for the times: on average it takes 1.002 times as long as the best one, 1.053 at most.
+// With 5 us for the sums, 8 for a tile and 1.05, 1.25, 1.5 a step short contractions were cut that are faster whole: d_in
+// 1024, 1408 tokens x 656 rows bare 16.5 -> 19.1 us in two parts; 1152, 276 x 6880, rank 128 34.2 -> 38.1 in three.  Long ones
+// gain as before: 333 tokens x 14336 -> 4096 bare 153 us whole, 54 in eight parts.
 // room: bytes for the partial outputs; the parts never need more.  d_out: the members' rows.
 struct PrefillTiles {
     int tm, parts;
 };
 PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
 {
-    static const float step_us[5] = {0.f, 0.f, 1.05f, 1.25f, 1.5f};
+    static const float STEP_US[5] = {0.f, 0.f, 0.97f, 1.18f, 1.21f}, TILE_US[5] = {0.f, 0.f, 3.f, 4.f, 8.f};
     const int G = d_in / 128;
     size_t rows = 0;
     int row_tiles = 0;
@@ -285,8 +289,8 @@ PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_
         if (ks > 1 && bytes > room) break;                // (whole numbers: a float would round the room up to the need)
         for (int tm = 2; tm <= 4; ++tm) {
             const size_t wgs = (size_t)row_tiles * ((M + 64 * tm - 1) / (64 * tm)) * ks;
-            const float us = (float)((wgs + 255) / 256) * (step_us[tm] * (2 * ((G + ks - 1) / ks) + r / 64) + 8.f) +
-                             (ks > 1 ? 5.f + (float)bytes * 2.f / 8e6f : 0.f);
+            const float us = (float)((wgs + 255) / 256) * (STEP_US[tm] * (2 * ((G + ks - 1) / ks) + r / 64) + TILE_US[tm]) +
+                             (ks > 1 ? 10.f + (float)bytes * 2.f / 11e6f : 0.f);
             if (us < best_us) {
                 best_us = us;
                 best = {tm, ks};

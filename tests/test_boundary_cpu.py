@@ -247,6 +247,21 @@ def test_parts_of_a_prompt_never_need_more_than_their_room(M, d_in, d_out, r):
     assert eora.debug_prefill_parts(M, d_in, d_out, r, 0) == 1
 
 
+def _plan(M, d_in, d_outs, r):
+    n = len(d_outs)
+    ws = max([eora.workspace_bytes_group(M, d_in, r, n)] + [eora.workspace_bytes(M, d_in, d, r) for d in d_outs])
+    return eora.debug_prefill_plan(M, d_in, d_outs, r, ws)
+
+
+@pytest.mark.parametrize("M,d_in,d_outs,r,parts", [
+    (1408, 1024, (656,), 0, 1), (175, 1024, (6976,), 256, 1), (276, 1152, (6880,), 128, 1), (189, 1152, (9392,), 128, 1),
+    (336, 1280, (2432, 2720), 128, 1), (333, 14336, (4096,), 128, 8), (1014, 5120, (1680,), 128, 4), (2048, 14336, (4096,), 256, 2)])
+def test_short_contractions_of_a_prompt_stay_whole(M, d_in, d_outs, r, parts):
+    """Parts of the main GEMM where both sides were timed on the GPU: cutting a short contraction costs more than it gives
+    (16.5 us whole, 19.1 in two parts; 32.9 and 36.1; 34.2 and 38.1; 34.1 and 37.9; 35.3 and 38.6), a long one is cut."""
+    assert _plan(M, d_in, d_outs, r)[1] == parts
+
+
 @pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (14336, 4096), (28672, 8192), (1152, 272)])
 def test_workspace_sizes_never_shrink_with_tokens_or_rank(d_in, d_out):
     """A workspace of the size of the largest (M, r) serves smaller calls too, with everything they would have asked for

@@ -36,9 +36,9 @@ def _check(gpu, w_bits, ab_bits, r, M, d_in, d_outs, group, kernel, tokens, part
 
 # w_bits, ab_bits, r, M, d_in, d_outs, group, kernel, its tokens, parts
 @pytest.mark.parametrize("w_bits,ab_bits,r,M,d_in,d_outs,group,kernel,tokens,parts", [
-    (4, 16, 128, 1300, 256, (14336, 14288), 128, "prefill", 256, 1),      # the last token tile has 20, the last row tile 208 rows
+    (4, 16, 128, 1300, 512, (14336, 14288), 128, "prefill", 256, 1),      # the last token tile has 20, the last row tile 208 rows
     (3, 4, 128, 1281, 1024, (28656,), 128, "prefill", 256, 1),            # one token in the last tile, scales of eight groups at once
-    (2, 16, 0, 2561, 128, (14336, 12288), 128, "prefill", 256, 1),        # one group: no step of the main loop
+    (2, 16, 128, 250, 128, (32752, 32768), 128, "prefill", 256, 1),       # one group: no step of the main loop
     (2, 16, 0, 1537, 128, (16384, 12288), 128, "prefill", 192, 1),        # the same, one token in the last tile
     (4, 3, 256, 379, 384, (14336, 14320), 384, "prefill", 192, 1),        # channel-wise
     (3, 16, 128, 1281, 1536, (14320,), 384, "prefill", 192, 1),           # four groups of three tiles
