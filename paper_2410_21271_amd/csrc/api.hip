@@ -276,6 +276,11 @@ int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 struct PrefillTiles {
     int tm, parts;
 };
+
+// prefill.hip addresses the rows of x in a tile with 32-bit byte offsets from its first one (prefill128.hip with 64 bits): some
+// eight million columns with 256 tokens
+bool near_rows(int tm, int d_in) { return ((size_t)(64 * tm - 1) * d_in + 64) * 2 + 4096 <= 0xFFFFFFFFull; }
+
 PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
 {
     static const float STEP_US[5] = {0.f, 0.f, 0.97f, 1.18f, 1.21f}, TILE_US[5] = {0.f, 0.f, 3.f, 4.f, 8.f};
@@ -291,7 +296,7 @@ PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_
     for (int ks = 1; ks <= 8 && (ks == 1 || ks * 4 <= G + 3); ++ks) {
         const size_t bytes = (size_t)ks * M * rows * sizeof(float);
         if (ks > 1 && bytes > room) break;                // (whole numbers: a float would round the room up to the need)
-        for (int tm = 2; tm <= 4; ++tm) {
+        for (int tm = 2; tm <= 4 && (tm == 2 || near_rows(tm, d_in)); ++tm) {
             const size_t wgs = (size_t)row_tiles * ((M + 64 * tm - 1) / (64 * tm)) * ks;
             const float us = (float)((wgs + 255) / 256) * (STEP_US[tm] * (2 * ((G + ks - 1) / ks) + r / 64) + TILE_US[tm]) +
                              (ks > 1 ? 10.f + (float)bytes * 2.f / 11e6f : 0.f);
@@ -331,7 +336,7 @@ PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     size_t wgs = 0;
     for (int m = 0; m < n; ++m) wgs += (d_out[m] + 255) / 256;
     wgs *= (size_t)((M + 127) / 128) * p.parts;
-    p.by128 = p.tm == 2 && wgs <= 248;
+    p.by128 = p.tm == 2 && (wgs <= 248 || !near_rows(2, d_in));
     return p;
 }
 

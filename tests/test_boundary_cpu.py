@@ -272,6 +272,15 @@ def test_parts_of_a_prompts_down_projection(M, d_in, d_outs, r, parts):
     assert _plan(M, d_in, d_outs, r)[2] == parts
 
 
+@pytest.mark.parametrize("M,d_in,d_out", [(333, 1 << 20, 4096), (400, 8421376, 4096), (512, 8421504, 4096), (1000, 11 << 20, 8192), (2048, 1 << 24, 4096),
+                                          (2048, 17 << 20, 4096), (512, 1 << 25, 4096), (2048, 1 << 27, 4096)])
+def test_rows_of_x_in_a_tile_stay_within_32_bit_offsets(M, d_in, d_out):
+    """The kernel with 32-bit offsets takes a tile only if its last row's last byte has one (and row times columns is a whole
+    number of 31 bits); beyond, 128 tokens on the kernel that indexes with 64 bits."""
+    tokens, _, _, by128 = eora.debug_prefill_plan(M, d_in, [d_out], 0, 1 << 62)
+    assert by128 or ((tokens - 1) * d_in < 2 ** 31 and (tokens - 1) * d_in * 2 + 128 + 3072 < 2 ** 32), (tokens, by128)
+
+
 @pytest.mark.parametrize("d_in,d_out", [(4096, 4096), (14336, 4096), (28672, 8192), (1152, 272)])
 def test_workspace_sizes_never_shrink_with_tokens_or_rank(d_in, d_out):
     """A workspace of the size of the largest (M, r) serves smaller calls too, with everything they would have asked for
