@@ -133,7 +133,6 @@ __device__ __forceinline__ void place_w(WSeg& a, int rb, int lane)
     else a.tile_off = (uint32_t)(rb * (a.K / 128) * 64 + 16 * q + n) * (4u * Fmt<FMT>::WORDS);
     a.scale_off = (uint32_t)(rb * 16 + n) * a.ng * 2u;
     a.zero_off = (uint32_t)(rb * 16 + n) * ((a.ng + 7) / 8) * 4u;
-    a.by8 = a.gdiv == 1 && a.ng % 8 == 0;
 }
 
 // step s: columns 64 s .. 64 s + 63 of the segment
@@ -169,20 +168,6 @@ __device__ __forceinline__ void load_scale(WScale& r, const WSeg& a, int s)
 // whether step s is the first that the values loaded before it do not cover
 template <int FMT>
 __device__ __forceinline__ bool scale_due(const WSeg& a, int s) { return FMT != S_F16 && (s & (a.by8 ? 15 : 1)) == 0; }
-
-template <int FMT>
-__device__ __forceinline__ void pick_scale(const WScale& r, const WSeg& a, int s, uint32_t& sraw, uint32_t& z)
-{
-    sraw = 0;
-    z = FMT == S_Q3S128 ? 4u : 8u;
-    if constexpr (FMT != S_F16) {
-        const uint32_t g = s >> 1, grp = a.by8 || a.gdiv == 1 ? g : __umulhi(g, a.gmagic);
-        const uint32_t s0 = r.s[0], s1 = r.s[1], s2 = r.s[2], s3 = r.s[3];
-        const uint32_t o = a.by8 ? g & 7 : 0, lo = o & 2 ? s1 : s0, hi = o & 2 ? s3 : s2;
-        sraw = (o & 4 ? hi : lo) >> (16 * (o & 1));
-        if constexpr (Fmt<FMT>::ASYM) z = (r.z >> (4 * (grp & 7))) & 0xFu;
-    }
-}
 
 // fragment T (of four) of the lane's chunks into the slab; the group's scale is folded in (one fp16 rounding per weight).
 // wl: the lane's first chunk in the slab
@@ -230,6 +215,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
     w1.gdiv = ga.group / 128;
     w1.gmagic = w1.gdiv > 1 ? (uint32_t)((0x100000000ull + w1.gdiv - 1) / w1.gdiv) : 0u;
     w1.ng = K1 / 128 / (int)w1.gdiv;
+    w1.by8 = w1.gdiv == 1 && w1.ng % 8 == 0;
     w1.tiles = pf_rsrc((const uint32_t*)ga.w[mem] + (size_t)R0 * (K1 / Fmt<FM>::KT) * 64 * Fmt<FM>::WORDS);
     w1.scales = pf_rsrc((const uint16_t*)ga.w_scales[mem] + (size_t)R0 * 16 * w1.ng);
     w1.zeros = pf_rsrc(ga.w_zeros[mem] + (size_t)R0 * 16 * ((w1.ng + 7) / 8));
@@ -240,6 +226,7 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
         w2.gdiv = 1;
         w2.gmagic = 0;
         w2.ng = K2 / 128;
+        w2.by8 = false;                                           // (a rank has four groups at most)
         w2.tiles = pf_rsrc((const uint32_t*)ga.w2[mem] + (size_t)R0 * (K2 / Fmt<FX>::KT) * 64 * Fmt<FX>::WORDS);
         w2.scales = pf_rsrc((const uint16_t*)ga.w2_scales[mem] + (size_t)R0 * 16 * w2.ng);
         place_w<FX>(w2, rb, lane);
@@ -364,12 +351,11 @@ __global__ __launch_bounds__(PF_NT, 2) void prefill_kernel(PrefillArgs ga)
         if constexpr (EXT && !MAIN) {
             if (ext1) {                                           // (a handful of steps: all at once)
                 const uint32_t wx = W0 + wave * 32 * 128 + pf_slot(row32, FX == S_F16 ? q : 4 * q) + NXT * PF_WS;
-                uint32_t sraw2, z2;
-                pick_scale<FX>(se2, w2, s + 1 - H1, sraw2, z2);
-                store_w<FX, 0>(we, sraw2, z2, wx);
-                store_w<FX, 1>(we, sraw2, z2, wx);
-                store_w<FX, 2>(we, sraw2, z2, wx);
-                store_w<FX, 3>(we, sraw2, z2, wx);
+                constexpr uint32_t Z2 = FX == S_Q3S128 ? 4u : 8u;             // (symmetric formats, one group in two steps)
+                store_w<FX, 0>(we, se2.s[0], Z2, wx);
+                store_w<FX, 1>(we, se2.s[0], Z2, wx);
+                store_w<FX, 2>(we, se2.s[0], Z2, wx);
+                store_w<FX, 3>(we, se2.s[0], Z2, wx);
             }
             if (s + 2 == se && GT > se) {                         // from here on x is t
                 place_x(ga.ldx2);

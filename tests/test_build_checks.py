@@ -38,3 +38,11 @@ def test_every_source_is_listed_once():
     on_disk = sorted(f for f in os.listdir(b.CSRC) if f.endswith((".hip", ".cpp")))
     assert sorted(b.SOURCES) == on_disk
     assert set(b.NO_SPILL) <= set(b.SOURCES)
+
+
+def test_spill_in_the_gemm_for_many_tokens_fails_the_build():
+    b = _build_module()
+    text = REMARKS.replace("resident_kernelILi1ELi5ELi5ELi8EEEvNS_10StreamArgsE", "prefill_kernelILi1ELi7ELi4EEEvNS_11PrefillArgsE")
+    b._check_resources("prefill.hip", text % (0, 64))
+    with pytest.raises(RuntimeError):
+        b._check_resources("prefill.hip", text % (8, 0))
