@@ -331,8 +331,11 @@ PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     const PrefillTiles t = pick_prefill(M, d_in, r, d_out, n, left > round256(least) ? room : 0);
     p.tm = t.tm;
     p.parts = t.parts;
-    // 128 tokens: with (nearly) all compute units busy the card's power decides, and the 16x16x32 MFMAs of prefill.hip win
-    // (2048 tokens x 4096 -> 4096, 256 workgroups: 88.7 us a call against 91.4); with fewer the shorter steps of prefill128.hip
+    // 128 tokens: on a partly filled chip the shorter steps of prefill128.hip win, with (nearly) all compute units busy the card's
+    // power decides, and the 16x16x32 MFMAs of prefill.hip win.  Time of a call on prefill.hip over that on prefill128.hip, calls of
+    // 402 shapes: up to 128 workgroups 1.06, 129 .. 192 1.03, 193 .. 224 1.01, 225 .. 248 0.994, 249 .. 256 0.983, 257 .. 384 1.004,
+    // 385 .. 448 0.990, 449 .. 512 0.978, more 1.004.  Where 128 tokens are the cheapest tile, lines by how full the rounds are gain 0.1 %.
+    // (pick_prefill reckons with one length of a step for both.)
     size_t wgs = 0;
     for (int m = 0; m < n; ++m) wgs += (d_out[m] + 255) / 256;
     wgs *= (size_t)((M + 127) / 128) * p.parts;

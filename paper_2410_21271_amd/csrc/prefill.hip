@@ -22,8 +22,10 @@
 //     of the group: one rounding, relative error <= 2^-11 per weight) and writes them to LDS as four 16-byte chunks, between
 //     the MFMAs of the step before; the words are requested two steps ahead.
 //   - x goes from memory to LDS without passing registers, one step ahead (through registers and ds_write: 1600 us).
-//   - Both slabs are rows of 64 columns with the 16-byte chunks of a row XOR-ed by half the row's number: reads and writes
-//     of 16 bytes per lane are served in groups of 16 lanes {0-3, 12-15, 20-23, 24-27}, ..., and none has two lanes on a bank.
+//   - Both slabs are rows of 64 columns with the 16-byte chunks of a row XOR-ed by half the row's number: taking it that
+//     accesses of 16 bytes per lane are served in groups of 16 lanes {0-3, 12-15, 20-23, 24-27}, ..., none has two lanes on a
+//     bank.  The counters do not bear that out whole: 21 % of the LDS cycles are conflicts (2048 tokens, 256 a tile), of
+//     which accesses is not known.
 //   - A step has one barrier.  The last quarter of its MFMAs is carried out behind it, under the first LDS reads of the next.
 //   - Requests for x are spread over the step (all at once, every wavefront waits for 350 cycles to get rid of them: 1572 us
 //     instead of 1542), and a wavefront's priority falls as it gets through the step: left to age, wavefronts 0..3 run ahead

@@ -2,7 +2,8 @@
 // compute units idle, and for t = x.A^T.  On a partly filled chip the length of a step decides: with a barrier only every 128
 // columns and weights that go from memory to the registers of the wavefront that needs them, 64 columns take 0.97 us here and
 // 1.12 in prefill.hip with 128 tokens (1500 tokens x 14336 -> 4096, 192 workgroups: 224 us against 260).  With (nearly) all
-// compute units busy the card's power decides, and prefill.hip wins (2048 tokens x 4096 -> 4096: 88.7 us a call against 91.4).
+// compute units busy the card's power decides, and prefill.hip wins (2048 tokens x 4096 -> 4096: 88.7 us a call against 91.4;
+// the line between them: plan_prefill).
 //
 // Workgroup: 8 wavefronts, tile = 128 tokens x 256 output rows, contraction in steps of 128 (one
 // quantisation group); each wavefront owns all 128 tokens x 32 rows = 4 accumulator blocks of
@@ -55,13 +56,13 @@ struct P1View {
 };
 
 constexpr int P1_BM = 128, P1_BN = 256;
-constexpr int P1_NW = 8, P1_NT = P1_NW * 64;         // wavefronts: 2 (tokens) x 4 (rows)
+constexpr int P1_NW = 8, P1_NT = P1_NW * 64;         // wavefronts, side by side along the rows: 128 tokens x 32 rows each
 constexpr int P1_XS = 32 * 1024;                      // one x slab: 4 token blocks x 8 slices x 1 KiB
 constexpr int P1_LDS = 2 * P1_XS;                     // the two x slabs; the epilogue's staging tiles (40 KiB) reuse them
 
 __device__ __forceinline__ f16v mfma32(h8 a, h8 b, f16v c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
 
-// weights of one 128-wide step for the wavefront's two pairs of row blocks, exactly as loaded: nothing
+// weights of one 128-wide step for the wavefront's pair of row blocks, exactly as loaded: nothing
 // here is touched before decode_wpre(), a whole step later (any arithmetic on a loaded value at load
 // time would make the wavefront wait for the request it has just issued)
 template <int FMT>
@@ -126,7 +127,7 @@ __device__ __forceinline__ void load_b_frags(h8 (&bf)[8], const void* __restrict
     for (int f = 0; f < 8; ++f) bf[f] = __builtin_bit_cast(h8, p[(f >> 1) * 64 + 16 * (2 * (f & 1) + kg)]);
 }
 
-// x slab of one step: thread tid owns the 16-byte chunks c = tid + 256*i, i = 0..7; chunk c is token row
+// x slab of one step: thread tid owns the 16-byte chunks c = tid + 512*i, i = 0..3; chunk c is token row
 // c / 16 of the tile and columns 8*(c % 16) .. +7 of the step (coalesced: 256 bytes per row).
 constexpr int P1_XC = 2048 / P1_NT;                   // 16-byte chunks of the slab per thread
 __device__ __forceinline__ void load_x(u4 (&v)[P1_XC], const _Float16* __restrict__ act, int ld, int M, int m0, int col0, int tid)
@@ -347,8 +348,7 @@ __global__ __launch_bounds__(P1_NT, 2) void prefill128_kernel(PrefillArgs ga)
         return;
     }
     // ---- epilogue: fp32 -> fp16, transpose through LDS, 128-byte row stores ----------------------------
-    // (wavefront-private staging tiles of 64 tokens, two passes: 40 KiB, so that the kernel's LDS stays at the
-    // two x slabs and two workgroups fit a compute unit)
+    // (wavefront-private staging tiles of 64 tokens, two passes: 40 KiB over the two x slabs)
     constexpr int TS = 40;                                        // halves per token row in the staging tile (32 + pad)
     _Float16* tile = (_Float16*)eora_smem + wave * 64 * TS;
 #pragma unroll
