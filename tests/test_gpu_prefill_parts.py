@@ -100,3 +100,14 @@ def test_workspace_of_a_long_prompt_serves_short_ones_alike(gpu):
         assert "parts=" in gpu.debug_last_launch(), gpu.debug_last_launch()
         for y, q in zip(ys, w):
             _check(y, q.oracle_y(x=w[0].x))
+
+
+@pytest.mark.parametrize("groups", [1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 17, 18, 33])
+def test_parts_of_the_down_projection_add_up(gpu, groups):
+    """The sum of t's parts takes three or eight of them at a time: every remainder, with one part per quantisation group."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q
+    c = QCase(9990 + groups, 128 * groups, 16, 130, 128, 4, packer=gpu)
+    ws = gpu.new_workspace(130, 128 * groups, 16, 128)
+    assert gpu.debug_prefill_plan(130, 128 * groups, [16], 128, ws.numel())[2] == groups
+    _check(run_linear_q(c, ws=ws), c.oracle_y())
