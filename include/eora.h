@@ -153,8 +153,9 @@ int eora_debug_last_launch(char* out, size_t capacity);
  * (each part needs 4 * M * d_out; one linear, M >= 128; nothing is enqueued), or a negative status. */
 int eora_debug_prefill_parts(int M, int d_in, int d_out, int r, size_t room);
 /* HOST, test hook: what a prompt's launches do for n_members linears of d_out[..] rows that share x, with a workspace of so many
- * bytes (M >= 128, r a multiple of 128; nothing is enqueued).  plan: four integers, the tokens per workgroup (128, 192 or 256),
- * the parts of the contraction, those of the down-projection's, and 1 if 128 tokens take the kernel for launches of few tiles. */
+ * bytes (M >= 128, r a multiple of 128; nothing is enqueued).  plan: five integers, the tokens per workgroup (128, 192 or 256),
+ * the parts of the contraction, those of the down-projection's, 1 if 128 tokens take the kernel for launches of few tiles, and 1 if
+ * the parts of the contraction take the place of those of the down-projection for want of room. */
 int eora_debug_prefill_plan(int M, int d_in, const int* d_out, int n_members, int r, size_t workspace_bytes, int* plan);
 /* HOST, test hook: like eora_debug_last_launch(), the kernel and the tokens per workgroup of the most recent prompt's GEMM:
  * "prefill tokens=256", or "prefill128 tokens=128" for the kernel for launches of few tiles. */

@@ -298,10 +298,11 @@ def debug_prefill_parts(M, d_in, d_out, r, room):
 
 
 def debug_prefill_plan(M, d_in, d_outs, r, workspace_nbytes):
-    """(tokens per workgroup, parts, parts of the down-projection, kernel for few tiles) of a prompt; host only, nothing is enqueued."""
-    rows, plan = (ctypes.c_int * len(d_outs))(*d_outs), (ctypes.c_int * 4)()
+    """(tokens per workgroup, parts, parts of the down-projection, kernel for few tiles, one set of parts in the other's place) of a
+    prompt; host only, nothing is enqueued."""
+    rows, plan = (ctypes.c_int * len(d_outs))(*d_outs), (ctypes.c_int * 5)()
     _check(lib.eora_debug_prefill_plan(int(M), int(d_in), rows, len(d_outs), int(r), int(workspace_nbytes), plan), "debug_prefill_plan")
-    return plan[0], plan[1], plan[2], bool(plan[3])
+    return plan[0], plan[1], plan[2], bool(plan[3]), bool(plan[4])
 
 
 def debug_last_prefill():

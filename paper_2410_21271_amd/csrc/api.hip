@@ -313,7 +313,7 @@ PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_
 struct PrefillPlan {
     int tm, parts, t_parts;
     bool by128;               // tm == 2: the kernel of prefill128.hip
-    size_t own;               // where the fp32 parts begin
+    size_t own, main_at;      // where the fp32 parts of t and of the main GEMM begin
 };
 PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t workspace_bytes)
 {
@@ -331,6 +331,13 @@ PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     const PrefillTiles t = pick_prefill(M, d_in, r, d_out, n, left > round256(least) ? room : 0);
     p.tm = t.tm;
     p.parts = t.parts;
+    // The main GEMM's parts go behind t's where the workspace has the bytes of both, else in their place: written over lines that the
+    // other XCDs' caches have just read, they take longer (427 tokens x 2048 -> 752 + 512, rank 256: 37.7 us a call in t's place, 34.8 behind)
+    size_t rows = 0;
+    for (int m = 0; m < n; ++m) rows += d_out[m];
+    const size_t t_parts_bytes = p.t_parts > 1 ? round256((size_t)p.t_parts * M * n * r * sizeof(float)) : 0;
+    const size_t main_bytes = p.parts > 1 ? (size_t)p.parts * M * rows * sizeof(float) : 0;
+    p.main_at = p.own + (t_parts_bytes + main_bytes <= left ? t_parts_bytes : 0);
     // 128 tokens: on a partly filled chip the shorter steps of prefill128.hip win, with (nearly) all compute units busy the card's
     // power decides, and the 16x16x32 MFMAs of prefill.hip win.  Time of a call on prefill.hip over that on prefill128.hip, calls of
     // 402 shapes: up to 128 workgroups 1.06, 129 .. 192 1.03, 193 .. 224 1.01, 225 .. 248 0.994, 249 .. 256 0.983, 257 .. 384 1.004,
@@ -384,7 +391,7 @@ int launch_prefill_group(const void* x, const eora_q_member* members, int n, int
     p.ksplit = plan.parts;
     p.tm = plan.tm;
     p.by128 = plan.by128;
-    p.part = (float*)((char*)workspace + plan.own);
+    p.part = (float*)((char*)workspace + plan.main_at);
     for (int m = 0; m < n; ++m) {
         p.pcol[m] = p.ldp;
         p.ldp += members[m].d_out;
@@ -554,6 +561,7 @@ int eora_debug_prefill_plan(int M, int d_in, const int* d_out, int n_members, in
     plan[1] = p.parts;
     plan[2] = p.t_parts;
     plan[3] = p.by128;
+    plan[4] = p.main_at == p.own && p.parts > 1 && p.t_parts > 1;
     return EORA_OK;
 }
 
