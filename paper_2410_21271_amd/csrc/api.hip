@@ -266,9 +266,11 @@ int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 // the length of a contraction (333 tokens of the 8B layer: 32 tiles for a 4096 x 4096 linear), and tokens that are not there
 // cost as much as others.  The cheapest by rounds of 256 workgroups: STEP_US a step of 64 columns and TILE_US a tile for tm = 2, 3,
 // 4; the parts' fp32 outputs written and read at 11 TB/s (they stay in the caches), and 10 us for the launch that sums them, with
-// the caches written back in between.
+// the caches written back in between; 7 where a part's outputs are 2 MiB or less (192 tokens x 1024 -> 816, rank 256: 32.0 us
+// whole, 30.8 in two parts).  The line is drawn for one part, not for all of them: else a part would be saved to stay below it (378 x
+// 1280 -> 1008, rank 128: 31.3 us in three parts, 32.3 in two).
 // The constants are fitted to calls of 402 shapes (128 .. 8192 tokens, d_in 1024 .. 28672, every tm and one to eight parts of
-// each timed) for the choice they lead to, not for the times: on average it takes 1.002 times as long as the best one, 1.053 at most.
+// each timed) for the choice they lead to, not for the times: on average it takes 1.0016 times as long as the best one, 1.053 at most.
 // With 5 us for the sums, 8 for a tile and 1.05, 1.25, 1.5 a step short contractions were cut that are faster whole: d_in
 // 1024, 1408 tokens x 656 rows bare 16.5 -> 19.1 us in two parts; 1152, 276 x 6880, rank 128 34.2 -> 38.1 in three.  Long ones
 // gain as before: 333 tokens x 14336 -> 4096 bare 153 us whole, 54 in eight parts.
@@ -299,7 +301,7 @@ PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_
         for (int tm = 2; tm <= 4 && (tm == 2 || near_rows(tm, d_in)); ++tm) {
             const size_t wgs = (size_t)row_tiles * ((M + 64 * tm - 1) / (64 * tm)) * ks;
             const float us = (float)((wgs + 255) / 256) * (STEP_US[tm] * (2 * ((G + ks - 1) / ks) + r / 64) + TILE_US[tm]) +
-                             (ks > 1 ? 10.f + (float)bytes * 2.f / 11e6f : 0.f);
+                             (ks > 1 ? ((size_t)M * rows * sizeof(float) <= 2u << 20 ? 7.f : 10.f) + (float)bytes * 2.f / 11e6f : 0.f);
             if (us < best_us) {
                 best_us = us;
                 best = {tm, ks};

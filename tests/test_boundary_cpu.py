@@ -255,10 +255,13 @@ def _plan(M, d_in, d_outs, r):
 
 @pytest.mark.parametrize("M,d_in,d_outs,r,parts", [
     (1408, 1024, (656,), 0, 1), (175, 1024, (6976,), 256, 1), (276, 1152, (6880,), 128, 1), (189, 1152, (9392,), 128, 1),
-    (336, 1280, (2432, 2720), 128, 1), (333, 14336, (4096,), 128, 8), (1014, 5120, (1680,), 128, 4), (2048, 14336, (4096,), 256, 2)])
+    (336, 1280, (2432, 2720), 128, 1), (333, 14336, (4096,), 128, 8), (1014, 5120, (1680,), 128, 4), (2048, 14336, (4096,), 256, 2),
+    (192, 1024, (816,), 256, 2), (199, 1024, (752,), 256, 2), (176, 1024, (560,), 128, 2), (378, 1280, (1008,), 128, 3)])
 def test_short_contractions_of_a_prompt_stay_whole(M, d_in, d_outs, r, parts):
     """Parts of the main GEMM where both sides were timed on the GPU: cutting a short contraction costs more than it gives
-    (16.5 us whole, 19.1 in two parts; 32.9 and 36.1; 34.2 and 38.1; 34.1 and 37.9; 35.3 and 38.6), a long one is cut."""
+    (16.5 us whole, 19.1 in two parts; 32.9 and 36.1; 34.2 and 38.1; 34.1 and 37.9; 35.3 and 38.6), a long one is cut, and a
+    short one whose parts are a few hundred rows (32.0 us whole, 30.8 in two; 31.8 and 30.9; 29.3 and
+    27.7; 32.3 in two and 31.3 in three)."""
     assert _plan(M, d_in, d_outs, r)[1] == parts
 
 
