@@ -239,16 +239,18 @@ constexpr size_t PREFILL_SPLIT_BYTES = 48u << 20;
 // sum, as far as the workspace has room for the parts (it always has it for pick_ksplit's).  The parts cost more than the two
 // kernels show, because the caches are written back between them: 2048 tokens, rank 256, d_in 14336 in 8 parts 262 us a call
 // with the main GEMM, in 14 (which 4 TB/s would take) 267, and the kernels' own times say the opposite.  Contractions of up to
-// twelve groups take pick_ksplit's parts at least, if these are one round: their parts are small and stay in the caches, and 2 TB/s
-// would leave them whole or in two (1262 tokens, rank 256 twice, d_in 1280: 45.2 us a call in two parts, 40.3 in five; 1194, rank
-// 128 three times, d_in 1024: 39.0 whole, 36.0 in eight).  In two rounds it is no gain (1384, rank 256 three times, d_in 1024, eight
+// 24 groups take pick_ksplit's parts at least, if these are one round: their parts are small and stay in the caches, and 2 TB/s
+// would leave them whole or in too few (1262 tokens, rank 256 twice, d_in 1280: 45.2 us a call in two parts, 40.3 in five; 1194, rank
+// 128 three times, d_in 1024: 39.0 whole, 36.0 in eight; 2028, rank 128 twice, d_in 2688: 52.7 in three, 51.0 in seven; 1207, rank
+// 256 twice, d_in 2304: 56.7 in three, 54.4 in six; 29 shapes of 13 .. 24 groups 0.986 on average, 1.007 at most).  With 32 groups
+// single calls lose 2 %.  In two rounds it is no gain (1384, rank 256 three times, d_in 1024, eight
 // parts of 33 workgroups: 52.1 us, whole 45.7).
 int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 {
     const int G = d_in / 128, tiles = ((M + 127) / 128) * n * ((r + 255) / 256), least = pick_ksplit(M, d_in, n * r);
     int best = least;
     float best_us = 1e30f;
-    for (int ks = G <= 12 && tiles * least <= 256 ? least : 1; ks <= G && ks <= 64; ++ks) {
+    for (int ks = G <= 24 && tiles * least <= 256 ? least : 1; ks <= G && ks <= 64; ++ks) {
         const size_t bytes = ks > 1 ? (size_t)ks * M * n * r * sizeof(float) : 0;
         if (ks > least && bytes > room) break;
         const int steps = 2 * ((G + ks - 1) / ks);

@@ -267,10 +267,13 @@ def test_short_contractions_of_a_prompt_stay_whole(M, d_in, d_outs, r, parts):
 
 @pytest.mark.parametrize("M,d_in,d_outs,r,parts", [
     (1262, 1280, (1632, 1552), 256, 5), (1194, 1024, (752, 1296, 2832), 128, 8), (604, 1280, (1728, 1008, 2736), 256, 5),
-    (1384, 1024, (1232, 1664, 2672), 256, 1), (1814, 1536, (656, 9216, 2512), 128, 3), (2048, 14336, (4096,), 256, 8), (333, 14336, (4096,), 128, 38)])
+    (1384, 1024, (1232, 1664, 2672), 256, 1), (1814, 1536, (656, 9216, 2512), 128, 3),
+    (2028, 2688, (640, 560), 128, 7), (1207, 2304, (1328, 1648), 256, 6), (1179, 2048, (2288,), 256, 8), (823, 3072, (3040, 1984), 256, 8),
+    (2048, 4096, (4096,), 256, 4), (2048, 14336, (4096,), 256, 8), (333, 14336, (4096,), 128, 38)])
 def test_parts_of_a_prompts_down_projection(M, d_in, d_outs, r, parts):
     """Parts of t's contraction where both sides were timed on the GPU: a short one in as many as are one round of workgroups (40.3
-    us a call instead of 45.2 in two; 36.0 instead of 39.0 whole; 41.0 instead of 43.3), but not in more than a round (45.7 us
+    us a call instead of 45.2 in two; 36.0 instead of 39.0 whole; 41.0 instead of 43.3; up to 24 groups: 51.0 instead of 52.7, 54.4
+    instead of 56.7, 47.3 instead of 48.2, 64.1 instead of 64.9), but not in more than a round (45.7 us
     whole, 52.1 in eight parts)."""
     assert _plan(M, d_in, d_outs, r)[2] == parts
 
