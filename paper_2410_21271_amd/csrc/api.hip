@@ -276,6 +276,9 @@ int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 // With 5 us for the sums, 8 for a tile and 1.05, 1.25, 1.5 a step short contractions were cut that are faster whole: d_in
 // 1024, 1408 tokens x 656 rows bare 16.5 -> 19.1 us in two parts; 1152, 276 x 6880, rank 128 34.2 -> 38.1 in three.  Long ones
 // gain as before: 333 tokens x 14336 -> 4096 bare 153 us whole, 54 in eight parts.
+// Without factors a step with 128 tokens is reckoned at BARE_STEP_US: tiles of 128 tokens in fewer parts win there where the same step
+// as with factors took more parts of larger tiles (512 x 4096 -> 4096 + 1024 + 1024: 41.5 us in four parts of 256 tokens, 40.5 in
+// two; 968 x 3072 -> 688 + 1040 + 1424 35.7 and 33.9; 595 x 2048 -> 5952 30.2 in two parts and 28.7 whole).
 // room: bytes for the partial outputs; the parts never need more.  d_out: the members' rows.
 struct PrefillTiles {
     int tm, parts;
@@ -288,6 +291,7 @@ bool near_rows(int tm, int d_in) { return ((size_t)(64 * tm - 1) * d_in + 64) * 
 PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_t room)
 {
     static const float STEP_US[5] = {0.f, 0.f, 0.97f, 1.18f, 1.21f}, TILE_US[5] = {0.f, 0.f, 3.f, 4.f, 8.f};
+    constexpr float BARE_STEP_US = 0.9f;
     const int G = d_in / 128;
     size_t rows = 0;
     int row_tiles = 0;
@@ -302,7 +306,8 @@ PrefillTiles pick_prefill(int M, int d_in, int r, const int* d_out, int n, size_
         if (ks > 1 && bytes > room) break;                // (whole numbers: a float would round the room up to the need)
         for (int tm = 2; tm <= 4 && (tm == 2 || near_rows(tm, d_in)); ++tm) {
             const size_t wgs = (size_t)row_tiles * ((M + 64 * tm - 1) / (64 * tm)) * ks;
-            const float us = (float)((wgs + 255) / 256) * (STEP_US[tm] * (2 * ((G + ks - 1) / ks) + r / 64) + TILE_US[tm]) +
+            const float step_us = tm == 2 && r == 0 ? BARE_STEP_US : STEP_US[tm];
+            const float us = (float)((wgs + 255) / 256) * (step_us * (2 * ((G + ks - 1) / ks) + r / 64) + TILE_US[tm]) +
                              (ks > 1 ? ((size_t)M * rows * sizeof(float) <= 2u << 20 ? 7.f : 10.f) + (float)bytes * 2.f / 11e6f : 0.f);
             if (us < best_us) {
                 best_us = us;
@@ -346,11 +351,14 @@ PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     // power decides, and the 16x16x32 MFMAs of prefill.hip win.  Time of a call on prefill.hip over that on prefill128.hip, calls of
     // 402 shapes: up to 128 workgroups 1.06, 129 .. 192 1.03, 193 .. 224 1.01, 225 .. 248 0.994, 249 .. 256 0.983, 257 .. 384 1.004,
     // 385 .. 448 0.990, 449 .. 512 0.978, more 1.004.  Where 128 tokens are the cheapest tile, lines by how full the rounds are gain 0.1 %.
-    // (pick_prefill reckons with one length of a step for both.)
+    // (pick_prefill reckons with one length of a step for both.)  Without factors prefill128.hip wins with all compute units busy too
+    // once a tile has 32 steps: beyond the line 1.06 on average (1024 tokens x 28672 -> 8192, w3: 453 and 432 us; 793 x 3072 ->
+    // 8784 + 5056 + 3840, w2: 106.3 and 94.1), 1.00 with fewer steps.
     size_t wgs = 0;
     for (int m = 0; m < n; ++m) wgs += (d_out[m] + 255) / 256;
     wgs *= (size_t)((M + 127) / 128) * p.parts;
-    p.by128 = p.tm == 2 && (wgs <= 248 || !near_rows(2, d_in));
+    const bool long_bare = r == 0 && 2 * ((d_in / 128 + p.parts - 1) / p.parts) >= 32;
+    p.by128 = p.tm == 2 && (wgs <= 248 || long_bare || !near_rows(2, d_in));
     return p;
 }
 

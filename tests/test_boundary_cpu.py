@@ -265,6 +265,18 @@ def test_short_contractions_of_a_prompt_stay_whole(M, d_in, d_outs, r, parts):
     assert _plan(M, d_in, d_outs, r)[1] == parts
 
 
+@pytest.mark.parametrize("M,d_in,d_outs,r,plan", [
+    (512, 4096, (4096, 1024, 1024), 0, (128, 2, True)), (968, 3072, (688, 1040, 1424), 0, (128, 2, True)), (595, 2048, (5952,), 0, (128, 1, True)),
+    (1024, 4096, (4096,), 0, (128, 2, True)), (1024, 28672, (8192,), 0, (128, 1, True)), (1044, 8064, (9600, 4432), 0, (128, 1, True)),
+    (793, 3072, (8784, 5056, 3840), 0, (128, 1, True)), (2048, 1024, (4096,), 0, (128, 1, False)), (1024, 28672, (8192,), 128, (128, 1, False))])
+def test_tiles_of_a_prompt_without_factors(M, d_in, d_outs, r, plan):
+    """Tokens of a tile, parts and kernel of calls without factors where both sides were timed on the GPU: 128 tokens in fewer parts
+    (41.5 us in larger tiles, 40.5; 35.7 and 33.9; 30.2 and 28.7), and from 32 steps on prefill128.hip at any number of workgroups
+    (46.0 us on the other, 44.3; 453 and 432; 236.5 and 215.6; 106.3 and 94.1)."""
+    tokens, parts, _, by128, _ = _plan(M, d_in, d_outs, r)
+    assert (tokens, parts, by128) == plan
+
+
 @pytest.mark.parametrize("M,d_in,d_outs,r,parts", [
     (1262, 1280, (1632, 1552), 256, 5), (1194, 1024, (752, 1296, 2832), 128, 8), (604, 1280, (1728, 1008, 2736), 256, 5),
     (1384, 1024, (1232, 1664, 2672), 256, 1), (1814, 1536, (656, 9216, 2512), 128, 3),
