@@ -271,8 +271,9 @@ int pick_t_parts(int M, int d_in, int r, int n, size_t room)
 // the caches written back in between; 7 where a part's outputs are 2 MiB or less (192 tokens x 1024 -> 816, rank 256: 32.0 us
 // whole, 30.8 in two parts).  The line is drawn for one part, not for all of them: else a part would be saved to stay below it (378 x
 // 1280 -> 1008, rank 128: 31.3 us in three parts, 32.3 in two).
-// The constants are fitted to calls of 402 shapes (128 .. 8192 tokens, d_in 1024 .. 28672, every tm and one to eight parts of
-// each timed) for the choice they lead to, not for the times: on average it takes 1.0016 times as long as the best one, 1.053 at most.
+// The constants are fitted to calls of 402 shapes (128 .. 8192 tokens, d_in 1024 .. 28672, every tm and one to eight parts of each
+// timed) for the choice they lead to, not for the times; over 722, part of them the same, it takes 1.005 times as long as the best one
+// on average, 1.14 at most; with the constants of the next lines 1.011 and 1.29.
 // With 5 us for the sums, 8 for a tile and 1.05, 1.25, 1.5 a step short contractions were cut that are faster whole: d_in
 // 1024, 1408 tokens x 656 rows bare 16.5 -> 19.1 us in two parts; 1152, 276 x 6880, rank 128 34.2 -> 38.1 in three.  Long ones
 // gain as before: 333 tokens x 14336 -> 4096 bare 153 us whole, 54 in eight parts.
@@ -348,9 +349,9 @@ PrefillPlan plan_prefill(int M, int d_in, int r, const int* d_out, int n, size_t
     const size_t main_bytes = p.parts > 1 ? (size_t)p.parts * M * rows * sizeof(float) : 0;
     p.main_at = p.own + (t_parts_bytes + main_bytes <= left ? t_parts_bytes : 0);
     // 128 tokens: on a partly filled chip the shorter steps of prefill128.hip win, with (nearly) all compute units busy the card's
-    // power decides, and the 16x16x32 MFMAs of prefill.hip win.  Time of a call on prefill.hip over that on prefill128.hip, calls of
-    // 402 shapes: up to 128 workgroups 1.06, 129 .. 192 1.03, 193 .. 224 1.01, 225 .. 248 0.994, 249 .. 256 0.983, 257 .. 384 1.004,
-    // 385 .. 448 0.990, 449 .. 512 0.978, more 1.004.  Where 128 tokens are the cheapest tile, lines by how full the rounds are gain 0.1 %.
+    // power decides, and the 16x16x32 MFMAs of prefill.hip win.  Time of a call with factors on prefill.hip over that on prefill128.hip,
+    // 722 shapes: up to 128 workgroups 1.037, 129 .. 192 1.019, 193 .. 224 1.003, 225 .. 248 0.994, 249 .. 256 0.983, 257 .. 384 0.997, 385 .. 448
+    // 0.985, 449 .. 512 0.977, more 1.008.  Where 128 tokens are the cheapest tile, lines by how full the rounds are gain 0.1 %.
     // (pick_prefill reckons with one length of a step for both.)  Without factors prefill128.hip wins with all compute units busy too
     // once a tile has 32 steps: beyond the line 1.06 on average (1024 tokens x 28672 -> 8192, w3: 453 and 432 us; 793 x 3072 ->
     // 8784 + 5056 + 3840, w2: 106.3 and 94.1), 1.00 with fewer steps.
