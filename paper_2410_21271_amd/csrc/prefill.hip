@@ -474,21 +474,37 @@ static hipError_t launch_pf(const PrefillArgs& a, hipStream_t stream)
     }
 }
 
-// W parts' loads at a time on their way, also where fewer are left: beyond the last part that one again, not added (one by one, 32 parts
-// of 1 MiB take 15 us, and the seven behind the first of eight parts cost a call of 427 tokens x 2048, rank 256 twice, 0.9 of 38.6 us)
+// W parts behind ks, in order, their loads on their way together
 template <int W>
+static __device__ __forceinline__ void add_parts(const float* __restrict__ p, size_t count, int& ks, f4& v)
+{
+    f4 w[W];
+#pragma unroll
+    for (int e = 0; e < W; ++e) w[e] = *(const f4*)(p + (ks + e) * count);
+#pragma unroll
+    for (int e = 0; e < W; ++e) v += w[e];
+    ks += W;
+}
+
+// Eight parts at a time, then what is left of them together (one by one, 32 parts of 1 MiB take 15 us, and the seven behind the first of
+// eight parts cost a call of 427 tokens x 2048, rank 256 twice, 0.9 of 38.6 us; the last part again in place of those that are not
+// there costs up to 2 % of a call: 318 tokens x 1280 -> 944, rank 128, ten parts, 28.8 -> 29.4 us; 333 x 14336, 38 parts, 68.4 -> 69.7)
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restrict__ part, _Float16* __restrict__ T, size_t count, int ksplit)
 {
     const size_t i = 4 * ((size_t)blockIdx.x * 256 + threadIdx.x);
     if (i >= count) return;
-    f4 v = *(const f4*)(part + i);
-    for (int ks = 1; ks < ksplit; ks += W) {                      // fixed order
-        f4 w[W];
-#pragma unroll
-        for (int e = 0; e < W; ++e) w[e] = *(const f4*)(part + (ks + e < ksplit ? ks + e : ksplit - 1) * count + i);
-#pragma unroll
-        for (int e = 0; e < W; ++e)
-            if (ks + e < ksplit) v += w[e];
+    const float* __restrict__ p = part + i;
+    f4 v = *(const f4*)p;
+    int ks = 1;
+    while (ks + 8 <= ksplit) add_parts<8>(p, count, ks, v);
+    switch (ksplit - ks) {
+        case 1: add_parts<1>(p, count, ks, v); break;
+        case 2: add_parts<2>(p, count, ks, v); break;
+        case 3: add_parts<3>(p, count, ks, v); break;
+        case 4: add_parts<4>(p, count, ks, v); break;
+        case 5: add_parts<5>(p, count, ks, v); break;
+        case 6: add_parts<6>(p, count, ks, v); break;
+        case 7: add_parts<7>(p, count, ks, v); break;
     }
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     *(h4*)(T + i) = h4{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
@@ -496,8 +512,7 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
 
 hipError_t launch_reduce_parts(const float* part, void* T, size_t count, int ksplit, hipStream_t stream)
 {
-    auto kern = ksplit <= 4 ? reduce_parts_kernel<3> : reduce_parts_kernel<8>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, stream, part, (_Float16*)T, count, ksplit);
+    hipLaunchKernelGGL(reduce_parts_kernel, dim3((unsigned)((count / 4 + 255) / 256)), dim3(256), 0, stream, part, (_Float16*)T, count, ksplit);
     return hipGetLastError();
 }
 
