@@ -136,12 +136,6 @@ __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H
 // result register v holds D[i = 4 v + g][j = n].
 typedef double d4 __attribute__((ext_vector_type(4)));
 constexpr int BJ_NT = 512, BJ_NW = BJ_NT / 64;
-// Sweeps over the 16 x 16 matrix per round: what one leaves is finished in the next sweep over the rows.  Those are as many as with two
-// to one or two of some twenty, both ways, for the block of a subspace iteration, for all rows and for the eigendecomposition; a round of 256
-// rows takes 12 us instead of 16 (1024 x 1024 with all rows: 17 sweeps, 53.9 -> 41.8 ms; its eigendecomposition route 116 -> 93 ms;
-// 4096 x 4096 with all rows 22 and 21 sweeps, 672 -> 604 ms).
-constexpr int BJ_INNER_SWEEPS = 1;
-
 __device__ __forceinline__ d4 mfma64(double a, double b, d4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
 
 __device__ __forceinline__ double rcp_approx(double v) { return __builtin_amdgcn_rcp(v); }
@@ -156,21 +150,140 @@ __device__ __forceinline__ double rsq_newton(double v)
     return y;
 }
 
-// Cosine and sine of the plane rotation that makes [a c; c b] diagonal.  The 30 steps of a 16 x 16 matrix are a chain in which
+// Cosine and sine of the plane rotation that makes [a c; c b] diagonal.  The steps of a 16 x 16 matrix are a chain in which
 // each waits for these values, and the library's division and square root are some 30 dependent instructions each.  The
 // angle may be off in its last bits (what it leaves of c the next sweep finds), the rotation may not: cosine and sine come
 // from one t, so their squares add to 1 to rounding whatever t is.
 __device__ __forceinline__ void jacobi_angle(double a, double b, double c, double& co, double& si)
 {
     const double d = b - a, h = c + c, rh = rcp_approx(h), q0 = d * rh;
-    double zeta = fma(fma(-h, q0, d), rh, q0);
-    zeta = fmin(fmax(zeta, -1e100), 1e100);               // (c that is next to nothing: no infinities further on)
-    const double az = fabs(zeta), w = fma(az, az, 1.0), root = w * rsq_approx(w);
+    const double zeta = fma(fma(-h, q0, d), rh, q0);
+    const double az = fmin(fabs(zeta), 1e100);            // (c that is next to nothing: no infinities further on)
+    const double w = fma(az, az, 1.0), root = w * rsq_approx(w);
     double t = rcp_approx(az + root);                     // the smaller root of t^2 + 2 |zeta| t - 1
     t = fma(-fma(t, t + 2.0 * az, -1.0), 0.5 * rcp_approx(t + az), t);
     t = copysign(t, zeta);
     co = rsq_newton(fma(t, t, 1.0));
     si = co * t;
+}
+
+// value of lane `from` (4 times its number) in every lane
+__device__ __forceinline__ double lane_value(double v, int from4)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_ds_bpermute(from4, (int)(unsigned)u);
+    const unsigned hi = (unsigned)__builtin_amdgcn_ds_bpermute(from4, (int)(unsigned)(u >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// Whether a pair of rows with squared norms a, b and product c is to be rotated
+__device__ __forceinline__ bool rotation_due(double a, double b, double c, double tol, double abs_floor)
+{
+    return a > abs_floor && b > abs_floor && fabs(c) > tol * (a * rsq_approx(a)) * (b * rsq_approx(b));
+}
+
+// S (Gram matrix of 16 rows: a block of eight, P, and another, Q) -> J orthogonal, after one rotation of each of the 64 pairs of a
+// row of P and a row of Q, in eight steps of eight disjoint pairs (i, (i + step) mod 8).  One wavefront; true if any was rotated.
+// Lane (i, j) holds the 2 x 2 block of S in the rows of pair i and the columns of pair j, and rows 2 i, 2 i + 1 of J's columns of
+// pair j.  From one step to the next P's places stay and Q's move up by one lane of their index, so the matrix never leaves the
+// registers; the eight lanes (i, i) find the angles, every lane fetches those of its two pairs.  (Through LDS, with every lane
+// forming its two angles, a step took 1270 cycles, and a round of rows took all 120 pairs in 15 steps: those within P and within Q
+// belong to one round of a sweep.)
+__device__ __forceinline__ bool rotate_cross_pairs(const double (*S)[17], double (*J)[17], int lane, double tol, double abs_floor)
+{
+    const int i = lane >> 3, j = lane & 7;
+    if (!__any(rotation_due(S[i][i], S[8 + j][8 + j], S[i][8 + j], tol, abs_floor))) return false;
+    double pp = S[i][j], pq = S[i][8 + j], qp = S[8 + i][j], qq = S[8 + i][8 + j];
+    double jp0 = 2 * i == j ? 1.0 : 0.0, jp1 = 2 * i + 1 == j ? 1.0 : 0.0, jq0 = 2 * i == 8 + j ? 1.0 : 0.0, jq1 = 2 * i + 1 == 8 + j ? 1.0 : 0.0;
+    const int row = 4 * 9 * i, col = 4 * 9 * j;           // lanes (i, i) and (j, j)
+    const int nr = 4 * (8 * ((i + 1) & 7) + j), nc = 4 * (8 * i + ((j + 1) & 7)), nrc = 4 * (8 * ((i + 1) & 7) + ((j + 1) & 7));
+#pragma unroll 1
+    for (int step = 0; step < 8; ++step) {
+        double co, si;
+        jacobi_angle(pp, qq, pq, co, si);
+        const bool on = rotation_due(pp, qq, pq, tol, abs_floor);      // (of lanes (i, i); the others' are nobody's)
+        co = on ? co : 1.0;
+        si = on ? si : 0.0;
+        const double co0 = lane_value(co, row), si0 = lane_value(si, row), co1 = lane_value(co, col), si1 = lane_value(si, col);
+        const double tpp = co0 * pp - si0 * qp, tqp = si0 * pp + co0 * qp;      // rows
+        const double tpq = co0 * pq - si0 * qq, tqq = si0 * pq + co0 * qq;
+        pp = co1 * tpp - si1 * tpq;                                             // columns
+        pq = lane_value(si1 * tpp + co1 * tpq, nc);
+        qp = lane_value(co1 * tqp - si1 * tqq, nr);
+        qq = lane_value(si1 * tqp + co1 * tqq, nrc);
+        const double n0 = si1 * jp0 + co1 * jq0, n1 = si1 * jp1 + co1 * jq1;
+        jp0 = co1 * jp0 - si1 * jq0;
+        jp1 = co1 * jp1 - si1 * jq1;
+        jq0 = lane_value(n0, nc);
+        jq1 = lane_value(n1, nc);
+    }
+    J[2 * i][j] = jp0;
+    J[2 * i + 1][j] = jp1;
+    J[2 * i][8 + j] = jq0;
+    J[2 * i + 1][8 + j] = jq1;
+    return true;
+}
+
+// The same for all 120 pairs of the 16 rows, in fifteen steps of eight: the rounds that also see to the pairs within a block.
+// Lane (i, j) owns the 2 x 2 block of S in the rows of pair i and the columns of pair j, forms both pairs' rotations by
+// itself and applies them from either side at once, and turns rows 2 i, 2 i + 1 of J's columns of pair j: one round through
+// LDS per step (one wavefront's LDS operations are carried out in order).
+__device__ __forceinline__ bool rotate_all_pairs(double (*S)[17], double (*J)[17], int lane, double tol, double abs_floor)
+{
+    const int pi = lane >> 3, pj = lane & 7;
+    bool some = false;                                // whether any of the 120 pairs is to be rotated (in the last sweeps most rounds have none)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int r = (lane >> 4) + 4 * e, c = lane & 15;
+        some = some || (r < c && rotation_due(S[r][r], S[c][c], S[r][c], tol, abs_floor));
+        J[r][c] = r == c ? 1.0 : 0.0;
+    }
+    if (!__any(some)) return false;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    bool any = false;
+#pragma unroll 1
+    for (int step = 0; step < 15; ++step) {
+        auto pair = [&](int t, int& p, int& q) {
+            p = t == 0 ? step : step + t >= 15 ? step + t - 15 : step + t;
+            q = t == 0 ? 15 : step + 15 - t >= 15 ? step - t : step + 15 - t;
+        };
+        int p0, q0, p1, q1;
+        pair(pi, p0, q0);
+        pair(pj, p1, q1);
+        const double a0 = S[p0][p0], b0 = S[q0][q0], c0 = S[p0][q0], a1 = S[p1][p1], b1 = S[q1][q1], c1 = S[p1][q1];
+        const double spp = S[p0][p1], spq = S[p0][q1], sqp = S[q0][p1], sqq = S[q0][q1];
+        const double jp0 = J[2 * pi][p1], jq0 = J[2 * pi][q1], jp1 = J[2 * pi + 1][p1], jq1 = J[2 * pi + 1][q1];
+        double co0, si0, co1, si1;
+        jacobi_angle(a0, b0, c0, co0, si0);
+        jacobi_angle(a1, b1, c1, co1, si1);
+        const bool on0 = rotation_due(a0, b0, c0, tol, abs_floor), on1 = rotation_due(a1, b1, c1, tol, abs_floor);
+        co0 = on0 ? co0 : 1.0;
+        si0 = on0 ? si0 : 0.0;
+        co1 = on1 ? co1 : 1.0;
+        si1 = on1 ? si1 : 0.0;
+        if (!__any(on1)) continue;                    // uniform: nothing to rotate in this step
+        any = true;
+        const double tpp = co0 * spp - si0 * sqp, tqp = si0 * spp + co0 * sqp;      // rows
+        const double tpq = co0 * spq - si0 * sqq, tqq = si0 * spq + co0 * sqq;
+        S[p0][p1] = co1 * tpp - si1 * tpq;                                          // columns
+        S[p0][q1] = si1 * tpp + co1 * tpq;
+        S[q0][p1] = co1 * tqp - si1 * tqq;
+        S[q0][q1] = si1 * tqp + co1 * tqq;
+        J[2 * pi][p1] = co1 * jp0 - si1 * jq0;
+        J[2 * pi][q1] = si1 * jp0 + co1 * jq0;
+        J[2 * pi + 1][p1] = co1 * jp1 - si1 * jq1;
+        J[2 * pi + 1][q1] = si1 * jp1 + co1 * jq1;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    return any;
+}
+
+// The two blocks of eight rows of workgroup i in round `round` of nb / 2 (round-robin over nb blocks)
+__device__ __forceinline__ void block_pair(int i, int round, int nb, int& P, int& Q)
+{
+    const int mm = nb - 1;
+    P = i == 0 ? round : (round + i) % mm;
+    Q = i == 0 ? mm : (round + mm - i) % mm;
 }
 
 // rows <- J^T rows for the 16 rows (block P, block Q) of X (row length len, a multiple of 128)
@@ -218,15 +331,8 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
     __shared__ int s_rotated;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int n = lane & 15, g = lane >> 4;
-    const int nb = m / 8, mm = nb - 1, i = blockIdx.x;
     int P, Q;
-    if (i == 0) {
-        P = round;
-        Q = mm;
-    } else {
-        P = (round + i) % mm;
-        Q = (round + mm - i) % mm;
-    }
+    block_pair(blockIdx.x, round, m / 8, P, Q);
     // ---- Gram matrix of the 16 rows: lane (n, g) feeds row n, both operands of the MFMA are the same register
     {
         const double* row = H + (size_t)(n < 8 ? 8 * P + n : 8 * Q + n - 8) * L;
@@ -252,63 +358,12 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 #pragma unroll
         for (int w = 0; w < BJ_NW; ++w) t += Sw[w][r][c];
         S[r][c] = t;
-        J[r][c] = r == c ? 1.0 : 0.0;
     }
     __syncthreads();
-    // ---- S = J D J^T by two-sided Jacobi: eight disjoint pairs per step, fifteen steps per sweep.  One wavefront does it
-    // alone (its LDS operations are carried out in order; three workgroup barriers per step cost more than they shared out).
-    // Lane (i, j) owns the 2 x 2 block of S in the rows of pair i and the columns of pair j, forms both pairs' rotations by
-    // itself and applies them from either side at once, and turns rows 2 i, 2 i + 1 of J's columns of pair j: one round through
-    // LDS per step (the chain of reads, rotation and writes is what a round of the rows waits for).
+    // ---- by one wavefront alone (three workgroup barriers per step cost more than they shared out)
     if (wave == 0) {
-        const int pi = lane >> 3, pj = lane & 7;
-        auto due = [&](double a, double b, double c) { return a > abs_floor && b > abs_floor && fabs(c) > tol * (a * rsq_approx(a)) * (b * rsq_approx(b)); };
-        bool some = false;                            // whether any of the 120 pairs is to be rotated (in the last sweeps most rounds have none)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int r = (lane >> 4) + 4 * e, c = lane & 15;
-            some = some || (r < c && due(S[r][r], S[c][c], S[r][c]));
-        }
-        bool rotated = false;
-        for (int sweep = 0; sweep < BJ_INNER_SWEEPS && __any(some); ++sweep) {
-            bool any = false;
-            for (int step = 0; step < 15; ++step) {
-                auto pair = [&](int t, int& p, int& q) {
-                    p = t == 0 ? step : step + t >= 15 ? step + t - 15 : step + t;
-                    q = t == 0 ? 15 : step + 15 - t >= 15 ? step - t : step + 15 - t;
-                };
-                int p0, q0, p1, q1;
-                pair(pi, p0, q0);
-                pair(pj, p1, q1);
-                const double a0 = S[p0][p0], b0 = S[q0][q0], c0 = S[p0][q0], a1 = S[p1][p1], b1 = S[q1][q1], c1 = S[p1][q1];
-                const double spp = S[p0][p1], spq = S[p0][q1], sqp = S[q0][p1], sqq = S[q0][q1];
-                const double jp0 = J[2 * pi][p1], jq0 = J[2 * pi][q1], jp1 = J[2 * pi + 1][p1], jq1 = J[2 * pi + 1][q1];
-                double co0, si0, co1, si1;
-                jacobi_angle(a0, b0, c0, co0, si0);
-                jacobi_angle(a1, b1, c1, co1, si1);
-                const bool on0 = due(a0, b0, c0), on1 = due(a1, b1, c1);
-                co0 = on0 ? co0 : 1.0;
-                si0 = on0 ? si0 : 0.0;
-                co1 = on1 ? co1 : 1.0;
-                si1 = on1 ? si1 : 0.0;
-                if (!__any(on1)) continue;            // uniform: nothing to rotate in this step
-                any = true;
-                const double tpp = co0 * spp - si0 * sqp, tqp = si0 * spp + co0 * sqp;      // rows
-                const double tpq = co0 * spq - si0 * sqq, tqq = si0 * spq + co0 * sqq;
-                S[p0][p1] = co1 * tpp - si1 * tpq;                                          // columns
-                S[p0][q1] = si1 * tpp + co1 * tpq;
-                S[q0][p1] = co1 * tqp - si1 * tqq;
-                S[q0][q1] = si1 * tqp + co1 * tqq;
-                J[2 * pi][p1] = co1 * jp0 - si1 * jq0;
-                J[2 * pi][q1] = si1 * jp0 + co1 * jq0;
-                J[2 * pi + 1][p1] = co1 * jp1 - si1 * jq1;
-                J[2 * pi + 1][q1] = si1 * jp1 + co1 * jq1;
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            }
-            if (!any) break;
-            rotated = true;
-        }
-        if (lane == 0) s_rotated = rotated ? 1 : 0;
+        const bool any = round == 0 ? rotate_all_pairs(S, J, lane, tol, abs_floor) : rotate_cross_pairs(S, J, lane, tol, abs_floor);
+        if (lane == 0) s_rotated = any ? 1 : 0;
     }
     __syncthreads();
     const bool rotated = s_rotated != 0;
@@ -316,6 +371,76 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
     if (tid == 0) atomicAdd(rotations, 1u);
     apply_rotation(H, L, P, Q, J, wave, lane);
     if (V) apply_rotation(V, m, P, Q, J, wave, lane);
+}
+
+// A round over rows of 8 CW values (the Ritz matrices of the subspace iteration), without eigenvector rows.  A chain of latencies:
+// a wavefront's CW columns of the 16 rows are requested twice, as the operands of the Gram matrix and as those of the
+// rotation, and stay in registers.  Of 256 rows: 5.7 us a round, where the kernel above took 12.0 with all 120 pairs through LDS.
+template <int CW>
+__global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __restrict__ H, int m, int round, double tol, double abs_floor, unsigned* __restrict__ rotations)
+{
+    constexpr int L = BJ_NW * CW;
+    __shared__ double Sw[BJ_NW][16][17];
+    __shared__ double S[16][17], J[16][17];
+    __shared__ int s_rotated;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int n = lane & 15, g = lane >> 4;
+    int P, Q;
+    block_pair(blockIdx.x, round, m / 8, P, Q);
+    auto row_of = [&](int r) { return H + (size_t)(r < 8 ? 8 * P + r : 8 * Q + r - 8) * L + CW * wave; };
+    double2 ga[CW / 8];                 // row n, columns 8 e + 2 g, + 1
+    double xa[CW / 16][4];              // row 4 kk + g, column 16 u + n
+    {
+        const double* const row = row_of(n);
+#pragma unroll
+        for (int e = 0; e < CW / 8; ++e) ga[e] = *reinterpret_cast<const double2*>(row + 8 * e + 2 * g);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const double* const row = row_of(4 * kk + g);
+#pragma unroll
+        for (int u = 0; u < CW / 16; ++u) xa[u][kk] = row[16 * u + n];
+    }
+    d4 acc = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < CW / 8; ++e) {
+        acc = mfma64(ga[e].x, ga[e].x, acc);
+        acc1 = mfma64(ga[e].y, ga[e].y, acc1);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Sw[wave][4 * v + g][n] = acc[v] + acc1[v];
+    __syncthreads();
+    if (tid < 256) {
+        const int r = tid >> 4, c = tid & 15;
+        double t = 0;
+#pragma unroll
+        for (int w = 0; w < BJ_NW; ++w) t += Sw[w][r][c];
+        S[r][c] = t;
+    }
+    __syncthreads();
+    if (wave == 0) {
+        const bool any = round == 0 ? rotate_all_pairs(S, J, lane, tol, abs_floor) : rotate_cross_pairs(S, J, lane, tol, abs_floor);
+        if (lane == 0) s_rotated = any ? 1 : 0;
+    }
+    __syncthreads();
+    if (s_rotated == 0) return;         // (uniform over the workgroup)
+    if (tid == 0) atomicAdd(rotations, 1u);
+    double aJ[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) aJ[kk] = J[4 * kk + g][n];
+    d4 d[CW / 16];
+#pragma unroll
+    for (int u = 0; u < CW / 16; ++u) d[u] = d4{0, 0, 0, 0};
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int u = 0; u < CW / 16; ++u) d[u] = mfma64(aJ[kk], xa[u][kk], d[u]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        double* const row = row_of(4 * v + g);
+#pragma unroll
+        for (int u = 0; u < CW / 16; ++u) row[16 * u + n] = d[u][v];
+    }
 }
 
 // C[i][j] = beta * C[i][j] + alpha * sum_k A[i*ai + k*ak] * B[j*bj + k*bk], i < M, j < N, k < K (beta == 0: C is
@@ -999,7 +1124,7 @@ __global__ void ritz_matrix_kernel(const double* __restrict__ src, double* __res
     G[e] = v;
 }
 
-// rank of lam[i] among p values (descending): out row rank <- row i of R, theta[rank] = lam[i]
+// rank of lam[i], the squared norm of row i of R, among p values (descending): out row rank <- that row divided by its norm, theta[rank] = lam[i]
 __global__ __launch_bounds__(256) void sort_rows_kernel(const double* __restrict__ R, const double* __restrict__ lam, int p, double* __restrict__ out,
                                                         double* __restrict__ theta)
 {
@@ -1014,7 +1139,8 @@ __global__ __launch_bounds__(256) void sort_rows_kernel(const double* __restrict
     __syncthreads();
     rank = s_rank;
     if (threadIdx.x == 0) theta[rank] = v;
-    for (int k = threadIdx.x; k < p; k += 256) out[(size_t)rank * p + k] = R[(size_t)i * p + k];
+    const double f = v > 0.0 ? 1.0 / sqrt(v) : 0.0;
+    for (int k = threadIdx.x; k < p; k += 256) out[(size_t)rank * p + k] = R[(size_t)i * p + k] * f;
 }
 
 inline unsigned blocks(size_t n, int per = 256) { return (unsigned)((n + per - 1) / per); }
@@ -1140,8 +1266,12 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
     for (int sweep = 1; sweep <= MAX_SWEEPS; ++sweep) {
         hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, rot);
         if (block_rounds_fit(L, V != nullptr, m)) {
-            for (int round = 0; round < m / 8 - 1; ++round)
-                hipLaunchKernelGGL(jacobi_block_round_kernel, dim3(m / 16), dim3(BJ_NT), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+            auto short_rows = V ? nullptr : L == 128 ? jacobi_short_round_kernel<16> : L == 256 ? jacobi_short_round_kernel<32> :
+                              L == 384 ? jacobi_short_round_kernel<48> : L == 512 ? jacobi_short_round_kernel<64> : nullptr;
+            for (int round = 0; round < m / 8 - 1; ++round) {
+                if (short_rows) hipLaunchKernelGGL(short_rows, dim3(m / 16), dim3(BJ_NT), 0, st, H, m, round, tol, abs_floor, rot);
+                else hipLaunchKernelGGL(jacobi_block_round_kernel, dim3(m / 16), dim3(BJ_NT), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+            }
         } else {
             for (int round = 0; round < m - 1; ++round) jacobi_round(H, L, V, m, round, tol, abs_floor, rot, st);
         }
@@ -1223,11 +1353,14 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         if (nl > 0)                                       // Y orthogonal to the locked rows: their products with it are F's first columns
             gemm((const double*)(F + (size_t)nl * p), (long)p, 1L, (const double*)Z, 1L, (long)m, Y + (size_t)nl * m, (long)m, p - nl, m, nl, st, -1.0, 1.0);
         hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
-        hipLaunchKernelGGL(identity_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, R, p);
+        // G = C C^T; the rows of C^T made orthogonal are the roots of G's eigenvalues times its eigenvectors: no rotations to be
+        // gathered, and rows that are unit vectors orthogonal to rounding
+        cholesky(G, p, 1e-15, thr, flag, F, st, false);
+        hipLaunchKernelGGL(transpose_kernel, dim3((p + 31) / 32, (p + 31) / 32), dim3(256), 0, st, (const double*)G, R, p);
         double rotations = 0;
-        const int swept = jacobi_sweeps(G, p, R, p, lam, rot, st, &rotations);
+        const int swept = jacobi_sweeps(R, p, nullptr, p, lam, rot, st, &rotations);
         if (swept < 0) return swept == -1 ? 0 : -2;       // (a runtime error is not "did not settle")
-        hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, (const double*)G, (const double*)R, p, lam);
+        hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)R, p, lam);
         hipLaunchKernelGGL(sort_rows_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)lam, p, F, theta);
         gemm((const double*)F, (long)p, 1L, (const double*)Z, 1L, (long)m, U, (long)m, p, m, p, st);
         copy_doubles(U, Z, (size_t)p * m, st);

@@ -92,3 +92,21 @@ def test_factors_of_a_well_conditioned_gram_to_rounding(gpu, d_in, d_out, r, rou
     want = np.linalg.norm(Bo, axis=0)
     off = np.abs(sig.cpu().numpy() / want - 1).max()
     assert off <= (3.5e-12 if route else 1.1e-12)
+
+
+@pytest.mark.parametrize("d,r,block", [(1024, 128, 256), (1536, 192, 384), (2048, 256, 512)])
+def test_ritz_rotations_of_every_short_row(gpu, d, r, block):
+    """Subspace iterations whose blocks are 256, 384 and 512 vectors (128: the shapes above): one instance each of the rounds over short
+    rows.  The singular values and the correction against LAPACK on the Cholesky factor of the same Gram matrix (any square root gives
+    the same factors); the bounds of the other calibration tests."""
+    from tests.test_gpu_calibrate import _factors_with_stats, _inputs
+    W, W_hat, Xt = _inputs(7700 + d, d, d, 2 * d)
+    B, A, sig, st = _factors_with_stats(gpu, W, W_hat, Xt, r)
+    assert 0 < st["subspace_cycles"] <= 6, st
+    X = Xt.astype(np.float64)
+    L = np.linalg.cholesky(X @ X.T)
+    dW = W.astype(np.float64) - W_hat
+    U, s, _ = np.linalg.svd(dW @ L, full_matrices=False)
+    assert np.allclose(sig, s[:r], rtol=1e-9, atol=0), np.abs(sig / s[:r] - 1).max()
+    want = U[:, :r] @ (U[:, :r].T @ dW)
+    assert np.abs(B @ A - want).max() <= 1e-8 * np.abs(want).max()
