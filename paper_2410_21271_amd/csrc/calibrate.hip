@@ -447,9 +447,10 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __res
 // not read).  shape: GM_LOWER, only the tiles that touch the lower triangle (j0 <= i0) are computed (symmetric updates);
 // GM_B_LOWER, B[j][k] is zero for k < j (a lower triangle): the contraction begins at the tile's first column.
 // Bound by the fp64 matrix cores: 64 x 64 outputs per workgroup, a quarter per wavefront as 2 x 2 blocks of
-// v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS 32 k at a time.  256 rows x 4096 are one workgroup per
-// compute unit, so one wavefront per SIMD, and a stage lasts 0.9 us: its operands are requested two stages ahead (256 x 4096 x
-// 4096: 166 us, 52 TFLOP/s; 16 k and one stage ahead took 277).  The Gram matrix of 4096 x 8192: 3.7 ms (4.6).  Tiles of 128
+// v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS 32 k at a time and requested two stages ahead (16 k and one
+// ahead: 256 x 4096 x 4096 took 277 us).  256 rows x 4096 are one workgroup per compute unit, so one wavefront per SIMD and
+// nothing to do while it stages: in two parts, two workgroups a unit, 213 -> 174 us and 6 for the sum; with fragments of two k a
+// lane (one 16-byte LDS read where two of 8 were) 168, 51 TFLOP/s.  The Gram matrix of 4096 x 8192: 3.6 ms (3.7 before).  Tiles of 128
 // halve the operand traffic but leave fewer of them to share out (4.4 ms).  LDS rows of 34 doubles: the sixteen rows of a
 // fragment start in different banks.
 // part: null, or room for gridDim.z partial products, each over its share of k (gemm_sum_kernel adds them).
@@ -482,7 +483,7 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
                                                    double alpha, double beta, int shape, double* part)
 {
     constexpr int TILE = GM_TILE, KT = GM_KT, ST = KT + 2, E = TILE * KT / 256, FR = TILE / 32;
-    __shared__ double As[2][TILE * ST], Bs[2][TILE * ST];
+    __shared__ __attribute__((aligned(16))) double As[2][TILE * ST], Bs[2][TILE * ST];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
     const int i0 = blockIdx.y * TILE, j0 = blockIdx.x * TILE;
@@ -545,17 +546,21 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
         for (int f = 0; f < FR; ++f) acc[e][f] = d4{0, 0, 0, 0};
     auto contract = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int kk = 0; kk < KT / 4; ++kk) {
-            double a[FR], b[FR];
+        for (int kp = 0; kp < KT / 8; ++kp) {             // (eight k a pair of MFMAs: lane group g has 2 g and 2 g + 1 of them, one 16-byte read)
+            double2 a[FR], b[FR];
 #pragma unroll
             for (int e = 0; e < FR; ++e) {
-                a[e] = As[buf][(wi + 16 * e + n) * ST + 4 * kk + g];
-                b[e] = Bs[buf][(wj + 16 * e + n) * ST + 4 * kk + g];
+                a[e] = *reinterpret_cast<const double2*>(&As[buf][(wi + 16 * e + n) * ST + 8 * kp + 2 * g]);
+                b[e] = *reinterpret_cast<const double2*>(&Bs[buf][(wj + 16 * e + n) * ST + 8 * kp + 2 * g]);
             }
 #pragma unroll
             for (int e = 0; e < FR; ++e)
 #pragma unroll
-                for (int f = 0; f < FR; ++f) acc[e][f] = mfma64(a[e], b[f], acc[e][f]);
+                for (int f = 0; f < FR; ++f) acc[e][f] = mfma64(a[e].x, b[f].x, acc[e][f]);
+#pragma unroll
+            for (int e = 0; e < FR; ++e)
+#pragma unroll
+                for (int f = 0; f < FR; ++f) acc[e][f] = mfma64(a[e].y, b[f].y, acc[e][f]);
         }
     };
     // Stage sb + i waits in LDS buffer i % 2 and, two stages ahead, in register set i % 2 (stages past the end: the last one, not
@@ -1152,7 +1157,8 @@ void copy_doubles(const double* src, double* dst, size_t n, hipStream_t st)
 }
 
 // scratch (room for `room` doubles): where there are few tiles and a long contraction the compute units share the contraction
-// (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are added in order.
+// (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are added in order.  From 65 to 256
+// tiles are two and more workgroups a unit (gemm_kernel), as far as there is room.
 template <typename TA, typename TB>
 void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
           hipStream_t st, double alpha = 1.0, double beta = 0.0, int shape = GM_FULL, double* scratch = nullptr, size_t room = 0)
@@ -1163,8 +1169,8 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
     // 4096 x 4096 takes 46.5 ms instead of 46.1)
     if constexpr (std::is_same_v<TA, float>)
         if (!near_offsets(ai, ak, sizeof(TA)) || !near_offsets(bj, bk, sizeof(TB))) kern = gemm_kernel<TA, TB, true>;
-    if (scratch && tiles <= 64 && K >= 512 && shape != GM_B_LOWER) {
-        size_t parts = 256 / tiles;
+    if (scratch && tiles <= 256 && K >= 512 && shape != GM_B_LOWER) {
+        size_t parts = (tiles <= 64 ? 256 : 512) / tiles;
         if (parts > (size_t)K / 128) parts = K / 128;     // at least four stages each
         if (parts > room / ((size_t)M * N)) parts = room / ((size_t)M * N);
         if (parts > 1) {
@@ -1324,16 +1330,17 @@ void row_products(const double* T, int m, int n, double* S, hipStream_t st)
 
 // T: m x n.  On success (1) the first p rows of `work` (p x m) are an orthonormal basis that holds the r leading left
 // singular vectors of T; 0: not converged or not of rank p (the caller takes another way), < 0: runtime error.
-// S: m x m, T1: m x n, XT: r x n, work: 3 p m + 3 p^2 doubles, theta / res / lam: p doubles each.  *cycles: filters applied.
-int leading_subspace(const double* T, int m, int n, int r, int p, double* S, double* T1, double* XT, double* work, double* theta, double* res,
+// S: m x m, T1: m x n, XT: r x n, work: room_all >= 3 p m + 3 p^2 doubles, theta / res / lam: p doubles each.  *cycles: filters applied.
+int leading_subspace(const double* T, int m, int n, int r, int p, double* S, double* T1, double* XT, double* work, size_t room_all, double* theta, double* res,
                      double* lam, unsigned* rot, unsigned* flag, double* thr, hipStream_t st, int* cycles)
 {
     double* const Z = work;
     double* const Y = Z + (size_t)p * m;
-    double* const U = Y + (size_t)p * m;                  // scratch of the rotations
-    double* const G = U + (size_t)p * m;
+    double* const G = Y + (size_t)p * m;
     double* const R = G + (size_t)p * p;
     double* const F = R + (size_t)p * p;
+    double* const U = F + (size_t)p * p;                  // scratch of the rotations and of products in parts: the rest
+    const size_t room = room_all - 2 * (size_t)p * m - 3 * (size_t)p * p;
     double* const host = (double*)malloc(sizeof(double) * 2 * p);
     if (!host) return -2;
     double* const h_theta = host;
@@ -1344,12 +1351,12 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     *cycles = 0;
     row_products(T, m, n, S, st);
     auto times_s = [&](const double* A, double* C, int rows, double alpha, double beta) {
-        gemm(A, (long)m, 1L, (const double*)S, (long)m, 1L, C, (long)m, rows, m, m, st, alpha, beta);
+        gemm(A, (long)m, 1L, (const double*)S, (long)m, 1L, C, (long)m, rows, m, m, st, alpha, beta, GM_FULL, U, room);
     };
     // Ritz rotation of all p rows: Z <- Ritz vectors (descending), Y <- Z S, theta, residuals, on the host too
     auto ritz = [&]() -> int {
         times_s(Z, Y, p, 1.0, 0.0);
-        gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st, 1.0, 0.0, GM_FULL, U, (size_t)p * m);
+        gemm((const double*)Y, (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)p, p, p, m, st, 1.0, 0.0, GM_FULL, U, room);
         if (nl > 0)                                       // Y orthogonal to the locked rows: their products with it are F's first columns
             gemm((const double*)(F + (size_t)nl * p), (long)p, 1L, (const double*)Z, 1L, (long)m, Y + (size_t)nl * m, (long)m, p - nl, m, nl, st, -1.0, 1.0);
         hipLaunchKernelGGL(ritz_matrix_kernel, dim3(blocks((size_t)p * p)), dim3(256), 0, st, (const double*)F, G, p, nl, (const double*)theta, shift);
@@ -1377,7 +1384,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     hipLaunchKernelGGL(random_rows_kernel, dim3(blocks((size_t)p * m)), dim3(256), 0, st, Y, (size_t)p * m);
     for (int it = 0; it < 2; ++it) {
         times_s(Y, Z, p, 1.0, 0.0);
-        orthonormalise(Z, p, m, F, R, U, (size_t)p * m, thr, flag, st);
+        orthonormalise(Z, p, m, F, R, U, room, thr, flag, st);
         if (it == 0) copy_doubles(Z, Y, (size_t)p * m, st);
     }
     int rc = ritz(), stalled = 0;
@@ -1406,10 +1413,10 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         }
         if (y1 != Z + (size_t)nl * m) copy_doubles(y1, Z + (size_t)nl * m, (size_t)rows * m, st);
         if (nl > 0) {                                     // against the rows taken out: z -= (z X^T) X
-            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st, 1.0, 0.0, GM_FULL, U, (size_t)p * m);
+            gemm((const double*)(Z + (size_t)nl * m), (long)m, 1L, (const double*)Z, (long)m, 1L, F, (long)nl, rows, nl, m, st, 1.0, 0.0, GM_FULL, U, room);
             gemm((const double*)F, (long)nl, 1L, (const double*)Z, 1L, (long)m, Z + (size_t)nl * m, (long)m, rows, m, nl, st, -1.0, 1.0);
         }
-        orthonormalise(Z + (size_t)nl * m, rows, m, F, R, U, (size_t)p * m, thr, flag, st);
+        orthonormalise(Z + (size_t)nl * m, rows, m, F, R, U, room, thr, flag, st);
         rc = ritz();
         if (rc != 1) break;
         double worst = 0.0;
@@ -1620,7 +1627,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
         if (timed) hipEventRecord(e0, st);
         int cycles = 0;
-        sub = leading_subspace(T, m, n, r, p, H, T0, by_rows ? Ap : Bn, V, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st, &cycles);
+        sub = leading_subspace(T, m, n, r, p, H, T0, by_rows ? Ap : Bn, V, (size_t)k * k, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st, &cycles);
         if (stats) stats[0] = sub == 1 ? cycles : -cycles;
         if (sub == 1) {
             gemm((const double*)V, (long)m, 1L, (const double*)T, 1L, (long)n, T0, (long)n, p, n, m, st);      // Z T
