@@ -656,7 +656,7 @@ __global__ __launch_bounds__(1024) void pivot_floor_kernel(const double* __restr
 // below and the trailing ones are products on the matrix cores.  The block's strict upper part is zeroed.  Then, unless
 // inv is null, inv = L11^-1 (always 64 x 64, row-major), blockwise on the matrix cores too, so that the rows below the
 // block and the right-hand sides of a solve are products.  Bound by the chain of 64 pivots.  (Left-looking over the whole 64
-// columns by one wavefront, two LDS reads per multiplication: 94 us; now 21.)
+// columns by one wavefront, two LDS reads per multiplication: 94 us; with the inverse behind the factor 21; in one pass over the columns 19.)
 // the value of lane LANE of the caller's row of 16 lanes
 template <int LANE>
 __device__ __forceinline__ double row_value(double v)
@@ -705,34 +705,29 @@ __global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A
     for (int jb = 0; jb < 4; ++jb) {
         if (wave == 0) {
             bool bad = false;
-            double a[16], rinv[16];
+            double a[16], y[16];        // row n of the block; column n of its inverse (until y[j] is due: the identity's less what was eliminated)
 #pragma unroll
-            for (int c = 0; c < 16; ++c) a[c] = S[16 * jb + n][16 * jb + c];
+            for (int c = 0; c < 16; ++c) {
+                a[c] = S[16 * jb + n][16 * jb + c];
+                y[c] = c == n ? 1.0 : 0.0;
+            }
             unrolled<16>([&](auto jt) __attribute__((always_inline)) {
                 constexpr int j = decltype(jt)::value;
                 double d = row_value<j>(a[j]);
                 const bool low = 16 * jb + j < nb && !(d > floor_abs);       // not (numerically) positive definite: give up, stay finite
                 bad = bad || low;
                 d = low ? (floor_abs > 0.0 ? floor_abs : 1.0) : d;
-                const double y = rsq_newton(d);
-                double root = d * y;
-                root = fma(fma(-root, root, d), 0.5 * y, root);
-                rinv[j] = y;
-                a[j] = n == j ? root : a[j] * y;
+                const double rinv = rsq_newton(d);
+                double root = d * rinv;
+                root = fma(fma(-root, root, d), 0.5 * rinv, root);
+                a[j] = n == j ? root : a[j] * rinv;
+                y[j] *= rinv;
                 unrolled<15 - j>([&](auto kt) __attribute__((always_inline)) {
                     constexpr int k = j + 1 + decltype(kt)::value;
-                    a[k] = fma(-a[j], row_value<k>(a[j]), a[k]);
+                    const double l = row_value<k>(a[j]);  // (the entry that eliminates in the block and in its inverse)
+                    a[k] = fma(-a[j], l, a[k]);
+                    y[k] = fma(-l, y[j], y[k]);
                 });
-            });
-            double y[16];
-            unrolled<16>([&](auto rt) __attribute__((always_inline)) {
-                constexpr int r = decltype(rt)::value;
-                double v = r == n ? 1.0 : 0.0;
-                unrolled<r>([&](auto kt) __attribute__((always_inline)) {
-                    constexpr int k = decltype(kt)::value;
-                    v = fma(-row_value<r>(a[k]), y[k], v);
-                });
-                y[r] = v * rinv[r];
             });
             if (lane < 16) {
 #pragma unroll
@@ -1294,6 +1289,10 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
 
 // ---- host side of the filtered subspace iteration (see random_rows_kernel) ----------------------------------
 constexpr int SUB_CYCLES = 14;
+// Products with S before the first Ritz rotation, whose sweeps are the most expensive (11 of 31 rounds from a random block, some 0.2 ms
+// each, where a product and one orthonormalisation take 0.4 ms).  Two, five, seven and nine, in ms: 4096 x 4096, rank 128 37.2, 34.2,
+// 35.0, 34.9; 1024 x 4096, rank 64 -, 9.3, 8.5, 8.3; 640 x 578, rank 32 -, 6.9, 5.9, 6.1.
+constexpr int SUB_POWERS = 7;
 constexpr double SUB_SPREAD = 27.6;         // ln 1e12: growth of the largest Ritz direction over the smallest per filter
 constexpr double SUB_TOL = 1e-12;           // residual of a leading vector, relative to its Ritz value
 constexpr double SUB_DOWNDATE = 1e4;        // spread of the Ritz values up to which S is updated instead of formed again
@@ -1304,13 +1303,13 @@ int subspace_size(int r) { return ((2 * r > r + 64 ? 2 * r : r + 64) + 127) / 12
 // rows cost more: 4096 x 4096 with r = 128, 0.78 s of sweeps)
 bool subspace_fits(int m, int r) { return subspace_size(r) <= m / 4; }
 
-// the p rows of Z (length L) made orthonormal; F, inv: p x p scratch each (p >= 64), scratch: `room` doubles
-void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* scratch, size_t room, double* thr, unsigned* flag, hipStream_t st)
+// the p rows of Z (length L) made orthonormal (passes == 1: nearly, for a block that another product follows); F, inv: p x p scratch each (p >= 64), scratch: `room` doubles
+void orthonormalise(double* Z, int p, int L, double* F, double* inv, double* scratch, size_t room, double* thr, unsigned* flag, hipStream_t st, bool clear = true, int passes = 2)
 {
     hipLaunchKernelGGL(normalise_rows_kernel, dim3(p), dim3(256), 0, st, Z, L);
-    for (int pass = 0; pass < 2; ++pass) {
+    for (int pass = 0; pass < passes; ++pass) {
         gemm((const double*)Z, (long)L, 1L, (const double*)Z, (long)L, 1L, F, (long)p, p, p, L, st, 1.0, 0.0, GM_LOWER, scratch, room);
-        cholesky(F, p, 1e-14, thr, flag, inv, st, pass == 0, true);
+        cholesky(F, p, 1e-14, thr, flag, inv, st, clear && pass == 0, true);
         for (int j0 = 0; j0 < p; j0 += CH_NB) {
             const int nb = p - j0 < CH_NB ? p - j0 : CH_NB;
             if (j0 > 0)                     // rows j0 .. -= F[j0 .., 0 .. j0) Z[0 .. j0)
@@ -1382,11 +1381,11 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         return bad == 0 && h_theta[p - 1] > 0.0 && std::isfinite(h_theta[0]) ? 1 : 0;
     };
     hipLaunchKernelGGL(random_rows_kernel, dim3(blocks((size_t)p * m)), dim3(256), 0, st, Y, (size_t)p * m);
-    for (int it = 0; it < 2; ++it) {
-        times_s(Y, Z, p, 1.0, 0.0);
-        orthonormalise(Z, p, m, F, R, U, room, thr, flag, st);
-        if (it == 0) copy_doubles(Z, Y, (size_t)p * m, st);
+    for (int it = 0; it < SUB_POWERS; ++it) {
+        times_s(it & 1 ? Z : Y, it & 1 ? Y : Z, p, 1.0, 0.0);
+        orthonormalise(it & 1 ? Y : Z, p, m, F, R, U, room, thr, flag, st, it == 0, it == SUB_POWERS - 1 ? 2 : 1);
     }
+    static_assert(SUB_POWERS % 2 == 1, "the last product goes to Z");
     int rc = ritz(), stalled = 0;
     double before = 1.0;
     for (int cycle = 0; rc == 1 && cycle < SUB_CYCLES; ++cycle) {
