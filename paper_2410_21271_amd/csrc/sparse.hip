@@ -354,10 +354,13 @@ __device__ __forceinline__ void sparse_body(const SparseArgs& a, const int gbid,
 
 
 // ---------------------------------------------------------------------------------------------------
-// More than 4 tokens and many output rows: one wavefront per row block (whole contraction length), NW row
-// blocks and up to TB token blocks of 16 per workgroup.  A token block's x is 1.8x the bytes of a row
+// More than 4 tokens and many output rows: RW row blocks per wavefront (whole contraction length), NW wavefronts
+// and up to TB token blocks of 16 per workgroup.  A token block's x is 1.8x the bytes of a row
 // block's weights, so x is shared through LDS by the NW wavefronts, and a stored tile, once in registers,
-// serves all TB token blocks.  Per step one 128-column chunk: x[16 TB tokens][128] goes global ->
+// serves all TB token blocks.  Every wavefront reads the whole chunk of x from LDS: sixteen row blocks as eight wavefronts of
+// two read half of what sixteen of one did.  A tile is decoded while the one before it is multiplied.  70B gate + up at 64 tokens,
+// 4-bit kept values 92 -> 84.5 us, o 26.9 -> 25.1, fp16 values 119 -> 115; two members of 14336 rows, d_in 4096: 44 -> 36.4.  What is
+// left of a step (1.25 us of 128 columns) is no one unit's: without the products 0.82 of it, without the tiles 0.77, without decoding 0.82.  Per step one 128-column chunk: x[16 TB tokens][128] goes global ->
 // registers (requested XW_D steps before its LDS write) -> one of two LDS slots, and the wavefront's stored
 // tile of the same columns is requested XW_D steps ahead as well.  All requests are plain loads: with
 // global -> LDS copies among them the compiler would no longer count on in-order answers and would drain
@@ -367,7 +370,7 @@ __device__ __forceinline__ void sparse_body(const SparseArgs& a, const int gbid,
 // LDS slot layout: 16-byte piece q of token row t (columns 8q .. 8q+7 of the chunk) sits at piece index
 // 16 t + (q ^ (t & 15)): the 16 lanes that read one q for 16 tokens hit 16 different bank groups.
 // Producers, flags, partials and the continuation are those of the kernel above.
-template <int FA, int NW, int TB, int XW_D, bool VQ, bool ONCE>      // XW_D: steps between a request and its use; divides d_in / 128; ONCE: one group of token blocks, so every stored tile is read by one workgroup
+template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE>      // RW: row blocks per wavefront; XW_D: steps between a request and its use; divides d_in / 128; ONCE: one group of token blocks, so every stored tile is read by one workgroup
 __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int gbid, const int bid, const int flag0)
 {
     constexpr bool LOWRANK = FA != S_NONE;
@@ -439,9 +442,12 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
     const int cidx = (bid - nprod) / KS;
     const int tg = cidx % NTG, rg = cidx / NTG;
     const int m0 = tg * TB * 16;                          // first token of the group
-    const int Rw = rg * NW + wave;
-    const bool active = Rw < RBs;                         // a ragged last row group: the wavefront only helps staging
-    const int R = active ? Rw : RBs - 1;
+    int R[RW];
+#pragma unroll
+    for (int rw = 0; rw < RW; ++rw) {
+        const int Rw = (rg * NW + wave) * RW + rw;
+        R[rw] = Rw < RBs ? Rw : RBs - 1;                  // a ragged last row group: computed on the last block, not stored
+    }
     const int G = a.d_in / 128;                           // chunks = stored tiles per row block
     const int Gs = G / KS, c0 = ks * Gs;                  // this range's chunks
     // piece q of a chunk: token rows 4 q .. 4 q + 3, lane -> row 4 q + lane / 16, 16-byte piece lane % 16
@@ -454,14 +460,23 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
         xsrc[i] = a.x + (size_t)grow * a.d_in + (size_t)c0 * 128 + 8 * (lane & 15);      // (chunk s of the range at + s * 128)
         xdst[i] = (trow * 16 + ((lane & 15) ^ (trow & 15))) * 16;
     }
-    auto load_tile = [&](SpT<VQ>& t, int c) { load_sptile<VQ, ONCE>(t, a, R, c0 + c, G, lane); };      // c: chunk within the range
-    SpT<VQ> buf[XW_D];
+    auto load_tile = [&](SpT<VQ>& t, int rw, int c) { load_sptile<VQ, ONCE>(t, a, R[rw], c0 + c, G, lane); };      // c: chunk within the range
+    SpT<VQ> buf[XW_D][RW];
     u4 xr[XW_D][XN];
+    // Requests in the order of the loop below (chunk c + 1 of x before tile c), so that the compiler counts as many behind the one it
+    // waits for at the loop's entry as within it: a wait serves both, and in any other order it is for requests of a step or two ago.
+    auto load_x = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < XN; ++i) xr[c % XW_D][i] = *(const u4*)(xsrc[i] + (c < Gs ? c : Gs - 1) * 128);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load_x(0);
 #pragma unroll
     for (int s = 0; s < XW_D; ++s) {                      // Gs is a multiple of XW_D
+        if (s + 1 < XW_D) load_x(s + 1);
 #pragma unroll
-        for (int i = 0; i < XN; ++i) xr[s][i] = *(const u4*)(xsrc[i] + s * 128);
-        load_tile(buf[s], s);
+        for (int rw = 0; rw < RW; ++rw) load_tile(buf[s][rw], rw, s);
+        __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (LOWRANK) {
         if (tid == 0) {
@@ -471,51 +486,65 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
     }
     // chunk 0 -> slot 0; its registers take chunk XW_D
 #pragma unroll
-    for (int i = 0; i < XN; ++i) {
-        *(u4*)(eora_smem + xdst[i]) = xr[0][i];
-        xr[0][i] = *(const u4*)(xsrc[i] + (XW_D < Gs ? XW_D : Gs - 1) * 128);
-    }
+    for (int i = 0; i < XN; ++i) *(u4*)(eora_smem + xdst[i]) = xr[0][i];
+    load_x(XW_D);
 
-    f4 acc[TB];
+    f4 acc[RW][TB];
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) acc[tb] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int rw = 0; rw < RW; ++rw)
+#pragma unroll
+        for (int tb = 0; tb < TB; ++tb) acc[rw][tb] = f4{0.f, 0.f, 0.f, 0.f};
     // piece offsets of this lane's four dense-operand reads of a token block: (blk, half) -> piece 8 blk + 4 half + j
     int poff[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) poff[q] = (n * 16 + ((8 * (q >> 1) + 4 * (q & 1) + j) ^ n)) * 16;
 
+    // the tile of a chunk is decoded while the one before it is multiplied, and a token block's fragments are read a token block ahead
+    h8 sa[2][RW][2];
+#pragma unroll
+    for (int rw = 0; rw < RW; ++rw) sp_operands<VQ>(buf[0][rw], sa[0][rw][0], sa[0][rw][1]);
+    static_assert(XW_D % 2 == 0, "two sets of operands in turn");
     for (int base = 0; base < Gs; base += XW_D) {
 #pragma unroll
         for (int s = 0; s < XW_D; ++s) {
             const int c = base + s;
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // own LDS writes of chunk c done
             __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const unsigned char* xs = eora_smem + (c & 1) * SLOT;
+            h8 xf[2][4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) xf[0][q] = *(const h8*)(xs + poff[q]);
             // chunk c + 1 -> the slot everyone has just left; its registers take the chunk XW_D further on
             // (past the end: the last chunk again, never used)
             const int s1 = (s + 1) % XW_D;
             const int cx = c + 1 + XW_D < Gs ? c + 1 + XW_D : Gs - 1;
-#pragma unroll
-            for (int i = 0; i < XN; ++i) {
-                *(u4*)(eora_smem + ((c + 1) & 1) * SLOT + xdst[i]) = xr[s1][i];
-                xr[s1][i] = *(const u4*)(xsrc[i] + cx * 128);
-            }
             __builtin_amdgcn_sched_barrier(0);
-            const unsigned char* xs = eora_smem + (c & 1) * SLOT;
-            h8 sa0, sa1;
-            sp_operands<VQ>(buf[s], sa0, sa1);
 #pragma unroll
             for (int tb = 0; tb < TB; ++tb) {
-                const unsigned char* px = xs + tb * 4096;
-                const h8 x00 = *(const h8*)(px + poff[0]), x01 = *(const h8*)(px + poff[1]);
-                const h8 x10 = *(const h8*)(px + poff[2]), x11 = *(const h8*)(px + poff[3]);
-                const h16 xa = __builtin_shufflevector(x00, x01, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                const h16 xb = __builtin_shufflevector(x10, x11, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
-                acc[tb] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(sa0, xa, acc[tb], sp_idx(buf[s]), 0, 0);
-                acc[tb] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(sa1, xb, acc[tb], sp_idx(buf[s]), 0, 1);
+                if (tb + 1 < TB) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) xf[(tb + 1) & 1][q] = *(const h8*)(xs + (tb + 1) * 4096 + poff[q]);
+                }
+                const h16 xa = __builtin_shufflevector(xf[tb & 1][0], xf[tb & 1][1], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+                const h16 xb = __builtin_shufflevector(xf[tb & 1][2], xf[tb & 1][3], 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
+#pragma unroll
+                for (int rw = 0; rw < RW; ++rw) acc[rw][tb] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(sa[s & 1][rw][0], xa, acc[rw][tb], sp_idx(buf[s][rw]), 0, 0);
+#pragma unroll
+                for (int rw = 0; rw < RW; ++rw) acc[rw][tb] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(sa[s & 1][rw][1], xb, acc[rw][tb], sp_idx(buf[s][rw]), 0, 1);
+#pragma unroll
+                for (int rw = 0; rw < RW; ++rw)
+                    if (rw * TB / RW == tb) sp_operands<VQ>(buf[s1][rw], sa[(s + 1) & 1][rw][0], sa[(s + 1) & 1][rw][1]);
+#pragma unroll
+                for (int i = XN * tb / TB; i < XN * (tb + 1) / TB; ++i) {
+                    *(u4*)(eora_smem + ((c + 1) & 1) * SLOT + xdst[i]) = xr[s1][i];
+                    xr[s1][i] = *(const u4*)(xsrc[i] + cx * 128);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
             // the tile's registers are free again: the request for the tile XW_D chunks on goes out last
-            __builtin_amdgcn_sched_barrier(0);
-            load_tile(buf[s], c + XW_D < Gs ? c + XW_D : Gs - 1);
+#pragma unroll
+            for (int rw = 0; rw < RW; ++rw) load_tile(buf[s][rw], rw, c + XW_D < Gs ? c + XW_D : Gs - 1);
         }
     }
 
@@ -529,9 +558,11 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
         const int nb = lds_floats / tsz;                  // >= 1
         const Factor fb{(const uint32_t*)a.B, nullptr, a.r / 32};
         constexpr int BPRE = 4;                           // B's first tiles are requested before the wait for t
-        FTile<S_F16> bt[BPRE];
+        FTile<S_F16> bt[BPRE][RW];
 #pragma unroll
-        for (int g = 0; g < BPRE; ++g) load_ftile<S_F16, ONCE>(bt[g], fb, R, g < fb.ntk ? g : 0, lane);
+        for (int g = 0; g < BPRE; ++g)
+#pragma unroll
+            for (int rw = 0; rw < RW; ++rw) load_ftile<S_F16, ONCE>(bt[g][rw], fb, R[rw], g < fb.ntk ? g : 0, lane);
         __syncthreads();                                  // nobody reads x any more
         const uint32_t epoch = s_epoch;
         if (wave == 0) {
@@ -584,9 +615,7 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
                     const int mt = a.M - 16 * yb < 16 ? a.M - 16 * yb : 16;
                     const int mrow = n < mt ? n : 0;
                     const float* tq = ts + (tb % nb) * tsz + mrow * a.r + 8 * j;
-                    auto contract = [&](const FTile<S_F16>& cur, int g) {
-                        h8 b[1];
-                        decode_tile<S_F16>(cur.w, 0u, b);
+                    auto contract = [&](const FTile<S_F16> (&cur)[RW], int g) {
                         const float* p = tq + g * 32;
                         const f4 v0 = *(const f4*)p, v1 = *(const f4*)(p + 4);
                         const float e0[4] = {v0.x, v0.y, v0.z, v0.w}, e1[4] = {v1.x, v1.y, v1.z, v1.w};
@@ -599,15 +628,21 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
                             lo[i] = (_Float16)(e0[i] - (float)h0);
                             lo[4 + i] = (_Float16)(e1[i] - (float)h1);
                         }
-                        acc[tb] = mfma16(b[0], hi, acc[tb]);
-                        acc[tb] = mfma16(b[0], lo, acc[tb]);
+#pragma unroll
+                        for (int rw = 0; rw < RW; ++rw) {
+                            h8 b[1];
+                            decode_tile<S_F16>(cur[rw].w, 0u, b);
+                            acc[rw][tb] = mfma16(b[0], hi, acc[rw][tb]);
+                            acc[rw][tb] = mfma16(b[0], lo, acc[rw][tb]);
+                        }
                     };
 #pragma unroll
                     for (int g = 0; g < BPRE; ++g)
                         if (g < fb.ntk) contract(bt[g], g);
                     for (int g = BPRE; g < fb.ntk; ++g) {
-                        FTile<S_F16> cur;
-                        load_ftile<S_F16, ONCE>(cur, fb, R, g, lane);
+                        FTile<S_F16> cur[RW];
+#pragma unroll
+                        for (int rw = 0; rw < RW; ++rw) load_ftile<S_F16, ONCE>(cur[rw], fb, R[rw], g, lane);
                         contract(cur, g);
                     }
                 }
@@ -620,14 +655,16 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
 #pragma unroll
     for (int tb = 0; tb < TB; ++tb) {
         const int m = m0 + 16 * tb + n;
-        if (active && m < a.M) {
-            const f4 v = acc[tb];
+#pragma unroll
+        for (int rw = 0; rw < RW; ++rw) {
+            if ((rg * NW + wave) * RW + rw >= RBs || m >= a.M) continue;
+            const f4 v = acc[rw][tb];
             if (KS > 1) {                                 // this range's fp32 partial output
-                *(f4*)(a.ypart + ((size_t)ks * a.M + m) * a.d_out + R * 16 + 4 * j) = v;
+                *(f4*)(a.ypart + ((size_t)ks * a.M + m) * a.d_out + R[rw] * 16 + 4 * j) = v;
             } else {
                 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
                 const h4 o = {(_Float16)v.x, (_Float16)v.y, (_Float16)v.z, (_Float16)v.w};
-                *(h4*)(a.y + (size_t)m * a.d_out + R * 16 + 4 * j) = o;
+                *(h4*)(a.y + (size_t)m * a.d_out + R[rw] * 16 + 4 * j) = o;
             }
         }
     }
@@ -662,17 +699,22 @@ __global__ __launch_bounds__(NW * 64, 6) void sparse_group_kernel(SparseGroupArg
     sparse_body<FA, FE, NW, XLDS, VQ>(grp.m[mem], blockIdx.x, (int)blockIdx.x - grp.first[mem], grp.flag0[mem]);
 }
 
-template <int FA, int NW, int TB, int XW_D, bool VQ, bool ONCE>
-__global__ __launch_bounds__(NW * 64) void sparse_wide_kernel(SparseArgs a)
+// Wavefronts per SIMD that the registers of a single linear's kernel leave room for: two workgroups of eight row blocks a compute unit
+// with 4-bit kept values (28672 -> 8192 in four ranges, 256 workgroups and the producers: 56.6 us with 133 registers, 54 with
+// 128).  A group's kernel needs five registers more and spills at 128 (two members of 14336 rows, d_in 4096: 36.4 us, 45.9 with the spills).
+constexpr int sp_waves(int nw, int rw, bool vq) { return vq && nw == 8 && rw == 1 ? 4 : 1; }
+
+template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE>
+__global__ __launch_bounds__(NW * 64, sp_waves(NW, RW, VQ)) void sparse_wide_kernel(SparseArgs a)
 {
-    sparse_wide_body<FA, NW, TB, XW_D, VQ, ONCE>(a, blockIdx.x, blockIdx.x, 0);
+    sparse_wide_body<FA, NW, RW, TB, XW_D, VQ, ONCE>(a, blockIdx.x, blockIdx.x, 0);
 }
 
-template <int FA, int NW, int TB, int XW_D, bool VQ, bool ONCE>
+template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE>
 __global__ __launch_bounds__(NW * 64) void sparse_wide_group_kernel(SparseGroupArgs grp)
 {
     const int mem = sparse_member(grp);
-    sparse_wide_body<FA, NW, TB, XW_D, VQ, ONCE>(grp.m[mem], blockIdx.x, (int)blockIdx.x - grp.first[mem], grp.flag0[mem]);
+    sparse_wide_body<FA, NW, RW, TB, XW_D, VQ, ONCE>(grp.m[mem], blockIdx.x, (int)blockIdx.x - grp.first[mem], grp.flag0[mem]);
 }
 
 // fills the member table; blocks(i) = workgroups of member i
@@ -690,7 +732,7 @@ static int fill_group(SparseGroupArgs& g, const SparseArgs* members, int n, int 
     return total;
 }
 
-template <int FA, int NW, int TB, int XW_D, bool VQ, bool ONCE = false>
+template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE = false>
 static hipError_t launch_sparse_wide(const SparseArgs* members, int n, hipStream_t stream)
 {
     const SparseArgs& a = members[0];
@@ -698,10 +740,10 @@ static hipError_t launch_sparse_wide(const SparseArgs* members, int n, hipStream
     const size_t lds = xb > tb ? xb : tb;
     const int yblocks = (a.M + 15) / 16;
     const int units = (FA != S_NONE) ? (a.r / 16) * a.kcn : 0;
-    auto blocks = [&](const SparseArgs& m) { return ((m.d_out / 16 + NW - 1) / NW) * ((yblocks + TB - 1) / TB) * m.ksplit + units * yblocks; };
-    note_launch("sparse_wide FA=%d NW=%d TB=%d VQ=%d n=%d ksplit=%d", FA, NW, TB, (int)VQ, n, a.ksplit);
+    auto blocks = [&](const SparseArgs& m) { return ((m.d_out / 16 + NW * RW - 1) / (NW * RW)) * ((yblocks + TB - 1) / TB) * m.ksplit + units * yblocks; };
+    note_launch("sparse_wide FA=%d NW=%d TB=%d VQ=%d n=%d ksplit=%d", FA, NW * RW, TB, (int)VQ, n, a.ksplit);
     if (n == 1) {
-        auto kern = sparse_wide_kernel<FA, NW, TB, XW_D, VQ, ONCE>;
+        auto kern = sparse_wide_kernel<FA, NW, RW, TB, XW_D, VQ, ONCE>;
         if (lds > 48 * 1024) {
             hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
@@ -712,7 +754,7 @@ static hipError_t launch_sparse_wide(const SparseArgs* members, int n, hipStream
         // y = fp16(sum of the ranges' partial outputs, in the order of the ranges)
         return launch_reduce_parts(a.ypart, a.y, (size_t)a.M * a.d_out, a.ksplit, stream);
     }
-    auto kern = sparse_wide_group_kernel<FA, NW, TB, XW_D, VQ, ONCE>;
+    auto kern = sparse_wide_group_kernel<FA, NW, RW, TB, XW_D, VQ, ONCE>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -736,16 +778,16 @@ static hipError_t launch_sparse_wide_cfg(const SparseArgs* members, int n, int n
     // (70B 2:4 layer at 64 tokens: gate+up 120.7 -> 110.2 us with non-temporal requests; the launches in which two
     // groups of token blocks read the same tiles lose 6-10 % with them and keep ordinary loads)
     const bool once = members[0].M <= 16 * tb;
-    if (nw == 16) return once ? launch_sparse_wide<FA, 16, 4, 4, VQ, true>(members, n, stream)       // sixteen row blocks: four token blocks (one 1 KiB piece per wavefront)
-                              : launch_sparse_wide<FA, 16, 4, 4, VQ>(members, n, stream);
+    if (nw == 16) return once ? launch_sparse_wide<FA, 8, 2, 4, 4, VQ, true>(members, n, stream)       // sixteen row blocks: four token blocks
+                              : launch_sparse_wide<FA, 8, 2, 4, 4, VQ>(members, n, stream);
     if (nw == 8) {                                        // eight row blocks: two or four token blocks (whole 1 KiB pieces per wavefront)
-        if (tb == 2) return launch_sparse_wide<FA, 8, 2, 4, VQ>(members, n, stream);
-        return once ? launch_sparse_wide<FA, 8, 4, 4, VQ, true>(members, n, stream) : launch_sparse_wide<FA, 8, 4, 4, VQ>(members, n, stream);
+        if (tb == 2) return launch_sparse_wide<FA, 8, 1, 2, 4, VQ>(members, n, stream);
+        return once ? launch_sparse_wide<FA, 8, 1, 4, 4, VQ, true>(members, n, stream) : launch_sparse_wide<FA, 8, 1, 4, 4, VQ>(members, n, stream);
     }
     // four row blocks: one or two token blocks (with three or four of them the eight-row-block split above
     // always has its 192 workgroups too, and comes first)
-    if (tb == 2) return launch_sparse_wide<FA, 4, 2, 4, VQ>(members, n, stream);
-    if (tb == 1) return launch_sparse_wide<FA, 4, 1, 4, VQ>(members, n, stream);
+    if (tb == 2) return launch_sparse_wide<FA, 4, 1, 2, 4, VQ>(members, n, stream);
+    if (tb == 1) return launch_sparse_wide<FA, 4, 1, 1, 4, VQ>(members, n, stream);
     return hipErrorInvalidValue;
 }
 

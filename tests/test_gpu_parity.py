@@ -419,6 +419,21 @@ def test_linear_sp24_many_tokens_many_rows(gpu, r, M, d_in, d_out):
     assert np.array_equal(y, run_linear_sp24(c))
 
 
+@pytest.mark.parametrize("d_out", [24368, 24576])
+@pytest.mark.parametrize("r", [0, 64])
+@pytest.mark.parametrize("quantised", [False, True])
+def test_sparse_two_row_blocks_per_wavefront(gpu, quantised, r, d_out):
+    """Sixteen row blocks per workgroup, two per wavefront: with a last group of three of them (a wavefront with one row block, six with
+    none) and whole; token blocks of which the last is ragged; the shortest contraction."""
+    from tests.cases import SparseCase, SparseQCase
+    from tests.gpu_util import run_linear_sp24, run_linear_sp24q4
+    case, run = (SparseQCase, run_linear_sp24q4) if quantised else (SparseCase, run_linear_sp24)
+    c = case(2500 + r + d_out, 512, d_out, 100, r, packer=gpu)
+    y = run(c)
+    assert gpu.debug_last_launch() == "sparse_wide FA=%d NW=16 TB=4 VQ=%d n=1 ksplit=1" % (5 if r else 0, quantised), gpu.debug_last_launch()
+    _check(y, c.oracle_y())
+
+
 def test_sparse_many_tokens_different_inputs_on_one_workspace(gpu):
     """The many-token 2:4 kernel hands t over as untagged fp32 partials behind flags: two different activations, then
     a different layer, then the first again, back to back on ONE workspace that is never cleared in between.  A
