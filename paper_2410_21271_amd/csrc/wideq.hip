@@ -793,7 +793,7 @@ static WidePlan wide_plan(const WideArgs& a)
     // 21.4 -> 22.7) and 8 stays.  Measured on one-linear launches of 64 and 24 tokens, contractions of 4096 .. 14336 (down
     // projection of the 8B layer, 64 tokens: two row blocks per workgroup and one part 46.9 us, eight and seven parts 27.3).
     static const int per[4] = {8, 4, 2, 1}, ranges[4] = {2, 2, 4, 8};
-    static const float STEP[3][4] = {{0.5f, 0.4f, 0.45f, 0.6f}, {0.85f, 0.55f, 0.65f, 1.2f}, {1.2f, 0.85f, 1.3f, 2.8f}};
+    static const float STEP[4][4] = {{0.5f, 0.4f, 0.45f, 0.6f}, {0.85f, 0.55f, 0.65f, 1.2f}, {1.f, 0.7f, 1.f, 2.f}, {1.2f, 0.85f, 1.3f, 2.8f}};
     const int yblocks = (a.M + 15) / 16, G = a.d_in / 128;
     size_t rows = 0;
     for (int i = 0; i < a.n; ++i) rows += a.d_out[i];
@@ -803,10 +803,16 @@ static WidePlan wide_plan(const WideArgs& a)
         for (int i = 0; i < a.n; ++i) cons += (a.d_out[i] / 16 + per[c] - 1) / per[c] * ntg;
         return cons * S + (a.r > 0 ? a.n * (a.r / 16) * wide_kcn(a, tb) * ntg : 0);
     };
-    WidePlan best{yblocks >= 3 ? 4 : yblocks, 0, 1};
+    // Three token blocks where they make as many groups as four would (33..48, 65..96, 129..144 tokens): a step's requests for x,
+    // fragments and MFMAs are a quarter fewer.  40 x 4096 x 2 x 14336 W4, rank 128: 29.2 -> 27.0 us; 48 x 8192 x 28672 W3 49.8 -> 44.9;
+    // 96 x 8192 x 8192 W3 46.5 -> 41.0; 70 tokens, q+k+v of 4096, W2 24.5 -> 21.4.  Contractions beyond 32768 were not measured and keep
+    // four.  The sum of parts costs a launch more here (1 instead of 2.5: 37 x 7296 x 2688 W3 in five parts 18.7 us, whole with two
+    // token blocks 18.1).
+    const bool three = G <= 256 && (yblocks + 2) / 3 == (yblocks + 3) / 4;
+    WidePlan best{yblocks < 3 ? yblocks : three ? 3 : 4, 0, 1};
     const int tb = best.tb;
-    const float* const step_us = STEP[tb == 4 ? 2 : tb - 1];
-    const float sum0 = tb == 4 ? 1.f : 8.f, sum_part = tb == 4 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
+    const float* const step_us = STEP[tb - 1];
+    const float sum0 = tb == 4 ? 1.f : tb == 3 ? 2.5f : 8.f, sum_part = tb >= 3 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
     float best_us = 1e30f;
     for (int c = a.M <= 4 ? 1 : 0; c < 4; ++c) {
         // workgroups the chip holds (registers)
@@ -875,12 +881,14 @@ static hipError_t launch_wide_fm(WideArgs a, hipStream_t stream)
         switch (p.tb) {
             case 1: return launch_wide_cfg<FM, 1, true>(a, p.cfg, stream);
             case 2: return launch_wide_cfg<FM, 2, true>(a, p.cfg, stream);
+            case 3: return launch_wide_cfg<FM, 3, true>(a, p.cfg, stream);
             default: return launch_wide_cfg<FM, 4, true>(a, p.cfg, stream);
         }
     }
     switch (p.tb) {
         case 1: return launch_wide_cfg<FM, 1, false>(a, p.cfg, stream);
         case 2: return launch_wide_cfg<FM, 2, false>(a, p.cfg, stream);
+        case 3: return launch_wide_cfg<FM, 3, false>(a, p.cfg, stream);
         default: return launch_wide_cfg<FM, 4, false>(a, p.cfg, stream);
     }
 }

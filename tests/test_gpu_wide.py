@@ -173,6 +173,25 @@ def test_smaller_workspace_leaves_the_contraction_whole(gpu):
     assert _parts(gpu)[0] == 1
 
 
+@pytest.mark.parametrize("M,d_in,d_out,r,w_bits,ab_bits", [
+    (33, 640, 9216, 32, 3, 16),             # one group, its last block with one token
+    (48, 256, 20480, 64, 4, 4),             # full; two row blocks per wavefront; a single tile per range
+    (65, 384, 6160, 96, 2, 16),             # two groups, the second with two blocks; an odd number of chunks, a ragged last row group
+    (96, 16640, 2048, 0, 4, 16),            # parts of a long contraction
+    (144, 256, 4112, 32, 4, 16),            # three groups, the most tokens that take three blocks
+])
+def test_wide_three_token_blocks(gpu, M, d_in, d_out, r, w_bits, ab_bits):
+    """33..48, 65..96 and 129..144 tokens: three token blocks per workgroup."""
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q
+    c = QCase(9460 + M, d_in, d_out, M, r, w_bits, ab_bits=ab_bits, packer=gpu)
+    ws = gpu.new_workspace(M, d_in, d_out, r)
+    y = run_linear_q(c, ws=ws)
+    assert " TB=3 " in gpu.debug_last_launch(), gpu.debug_last_launch()
+    _check(y, c.oracle_y())
+    assert np.array_equal(y, run_linear_q(c, ws=ws))
+
+
 # M, d_in, d_outs, r, w_bits, ab_bits, token blocks and row groups of a workgroup
 FEWER_BLOCKS = [
     (33, 4096, (1024,), 64, 4, 16, 1, 1),                # three groups of one token block, the last with one token
