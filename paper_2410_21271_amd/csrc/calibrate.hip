@@ -445,12 +445,15 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __res
 
 // C[i][j] = beta * C[i][j] + alpha * sum_k A[i*ai + k*ak] * B[j*bj + k*bk], i < M, j < N, k < K (beta == 0: C is
 // not read).  shape: GM_LOWER, only the tiles that touch the lower triangle (j0 <= i0) are computed (symmetric updates);
-// GM_B_LOWER, B[j][k] is zero for k < j (a lower triangle): the contraction begins at the tile's first column.
+// GM_B_LOWER, B[j][k] is zero for k < j (a lower triangle): the contraction begins at the tile's first column; GM_A_LOWER, the same of
+// A[i][k].  Workgroups go to the eight dies in turn, so the grid has the lower triangle's tiles and no others (a square grid with empty
+// upper tiles gives the die of the first columns a quarter more than that of the last: 70 % of the compute units' time used), and tiles
+// with the longest contractions come first.
 // Bound by the fp64 matrix cores: 64 x 64 outputs per workgroup, a quarter per wavefront as 2 x 2 blocks of
 // v_mfma_f64_16x16x4_f64 (64 cycles each), operands staged through LDS 32 k at a time and requested two stages ahead (16 k and one
 // ahead: 256 x 4096 x 4096 took 277 us).  256 rows x 4096 are one workgroup per compute unit, so one wavefront per SIMD and
 // nothing to do while it stages: in two parts, two workgroups a unit, 213 -> 174 us and 6 for the sum; with fragments of two k a
-// lane (one 16-byte LDS read where two of 8 were) 168, 51 TFLOP/s.  The Gram matrix of 4096 x 8192: 3.6 ms (3.7 before).  Tiles of 128
+// lane (one 16-byte LDS read where two of 8 were) 168, 51 TFLOP/s.  The Gram matrix of 4096 x 8192: 2.8 ms (3.6 on the square grid).  Tiles of 128
 // halve the operand traffic but leave fewer of them to share out (4.4 ms).  LDS rows of 34 doubles: the sixteen rows of a
 // fragment start in different banks.
 // part: null, or room for gridDim.z partial products, each over its share of k (gemm_sum_kernel adds them).
@@ -467,7 +470,7 @@ __device__ __forceinline__ T load_at(const T* base, uint32_t off)
         return __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
     }
 }
-enum { GM_FULL = 0, GM_LOWER = 1, GM_B_LOWER = 2 };
+enum { GM_FULL = 0, GM_LOWER = 1, GM_B_LOWER = 2, GM_A_LOWER = 3 };
 constexpr int GM_TILE = 64, GM_KT = 32;
 
 // Whether every byte that a lane reads of a stage of an operand lies within 32 bits of the tile's address there (with one of the strides
@@ -478,7 +481,8 @@ inline bool near_offsets(long row_stride, long k_stride, size_t size)
     return ((size_t)(GM_TILE - 1) * row_stride + (size_t)(GM_KT - 1) * k_stride + 1) * size <= 0xFFFFFFFFull;
 }
 
-template <typename TA, typename TB, bool FAR>
+// ADD: beta is not 0 and there are no parts; the tile of C is then requested before the contraction
+template <typename TA, typename TB, bool FAR, bool ADD>
 __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
                                                    double alpha, double beta, int shape, double* part)
 {
@@ -486,11 +490,21 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
     __shared__ __attribute__((aligned(16))) double As[2][TILE * ST], Bs[2][TILE * ST];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
-    const int i0 = blockIdx.y * TILE, j0 = blockIdx.x * TILE;
-    if (shape == GM_LOWER && j0 > i0) return;
+    int ty = blockIdx.y, tx = blockIdx.x;
+    if (shape == GM_LOWER) {                              // tile t of the lower triangle, row after row
+        const int t = tx;
+        ty = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
+        ty = ty * (ty + 1) / 2 > t ? ty - 1 : ty;
+        ty = (ty + 1) * (ty + 2) / 2 <= t ? ty + 1 : ty;
+        tx = t - ty * (ty + 1) / 2;
+    } else if (shape == GM_B_LOWER) {                     // columns, the longest contractions, first
+        ty = blockIdx.x;
+        tx = blockIdx.y;
+    }
+    const int i0 = ty * TILE, j0 = tx * TILE;
     const int wi = TILE / 2 * (wave & 1), wj = TILE / 2 * (wave >> 1);
     const int stages = (K - 1) / KT + 1, parts = gridDim.z, z = blockIdx.z;
-    const int first = shape == GM_B_LOWER ? j0 / KT : 0;
+    const int first = shape == GM_B_LOWER ? j0 / KT : shape == GM_A_LOWER ? i0 / KT : 0;
     const int sb = first + (int)((long)(stages - first) * z / parts), se = first + (int)((long)(stages - first) * (z + 1) / parts);
     // This thread's elements of a stage: consecutive threads along whichever index is contiguous in memory.  A lane's offsets
     // (32 bits, where near_offsets says that they fit) stay the same, the tile's address moves; rows beyond the last one re-read
@@ -539,7 +553,7 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
             Bs[buf][lb + sbk * e] = (double)rb[set][e];
         }
     };
-    d4 acc[FR][FR];
+    d4 acc[FR][FR], old[FR][FR];
 #pragma unroll
     for (int e = 0; e < FR; ++e)
 #pragma unroll
@@ -567,6 +581,17 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
     // used).  No branch in the loop touches the accumulators: where paths meet the compiler copies them.
     if (sb < se) {
         fetch(0, sb);
+        if constexpr (ADD) {                              // (an element outside C: the last one of its row or column, not used)
+#pragma unroll
+            for (int e = 0; e < FR; ++e)
+#pragma unroll
+                for (int f = 0; f < FR; ++f)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int gi = i0 + wi + 16 * e + 4 * v + g, gj = j0 + wj + 16 * f + n;
+                        old[e][f][v] = C[(size_t)(gi < M ? gi : M - 1) * ldc + (gj < N ? gj : N - 1)];
+                    }
+        }
         stage(0, 0);
         fetch(1, sb + 1 < se ? sb + 1 : se - 1);
         __syncthreads();
@@ -595,7 +620,7 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
                         part[((size_t)z * M + gi) * N + gj] = acc[e][f][v];
                     } else {
                         double c = alpha * acc[e][f][v];
-                        if (beta != 0.0) c += beta * C[(size_t)gi * ldc + gj];
+                        if constexpr (ADD) c += beta * old[e][f][v];
                         C[(size_t)gi * ldc + gj] = c;
                     }
                 }
@@ -1159,23 +1184,27 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
           hipStream_t st, double alpha = 1.0, double beta = 0.0, int shape = GM_FULL, double* scratch = nullptr, size_t room = 0)
 {
     const int ti = (M + 63) / 64, tj = (N + 63) / 64, tiles = shape == GM_LOWER ? ti * (ti + 1) / 2 : ti * tj;
-    auto kern = gemm_kernel<TA, TB, false>;
+    dim3 grid = shape == GM_LOWER ? dim3(tiles) : shape == GM_B_LOWER ? dim3(ti, tj) : dim3(tj, ti);
+    auto kern = gemm_kernel<TA, TB, false, false>;
     // (fp64 operands are matrices of at most MAX_DIM columns.  An instance of its own: tested in the kernel instead, a call at
     // 4096 x 4096 takes 46.5 ms instead of 46.1)
     if constexpr (std::is_same_v<TA, float>)
-        if (!near_offsets(ai, ak, sizeof(TA)) || !near_offsets(bj, bk, sizeof(TB))) kern = gemm_kernel<TA, TB, true>;
-    if (scratch && tiles <= 256 && K >= 512 && shape != GM_B_LOWER) {
+        if (!near_offsets(ai, ak, sizeof(TA)) || !near_offsets(bj, bk, sizeof(TB))) kern = gemm_kernel<TA, TB, true, false>;            // (no call with calibration tokens adds to C)
+    if (scratch && tiles <= 256 && K >= 512 && (shape == GM_FULL || shape == GM_LOWER)) {
         size_t parts = (tiles <= 64 ? 256 : 512) / tiles;
         if (parts > (size_t)K / 128) parts = K / 128;     // at least four stages each
         if (parts > room / ((size_t)M * N)) parts = room / ((size_t)M * N);
         if (parts > 1) {
-            hipLaunchKernelGGL(kern, dim3(tj, ti, (unsigned)parts), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, scratch);
+            grid.z = (unsigned)parts;
+            hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, scratch);
             hipLaunchKernelGGL(gemm_sum_kernel, dim3(blocks((size_t)M * N)), dim3(256), 0, st, (const double*)scratch, (int)parts, C, ldc, M, N, alpha, beta,
                                shape == GM_LOWER);
             return;
         }
     }
-    hipLaunchKernelGGL(kern, dim3(tj, ti), dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, (double*)nullptr);
+    if constexpr (std::is_same_v<TA, double>)
+        if (beta != 0.0) kern = gemm_kernel<TA, TB, false, true>;
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, (double*)nullptr);
 }
 static_assert(((size_t)(GM_TILE - 1) * MAX_DIM + GM_KT) * sizeof(double) <= 0xFFFFFFFFull, "fp64 operands have near offsets");
 
@@ -1602,7 +1631,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     } else {
         if (chol) {
             // T = (dW L)^T (k x d_out): T[j][o] = sum_i L[i][j] dW[o][i]
-            gemm(H, 1L, (long)k, dW, (long)k, 1L, T, (long)d_out, k, d_out, k, st);
+            gemm(H, 1L, (long)k, dW, (long)k, 1L, T, (long)d_out, k, d_out, k, st, 1.0, 0.0, GM_A_LOWER);
         } else {
             // T[j][o] = root[j] * sum_i V[j][i] dW[o][i]
             gemm(V, (long)k, 1L, dW, (long)k, 1L, T, (long)d_out, k, d_out, k, st);
@@ -1629,7 +1658,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         sub = leading_subspace(T, m, n, r, p, H, T0, by_rows ? Ap : Bn, V, (size_t)k * k, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st, &cycles);
         if (stats) stats[0] = sub == 1 ? cycles : -cycles;
         if (sub == 1) {
-            gemm((const double*)V, (long)m, 1L, (const double*)T, 1L, (long)n, T0, (long)n, p, n, m, st);      // Z T
+            gemm((const double*)V, (long)m, 1L, (const double*)T, 1L, (long)n, T0, (long)n, p, n, m, st, 1.0, 0.0, GM_FULL, H, (size_t)k * k);      // Z T
             sweeps = jacobi(T0, n, nullptr, p, sq, rot, st, stats ? stats + 4 : nullptr);
             if (sweeps < 0) return sweeps == -1 ? EORA_ERR_NOT_CONVERGED : EORA_ERR_LAUNCH;
             hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, T0, T0, n, sq);
@@ -1683,11 +1712,12 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         hipLaunchKernelGGL(top_rows_kernel, dim3(blocks(m)), dim3(256), 0, st, sq, m, r, idx, sigma);
         if (stats && chol) stats[2] = n;
     }
+    // (the Gram matrix, its factor, S or the square factor in H are done with: room for the parts of the products below)
     const double* Tc = sub || square ? T0 : T;  // rows idx[i]: sigma_i z_i^T
     if (by_rows) {
         // z_i = v_i: A' = rows of V'^T; B' = U' Sigma' = dW' A'^T
         hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks((size_t)r * k)), dim3(256), 0, st, Tc, k, idx, sigma, -1, Ap, r);
-        gemm(Tkeep, (long)k, 1L, Ap, (long)k, 1L, (double*)B_f64, (long)r, d_out, r, k, st);
+        gemm(Tkeep, (long)k, 1L, Ap, (long)k, 1L, (double*)B_f64, (long)r, d_out, r, k, st, 1.0, 0.0, GM_FULL, H, (size_t)k * k);
         // Cholesky route, step 6: A = Sigma'^-2 B'^T dW
         if (chol) hipLaunchKernelGGL(scaled_transpose_kernel, dim3(blocks((size_t)r * d_out)), dim3(256), 0, st, (const double*)B_f64, sigma, d_out, r, Bn);
     } else {
@@ -1697,15 +1727,15 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         // A' = Sigma'^-1 U'^T dW' : A'[i][j] = sum_o (sigma_i u_i[o] / sigma_i^2) dW'[o][j]
         hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks((size_t)r * d_out)), dim3(256), 0, st, Tc, d_out, idx, sigma, -2, Bn,
                            r);
-        if (!chol) gemm(Bn, (long)d_out, 1L, Tkeep, (long)d_out, 1L, Ap, (long)k, r, k, d_out, st);
+        if (!chol) gemm(Bn, (long)d_out, 1L, Tkeep, (long)d_out, 1L, Ap, (long)k, r, k, d_out, st, 1.0, 0.0, GM_FULL, H, (size_t)k * k);
     }
     if (chol) {
         // step 6 without an inverse: A[i][j] = sum_o (sigma_i u_i[o] / sigma_i^2) dW[o][j]
-        gemm(Bn, (long)d_out, 1L, dW, 1L, (long)k, (double*)A_f64, (long)k, r, k, d_out, st);
+        gemm(Bn, (long)d_out, 1L, dW, 1L, (long)k, (double*)A_f64, (long)k, r, k, d_out, st, 1.0, 0.0, GM_FULL, H, (size_t)k * k);
     } else {
         // step 6: A = A' sqrt(Lambda)^-1 Q^T : A[i][j] = sum_e A'[i][e] inv[e] V[e][j]
         hipLaunchKernelGGL(scale_kernel, dim3(blocks((size_t)r * k)), dim3(256), 0, st, Ap, r, k, inv, 0);
-        gemm(Ap, (long)k, 1L, V, 1L, (long)k, (double*)A_f64, (long)k, r, k, k, st);
+        gemm(Ap, (long)k, 1L, V, 1L, (long)k, (double*)A_f64, (long)k, r, k, k, st, 1.0, 0.0, GM_FULL, H, (size_t)k * k);
     }
     if (sigma_f64) hipLaunchKernelGGL(copy_kernel, dim3(blocks(r)), dim3(256), 0, st, sigma, (double*)sigma_f64, (size_t)r);
     if (hipGetLastError() != hipSuccess) return EORA_ERR_LAUNCH;
