@@ -482,12 +482,14 @@ inline bool near_offsets(long row_stride, long k_stride, size_t size)
 }
 
 // ADD: beta is not 0 and there are no parts; the tile of C is then requested before the contraction
+struct alignas(16) GemmLds { double a[2][GM_TILE * (GM_KT + 2)], b[2][GM_TILE * (GM_KT + 2)]; };
 template <typename TA, typename TB, bool FAR, bool ADD>
-__global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
-                                                   double alpha, double beta, int shape, double* part)
+__device__ __forceinline__ void gemm_tile(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
+                                          double alpha, double beta, int shape, double* part, GemmLds& lds)
 {
     constexpr int TILE = GM_TILE, KT = GM_KT, ST = KT + 2, E = TILE * KT / 256, FR = TILE / 32;
-    __shared__ __attribute__((aligned(16))) double As[2][TILE * ST], Bs[2][TILE * ST];
+    auto& As = lds.a;
+    auto& Bs = lds.b;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
     int ty = blockIdx.y, tx = blockIdx.x;
@@ -627,6 +629,14 @@ __global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long
             }
 }
 
+template <typename TA, typename TB, bool FAR, bool ADD>
+__global__ __launch_bounds__(256, 2) void gemm_kernel(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
+                                                   double alpha, double beta, int shape, double* part)
+{
+    __shared__ GemmLds lds;
+    gemm_tile<TA, TB, FAR, ADD>(A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, part, lds);
+}
+
 // C = beta * C + alpha * (the partial products, in order); lower: where their tiles of 64 touch the lower triangle
 __global__ __launch_bounds__(256) void gemm_sum_kernel(const double* __restrict__ part, int parts, double* __restrict__ C, long ldc, int M, int N, double alpha,
                                                        double beta, int lower)
@@ -700,15 +710,16 @@ __device__ __forceinline__ void unrolled(F&& f)
     }
 }
 
-__global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A, long lda, int j0, int nb, const double* __restrict__ thr,
-                                                         unsigned* __restrict__ flag, double* __restrict__ inv)
+// S: the matrix; once a column of blocks is done, the blocks of the inverse below the diagonal go to the mirrored places
+// above it (block (i, j) of the inverse, i > j, at block (j, i), not transposed).  D: inverses of the diagonal blocks.
+struct PotrfLds { double S[CH_NB][CH_NB + 2], D[4][16][18]; int bad; };
+__device__ __forceinline__ void potrf_block(double* blk, long lda, int nb, const double* __restrict__ thr, unsigned* __restrict__ flag,
+                                            double* __restrict__ inv, PotrfLds& lds)
 {
-    // S: the matrix; once a column of blocks is done, the blocks of the inverse below the diagonal go to the mirrored places
-    // above it (block (i, j) of the inverse, i > j, at block (j, i), not transposed).  D: inverses of the diagonal blocks.
-    __shared__ double S[CH_NB][CH_NB + 2], D[4][16][18];
-    __shared__ int s_bad;
+    auto& S = lds.S;
+    auto& D = lds.D;
+    int& s_bad = lds.bad;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 15, g = lane >> 4;
-    double* const blk = A + (size_t)j0 * lda + j0;
     {
         double v[16];
         const int c = lane < nb ? lane : 0;
@@ -736,23 +747,34 @@ __global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A
                 a[c] = S[16 * jb + n][16 * jb + c];
                 y[c] = c == n ? 1.0 : 0.0;
             }
-            unrolled<16>([&](auto jt) __attribute__((always_inline)) {
+            double d, rinv;
+            auto pivot = [&](auto jt) __attribute__((always_inline)) {
                 constexpr int j = decltype(jt)::value;
-                double d = row_value<j>(a[j]);
+                d = row_value<j>(a[j]);
                 const bool low = 16 * jb + j < nb && !(d > floor_abs);       // not (numerically) positive definite: give up, stay finite
                 bad = bad || low;
                 d = low ? (floor_abs > 0.0 ? floor_abs : 1.0) : d;
-                const double rinv = rsq_newton(d);
+                rinv = rsq_newton(d);
+            };
+            pivot(std::integral_constant<int, 0>{});
+            unrolled<16>([&](auto jt) __attribute__((always_inline)) {
+                constexpr int j = decltype(jt)::value;
                 double root = d * rinv;
                 root = fma(fma(-root, root, d), 0.5 * rinv, root);
                 a[j] = n == j ? root : a[j] * rinv;
                 y[j] *= rinv;
+                // the next pivot's column first, so that its root is found beside the other columns' elimination
                 unrolled<15 - j>([&](auto kt) __attribute__((always_inline)) {
                     constexpr int k = j + 1 + decltype(kt)::value;
                     const double l = row_value<k>(a[j]);  // (the entry that eliminates in the block and in its inverse)
                     a[k] = fma(-a[j], l, a[k]);
                     y[k] = fma(-l, y[j], y[k]);
+                    if constexpr (k == j + 1) pivot(std::integral_constant<int, k>{});
                 });
+                // (or the compiler puts the elimination in the inverse off and keeps all 120 entries for it: 370 registers instead of 145)
+#pragma unroll
+                for (int c = 0; c < 16; ++c) asm volatile("" : "+v"(y[c]), "+v"(a[c]));
+                __builtin_amdgcn_sched_barrier(0);
             });
             if (lane < 16) {
 #pragma unroll
@@ -773,7 +795,9 @@ __global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A
         }
         __syncthreads();
         int turn = 0;
+#pragma unroll 1
         for (int ib = jb + 1; ib < 4; ++ib)
+#pragma unroll 1
             for (int kb = jb + 1; kb <= ib; ++kb) {
                 if ((turn++ & 3) != wave) continue;
                 d4 c;
@@ -796,10 +820,12 @@ __global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A
     // X(i, j) = -D(i) sum over j <= k < i of L(i, k) X(k, j): the three diagonals of blocks below the main one in turn, a block a
     // wavefront (the places above the diagonal they go to are zeros that nobody reads as L any more)
     __syncthreads();
+#pragma unroll 1
     for (int dist = 1; dist < 4; ++dist) {
         const int j = wave, i = wave + dist;
         if (i < 4) {
             d4 w = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+#pragma unroll 1
             for (int k = j; k < i; ++k)
 #pragma unroll
                 for (int kk = 0; kk < 4; ++kk)
@@ -817,6 +843,26 @@ __global__ __launch_bounds__(256) void potrf_block_kernel(double* __restrict__ A
         const double below = S[16 * bj + (r & 15)][16 * bi + n], diag = D[bi][r & 15][n];
         inv[r * CH_NB + lane] = bi < bj ? 0.0 : bi == bj ? diag : below;
     }
+}
+
+// the first diagonal block, nb x nb at A
+__global__ __launch_bounds__(256, 2) void potrf_block_kernel(double* A, long lda, int nb, const double* __restrict__ thr, unsigned* __restrict__ flag, double* __restrict__ inv)
+{
+    __shared__ PotrfLds lds;
+    potrf_block(A, lda, nb, thr, flag, inv, lds);
+}
+
+// The trailing matrix C (rest x rest) less P P^T (P: rest x nb), and its first block, the next diagonal one, factored by the
+// workgroup that has just finished it: the chain of diagonal blocks (20 us each, one workgroup) goes on beside the other
+// tiles (8 to 70 us).  4096 x 4096, rank 128: 32.0 -> 31.3 ms.
+__global__ __launch_bounds__(256, 2) void update_factor_kernel(const double* P, double* C, long ld, int rest, int nb, const double* __restrict__ thr,
+                                                              unsigned* __restrict__ flag, double* __restrict__ inv)
+{
+    __shared__ union { GemmLds g; PotrfLds p; } lds;
+    gemm_tile<double, double, false, true>(P, ld, 1L, P, ld, 1L, C, ld, rest, rest, nb, -1.0, 1.0, GM_LOWER, nullptr, lds.g);
+    if (blockIdx.x != 0) return;
+    __syncthreads();                                      // the tile is in memory, its operands in LDS are dead
+    potrf_block(C, ld, rest < CH_NB ? rest : CH_NB, thr, flag, inv, lds.p);
 }
 
 __global__ void zero_upper_kernel(double* __restrict__ A, int n)
@@ -1220,13 +1266,15 @@ void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double*
     for (int j0 = 0; j0 < n; j0 += CH_NB) {
         const int nb = n - j0 < CH_NB ? n - j0 : CH_NB, rest = n - j0 - nb;
         double* const iv = inv + (keep_inv ? (size_t)j0 * CH_NB : 0);
-        hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(256), 0, st, G, (long)n, j0, nb, thr, flag, keep_inv || rest > 0 ? iv : nullptr);
+        if (j0 == 0) hipLaunchKernelGGL(potrf_block_kernel, dim3(1), dim3(256), 0, st, G, (long)n, nb, thr, flag, keep_inv || rest > 0 ? iv : nullptr);
         if (rest <= 0) break;
         // rows below: P <- P L11^-T, in place (a workgroup reads its 64 rows whole before it writes them)
         double* const P = G + (size_t)(j0 + nb) * n + j0;
         gemm((const double*)P, (long)n, 1L, (const double*)iv, (long)CH_NB, 1L, P, (long)n, rest, nb, nb, st);
-        // trailing matrix -= panel . panel^T (the tiles of its lower triangle)
-        gemm((const double*)P, (long)n, 1L, (const double*)P, (long)n, 1L, G + (size_t)(j0 + nb) * n + (j0 + nb), (long)n, rest, rest, nb, st, -1.0, 1.0, GM_LOWER);
+        // trailing matrix -= panel . panel^T (the tiles of its lower triangle), and the next diagonal block (whose inverse may take this one's place)
+        const int ti = (rest + GM_TILE - 1) / GM_TILE;
+        hipLaunchKernelGGL(update_factor_kernel, dim3(ti * (ti + 1) / 2), dim3(256), 0, st, (const double*)P, G + (size_t)(j0 + nb) * n + (j0 + nb), (long)n, rest, nb,
+                           (const double*)thr, flag, keep_inv ? iv + (size_t)nb * CH_NB : rest > CH_NB ? iv : nullptr);
     }
     hipLaunchKernelGGL(zero_upper_kernel, dim3(blocks((size_t)n * n)), dim3(256), 0, st, G, n);
 }
