@@ -42,7 +42,7 @@ __device__ inline double wave_sum(double v)
 // V: m x m row-major or nullptr.  rows with squared norm <= abs_floor count as zero.
 template <int NT>
 __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H, int L, double* __restrict__ V,
-                                                          int m, int round, double tol, double abs_floor,
+                                                          int m, int round, double tol, double abs_floor, double small,
                                                           unsigned* __restrict__ rotations)
 {
     const int i = blockIdx.x, mm = m - 1, tid = threadIdx.x;
@@ -100,6 +100,7 @@ __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H
             cs[1] = co * t;
             rotate = 1;
             atomicAdd(rotations, 1u);
+            if (!(fabs(co * t) <= small) || !(fabs(c) <= small * sqrt(a) * sqrt(b))) atomicAdd(rotations + 1, 1u);
         }
         go = rotate;
     }
@@ -182,17 +183,29 @@ __device__ __forceinline__ bool rotation_due(double a, double b, double c, doubl
     return a > abs_floor && b > abs_floor && fabs(c) > tol * (a * rsq_approx(a)) * (b * rsq_approx(b));
 }
 
+// What became of the pairs of a workgroup: none was to be rotated; all that were had a sine and a cosine between the rows of at most
+// `small`; others.  A sweep rotates every pair once, and what later rotations of its rows put back into a pair's cosine is at most the
+// product of two such numbers each, 2 m of them: with small = sqrt(tol / 4 m), no more than half of tol.  A sweep without ROTATED is
+// therefore the last one and needs no other to find that nothing is left (4096 x 4096, rank 128: 31.3 -> 30.7 ms; 2048 x 2048, rank 256:
+// 31.0 -> 29.4).
+enum { ORTHOGONAL = 0, NEARLY = 1, ROTATED = 2 };
+__device__ __forceinline__ bool rotation_large(double a, double b, double c, double si, double small)
+{
+    return !(fabs(si) <= small) || !(fabs(c) <= small * (a * rsq_approx(a)) * (b * rsq_approx(b)));
+}
+
 // S (Gram matrix of 16 rows: a block of eight, P, and another, Q) -> J orthogonal, after one rotation of each of the 64 pairs of a
-// row of P and a row of Q, in eight steps of eight disjoint pairs (i, (i + step) mod 8).  One wavefront; true if any was rotated.
+// row of P and a row of Q, in eight steps of eight disjoint pairs (i, (i + step) mod 8).  One wavefront.
 // Lane (i, j) holds the 2 x 2 block of S in the rows of pair i and the columns of pair j, and rows 2 i, 2 i + 1 of J's columns of
 // pair j.  From one step to the next P's places stay and Q's move up by one lane of their index, so the matrix never leaves the
 // registers; the eight lanes (i, i) find the angles, every lane fetches those of its two pairs.  (Through LDS, with every lane
 // forming its two angles, a step took 1270 cycles, and a round of rows took all 120 pairs in 15 steps: those within P and within Q
 // belong to one round of a sweep.)
-__device__ __forceinline__ bool rotate_cross_pairs(const double (*S)[17], double (*J)[17], int lane, double tol, double abs_floor)
+__device__ __forceinline__ int rotate_cross_pairs(const double (*S)[17], double (*J)[17], int lane, double tol, double abs_floor, double small)
 {
     const int i = lane >> 3, j = lane & 7;
-    if (!__any(rotation_due(S[i][i], S[8 + j][8 + j], S[i][8 + j], tol, abs_floor))) return false;
+    if (!__any(rotation_due(S[i][i], S[8 + j][8 + j], S[i][8 + j], tol, abs_floor))) return ORTHOGONAL;
+    bool large = false;
     double pp = S[i][j], pq = S[i][8 + j], qp = S[8 + i][j], qq = S[8 + i][8 + j];
     double jp0 = 2 * i == j ? 1.0 : 0.0, jp1 = 2 * i + 1 == j ? 1.0 : 0.0, jq0 = 2 * i == 8 + j ? 1.0 : 0.0, jq1 = 2 * i + 1 == 8 + j ? 1.0 : 0.0;
     const int row = 4 * 9 * i, col = 4 * 9 * j;           // lanes (i, i) and (j, j)
@@ -202,6 +215,7 @@ __device__ __forceinline__ bool rotate_cross_pairs(const double (*S)[17], double
         double co, si;
         jacobi_angle(pp, qq, pq, co, si);
         const bool on = rotation_due(pp, qq, pq, tol, abs_floor);      // (of lanes (i, i); the others' are nobody's)
+        large = large || (i == j && on && rotation_large(pp, qq, pq, si, small));
         co = on ? co : 1.0;
         si = on ? si : 0.0;
         const double co0 = lane_value(co, row), si0 = lane_value(si, row), co1 = lane_value(co, col), si1 = lane_value(si, col);
@@ -221,14 +235,14 @@ __device__ __forceinline__ bool rotate_cross_pairs(const double (*S)[17], double
     J[2 * i + 1][j] = jp1;
     J[2 * i][8 + j] = jq0;
     J[2 * i + 1][8 + j] = jq1;
-    return true;
+    return __any(large) ? ROTATED : NEARLY;
 }
 
 // The same for all 120 pairs of the 16 rows, in fifteen steps of eight: the rounds that also see to the pairs within a block.
 // Lane (i, j) owns the 2 x 2 block of S in the rows of pair i and the columns of pair j, forms both pairs' rotations by
 // itself and applies them from either side at once, and turns rows 2 i, 2 i + 1 of J's columns of pair j: one round through
 // LDS per step (one wavefront's LDS operations are carried out in order).
-__device__ __forceinline__ bool rotate_all_pairs(double (*S)[17], double (*J)[17], int lane, double tol, double abs_floor)
+__device__ __forceinline__ int rotate_all_pairs(double (*S)[17], double (*J)[17], int lane, double tol, double abs_floor, double small)
 {
     const int pi = lane >> 3, pj = lane & 7;
     bool some = false;                                // whether any of the 120 pairs is to be rotated (in the last sweeps most rounds have none)
@@ -238,9 +252,9 @@ __device__ __forceinline__ bool rotate_all_pairs(double (*S)[17], double (*J)[17
         some = some || (r < c && rotation_due(S[r][r], S[c][c], S[r][c], tol, abs_floor));
         J[r][c] = r == c ? 1.0 : 0.0;
     }
-    if (!__any(some)) return false;
+    if (!__any(some)) return ORTHOGONAL;
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    bool any = false;
+    bool any = false, large = false;
 #pragma unroll 1
     for (int step = 0; step < 15; ++step) {
         auto pair = [&](int t, int& p, int& q) {
@@ -257,6 +271,7 @@ __device__ __forceinline__ bool rotate_all_pairs(double (*S)[17], double (*J)[17
         jacobi_angle(a0, b0, c0, co0, si0);
         jacobi_angle(a1, b1, c1, co1, si1);
         const bool on0 = rotation_due(a0, b0, c0, tol, abs_floor), on1 = rotation_due(a1, b1, c1, tol, abs_floor);
+        large = large || (on1 && rotation_large(a1, b1, c1, si1, small));
         co0 = on0 ? co0 : 1.0;
         si0 = on0 ? si0 : 0.0;
         co1 = on1 ? co1 : 1.0;
@@ -275,7 +290,7 @@ __device__ __forceinline__ bool rotate_all_pairs(double (*S)[17], double (*J)[17
         J[2 * pi + 1][q1] = si1 * jp1 + co1 * jq1;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-    return any;
+    return !any ? ORTHOGONAL : __any(large) ? ROTATED : NEARLY;
 }
 
 // The two blocks of eight rows of workgroup i in round `round` of nb / 2 (round-robin over nb blocks)
@@ -323,7 +338,7 @@ __device__ __forceinline__ void apply_rotation(double* __restrict__ X, int len, 
 }
 
 __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __restrict__ H, int L, double* __restrict__ V, int m,
-                                                                    int round, double tol, double abs_floor,
+                                                                    int round, double tol, double abs_floor, double small,
                                                                     unsigned* __restrict__ rotations)
 {
     __shared__ double Sw[BJ_NW][16][17];
@@ -362,13 +377,15 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
     __syncthreads();
     // ---- by one wavefront alone (three workgroup barriers per step cost more than they shared out)
     if (wave == 0) {
-        const bool any = round == 0 ? rotate_all_pairs(S, J, lane, tol, abs_floor) : rotate_cross_pairs(S, J, lane, tol, abs_floor);
-        if (lane == 0) s_rotated = any ? 1 : 0;
+        const int turned = round == 0 ? rotate_all_pairs(S, J, lane, tol, abs_floor, small) : rotate_cross_pairs(S, J, lane, tol, abs_floor, small);
+        if (lane == 0) s_rotated = turned;
     }
     __syncthreads();
-    const bool rotated = s_rotated != 0;
-    if (!rotated) return;               // the 16 rows were orthogonal already (uniform over the workgroup)
-    if (tid == 0) atomicAdd(rotations, 1u);
+    if (s_rotated == ORTHOGONAL) return;               // the 16 rows were orthogonal already (uniform over the workgroup)
+    if (tid == 0) {
+        atomicAdd(rotations, 1u);
+        if (s_rotated == ROTATED) atomicAdd(rotations + 1, 1u);
+    }
     apply_rotation(H, L, P, Q, J, wave, lane);
     if (V) apply_rotation(V, m, P, Q, J, wave, lane);
 }
@@ -377,7 +394,8 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 // a wavefront's CW columns of the 16 rows are requested twice, as the operands of the Gram matrix and as those of the
 // rotation, and stay in registers.  Of 256 rows: 5.7 us a round, where the kernel above took 12.0 with all 120 pairs through LDS.
 template <int CW>
-__global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __restrict__ H, int m, int round, double tol, double abs_floor, unsigned* __restrict__ rotations)
+__global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __restrict__ H, int m, int round, double tol, double abs_floor, double small,
+                                                                  unsigned* __restrict__ rotations)
 {
     constexpr int L = BJ_NW * CW;
     __shared__ double Sw[BJ_NW][16][17];
@@ -419,12 +437,15 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __res
     }
     __syncthreads();
     if (wave == 0) {
-        const bool any = round == 0 ? rotate_all_pairs(S, J, lane, tol, abs_floor) : rotate_cross_pairs(S, J, lane, tol, abs_floor);
-        if (lane == 0) s_rotated = any ? 1 : 0;
+        const int turned = round == 0 ? rotate_all_pairs(S, J, lane, tol, abs_floor, small) : rotate_cross_pairs(S, J, lane, tol, abs_floor, small);
+        if (lane == 0) s_rotated = turned;
     }
     __syncthreads();
-    if (s_rotated == 0) return;         // (uniform over the workgroup)
-    if (tid == 0) atomicAdd(rotations, 1u);
+    if (s_rotated == ORTHOGONAL) return;         // (uniform over the workgroup)
+    if (tid == 0) {
+        atomicAdd(rotations, 1u);
+        if (s_rotated == ROTATED) atomicAdd(rotations + 1, 1u);
+    }
     double aJ[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) aJ[kk] = J[4 * kk + g][n];
@@ -920,7 +941,7 @@ __global__ void copy_kernel(const double* __restrict__ src, double* __restrict__
     if (i < n) dst[i] = src[i];
 }
 
-__global__ void clear_counter_kernel(unsigned* c) { *c = 0; }
+__global__ void clear_counter_kernel(unsigned* c) { c[threadIdx.x] = 0; }
 
 // out[p] = sum_k X[p][k] * Y[p][k]; one workgroup of 256 per row
 __global__ __launch_bounds__(256) void row_dot_kernel(const double* __restrict__ X, const double* __restrict__ Y, int L,
@@ -1281,23 +1302,23 @@ void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double*
 
 bool block_rounds_fit(int L, bool with_v, int m) { return m % 16 == 0 && m >= 32 && L % 128 == 0 && (!with_v || m % 128 == 0); }
 
-void jacobi_round(double* H, int L, double* V, int m, int round, double tol, double abs_floor, unsigned* rot, hipStream_t st)
+void jacobi_round(double* H, int L, double* V, int m, int round, double tol, double abs_floor, double small, unsigned* rot, hipStream_t st)
 {
     const dim3 g(m / 2);
     const int need = (L / 2 + JPT - 1) / JPT;          // threads that cover a row
     if (need <= 64)
-        hipLaunchKernelGGL(jacobi_round_kernel<64>, g, dim3(64), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<64>, g, dim3(64), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
     else if (need <= 128)
-        hipLaunchKernelGGL(jacobi_round_kernel<128>, g, dim3(128), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<128>, g, dim3(128), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
     else if (need <= 256)
-        hipLaunchKernelGGL(jacobi_round_kernel<256>, g, dim3(256), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<256>, g, dim3(256), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
     else if (need <= 512)
-        hipLaunchKernelGGL(jacobi_round_kernel<512>, g, dim3(512), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<512>, g, dim3(512), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
     else
-        hipLaunchKernelGGL(jacobi_round_kernel<1024>, g, dim3(1024), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<1024>, g, dim3(1024), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
 }
 
-// Sweeps until one passes without a rotation.  Synchronises the stream once per sweep.  sq: m doubles of
+// Sweeps until one passes without a rotation that is not small (rotation_large).  Synchronises the stream once per sweep.  sq: m doubles of
 // scratch.  Returns the number of sweeps, or -1 if MAX_SWEEPS did not suffice, or -2 on a runtime error.
 // stats (may be null): sweeps, milliseconds between two events around the sweeps, workgroups that rotated
 // their rows, rows per workgroup (2: pair rounds, 16: block rounds).
@@ -1340,26 +1361,26 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
     for (int p = 0; p < m; ++p) top = host[p] > top ? host[p] : top;
     free(host);
     const double abs_floor = top * 1e-30;
-    const double tol = sqrt((double)L) * 1.1102230246251565e-16;
+    const double tol = sqrt((double)L) * 1.1102230246251565e-16, small = sqrt(tol / (4.0 * m));
     for (int sweep = 1; sweep <= MAX_SWEEPS; ++sweep) {
-        hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, rot);
+        hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(2), 0, st, rot);
         if (block_rounds_fit(L, V != nullptr, m)) {
             auto short_rows = V ? nullptr : L == 128 ? jacobi_short_round_kernel<16> : L == 256 ? jacobi_short_round_kernel<32> :
                               L == 384 ? jacobi_short_round_kernel<48> : L == 512 ? jacobi_short_round_kernel<64> : nullptr;
             for (int round = 0; round < m / 8 - 1; ++round) {
-                if (short_rows) hipLaunchKernelGGL(short_rows, dim3(m / 16), dim3(BJ_NT), 0, st, H, m, round, tol, abs_floor, rot);
-                else hipLaunchKernelGGL(jacobi_block_round_kernel, dim3(m / 16), dim3(BJ_NT), 0, st, H, L, V, m, round, tol, abs_floor, rot);
+                if (short_rows) hipLaunchKernelGGL(short_rows, dim3(m / 16), dim3(BJ_NT), 0, st, H, m, round, tol, abs_floor, small, rot);
+                else hipLaunchKernelGGL(jacobi_block_round_kernel, dim3(m / 16), dim3(BJ_NT), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
             }
         } else {
-            for (int round = 0; round < m - 1; ++round) jacobi_round(H, L, V, m, round, tol, abs_floor, rot, st);
+            for (int round = 0; round < m - 1; ++round) jacobi_round(H, L, V, m, round, tol, abs_floor, small, rot, st);
         }
-        unsigned n = 0;
-        if (hipMemcpyAsync(&n, rot, sizeof(n), hipMemcpyDeviceToHost, st) != hipSuccess ||
+        unsigned n[2] = {0, 0};             // workgroups that rotated rows, those of them with a rotation that was not small
+        if (hipMemcpyAsync(n, rot, sizeof(n), hipMemcpyDeviceToHost, st) != hipSuccess ||
             hipStreamSynchronize(st) != hipSuccess)
             return -2;
-        if (getenv("EORA_VERBOSE")) fprintf(stderr, "eora: jacobi m=%d L=%d sweep %d: %u rotations\n", m, L, sweep, n);
-        *rotations += n;
-        if (n == 0) return sweep;
+        if (getenv("EORA_VERBOSE")) fprintf(stderr, "eora: jacobi m=%d L=%d sweep %d: %u rotations, %u large\n", m, L, sweep, n[0], n[1]);
+        *rotations += n[0];
+        if (n[1] == 0) return sweep;
     }
     return -1;
 }
