@@ -1,5 +1,6 @@
 """Pins for oracle/calibrate.py (Alg. 1 steps 1-6, Theorem 1)."""
 import numpy as np
+import pytest
 
 from oracle import calibrate, linear
 
@@ -209,3 +210,30 @@ def test_square_factor_of_step5_has_the_same_singular_values_and_left_vectors():
     assert np.allclose(Uc * sign[None, :], Ut, atol=1e-8)
     rows = (Uc[:, :r] * sign[None, :r]).T @ T
     assert np.allclose(rows, st[:r, None] * Vt[:r], atol=1e-9 * st[0])
+
+
+@pytest.mark.parametrize("m,ratio", [(16, 0.5), (32, 0.8), (48, 0.85)])
+def test_a_sweep_of_small_rotations_leaves_orthogonal_rows(m, ratio):
+    """The bound by which the Jacobi iteration on the device stops: one rotation of every pair, all with a sine and a cosine between
+    the rows of at most sqrt(tol / 4 m), leaves cosines of at most tol / 2 (2 m products of two such numbers).  In 80 bits, so that
+    the rounding of 64 does not hide it."""
+    ld = np.longdouble
+    rng = np.random.default_rng(m)
+    tol = ld(np.sqrt(m) * 1.1102230246251565e-16)
+    small = np.sqrt(tol / (4 * m))
+    rows = np.eye(m, dtype=ld) + ld(0.1) * small * rng.uniform(-1, 1, (m, m)).astype(ld)
+    rows *= (ld(ratio) ** np.arange(m, dtype=ld))[:, None]
+    largest = ld(0)
+    for p in range(m):
+        for q in range(p + 1, m):
+            a, b, c = rows[p] @ rows[p], rows[q] @ rows[q], rows[p] @ rows[q]
+            zeta = (b - a) / (2 * c)
+            t = np.copysign(ld(1), zeta) / (abs(zeta) + np.sqrt(1 + zeta * zeta))
+            co = 1 / np.sqrt(1 + t * t)
+            si = co * t
+            largest = max(largest, abs(si), abs(c) / np.sqrt(a * b))
+            rows[p], rows[q] = co * rows[p] - si * rows[q], si * rows[p] + co * rows[q]
+    assert largest <= small
+    unit = rows / np.sqrt((rows * rows).sum(1))[:, None]
+    left = np.abs(unit @ unit.T - np.eye(m, dtype=ld)).max()
+    assert left <= tol / 2
