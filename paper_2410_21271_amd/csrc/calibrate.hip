@@ -1244,8 +1244,10 @@ void copy_doubles(const double* src, double* dst, size_t n, hipStream_t st)
 }
 
 // scratch (room for `room` doubles): where there are few tiles and a long contraction the compute units share the contraction
-// (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are added in order.  From 65 to 256
-// tiles are two and more workgroups a unit (gemm_kernel), as far as there is room.
+// (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are added in order.  From 65 to 511
+// tiles the parts that cost least: 0.08 us a column of the contraction and round of two workgroups a unit, and the partial sums written and
+// read.  As many as fit one round, up to 256 tiles and one beyond, left 192 and 320 tiles (3072 and 5120 rows, a block of 256) at 1.3
+// and 1.6 times what they need: 3072 x 3072, rank 128 24.1 -> 23.4 ms, 5120 x 5120 47.9 -> 42.1.
 template <typename TA, typename TB>
 void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
           hipStream_t st, double alpha = 1.0, double beta = 0.0, int shape = GM_FULL, double* scratch = nullptr, size_t room = 0)
@@ -1257,8 +1259,18 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
     // 4096 x 4096 takes 46.5 ms instead of 46.1)
     if constexpr (std::is_same_v<TA, float>)
         if (!near_offsets(ai, ak, sizeof(TA)) || !near_offsets(bj, bk, sizeof(TB))) kern = gemm_kernel<TA, TB, true, false>;            // (no call with calibration tokens adds to C)
-    if (scratch && tiles <= 256 && K >= 512 && (shape == GM_FULL || shape == GM_LOWER)) {
-        size_t parts = (tiles <= 64 ? 256 : 512) / tiles;
+    if (scratch && tiles < 512 && K >= 512 && (shape == GM_FULL || shape == GM_LOWER)) {
+        size_t parts = tiles <= 64 ? 256 / tiles : 1;
+        if (tiles > 64) {
+            float best = 1e30f;
+            for (int c = 1; c <= 8; ++c) {
+                const float us = 0.08f * (float)((tiles * c + 511) / 512) * (float)K / (float)c + (c > 1 ? 4.f + 4e-6f * (float)M * (float)N * (float)c : 0.f);
+                if (us < best) {
+                    best = us;
+                    parts = c;
+                }
+            }
+        }
         if (parts > (size_t)K / 128) parts = K / 128;     // at least four stages each
         if (parts > room / ((size_t)M * N)) parts = room / ((size_t)M * N);
         if (parts > 1) {
