@@ -370,7 +370,7 @@ __device__ __forceinline__ void sparse_body(const SparseArgs& a, const int gbid,
 // LDS slot layout: 16-byte piece q of token row t (columns 8q .. 8q+7 of the chunk) sits at piece index
 // 16 t + (q ^ (t & 15)): the 16 lanes that read one q for 16 tokens hit 16 different bank groups.
 // Producers, flags, partials and the continuation are those of the kernel above.
-template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE>      // RW: row blocks per wavefront; XW_D: steps between a request and its use; divides d_in / 128; ONCE: one group of token blocks, so every stored tile is read by one workgroup
+template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE, bool AHEAD>      // RW: row blocks per wavefront; XW_D: steps between a request and its use; divides d_in / 128; ONCE: one group of token blocks, so every stored tile is read by one workgroup; AHEAD: decoding a step ahead
 __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int gbid, const int bid, const int flag0)
 {
     constexpr bool LOWRANK = FA != S_NONE;
@@ -501,8 +501,10 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
 
     // the tile of a chunk is decoded while the one before it is multiplied, and a token block's fragments are read a token block ahead
     h8 sa[2][RW][2];
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int rw = 0; rw < RW; ++rw) sp_operands<VQ>(buf[0][rw], sa[0][rw][0], sa[0][rw][1]);
+        for (int rw = 0; rw < RW; ++rw) sp_operands<VQ>(buf[0][rw], sa[0][rw][0], sa[0][rw][1]);
+    }
     static_assert(XW_D % 2 == 0, "two sets of operands in turn");
     for (int base = 0; base < Gs; base += XW_D) {
 #pragma unroll
@@ -520,6 +522,10 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
             const int s1 = (s + 1) % XW_D;
             const int cx = c + 1 + XW_D < Gs ? c + 1 + XW_D : Gs - 1;
             __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!AHEAD) {
+#pragma unroll
+                for (int rw = 0; rw < RW; ++rw) sp_operands<VQ>(buf[s][rw], sa[s & 1][rw][0], sa[s & 1][rw][1]);
+            }
 #pragma unroll
             for (int tb = 0; tb < TB; ++tb) {
                 if (tb + 1 < TB) {
@@ -534,7 +540,7 @@ __device__ __forceinline__ void sparse_wide_body(const SparseArgs& a, const int 
                 for (int rw = 0; rw < RW; ++rw) acc[rw][tb] = __builtin_amdgcn_smfmac_f32_16x16x64_f16(sa[s & 1][rw][1], xb, acc[rw][tb], sp_idx(buf[s][rw]), 0, 1);
 #pragma unroll
                 for (int rw = 0; rw < RW; ++rw)
-                    if (rw * TB / RW == tb) sp_operands<VQ>(buf[s1][rw], sa[(s + 1) & 1][rw][0], sa[(s + 1) & 1][rw][1]);
+                    if (AHEAD && rw * TB / RW == tb) sp_operands<VQ>(buf[s1][rw], sa[(s + 1) & 1][rw][0], sa[(s + 1) & 1][rw][1]);
 #pragma unroll
                 for (int i = XN * tb / TB; i < XN * (tb + 1) / TB; ++i) {
                     *(u4*)(eora_smem + ((c + 1) & 1) * SLOT + xdst[i]) = xr[s1][i];
@@ -701,20 +707,21 @@ __global__ __launch_bounds__(NW * 64, 6) void sparse_group_kernel(SparseGroupArg
 
 // Wavefronts per SIMD that the registers of a single linear's kernel leave room for: two workgroups of eight row blocks a compute unit
 // with 4-bit kept values (28672 -> 8192 in four ranges, 256 workgroups and the producers: 56.6 us with 133 registers, 54 with
-// 128).  A group's kernel needs five registers more and spills at 128 (two members of 14336 rows, d_in 4096: 36.4 us, 45.9 with the spills).
+// 128).  A group's kernel needs five registers more and spills at 128 (two members of 14336 rows, d_in 4096: 36.4 us, 45.9 with the spills); it
+// leaves room for a second workgroup where it does not decode ahead (decodes_ahead).
 constexpr int sp_waves(int nw, int rw, bool vq) { return vq && nw == 8 && rw == 1 ? 4 : 1; }
 
 template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE>
 __global__ __launch_bounds__(NW * 64, sp_waves(NW, RW, VQ)) void sparse_wide_kernel(SparseArgs a)
 {
-    sparse_wide_body<FA, NW, RW, TB, XW_D, VQ, ONCE>(a, blockIdx.x, blockIdx.x, 0);
+    sparse_wide_body<FA, NW, RW, TB, XW_D, VQ, ONCE, true>(a, blockIdx.x, blockIdx.x, 0);
 }
 
-template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE>
-__global__ __launch_bounds__(NW * 64) void sparse_wide_group_kernel(SparseGroupArgs grp)
+template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE, bool AHEAD>
+__global__ __launch_bounds__(NW * 64, AHEAD ? 1 : 4) void sparse_wide_group_kernel(SparseGroupArgs grp)
 {
     const int mem = sparse_member(grp);
-    sparse_wide_body<FA, NW, RW, TB, XW_D, VQ, ONCE>(grp.m[mem], blockIdx.x, (int)blockIdx.x - grp.first[mem], grp.flag0[mem]);
+    sparse_wide_body<FA, NW, RW, TB, XW_D, VQ, ONCE, AHEAD>(grp.m[mem], blockIdx.x, (int)blockIdx.x - grp.first[mem], grp.flag0[mem]);
 }
 
 // fills the member table; blocks(i) = workgroups of member i
@@ -730,6 +737,30 @@ static int fill_group(SparseGroupArgs& g, const SparseArgs* members, int n, int 
         if (i < n) total += blocks(members[i]);
     }
     return total;
+}
+
+// Whether a group of linears with 4-bit kept values, eight row blocks a workgroup, takes the kernel that decodes a step ahead.  Where two
+// workgroups share a compute unit the other one's work hides the decoding already.
+//  - Two token blocks (both kernels leave room for two workgroups): not from 257 to 512 workgroups, which all run at once.  q+k+v of the 70B layer, rank 128,
+//    65 tokens 43.5 us ahead and 42.7, rank 32 40.8 and 39.3, bare at 127 tokens 38.4 and 36.8; two members of 14336 rows, d_in 8192, rank 32, 20 tokens
+//    (256 workgroups) 33.2 and 38.1; two of 10240, rank 128, 64 tokens (576) 48.1 and 53.1.
+//  - Four token blocks: decoding ahead takes 131 registers, one workgroup a unit; without it 124, two.  One is better where every workgroup that does
+//    the layer's work gets a unit of its own, although those beyond the 256th wait for producers to end; two where there are more of them, or
+//    where the late ones are so few that they fit beside the first member's producers.  Over 672 groups of two to four members, 50 to 127 tokens, ranks 32 to
+//    256, d_in 1024 to 8192: two members of 14336 rows, d_in 4096, 64 tokens, rank 128 34.3 us with one and 45.1 with two, rank 32 28.7 and 27.1;
+//    three of 6912, d_in 2560, rank 128, 96 tokens 40.8 and 33.6; two of 10240, d_in 8192, bare 66.4 and 56.6.  With three and four members the
+//    later ones' producers start late themselves and units wait for them (three of 4096, d_in 8192, rank 256, 96 tokens: 1.57 times as long with
+//    one), unless there are at most 192, in whole rounds over the dies and their shader engines or with units to spare.
+template <typename F>
+static bool decodes_ahead(const SparseArgs* members, int n, int tb, int producers, F blocks)
+{
+    int total = 0;
+    for (int i = 0; i < n; ++i) total += blocks(members[i]);
+    if (total <= 256) return true;
+    if (tb == 2) return total > 512;
+    const int workers = total - n * producers;
+    if (workers > 256 || total - 256 <= producers) return false;
+    return n == 2 || (n * producers <= 192 && (workers <= 192 || (producers % 32 == 0 && members[0].M <= 64)));
 }
 
 template <int FA, int NW, int RW, int TB, int XW_D, bool VQ, bool ONCE = false>
@@ -754,7 +785,12 @@ static hipError_t launch_sparse_wide(const SparseArgs* members, int n, hipStream
         // y = fp16(sum of the ranges' partial outputs, in the order of the ranges)
         return launch_reduce_parts(a.ypart, a.y, (size_t)a.M * a.d_out, a.ksplit, stream);
     }
-    auto kern = sparse_wide_group_kernel<FA, NW, RW, TB, XW_D, VQ, ONCE>;
+    auto kern = sparse_wide_group_kernel<FA, NW, RW, TB, XW_D, VQ, ONCE, true>;
+    if constexpr (VQ && NW == 8 && RW == 1)
+        if (!decodes_ahead(members, n, TB, units * yblocks, blocks)) {
+            note_launch("sparse_wide FA=%d NW=%d TB=%d VQ=%d n=%d ksplit=%d two per unit", FA, NW * RW, TB, (int)VQ, n, a.ksplit);
+            kern = sparse_wide_group_kernel<FA, NW, RW, TB, XW_D, VQ, ONCE, false>;
+        }
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

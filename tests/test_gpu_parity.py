@@ -585,3 +585,31 @@ def test_sparse_group_of_layers_sharing_x(gpu, quantised, r, M, d_in, d_outs):
         assert np.array_equal(y, y2)
         if M <= 4:
             assert np.array_equal(y, run_linear_sp24q4(c) if quantised else run_linear_sp24(c))
+
+
+@pytest.mark.parametrize("r,M,d_in,d_outs,shared", [
+    (0, 65, 1536, (8960, 8960), True),               # four token blocks, 280 workgroups: two a compute unit
+    (0, 64, 512, (16384, 16368), False),             # 256, the last with seven row blocks: one a unit; the shortest contraction
+    (32, 50, 1024, (14336, 14336), True),            # 224 and 64 producers: the 32 late ones beside the first member's producers
+    (32, 50, 1024, (15360, 15360), False),           # 240: 48 late ones wait for a unit
+    (64, 65, 512, (6144, 6016, 80), False),          # ragged: a member of five row blocks; 192 workgroups of three members, 120 producers
+    (0, 65, 512, (8960, 8976, 80), True),            # ragged: 284 workgroups
+    (0, 127, 1024, (8192, 1024, 1040), True),        # two token blocks, 324 workgroups
+    (0, 20, 1024, (14336, 14336), False),            # 224
+    (128, 64, 512, (10240, 10240), False),           # 320 and 256 producers: more than two a unit
+])
+def test_sparse_group_with_two_workgroups_per_unit(gpu, r, M, d_in, d_outs, shared):
+    """Groups of eight row blocks a workgroup with 4-bit kept values: which of them run two workgroups a compute unit, without decoding
+    ahead (launches that a single one a unit takes 10 to 40 % longer for), on both sides of every line."""
+    from tests.cases import SparseQCase
+    from tests.gpu_util import run_linear_sp24_group
+    cases = [SparseQCase(2700 + r + M + i, d_in, d, M, r, packer=gpu) for i, d in enumerate(d_outs)]
+    for c in cases:
+        c.x = cases[0].x
+    ys = run_linear_sp24_group(cases)
+    launch = gpu.debug_last_launch()
+    assert launch.startswith("sparse_wide ") and " NW=8 " in launch and launch.endswith(" two per unit") == shared, launch
+    for c, y in zip(cases, ys):
+        _check(y, c.oracle_y())
+    for y, z in zip(ys, run_linear_sp24_group(cases)):
+        assert np.array_equal(y, z)
