@@ -38,6 +38,21 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
+// What became of the pairs of a workgroup: none was to be rotated; all that were had a sine and a cosine between the rows of at most
+// `small`; others.  A sweep rotates every pair once, and what later rotations of its rows put back into a pair's cosine is at most the
+// product of two such numbers each, 2 m of them: with small = sqrt(tol / 4 m), no more than half of tol.  A sweep without ROTATED is
+// therefore the last one and needs no other to find that nothing is left (4096 x 4096, rank 128: 31.3 -> 30.7 ms; 2048 x 2048, rank 256:
+// 31.0 -> 29.4).
+enum { ORTHOGONAL = 0, NEARLY = 1, ROTATED = 2 };
+
+// Workgroups that rotated rows in rotations[0], those of them with a rotation that was not small in rotations[1]: one addition to both, and behind
+// the workgroup's barrier, which would wait for it.  A round's workgroups all touch this word, one after the other: a round over 578 rows (289
+// workgroups) 6.1 us; with an addition to each, before the barrier, 7.8, and with a store to rotations[1] beside the addition 13.7.
+__device__ __forceinline__ void count_rotation(unsigned* rotations, int turned)
+{
+    atomicAdd(reinterpret_cast<unsigned long long*>(rotations), turned == ROTATED ? 0x100000001ull : 1ull);
+}
+
 // One round: workgroup i rotates the row pair (p, q) of the round-robin schedule.  H: m x L row-major;
 // V: m x m row-major or nullptr.  rows with squared norm <= abs_floor count as zero.
 template <int NT>
@@ -91,21 +106,20 @@ __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H
             b += red[1][w];
             c += red[2][w];
         }
-        int rotate = 0;
+        int rotate = ORTHOGONAL;
         if (a > abs_floor && b > abs_floor && fabs(c) > tol * sqrt(a) * sqrt(b)) {
             const double zeta = (b - a) / (2.0 * c);
             const double t = copysign(1.0, zeta) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
             const double co = 1.0 / sqrt(1.0 + t * t);
             cs[0] = co;
             cs[1] = co * t;
-            rotate = 1;
-            atomicAdd(rotations, 1u);
-            if (!(fabs(co * t) <= small) || !(fabs(c) <= small * sqrt(a) * sqrt(b))) atomicAdd(rotations + 1, 1u);
+            rotate = fabs(co * t) <= small && fabs(c) <= small * sqrt(a) * sqrt(b) ? NEARLY : ROTATED;
         }
         go = rotate;
     }
     __syncthreads();
-    if (!go) return;
+    if (go == ORTHOGONAL) return;
+    if (tid == 0) count_rotation(rotations, go);
     const double co = cs[0], si = cs[1];
 #pragma unroll
     for (int k = 0; k < JPT; ++k) {
@@ -183,12 +197,6 @@ __device__ __forceinline__ bool rotation_due(double a, double b, double c, doubl
     return a > abs_floor && b > abs_floor && fabs(c) > tol * (a * rsq_approx(a)) * (b * rsq_approx(b));
 }
 
-// What became of the pairs of a workgroup: none was to be rotated; all that were had a sine and a cosine between the rows of at most
-// `small`; others.  A sweep rotates every pair once, and what later rotations of its rows put back into a pair's cosine is at most the
-// product of two such numbers each, 2 m of them: with small = sqrt(tol / 4 m), no more than half of tol.  A sweep without ROTATED is
-// therefore the last one and needs no other to find that nothing is left (4096 x 4096, rank 128: 31.3 -> 30.7 ms; 2048 x 2048, rank 256:
-// 31.0 -> 29.4).
-enum { ORTHOGONAL = 0, NEARLY = 1, ROTATED = 2 };
 __device__ __forceinline__ bool rotation_large(double a, double b, double c, double si, double small)
 {
     return !(fabs(si) <= small) || !(fabs(c) <= small * (a * rsq_approx(a)) * (b * rsq_approx(b)));
@@ -382,10 +390,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
     }
     __syncthreads();
     if (s_rotated == ORTHOGONAL) return;               // the 16 rows were orthogonal already (uniform over the workgroup)
-    if (tid == 0) {
-        atomicAdd(rotations, 1u);
-        if (s_rotated == ROTATED) atomicAdd(rotations + 1, 1u);
-    }
+    if (tid == 0) count_rotation(rotations, s_rotated);
     apply_rotation(H, L, P, Q, J, wave, lane);
     if (V) apply_rotation(V, m, P, Q, J, wave, lane);
 }
@@ -442,10 +447,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __res
     }
     __syncthreads();
     if (s_rotated == ORTHOGONAL) return;         // (uniform over the workgroup)
-    if (tid == 0) {
-        atomicAdd(rotations, 1u);
-        if (s_rotated == ROTATED) atomicAdd(rotations + 1, 1u);
-    }
+    if (tid == 0) count_rotation(rotations, s_rotated);
     double aJ[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) aJ[kk] = J[4 * kk + g][n];

@@ -110,3 +110,36 @@ def test_ritz_rotations_of_every_short_row(gpu, d, r, block):
     assert np.allclose(sig, s[:r], rtol=1e-9, atol=0), np.abs(sig / s[:r] - 1).max()
     want = U[:, :r] @ (U[:, :r].T @ dW)
     assert np.abs(B @ A - want).max() <= 1e-8 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("route", [0, 1])
+@pytest.mark.parametrize("m,L", [
+    (66, 98), (210, 386),                # pair rounds: lengths that are no multiples of 128
+    (96, 128), (160, 256), (224, 384), (320, 512),       # block rounds over short rows
+    (336, 640), (528, 1024),             # block rounds
+])
+def test_rows_the_sweeps_leave_are_orthogonal(gpu, m, L, route):
+    """The sweeps end after one whose rotations were all small, without another that finds nothing left.  With more rows than columns in W
+    and every component asked for, the columns of B' are the rows that the sweeps rotated, all of them.  Their cosines: a pair
+    left alone is at most tol = sqrt(L) 1.1e-16 and later rotations of the sweep add 0.81 tol; the rounding of the product that was compared
+    with tol is the rest of 2 tol."""
+    import torch
+    rng = np.random.default_rng(m + L)
+    W = rng.standard_normal((L, m)).astype(np.float32)
+    W_hat = (np.round(W * 8) / 8).astype(np.float32)
+    Xt = rng.standard_normal((m, 16 * m)).astype(np.float32)
+    Wd, Whd, Xd = (torch.from_numpy(a).cuda() for a in (W, W_hat, Xt))
+    f64 = dict(dtype=torch.float64, device="cuda")
+    B, A, sig = torch.empty(L, m, **f64), torch.empty(m, m, **f64), torch.empty(m, **f64)
+    ws = torch.empty(gpu.factors_workspace_bytes(m, L, m), dtype=torch.uint8, device="cuda")
+    gpu.debug_set_factors_route(route)
+    try:
+        st = gpu.factors(Wd, Whd, Xd, B, A, sig, Xt.shape[1], m, L, m, 1e-12, ws, stats=True)
+    finally:
+        gpu.debug_set_factors_route(0)
+    rows = B.cpu().numpy().astype(np.longdouble)
+    rows /= np.sqrt((rows * rows).sum(0))
+    left = float(np.abs(rows.T @ rows - np.eye(m)).max())
+    tol = np.sqrt(L) * 1.1102230246251565e-16
+    assert st["svd_rows"] == (16 if m % 16 == 0 and L % 128 == 0 else 2)
+    assert left <= 2 * tol, left / tol
