@@ -1495,7 +1495,8 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
     hipLaunchKernelGGL(random_rows_kernel, dim3(blocks((size_t)p * m)), dim3(256), 0, st, Y, (size_t)p * m);
     for (int it = 0; it < SUB_POWERS; ++it) {
         times_s(it & 1 ? Z : Y, it & 1 ? Y : Z, p, 1.0, 0.0);
-        orthonormalise(it & 1 ? Y : Z, p, m, F, R, U, room, thr, flag, st, it == 0, it == SUB_POWERS - 1 ? 2 : 1);
+        // (the last one's flag counts: a block that the earlier ones leave nearly dependent, from a spread of S of some 5e7 on, is one that it makes good)
+        orthonormalise(it & 1 ? Y : Z, p, m, F, R, U, room, thr, flag, st, it == SUB_POWERS - 1, it == SUB_POWERS - 1 ? 2 : 1);
     }
     static_assert(SUB_POWERS % 2 == 1, "the last product goes to Z");
     int rc = ritz(), stalled = 0;

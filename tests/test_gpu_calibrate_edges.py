@@ -143,3 +143,26 @@ def test_rows_the_sweeps_leave_are_orthogonal(gpu, m, L, route):
     tol = np.sqrt(L) * 1.1102230246251565e-16
     assert st["svd_rows"] == (16 if m % 16 == 0 and L % 128 == 0 else 2)
     assert left <= 2 * tol, left / tol
+
+
+@pytest.mark.parametrize("m,r,large", [(512, 32, 8), (768, 64, 8), (768, 64, 100), (1024, 64, 100)])
+def test_leading_subspace_where_the_first_products_are_nearly_dependent(gpu, m, r, large):
+    """Rows of the error a factor 1e4 larger than the rest, fewer of them than the block has vectors: the Gram matrix of a random block's first product
+    with S (spread of its Ritz values 1e8) has no Cholesky factor in 64 bits.  The products after it mend that, and the iteration is
+    not given up for the sweeps over all rows.  Bounds of the other calibration tests."""
+    import torch
+    rng = np.random.default_rng(m + r)
+    W = rng.standard_normal((m, m)).astype(np.float32)
+    Xt = rng.standard_normal((m, 2 * m)).astype(np.float32)
+    W[:large] *= 1e4
+    Wd, Xd = torch.from_numpy(W).cuda(), torch.from_numpy(Xt).cuda()
+    f64 = dict(dtype=torch.float64, device="cuda")
+    B, A, sig = torch.empty(m, r, **f64), torch.empty(r, m, **f64), torch.empty(r, **f64)
+    ws = torch.empty(gpu.factors_workspace_bytes(m, m, r), dtype=torch.uint8, device="cuda")
+    st = gpu.factors(Wd, torch.zeros_like(Wd), Xd, B, A, sig, Xt.shape[1], m, m, r, 1e-12, ws, stats=True)
+    assert 0 < st["subspace_cycles"] <= 6, st
+    X = Xt.astype(np.float64)
+    U, s, _ = np.linalg.svd(W.astype(np.float64) @ np.linalg.cholesky(X @ X.T), full_matrices=False)
+    assert np.allclose(sig.cpu().numpy(), s[:r], rtol=1e-9, atol=0)
+    want = U[:, :r] @ (U[:, :r].T @ W.astype(np.float64))
+    assert np.abs((B @ A).cpu().numpy() - want).max() <= 1e-8 * np.abs(want).max()
