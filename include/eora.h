@@ -144,6 +144,9 @@ void eora_debug_set_factors_route(int route);
 /* HOST, test hook: 1 if eora_factors() addresses the activations of so many calibration tokens with 32-bit offsets within a
  * tile of 64 channels, 0 if with 64-bit indices (from some 17 million tokens on: the same sums, more slowly). */
 int eora_debug_factors_near(int n_tokens);
+/* HOST, test hook: the parts into which eora_factors() cuts the contraction (K) of an M x N product of doubles whose partial outputs have `room`
+ * doubles of scratch (nothing is enqueued), or a negative status. */
+int eora_debug_factors_parts(int M, int N, int K, size_t room);
 /* HOST, test hook: writes into out (capacity bytes, NUL-terminated) the name and template parameters of the
  * layer kernel the most recent forward launch of this process chose, e.g. "sparse_wide FA=5 NW=8 TB=4 VQ=0 n=1"
  * (empty before the first launch), so that a test can assert that its shape reaches the instantiation it is

@@ -59,6 +59,7 @@ def _load():
         "eora_debug_set_resident_min_blocks": (None, [ci]),
         "eora_debug_set_factors_route": (None, [ci]),
         "eora_debug_factors_near": (ci, [ci]),
+        "eora_debug_factors_parts": (ci, [ci, ci, ci, sz]),
         "eora_debug_last_launch": (ci, [ctypes.c_char_p, sz]),
         "eora_debug_prefill_parts": (ci, [ci, ci, ci, ci, sz]),
         "eora_debug_prefill_plan": (ci, [ci, ci, ctypes.POINTER(ci), ci, ci, sz, ctypes.POINTER(ci)]),
@@ -102,7 +103,7 @@ EXPORTS = ["eora_status_string", "eora_qweight_bytes", "eora_qzeros_bytes", "eor
            "eora_sp24q4_tiles_bytes", "eora_sp24q4_meta_bytes", "eora_pack_sp24q4", "eora_linear_sp24q4", "eora_expand_sp24q4",
            "eora_factors_workspace_bytes", "eora_factors", "eora_linear_q_multi", "eora_pack_factor_q3", "eora_factors_store_f16", "eora_factors_store_q", "eora_linear_sp24_group",
            "eora_debug_last_launch", "eora_debug_probe", "eora_linear_q_static", "eora_debug_set_resident_min_blocks", "eora_debug_set_factors_route",
-           "eora_debug_prefill_parts", "eora_debug_factors_near", "eora_debug_prefill_plan", "eora_debug_last_prefill"]
+           "eora_debug_prefill_parts", "eora_debug_factors_near", "eora_debug_factors_parts", "eora_debug_prefill_plan", "eora_debug_last_prefill"]
 
 
 def status_string(status):
@@ -283,6 +284,11 @@ def debug_set_factors_route(route):
 def debug_factors_near(n_tokens):
     """Test hook: whether eora_factors addresses so many tokens with 32-bit offsets within a tile."""
     return bool(lib.eora_debug_factors_near(int(n_tokens)))
+
+
+def debug_factors_parts(M, N, K, room):
+    """Test hook: parts of the contraction of an M x N product of eora_factors with so many doubles of scratch."""
+    return int(lib.eora_debug_factors_parts(int(M), int(N), int(K), int(room)))
 
 
 def debug_last_launch():

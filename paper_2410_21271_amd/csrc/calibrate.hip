@@ -1245,11 +1245,33 @@ void copy_doubles(const double* src, double* dst, size_t n, hipStream_t st)
     hipLaunchKernelGGL(copy_kernel, dim3(blocks(n)), dim3(256), 0, st, src, dst, n);
 }
 
-// scratch (room for `room` doubles): where there are few tiles and a long contraction the compute units share the contraction
-// (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are added in order.  From 65 to 511
-// tiles the parts that cost least: 0.08 us a column of the contraction and round of two workgroups a unit, and the partial sums written and
-// read.  As many as fit one round, up to 256 tiles and one beyond, left 192 and 320 tiles (3072 and 5120 rows, a block of 256) at 1.3
-// and 1.6 times what they need: 3072 x 3072, rank 128 24.1 -> 23.4 ms, 5120 x 5120 47.9 -> 42.1.
+// Parts of the contraction of a product of `tiles` tiles whose caller has `room` doubles of scratch: where there are few tiles and a long
+// contraction the compute units share it (256 x 256 with k = 4096: 10 tiles take 260 us, in parts 18, and 5 for their sum); the parts are
+// added in order.  From 65 to 511 tiles the parts that cost least of those that have at least four stages each and fit the scratch: a column of the contraction
+// takes 0.08 us with two workgroups a unit and 0.052 with one, full rounds of 512 come first and what is left over after them; then the partial
+// sums written and read.  Whole calls, in ms, with one to five parts of each product with S: 3072 x 3072, rank 192 (288 tiles) 30.1, 28.4, 27.7, 27.6, 27.5;
+// 2304 x 2304, rank 128 (144) 17.5, 16.8, 16.0, 16.2, 15.9; 5120 x 5120, rank 128 (320) 48.9, 44.1, 42.7, 42.2, 43.3; 2560 x 2560, rank 224 (320) 33.5, 32.5
+// and no room for more; 3072 x 3072, rank 256 (384) 36.9, 35.7, 36.2.  (With every begun round at 0.08 the cost says one part for the last two.)
+int gemm_parts(int tiles, int M, int N, int K, size_t room)
+{
+    if (tiles >= 512 || K < 512) return 1;
+    size_t most = room / ((size_t)M * N);
+    if (most > (size_t)K / 128) most = K / 128;
+    if (tiles <= 64) return (int)(most < 1 ? 1 : most < (size_t)(256 / tiles) ? most : 256 / tiles);
+    float best = 1e30f;
+    int parts = 1;
+    for (int c = 1; c <= 8 && (c == 1 || (size_t)c <= most); ++c) {
+        const int left = tiles * c % 512;
+        const float column = 0.08f * (float)(tiles * c / 512) + (left == 0 ? 0.f : left <= 256 ? 0.052f : 0.08f);
+        const float us = column * (float)K / (float)c + (c > 1 ? 4.f + 4e-6f * (float)M * (float)N * (float)c : 0.f);
+        if (us < best) {
+            best = us;
+            parts = c;
+        }
+    }
+    return parts;
+}
+
 template <typename TA, typename TB>
 void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* C, long ldc, int M, int N, int K,
           hipStream_t st, double alpha = 1.0, double beta = 0.0, int shape = GM_FULL, double* scratch = nullptr, size_t room = 0)
@@ -1261,24 +1283,12 @@ void gemm(const TA* A, long ai, long ak, const TB* B, long bj, long bk, double* 
     // 4096 x 4096 takes 46.5 ms instead of 46.1)
     if constexpr (std::is_same_v<TA, float>)
         if (!near_offsets(ai, ak, sizeof(TA)) || !near_offsets(bj, bk, sizeof(TB))) kern = gemm_kernel<TA, TB, true, false>;            // (no call with calibration tokens adds to C)
-    if (scratch && tiles < 512 && K >= 512 && (shape == GM_FULL || shape == GM_LOWER)) {
-        size_t parts = tiles <= 64 ? 256 / tiles : 1;
-        if (tiles > 64) {
-            float best = 1e30f;
-            for (int c = 1; c <= 8; ++c) {
-                const float us = 0.08f * (float)((tiles * c + 511) / 512) * (float)K / (float)c + (c > 1 ? 4.f + 4e-6f * (float)M * (float)N * (float)c : 0.f);
-                if (us < best) {
-                    best = us;
-                    parts = c;
-                }
-            }
-        }
-        if (parts > (size_t)K / 128) parts = K / 128;     // at least four stages each
-        if (parts > room / ((size_t)M * N)) parts = room / ((size_t)M * N);
+    if (scratch && (shape == GM_FULL || shape == GM_LOWER)) {
+        const int parts = gemm_parts(tiles, M, N, K, room);
         if (parts > 1) {
             grid.z = (unsigned)parts;
             hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, A, ai, ak, B, bj, bk, C, ldc, M, N, K, alpha, beta, shape, scratch);
-            hipLaunchKernelGGL(gemm_sum_kernel, dim3(blocks((size_t)M * N)), dim3(256), 0, st, (const double*)scratch, (int)parts, C, ldc, M, N, alpha, beta,
+            hipLaunchKernelGGL(gemm_sum_kernel, dim3(blocks((size_t)M * N)), dim3(256), 0, st, (const double*)scratch, parts, C, ldc, M, N, alpha, beta,
                                shape == GM_LOWER);
             return;
         }
@@ -1611,6 +1621,12 @@ int check_shape(int n_tokens, int d_in, int d_out, int r)
 using namespace eora;
 
 extern "C" void eora_debug_set_factors_route(int route) { g_factors_route = route == 1 ? 1 : 0; }
+
+extern "C" int eora_debug_factors_parts(int M, int N, int K, size_t room)
+{
+    if (M < 1 || N < 1 || K < 1) return EORA_ERR_SHAPE;
+    return gemm_parts(((M + 63) / 64) * ((N + 63) / 64), M, N, K, room);
+}
 
 extern "C" int eora_debug_factors_near(int n_tokens) { return near_offsets(n_tokens, 1, sizeof(float)) ? 1 : 0; }
 

@@ -362,3 +362,40 @@ assert binding._stream() == 77
 """
     p = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
     assert p.returncode == 0, p.stderr[-2000:]
+
+
+def test_parts_of_the_calibration_products_are_the_cheapest_that_fit():
+    """Algorithm 1's products of 65 to 511 tiles: rounds of two workgroups a compute unit make the time rise and fall with the parts, so
+    a number that the scratch does not hold must not be cut down to one that is dearer than another that fits.  Products of the subspace iteration at
+    every multiple of 128 from 512 to 3072 (p vectors of length m, what its buffers leave of k x k doubles), and others."""
+    def cost(c, tiles, M, N, K):
+        left = tiles * c % 512
+        column = 0.08 * (tiles * c // 512) + (0 if left == 0 else 0.052 if left <= 256 else 0.08)
+        return column * K / c + (4 + 4e-6 * M * N * c if c > 1 else 0)
+
+    def check(M, N, K, room):
+        tiles, got = -(-M // 64) * -(-N // 64), eora.debug_factors_parts(M, N, K, room)
+        most = max(1, min(K // 128, room // (M * N)))
+        if K < 512 or tiles >= 512:
+            assert got == 1
+        elif tiles <= 64:
+            assert got == min(256 // tiles, most)
+        else:
+            assert 1 <= got <= min(8, most)
+            best = min(cost(c, tiles, M, N, K) for c in range(1, min(8, most) + 1))
+            assert cost(got, tiles, M, N, K) <= best * (1 + 1e-5), (M, N, K, room, got)
+
+    for m in range(512, 3073, 128):
+        for r in range(32, 257, 32):
+            p = (max(2 * r, r + 64) + 127) // 128 * 128
+            if p <= m // 4:
+                for k in (m, m + 128, 2 * m):
+                    check(p, m, m, k * k - 2 * p * m - 3 * p * p)
+                    check(p, k, m, k * k)
+    for M, N, K, room in ((384, 2170, 2170, 10 ** 7), (64, 64, 512, 10 ** 6), (256, 4096, 4096, 0), (300, 5000, 511, 10 ** 8), (512, 4096, 640, 10 ** 8), (100, 100, 9000, 10 ** 6)):
+        check(M, N, K, room)
+    room = lambda p, m: m * m - 2 * p * m - 3 * p * p
+    assert eora.debug_factors_parts(384, 2176, 2176, room(384, 2176)) == 2        # five are the cheapest of all; three, which fit, are dearer than two
+    assert eora.debug_factors_parts(512, 3072, 3072, room(512, 3072)) == 2        # three fit
+    assert eora.debug_factors_parts(512, 2560, 2560, room(512, 2560)) == 2        # no more fit
+    assert eora.debug_factors_parts(0, 64, 512, 0) < 0

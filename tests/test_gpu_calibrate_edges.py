@@ -166,3 +166,27 @@ def test_leading_subspace_where_the_first_products_are_nearly_dependent(gpu, m, 
     assert np.allclose(sig.cpu().numpy(), s[:r], rtol=1e-9, atol=0)
     want = U[:, :r] @ (U[:, :r].T @ W.astype(np.float64))
     assert np.abs((B @ A).cpu().numpy() - want).max() <= 1e-8 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("d_in,d_out,r,parts", [
+    (2176, 2176, 160, 2),        # 204 tiles, of the parts that fit the cheapest
+    (2170, 2170, 160, 2),        # ragged rows, columns and contraction
+    (2816, 2816, 192, 3),        # 264 tiles: more than one round of a workgroup a compute unit
+])
+def test_products_with_s_in_parts(gpu, d_in, d_out, r, parts):
+    """Products of the subspace iteration's block with S of 65 tiles and more whose contraction is cut into parts, those that add to their output among
+    them (the filter's): singular values and correction against LAPACK, the bounds of the other calibration tests."""
+    from tests.test_gpu_calibrate import _factors_with_stats, _inputs
+    m, p = min(d_in, d_out), (max(2 * r, r + 64) + 127) // 128 * 128
+    assert gpu.debug_factors_parts(p, m, m, d_in * d_in - 2 * p * m - 3 * p * p) == parts
+    W, W_hat, Xt = _inputs(7900 + d_in, d_in, d_out, 2 * d_in, group=d_in)
+    B, A, sig, st = _factors_with_stats(gpu, W, W_hat, Xt, r)
+    assert 0 < st["subspace_cycles"] <= 6, st
+    X = Xt.astype(np.float64)
+    dW = W.astype(np.float64) - W_hat
+    T = dW @ np.linalg.cholesky(X @ X.T)
+    lam, U = np.linalg.eigh(T @ T.T)                          # (fifty times faster than the SVD; good to 1e-16 lam_1 / lam_r)
+    s, U = np.sqrt(lam[::-1][:r]), U[:, ::-1][:, :r]
+    assert np.allclose(sig, s, rtol=1e-9, atol=0), np.abs(sig / s - 1).max()
+    want = U @ (U.T @ dW)
+    assert np.abs(B @ A - want).max() <= 1e-8 * np.abs(want).max()
