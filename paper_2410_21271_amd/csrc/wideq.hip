@@ -788,12 +788,12 @@ static WidePlan wide_plan(const WideArgs& a)
     // The cheapest by steps.  A step of 128 columns per range costs STEP microseconds whatever the launch's size (LDS
     // traffic and the barrier), a workgroup's start, hand-over of t and end about 9; workgroups beyond the chip's slots come
     // in further rounds.  The sum of the parts: with three or four token blocks it grows with the parts and the output
-    // (fitted at 41 and 64 tokens, two to eight parts; against 8 microseconds whatever the size: 64 x 14336 x 4096 W4
+    // (fitted with four at 41 and 64 tokens, two to eight parts; against 8 microseconds whatever the size: 64 x 14336 x 4096 W4
     // 27.4 -> 27.5 us, 80 x 11008 x 4096 bare 26.0); with one or two the fit splits too much (24 x 14336 x 4096
     // 21.4 -> 22.7) and 8 stays.  Measured on one-linear launches of 64 and 24 tokens, contractions of 4096 .. 14336 (down
     // projection of the 8B layer, 64 tokens: two row blocks per workgroup and one part 46.9 us, eight and seven parts 27.3).
     static const int per[4] = {8, 4, 2, 1}, ranges[4] = {2, 2, 4, 8};
-    static const float STEP[4][4] = {{0.5f, 0.4f, 0.45f, 0.6f}, {0.85f, 0.55f, 0.65f, 1.2f}, {1.f, 0.7f, 1.f, 2.f}, {1.2f, 0.85f, 1.3f, 2.8f}};
+    static const float STEP[4][4] = {{0.5f, 0.4f, 0.45f, 0.6f}, {0.85f, 0.55f, 0.65f, 1.2f}, {0.95f, 0.7f, 1.f, 2.f}, {1.2f, 0.85f, 1.3f, 2.8f}};
     const int yblocks = (a.M + 15) / 16, G = a.d_in / 128;
     size_t rows = 0;
     for (int i = 0; i < a.n; ++i) rows += a.d_out[i];
@@ -806,13 +806,14 @@ static WidePlan wide_plan(const WideArgs& a)
     // Three token blocks where they make as many groups as four would (33..48, 65..96, 129..144 tokens): a step's requests for x,
     // fragments and MFMAs are a quarter fewer.  40 x 4096 x 2 x 14336 W4, rank 128: 29.2 -> 27.0 us; 48 x 8192 x 28672 W3 49.8 -> 44.9;
     // 96 x 8192 x 8192 W3 46.5 -> 41.0; 70 tokens, q+k+v of 4096, W2 24.5 -> 21.4.  Contractions beyond 32768 were not measured and keep
-    // four.  The sum of parts costs a launch more here (1 instead of 2.5: 37 x 7296 x 2688 W3 in five parts 18.7 us, whole with two
-    // token blocks 18.1).
+    // four.  Their steps and the 3 and 0.3 us of a sum of parts are fitted over 520 launches (20 shapes, 33 to 144 tokens, W4 and W3, ranks 0, 64
+    // and 128), every split of each timed: 1.4 % above the best split on average, none 3 % above the split of four blocks.  (A step of 1 for eight row blocks, 2.5
+    // and 0.5: 1.7 %; 48 x 14336 x 4096 W4, rank 128, 24.2 us in three parts of four row blocks, 22.3 with four token blocks, 21.8 in seven of eight.)
     const bool three = G <= 256 && (yblocks + 2) / 3 == (yblocks + 3) / 4;
     WidePlan best{yblocks < 3 ? yblocks : three ? 3 : 4, 0, 1};
     const int tb = best.tb;
     const float* const step_us = STEP[tb - 1];
-    const float sum0 = tb == 4 ? 1.f : tb == 3 ? 2.5f : 8.f, sum_part = tb >= 3 ? 0.5f + 4.2e-6f * (float)a.M * (float)rows : 0.f;
+    const float sum0 = tb == 4 ? 1.f : tb == 3 ? 3.f : 8.f, sum_part = tb >= 3 ? (tb == 4 ? 0.5f : 0.3f) + 4.2e-6f * (float)a.M * (float)rows : 0.f;
     float best_us = 1e30f;
     for (int c = a.M <= 4 ? 1 : 0; c < 4; ++c) {
         // workgroups the chip holds (registers)

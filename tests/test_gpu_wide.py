@@ -178,6 +178,7 @@ def test_smaller_workspace_leaves_the_contraction_whole(gpu):
     (48, 256, 20480, 64, 4, 4),             # full; two row blocks per wavefront; a single tile per range
     (65, 384, 6160, 96, 2, 16),             # two groups, the second with two blocks; an odd number of chunks, a ragged last row group
     (96, 16640, 2048, 0, 4, 16),            # parts of a long contraction
+    (48, 14336, 4096, 64, 4, 16),           # ... with factors: seven, of eight row blocks each
     (144, 256, 4112, 32, 4, 16),            # three groups, the most tokens that take three blocks
 ])
 def test_wide_three_token_blocks(gpu, M, d_in, d_out, r, w_bits, ab_bits):
@@ -188,6 +189,7 @@ def test_wide_three_token_blocks(gpu, M, d_in, d_out, r, w_bits, ab_bits):
     ws = gpu.new_workspace(M, d_in, d_out, r)
     y = run_linear_q(c, ws=ws)
     assert " TB=3 " in gpu.debug_last_launch(), gpu.debug_last_launch()
+    assert (M, d_in) != (48, 14336) or " parts=7 " in gpu.debug_last_launch(), gpu.debug_last_launch()
     _check(y, c.oracle_y())
     assert np.array_equal(y, run_linear_q(c, ws=ws))
 
