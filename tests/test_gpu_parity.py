@@ -434,6 +434,21 @@ def test_sparse_two_row_blocks_per_wavefront(gpu, quantised, r, d_out):
     _check(y, c.oracle_y())
 
 
+@pytest.mark.parametrize("r", [0, 64])
+@pytest.mark.parametrize("quantised", [False, True])
+def test_sparse_two_row_blocks_per_wavefront_in_a_ragged_group(gpu, quantised, r):
+    """The same in a group whose members end in a workgroup of one row block and one of three."""
+    from tests.cases import SparseCase, SparseQCase
+    from tests.gpu_util import run_linear_sp24_group
+    make = SparseQCase if quantised else SparseCase
+    cases = [make(2580 + r + i, 512, d, 62, r, packer=gpu) for i, d in enumerate((24592, 24624))]
+    cases[1].x = cases[0].x
+    ys = run_linear_sp24_group(cases)
+    assert gpu.debug_last_launch() == "sparse_wide FA=%d NW=16 TB=4 VQ=%d n=2 ksplit=1" % (5 if r else 0, quantised), gpu.debug_last_launch()
+    for c, y in zip(cases, ys):
+        _check(y, c.oracle_y())
+
+
 def test_sparse_many_tokens_different_inputs_on_one_workspace(gpu):
     """The many-token 2:4 kernel hands t over as untagged fp32 partials behind flags: two different activations, then
     a different layer, then the first again, back to back on ONE workspace that is never cleared in between.  A

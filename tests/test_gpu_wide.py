@@ -180,6 +180,7 @@ def test_smaller_workspace_leaves_the_contraction_whole(gpu):
     (96, 16640, 2048, 0, 4, 16),            # parts of a long contraction
     (48, 14336, 4096, 64, 4, 16),           # ... with factors: seven, of eight row blocks each
     (144, 256, 4112, 32, 4, 16),            # three groups, the most tokens that take three blocks
+    (40, 384, 9232, 128, 3, 3),             # 3-bit factors; a ragged last row group
 ])
 def test_wide_three_token_blocks(gpu, M, d_in, d_out, r, w_bits, ab_bits):
     """33..48, 65..96 and 129..144 tokens: three token blocks per workgroup."""
@@ -192,6 +193,34 @@ def test_wide_three_token_blocks(gpu, M, d_in, d_out, r, w_bits, ab_bits):
     assert (M, d_in) != (48, 14336) or " parts=7 " in gpu.debug_last_launch(), gpu.debug_last_launch()
     _check(y, c.oracle_y())
     assert np.array_equal(y, run_linear_q(c, ws=ws))
+
+
+@pytest.mark.parametrize("M,d_in,d_outs,r,w_bits,ab_bits", [
+    (37, 512, (4096, 4112, 1040), 32, 4, 16),            # ragged members
+    (96, 256, (2048, 4096, 2064), 128, 3, 3),            # two groups of token blocks
+    (48, 384, (8192, 8208), 0, 2, 16),
+])
+def test_wide_three_token_blocks_in_a_group(gpu, M, d_in, d_outs, r, w_bits, ab_bits):
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q_group
+    cases = [QCase(9500 + M + i, d_in, d, M, r, w_bits, ab_bits=ab_bits, packer=gpu) for i, d in enumerate(d_outs)]
+    ys = run_linear_q_group(cases, cases[0].x)
+    launch = gpu.debug_last_launch()
+    assert launch.startswith("wide_q ") and " TB=3 " in launch and launch.endswith(" n=%d" % len(cases)), launch
+    for c, y in zip(cases, ys):
+        _check(y, c.oracle_y(x=cases[0].x))
+
+
+@pytest.mark.parametrize("M,d_in,d_out,r,n", [(40, 512, 9216, 32, 4), (90, 256, 6160, 64, 3)])
+def test_wide_three_token_blocks_with_several_adapters(gpu, M, d_in, d_out, r, n):
+    from tests.cases import QCase
+    from tests.gpu_util import run_linear_q_multi
+    from tests.test_gpu_multi import _oracle
+    c = QCase(9540 + M, d_in, d_out, M, r * n, 4, packer=gpu)
+    sel = np.random.default_rng(M).integers(-1, n, M).astype(np.int32)
+    y = run_linear_q_multi(c, sel, r)
+    assert " TB=3 " in gpu.debug_last_launch(), gpu.debug_last_launch()
+    _check(y, _oracle(c, sel, r))
 
 
 # M, d_in, d_outs, r, w_bits, ab_bits, token blocks and row groups of a workgroup

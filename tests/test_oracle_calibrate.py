@@ -212,20 +212,16 @@ def test_square_factor_of_step5_has_the_same_singular_values_and_left_vectors():
     assert np.allclose(rows, st[:r, None] * Vt[:r], atol=1e-9 * st[0])
 
 
-@pytest.mark.parametrize("m,ratio", [(16, 0.5), (32, 0.8), (48, 0.85)])
-def test_a_sweep_of_small_rotations_leaves_orthogonal_rows(m, ratio):
-    """The bound by which the Jacobi iteration on the device stops: one rotation of every pair, all with a sine and a cosine between
-    the rows of at most sqrt(tol / 4 m), leaves cosines of at most tol / 2 (2 m products of two such numbers).  In 80 bits, so that
-    the rounding of 64 does not hide it."""
+def _sweep_of_small_rotations(m, ratio, limit):
+    """One sweep of a round-robin schedule over m rows whose norms fall by `ratio` and whose cosines are all 0.97 limit, in 80 bits (the
+    rounding of 64 would hide the result): largest sine or cosine that was rotated away, largest cosine left."""
     ld = np.longdouble
-    rng = np.random.default_rng(m)
-    tol = ld(np.sqrt(m) * 1.1102230246251565e-16)
-    small = np.sqrt(tol / (4 * m))
-    rows = np.eye(m, dtype=ld) + ld(0.1) * small * rng.uniform(-1, 1, (m, m)).astype(ld)
+    rows = np.eye(m, dtype=ld) + ld(0.97) * limit * np.tril(np.ones((m, m)), -1).astype(ld)
     rows *= (ld(ratio) ** np.arange(m, dtype=ld))[:, None]
     largest = ld(0)
-    for p in range(m):
-        for q in range(p + 1, m):
+    for step in range(m - 1):
+        for i in range(m // 2):
+            p, q = (step, m - 1) if i == 0 else ((step + i) % (m - 1), (step + m - 1 - i) % (m - 1))
             a, b, c = rows[p] @ rows[p], rows[q] @ rows[q], rows[p] @ rows[q]
             zeta = (b - a) / (2 * c)
             t = np.copysign(ld(1), zeta) / (abs(zeta) + np.sqrt(1 + zeta * zeta))
@@ -233,7 +229,19 @@ def test_a_sweep_of_small_rotations_leaves_orthogonal_rows(m, ratio):
             si = co * t
             largest = max(largest, abs(si), abs(c) / np.sqrt(a * b))
             rows[p], rows[q] = co * rows[p] - si * rows[q], si * rows[p] + co * rows[q]
-    assert largest <= small
     unit = rows / np.sqrt((rows * rows).sum(1))[:, None]
-    left = np.abs(unit @ unit.T - np.eye(m, dtype=ld)).max()
-    assert left <= tol / 2
+    return largest, np.abs(unit @ unit.T - np.eye(m, dtype=ld)).max()
+
+
+@pytest.mark.parametrize("m,ratio", [(16, 0.5), (32, 0.618), (48, 0.618), (48, 1.618)])
+def test_a_sweep_of_small_rotations_leaves_orthogonal_rows(m, ratio):
+    """The bound by which the Jacobi iteration on the device stops: one rotation of every pair, all with a sine and a cosine between
+    the rows of at most sqrt(tol / 4 m), leaves cosines of at most 0.81 tol (2 m sines times cosines times the ratio of two rows' norms, which is at most
+    1.62 where both are at the limit).  From cosines just below the limit, all of one sign, a quarter of that is left; from twice the
+    limit more than the bound would be, so a limit twice too large fails here."""
+    tol = np.longdouble(np.sqrt(m) * 1.1102230246251565e-16)
+    small = np.sqrt(tol / (4 * m))
+    largest, left = _sweep_of_small_rotations(m, ratio, small)
+    assert 0.9 * small <= largest <= small
+    assert 0.1 * tol <= left <= 0.81 * tol
+    assert _sweep_of_small_rotations(m, ratio, 2.2 * small)[1] > 0.81 * tol
