@@ -14,7 +14,7 @@
 // accumulated rotation R are eigenvectors of G and r_p . (R G)_p its eigenvalues.  For a general matrix T,
 // R T with orthogonal rows is Sigma V^T (row norms = singular values, R = U^T).  A round of the round-robin
 // schedule rotates m/2 disjoint pairs, one workgroup per pair, rows held in registers; m-1 rounds visit every
-// pair once (a sweep); sweeps repeat until one passes without a rotation.
+// pair once (a sweep); sweeps repeat until one passes whose rotations, if any, were all so small that nothing is left after them (NEARLY below).
 #include "eora.h"
 
 #include <hip/hip_runtime.h>
@@ -39,10 +39,11 @@ __device__ inline double wave_sum(double v)
 }
 
 // What became of the pairs of a workgroup: none was to be rotated; all that were had a sine and a cosine between the rows of at most
-// `small`; others.  A sweep rotates every pair once, and what later rotations of its rows put back into a pair's cosine is at most the
-// product of two such numbers each, 2 m of them: with small = sqrt(tol / 4 m), no more than half of tol.  A sweep without ROTATED is
-// therefore the last one and needs no other to find that nothing is left (4096 x 4096, rank 128: 31.3 -> 30.7 ms; 2048 x 2048, rank 256:
-// 31.0 -> 29.4).
+// `small`; others.  A sweep rotates every pair once.  A later rotation of one of its rows puts a sine times a cosine back into a pair's own
+// cosine, times the ratio of the two rotated rows' norms where the other one is larger: at most 1.62 small^2, as a large ratio makes the sine of
+// a given cosine small (s = c rho / (rho^2 - 1), both at the limit at rho = 1.62).  There are 2 m of them: with small = sqrt(tol / 4 m) they leave
+// 0.81 tol of a pair that was rotated, and 1.81 tol of one that was just below tol and left alone.  A sweep without ROTATED is therefore the last one and
+// needs no other to find that nothing is left (4096 x 4096, rank 128: 31.3 -> 30.7 ms; 2048 x 2048, rank 256: 31.0 -> 29.4; left in tests: 1.0 tol).
 enum { ORTHOGONAL = 0, NEARLY = 1, ROTATED = 2 };
 
 // Workgroups that rotated rows in rotations[0], those of them with a rotation that was not small in rotations[1]: one addition to both, and behind
@@ -398,6 +399,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 // A round over rows of 8 CW values (the Ritz matrices of the subspace iteration), without eigenvector rows.  A chain of latencies:
 // a wavefront's CW columns of the 16 rows are requested twice, as the operands of the Gram matrix and as those of the
 // rotation, and stay in registers.  Of 256 rows: 5.7 us a round, where the kernel above took 12.0 with all 120 pairs through LDS.
+// Instances for 128 to 512 values, the blocks of ranks up to 256; larger blocks, of which none was timed, take the kernel above.
 template <int CW>
 __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __restrict__ H, int m, int round, double tol, double abs_floor, double small,
                                                                   unsigned* __restrict__ rotations)
@@ -1411,9 +1413,11 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
 
 // ---- host side of the filtered subspace iteration (see random_rows_kernel) ----------------------------------
 constexpr int SUB_CYCLES = 14;
-// Products with S before the first Ritz rotation, whose sweeps are the most expensive (11 of 31 rounds from a random block, some 0.2 ms
-// each, where a product and one orthonormalisation take 0.4 ms).  Two, five, seven and nine, in ms: 4096 x 4096, rank 128 37.2, 34.2,
-// 35.0, 34.9; 1024 x 4096, rank 64 -, 9.3, 8.5, 8.3; 640 x 578, rank 32 -, 6.9, 5.9, 6.1.
+// Products with S before the first Ritz rotation, whose sweeps are the most expensive (9 of 32 from a random block, some 0.2 ms each at 256 rows,
+// where a product and one orthonormalisation take 0.4 ms).  Three, five, seven and nine, in ms: 4096 x 4096, rank 128 32.8, 29.9, 30.3, 31.5; rank 256 51.4,
+// 52.0, 45.3, 46.9; 1024 x 1024, rank 32 6.5, 6.4, 5.5, 5.7; 2048 x 2048, rank 256 32.6, 28.0, 28.7, 29.1; 4096 x 1024, rank 64 7.5, 7.4, 7.5, 7.6.  One number
+// for all: two products more cost 2 to 3 % where they save no cycle of the filter and gain up to 14 % where they do, which the spectrum decides and
+// not the size.
 constexpr int SUB_POWERS = 7;
 constexpr double SUB_SPREAD = 27.6;         // ln 1e12: growth of the largest Ritz direction over the smallest per filter
 constexpr double SUB_TOL = 1e-12;           // residual of a leading vector, relative to its Ritz value

@@ -358,9 +358,10 @@ __device__ __forceinline__ void sparse_body(const SparseArgs& a, const int gbid,
 // and up to TB token blocks of 16 per workgroup.  A token block's x is 1.8x the bytes of a row
 // block's weights, so x is shared through LDS by the NW wavefronts, and a stored tile, once in registers,
 // serves all TB token blocks.  Every wavefront reads the whole chunk of x from LDS: sixteen row blocks as eight wavefronts of
-// two read half of what sixteen of one did.  A tile is decoded while the one before it is multiplied.  70B gate + up at 64 tokens,
-// 4-bit kept values 92 -> 84.5 us, o 26.9 -> 25.1, fp16 values 119 -> 115; two members of 14336 rows, d_in 4096: 44 -> 36.4.  What is
-// left of a step (1.25 us of 128 columns) is no one unit's: without the products 0.82 of it, without the tiles 0.77, without decoding 0.82.  Per step one 128-column chunk: x[16 TB tokens][128] goes global ->
+// two read half of what sixteen of one did.  A tile is decoded while the one before it is multiplied.  Launches by themselves at 64 tokens,
+// rank 128: gate + up of the 70B layer, 4-bit kept values 84.5 -> 79.9 us, o 26.3 -> 25.3, gate + up with fp16 values 117.4 -> 113.5; two members of 14336 rows,
+// d_in 4096 44.7 -> 36.4.  A step of 128 columns takes 0.95 us (gate + up's rows at d_in 4096: 49.4).
+// Per step one 128-column chunk: x[16 TB tokens][128] goes global ->
 // registers (requested XW_D steps before its LDS write) -> one of two LDS slots, and the wavefront's stored
 // tile of the same columns is requested XW_D steps ahead as well.  All requests are plain loads: with
 // global -> LDS copies among them the compiler would no longer count on in-order answers and would drain
