@@ -46,12 +46,12 @@ __device__ inline double wave_sum(double v)
 // needs no other to find that nothing is left (4096 x 4096, rank 128: 31.3 -> 30.7 ms; 2048 x 2048, rank 256: 31.0 -> 29.4; left in tests: 1.0 tol).
 enum { ORTHOGONAL = 0, NEARLY = 1, ROTATED = 2 };
 
-// Workgroups that rotated rows in rotations[0], those of them with a rotation that was not small in rotations[1]: one addition to both, and behind
-// the workgroup's barrier, which would wait for it.  A round's workgroups all touch this word, one after the other: a round over 578 rows (289
-// workgroups) 6.1 us; with an addition to each, before the barrier, 7.8, and with a store to rotations[1] beside the addition 13.7.
-__device__ __forceinline__ void count_rotation(unsigned* rotations, int turned)
+// Every workgroup of a round counts in a word of its own: rounds in which it rotated rows in the low half, those of them with a rotation that was
+// not small in the high half.  One word for all makes a round's additions come one after the other, at its end: a round over 578 rows (289 workgroups) takes 4.5 us
+// so, 6.1 with one word; 640 x 578, rank 224 50.5 -> 36.6 ms, 300 x 300 18.8 -> 15.4.
+__device__ __forceinline__ void count_rotation(unsigned long long* mine, int turned)
 {
-    atomicAdd(reinterpret_cast<unsigned long long*>(rotations), turned == ROTATED ? 0x100000001ull : 1ull);
+    atomicAdd(mine, turned == ROTATED ? 0x100000001ull : 1ull);
 }
 
 // One round: workgroup i rotates the row pair (p, q) of the round-robin schedule.  H: m x L row-major;
@@ -59,7 +59,7 @@ __device__ __forceinline__ void count_rotation(unsigned* rotations, int turned)
 template <int NT>
 __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H, int L, double* __restrict__ V,
                                                           int m, int round, double tol, double abs_floor, double small,
-                                                          unsigned* __restrict__ rotations)
+                                                          unsigned long long* __restrict__ rotations)
 {
     const int i = blockIdx.x, mm = m - 1, tid = threadIdx.x;
     int p, q;
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(NT) void jacobi_round_kernel(double* __restrict__ H
     }
     __syncthreads();
     if (go == ORTHOGONAL) return;
-    if (tid == 0) count_rotation(rotations, go);
+    if (tid == 0) count_rotation(rotations + i, go);
     const double co = cs[0], si = cs[1];
 #pragma unroll
     for (int k = 0; k < JPT; ++k) {
@@ -348,7 +348,7 @@ __device__ __forceinline__ void apply_rotation(double* __restrict__ X, int len, 
 
 __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __restrict__ H, int L, double* __restrict__ V, int m,
                                                                     int round, double tol, double abs_floor, double small,
-                                                                    unsigned* __restrict__ rotations)
+                                                                    unsigned long long* __restrict__ rotations)
 {
     __shared__ double Sw[BJ_NW][16][17];
     __shared__ double S[16][17], J[16][17];
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
     }
     __syncthreads();
     if (s_rotated == ORTHOGONAL) return;               // the 16 rows were orthogonal already (uniform over the workgroup)
-    if (tid == 0) count_rotation(rotations, s_rotated);
+    if (tid == 0) count_rotation(rotations + blockIdx.x, s_rotated);
     apply_rotation(H, L, P, Q, J, wave, lane);
     if (V) apply_rotation(V, m, P, Q, J, wave, lane);
 }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_block_round_kernel(double* __res
 // Instances for 128 to 512 values, the blocks of ranks up to 256; larger blocks, of which none was timed, take the kernel above.
 template <int CW>
 __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __restrict__ H, int m, int round, double tol, double abs_floor, double small,
-                                                                  unsigned* __restrict__ rotations)
+                                                                  unsigned long long* __restrict__ rotations)
 {
     constexpr int L = BJ_NW * CW;
     __shared__ double Sw[BJ_NW][16][17];
@@ -449,7 +449,7 @@ __global__ __launch_bounds__(BJ_NT) void jacobi_short_round_kernel(double* __res
     }
     __syncthreads();
     if (s_rotated == ORTHOGONAL) return;         // (uniform over the workgroup)
-    if (tid == 0) count_rotation(rotations, s_rotated);
+    if (tid == 0) count_rotation(rotations + blockIdx.x, s_rotated);
     double aJ[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) aJ[kk] = J[4 * kk + g][n];
@@ -945,7 +945,13 @@ __global__ void copy_kernel(const double* __restrict__ src, double* __restrict__
     if (i < n) dst[i] = src[i];
 }
 
-__global__ void clear_counter_kernel(unsigned* c) { c[threadIdx.x] = 0; }
+__global__ void clear_flag_kernel(unsigned* flag) { *flag = 0; }
+
+__global__ void clear_counters_kernel(unsigned long long* __restrict__ c, int n)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) c[i] = 0;
+}
 
 // out[p] = sum_k X[p][k] * Y[p][k]; one workgroup of 256 per row
 __global__ __launch_bounds__(256) void row_dot_kernel(const double* __restrict__ X, const double* __restrict__ Y, int L,
@@ -1308,7 +1314,7 @@ static_assert(((size_t)(GM_TILE - 1) * MAX_DIM + GM_KT) * sizeof(double) <= 0xFF
 // block per diagonal block, which then holds their inverses.
 void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double* inv, hipStream_t st, bool clear = true, bool keep_inv = false)
 {
-    if (clear) hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(1), 0, st, flag);
+    if (clear) hipLaunchKernelGGL(clear_flag_kernel, dim3(1), dim3(1), 0, st, flag);
     hipLaunchKernelGGL(pivot_floor_kernel, dim3(1), dim3(1024), 0, st, G, n, rel, thr);
     for (int j0 = 0; j0 < n; j0 += CH_NB) {
         const int nb = n - j0 < CH_NB ? n - j0 : CH_NB, rest = n - j0 - nb;
@@ -1328,35 +1334,35 @@ void cholesky(double* G, int n, double rel, double* thr, unsigned* flag, double*
 
 bool block_rounds_fit(int L, bool with_v, int m) { return m % 16 == 0 && m >= 32 && L % 128 == 0 && (!with_v || m % 128 == 0); }
 
-void jacobi_round(double* H, int L, double* V, int m, int round, double tol, double abs_floor, double small, unsigned* rot, hipStream_t st)
+void jacobi_round(double* H, int L, double* V, int m, int round, double tol, double abs_floor, double small, unsigned long long* counters, hipStream_t st)
 {
     const dim3 g(m / 2);
     const int need = (L / 2 + JPT - 1) / JPT;          // threads that cover a row
     if (need <= 64)
-        hipLaunchKernelGGL(jacobi_round_kernel<64>, g, dim3(64), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<64>, g, dim3(64), 0, st, H, L, V, m, round, tol, abs_floor, small, counters);
     else if (need <= 128)
-        hipLaunchKernelGGL(jacobi_round_kernel<128>, g, dim3(128), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<128>, g, dim3(128), 0, st, H, L, V, m, round, tol, abs_floor, small, counters);
     else if (need <= 256)
-        hipLaunchKernelGGL(jacobi_round_kernel<256>, g, dim3(256), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<256>, g, dim3(256), 0, st, H, L, V, m, round, tol, abs_floor, small, counters);
     else if (need <= 512)
-        hipLaunchKernelGGL(jacobi_round_kernel<512>, g, dim3(512), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<512>, g, dim3(512), 0, st, H, L, V, m, round, tol, abs_floor, small, counters);
     else
-        hipLaunchKernelGGL(jacobi_round_kernel<1024>, g, dim3(1024), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
+        hipLaunchKernelGGL(jacobi_round_kernel<1024>, g, dim3(1024), 0, st, H, L, V, m, round, tol, abs_floor, small, counters);
 }
 
 // Sweeps until one passes without a rotation that is not small (rotation_large).  Synchronises the stream once per sweep.  sq: m doubles of
 // scratch.  Returns the number of sweeps, or -1 if MAX_SWEEPS did not suffice, or -2 on a runtime error.
 // stats (may be null): sweeps, milliseconds between two events around the sweeps, workgroups that rotated
 // their rows, rows per workgroup (2: pair rounds, 16: block rounds).
-int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot, hipStream_t st, double* rotations);
+int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, hipStream_t st, double* rotations);
 
-int jacobi(double* H, int L, double* V, int m, double* sq, unsigned* rot, hipStream_t st, double* stats)
+int jacobi(double* H, int L, double* V, int m, double* sq, hipStream_t st, double* stats)
 {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
     if (timed) hipEventRecord(e0, st);
     double rotations = 0;
-    const int sweeps = jacobi_sweeps(H, L, V, m, sq, rot, st, &rotations);
+    const int sweeps = jacobi_sweeps(H, L, V, m, sq, st, &rotations);
     if (timed) {
         float ms = 0;
         hipEventRecord(e1, st);
@@ -1372,7 +1378,7 @@ int jacobi(double* H, int L, double* V, int m, double* sq, unsigned* rot, hipStr
     return sweeps;
 }
 
-int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot, hipStream_t st, double* rotations)
+int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, hipStream_t st, double* rotations)
 {
     // rows far below the largest are zero for every purpose here, and rotating them would never settle
     hipLaunchKernelGGL(row_dot_kernel, dim3(m), dim3(256), 0, st, H, H, L, sq);
@@ -1385,30 +1391,46 @@ int jacobi_sweeps(double* H, int L, double* V, int m, double* sq, unsigned* rot,
     }
     double top = 0;
     for (int p = 0; p < m; ++p) top = host[p] > top ? host[p] : top;
-    free(host);
     const double abs_floor = top * 1e-30;
     const double tol = sqrt((double)L) * 1.1102230246251565e-16, small = sqrt(tol / (4.0 * m));
-    for (int sweep = 1; sweep <= MAX_SWEEPS; ++sweep) {
-        hipLaunchKernelGGL(clear_counter_kernel, dim3(1), dim3(2), 0, st, rot);
-        if (block_rounds_fit(L, V != nullptr, m)) {
+    // the counters of a round's workgroups (count_rotation) in place of the norms, cleared once and read after each sweep
+    const bool by_blocks = block_rounds_fit(L, V != nullptr, m);
+    const int workgroups = by_blocks ? m / 16 : m / 2;
+    unsigned long long* const counters = reinterpret_cast<unsigned long long*>(sq);
+    unsigned long long* const counted = reinterpret_cast<unsigned long long*>(host);
+    hipLaunchKernelGGL(clear_counters_kernel, dim3(blocks(workgroups)), dim3(256), 0, st, counters, workgroups);
+    unsigned long long large = 0;
+    int result = -1;
+    *rotations = 0;
+    for (int sweep = 1; sweep <= MAX_SWEEPS && result == -1; ++sweep) {
+        if (by_blocks) {
             auto short_rows = V ? nullptr : L == 128 ? jacobi_short_round_kernel<16> : L == 256 ? jacobi_short_round_kernel<32> :
                               L == 384 ? jacobi_short_round_kernel<48> : L == 512 ? jacobi_short_round_kernel<64> : nullptr;
             for (int round = 0; round < m / 8 - 1; ++round) {
-                if (short_rows) hipLaunchKernelGGL(short_rows, dim3(m / 16), dim3(BJ_NT), 0, st, H, m, round, tol, abs_floor, small, rot);
-                else hipLaunchKernelGGL(jacobi_block_round_kernel, dim3(m / 16), dim3(BJ_NT), 0, st, H, L, V, m, round, tol, abs_floor, small, rot);
+                if (short_rows) hipLaunchKernelGGL(short_rows, dim3(workgroups), dim3(BJ_NT), 0, st, H, m, round, tol, abs_floor, small, counters);
+                else hipLaunchKernelGGL(jacobi_block_round_kernel, dim3(workgroups), dim3(BJ_NT), 0, st, H, L, V, m, round, tol, abs_floor, small, counters);
             }
         } else {
-            for (int round = 0; round < m - 1; ++round) jacobi_round(H, L, V, m, round, tol, abs_floor, small, rot, st);
+            for (int round = 0; round < m - 1; ++round) jacobi_round(H, L, V, m, round, tol, abs_floor, small, counters, st);
         }
-        unsigned n[2] = {0, 0};             // workgroups that rotated rows, those of them with a rotation that was not small
-        if (hipMemcpyAsync(n, rot, sizeof(n), hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess)
-            return -2;
-        if (getenv("EORA_VERBOSE")) fprintf(stderr, "eora: jacobi m=%d L=%d sweep %d: %u rotations, %u large\n", m, L, sweep, n[0], n[1]);
-        *rotations += n[0];
-        if (n[1] == 0) return sweep;
+        if (hipMemcpyAsync(counted, counters, sizeof(*counted) * workgroups, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess) {
+            result = -2;
+            break;
+        }
+        unsigned long long all = 0, not_small = 0;         // rounds of workgroups that rotated rows, those of them with a rotation that was not small
+        for (int i = 0; i < workgroups; ++i) {
+            all += counted[i] & 0xFFFFFFFFull;
+            not_small += counted[i] >> 32;
+        }
+        if (getenv("EORA_VERBOSE"))
+            fprintf(stderr, "eora: jacobi m=%d L=%d sweep %d: %.0f rotations, %llu large\n", m, L, sweep, (double)all - *rotations, not_small - large);
+        *rotations = (double)all;
+        if (not_small == large) result = sweep;
+        large = not_small;
     }
-    return -1;
+    free(host);
+    return result;
 }
 
 // ---- host side of the filtered subspace iteration (see random_rows_kernel) ----------------------------------
@@ -1457,7 +1479,7 @@ void row_products(const double* T, int m, int n, double* S, hipStream_t st)
 // singular vectors of T; 0: not converged or not of rank p (the caller takes another way), < 0: runtime error.
 // S: m x m, T1: m x n, XT: r x n, work: room_all >= 3 p m + 3 p^2 doubles, theta / res / lam: p doubles each.  *cycles: filters applied.
 int leading_subspace(const double* T, int m, int n, int r, int p, double* S, double* T1, double* XT, double* work, size_t room_all, double* theta, double* res,
-                     double* lam, unsigned* rot, unsigned* flag, double* thr, hipStream_t st, int* cycles)
+                     double* lam, unsigned* flag, double* thr, hipStream_t st, int* cycles)
 {
     double* const Z = work;
     double* const Y = Z + (size_t)p * m;
@@ -1490,7 +1512,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
         cholesky(G, p, 1e-15, thr, flag, F, st, false);
         hipLaunchKernelGGL(transpose_kernel, dim3((p + 31) / 32, (p + 31) / 32), dim3(256), 0, st, (const double*)G, R, p);
         double rotations = 0;
-        const int swept = jacobi_sweeps(R, p, nullptr, p, lam, rot, st, &rotations);
+        const int swept = jacobi_sweeps(R, p, nullptr, p, lam, st, &rotations);
         if (swept < 0) return swept == -1 ? 0 : -2;       // (a runtime error is not "did not settle")
         hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)R, p, lam);
         hipLaunchKernelGGL(sort_rows_kernel, dim3(p), dim3(256), 0, st, (const double*)R, (const double*)lam, p, F, theta);
@@ -1578,7 +1600,7 @@ int leading_subspace(const double* T, int m, int n, int r, int p, double* S, dou
 inline size_t r256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 struct Layout {
-    size_t dW, H, V, T, T0, lam, root, inv, sq, sigma, idx, Ap, Bn, rot, total;
+    size_t dW, H, V, T, T0, lam, root, inv, sq, sigma, idx, Ap, Bn, flag, total;
 };
 
 Layout layout(int d_in, int d_out, int r)
@@ -1604,7 +1626,7 @@ Layout layout(int d_in, int d_out, int r)
     l.idx = take(4 * (size_t)r);
     l.Ap = take(8 * (size_t)r * d_in);
     l.Bn = take(8 * (size_t)r * d_out);
-    l.rot = take(256);
+    l.flag = take(256);
     l.total = o;
     return l;
 }
@@ -1666,7 +1688,8 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     int* idx = (int*)(ws + l.idx);
     double* Ap = (double*)(ws + l.Ap);
     double* Bn = (double*)(ws + l.Bn);
-    unsigned* rot = (unsigned*)(ws + l.rot);
+    unsigned* flag = (unsigned*)(ws + l.flag);
+    double* thr = (double*)(ws + l.flag + 128);
     const float* W = (const float*)W_f32;
     const float* What = (const float*)W_hat_f32;
     const float* Xt = (const float*)Xt_f32;
@@ -1685,8 +1708,6 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     // the test hook asks for it).
     bool chol = false;
     if (g_factors_route == 0) {
-        unsigned* flag = rot + 16;
-        double* thr = (double*)(rot + 32);
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
         if (timed) hipEventRecord(e0, st);
@@ -1713,7 +1734,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     if (!chol) {
         // step 2: eigenvectors as the rows of V
         hipLaunchKernelGGL(identity_kernel, dim3(blocks((size_t)k * k)), dim3(256), 0, st, V, k);
-        sweeps = jacobi(H, k, V, k, sq, rot, st, stats);
+        sweeps = jacobi(H, k, V, k, sq, st, stats);
         if (sweeps < 0) return sweeps == -1 ? EORA_ERR_NOT_CONVERGED : EORA_ERR_LAUNCH;
         hipLaunchKernelGGL(row_dot_kernel, dim3(k), dim3(256), 0, st, H, V, k, lam);
         // step 3: sqrt(Lambda), with eigenvalues below eig_floor * max raised to it
@@ -1759,11 +1780,11 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         const bool timed = stats && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess;
         if (timed) hipEventRecord(e0, st);
         int cycles = 0;
-        sub = leading_subspace(T, m, n, r, p, H, T0, by_rows ? Ap : Bn, V, (size_t)k * k, lam, root, inv, rot, rot + 16, (double*)(rot + 32), st, &cycles);
+        sub = leading_subspace(T, m, n, r, p, H, T0, by_rows ? Ap : Bn, V, (size_t)k * k, lam, root, inv, flag, thr, st, &cycles);
         if (stats) stats[0] = sub == 1 ? cycles : -cycles;
         if (sub == 1) {
             gemm((const double*)V, (long)m, 1L, (const double*)T, 1L, (long)n, T0, (long)n, p, n, m, st, 1.0, 0.0, GM_FULL, H, (size_t)k * k);      // Z T
-            sweeps = jacobi(T0, n, nullptr, p, sq, rot, st, stats ? stats + 4 : nullptr);
+            sweeps = jacobi(T0, n, nullptr, p, sq, st, stats ? stats + 4 : nullptr);
             if (sweeps < 0) return sweeps == -1 ? EORA_ERR_NOT_CONVERGED : EORA_ERR_LAUNCH;
             hipLaunchKernelGGL(row_dot_kernel, dim3(p), dim3(256), 0, st, T0, T0, n, sq);
             hipLaunchKernelGGL(top_rows_kernel, dim3(blocks(p)), dim3(256), 0, st, sq, p, r, idx, sigma);
@@ -1781,8 +1802,6 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         if (sub < 0) return EORA_ERR_LAUNCH;
     }
     if (chol && !sub && n >= 2 * m) {
-        unsigned* flag = rot + 16;
-        double* thr = (double*)(rot + 32);
         gemm(T, (long)n, 1L, T, (long)n, 1L, H, (long)m, m, m, n, st, 1.0, 0.0, GM_LOWER);
         cholesky(H, m, 1e-14, thr, flag, V, st);
         unsigned bad = 1;
@@ -1796,7 +1815,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
     } else if (square) {
         double* Y = V;                          // C^T
         hipLaunchKernelGGL(transpose_kernel, dim3((m + 31) / 32, (m + 31) / 32), dim3(256), 0, st, (const double*)H, Y, m);
-        sweeps = jacobi(Y, m, nullptr, m, sq, rot, st, stats ? stats + 4 : nullptr);
+        sweeps = jacobi(Y, m, nullptr, m, sq, st, stats ? stats + 4 : nullptr);
         if (sweeps < 0) return sweeps == -1 ? EORA_ERR_NOT_CONVERGED : EORA_ERR_LAUNCH;
         hipLaunchKernelGGL(row_dot_kernel, dim3(m), dim3(256), 0, st, Y, Y, m, sq);
         hipLaunchKernelGGL(top_rows_kernel, dim3(blocks(m)), dim3(256), 0, st, sq, m, r, idx, sigma);
@@ -1810,7 +1829,7 @@ extern "C" int eora_factors(const void* W_f32, const void* W_hat_f32, const void
         copy_doubles(T, T0, nw, st);
         Tkeep = T0;
         // step 5: rows of T -> sigma_i z_i^T
-        sweeps = jacobi(T, n, nullptr, m, sq, rot, st, stats ? stats + 4 : nullptr);
+        sweeps = jacobi(T, n, nullptr, m, sq, st, stats ? stats + 4 : nullptr);
         if (sweeps < 0) return sweeps == -1 ? EORA_ERR_NOT_CONVERGED : EORA_ERR_LAUNCH;
         hipLaunchKernelGGL(row_dot_kernel, dim3(m), dim3(256), 0, st, T, T, n, sq);
         hipLaunchKernelGGL(top_rows_kernel, dim3(blocks(m)), dim3(256), 0, st, sq, m, r, idx, sigma);
