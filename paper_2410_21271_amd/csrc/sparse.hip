@@ -742,9 +742,12 @@ static int fill_group(SparseGroupArgs& g, const SparseArgs* members, int n, int 
 
 // Whether a group of linears with 4-bit kept values, eight row blocks a workgroup, takes the kernel that decodes a step ahead.  Where two
 // workgroups share a compute unit the other one's work hides the decoding already.
-//  - Two token blocks (both kernels leave room for two workgroups): not from 257 to 512 workgroups, which all run at once.  q+k+v of the 70B layer, rank 128,
+//  - Two token blocks (both kernels leave room for two workgroups): not from 257 to 512 workgroups, which all run at once, and beyond only where up to three members
+//    have few.  q+k+v of the 70B layer, rank 128,
 //    65 tokens 43.5 us ahead and 42.7, rank 32 40.8 and 39.3, bare at 127 tokens 38.4 and 36.8; two members of 14336 rows, d_in 8192, rank 32, 20 tokens
-//    (256 workgroups) 33.2 and 38.1; two of 10240, rank 128, 64 tokens (576) 48.1 and 53.1.
+//    (256 workgroups) 33.2 and 38.1; two of 10240, rank 128, 64 tokens (576) 48.1 and 53.1.  Of 229 groups of more than 512, ranks 64 to 256, 20 to 112 tokens, the 73
+//    of up to three members with at most 320 doing the layer's work take 1.024 of the time before decoding ahead with it and 1.031 without (which of the late ones
+//    get a unit first decides: single launches differ by 15 % either way), the others 1.018 and 1.001 (two of 14336 rows, d_in 8192, rank 128, 34 tokens 54.3 and 52.4).
 //  - Four token blocks: decoding ahead takes 131 registers, one workgroup a unit; without it 124, two.  One is better where every workgroup that does
 //    the layer's work gets a unit of its own, although those beyond the 256th wait for producers to end; two where there are more of them, or
 //    where the late ones are so few that they fit beside the first member's producers.  Over 672 groups of two to four members, 50 to 127 tokens, ranks 32 to
@@ -758,8 +761,8 @@ static bool decodes_ahead(const SparseArgs* members, int n, int tb, int producer
     int total = 0;
     for (int i = 0; i < n; ++i) total += blocks(members[i]);
     if (total <= 256) return true;
-    if (tb == 2) return total > 512;
     const int workers = total - n * producers;
+    if (tb == 2) return total > 512 && workers <= 320 && n <= 3;
     if (workers > 256 || total - 256 <= producers) return false;
     return n == 2 || (n * producers <= 192 && (workers <= 192 || (producers % 32 == 0 && members[0].M <= 64)));
 }

@@ -612,6 +612,8 @@ def test_sparse_group_of_layers_sharing_x(gpu, quantised, r, M, d_in, d_outs):
     (0, 127, 1024, (8192, 1024, 1040), True),        # two token blocks, 324 workgroups
     (0, 20, 1024, (14336, 14336), False),            # 224
     (128, 64, 512, (10240, 10240), False),           # 320 and 256 producers: more than two a unit
+    (128, 40, 512, (11264, 11264), True),            # 352 and 192: more than two a unit, more of them than 320
+    (128, 34, 512, (5120, 5120, 5120, 5120), True),  # 320 and 384: four members
 ])
 def test_sparse_group_with_two_workgroups_per_unit(gpu, r, M, d_in, d_outs, shared):
     """Groups of eight row blocks a workgroup with 4-bit kept values: which of them run two workgroups a compute unit, without decoding
